@@ -381,24 +381,32 @@ int ts_build_page_meta(const ts_layout* layout, void* stream) {
     return TS_ERR_NULL;
   MetaParams p = meta_params(layout);
   if (p.B > 65535) return TS_ERR_UNSUPPORTED;
-  if (layout->kv_format == TS_KV_INT8) {
-    if (!layout->k_scale) return TS_ERR_NULL;
-    const int ppb = kThreads / layout->head_dim;   // pages per workgroup
-    dim3 grid8((p.Pmax + ppb - 1) / ppb, p.Hkv, p.B);
-    if (layout->head_dim == 64)
-      build_page_meta_i8_kernel<64><<<grid8, kThreads, 0, (hipStream_t)stream>>>(p);
-    else
-      build_page_meta_i8_kernel<128><<<grid8, kThreads, 0, (hipStream_t)stream>>>(p);
-    return launch_status();
-  }
-  const int pages_per_wg = kWaves * (kWave / (layout->head_dim / 8));
+  const bool int8 = layout->kv_format == TS_KV_INT8;
+  if (int8 && !layout->k_scale) return TS_ERR_NULL;
+  const int pages_per_wg = kWaves * (int8 ? 8 : kWave / (layout->head_dim / 8));
   // (the KV head is the fastest grid index: a physical page's tiles of all heads are
   // contiguous in the pool, and workgroups dispatched together then read neighbouring
   // memory: -3 % on the 16-head batch)
   if ((p.Pmax + pages_per_wg - 1) / pages_per_wg > 65535) return TS_ERR_UNSUPPORTED;
   dim3 grid(p.Hkv, (p.Pmax + pages_per_wg - 1) / pages_per_wg, p.B);
-  const bool half = layout->kv_format == TS_KV_FP16;
   hipStream_t s = (hipStream_t)stream;
+  if (int8) {   // (128 bytes of a page per load; up to sixteen loads in flight)
+#define TS_LAUNCH_BUILD8(DD, NN) build_page_meta_i8_kernel<DD, NN><<<grid, kThreads, 0, s>>>(p)
+    const int loads = p.S * layout->head_dim / 128;
+    if (layout->head_dim == 64) {
+      if (loads == 2) TS_LAUNCH_BUILD8(64, 2);
+      else if (loads == 4) TS_LAUNCH_BUILD8(64, 4);
+      else if (loads == 8) TS_LAUNCH_BUILD8(64, 8);
+      else TS_LAUNCH_BUILD8(64, 16);
+    } else {
+      if (loads == 4) TS_LAUNCH_BUILD8(128, 4);
+      else if (loads == 8) TS_LAUNCH_BUILD8(128, 8);
+      else TS_LAUNCH_BUILD8(128, 16);
+    }
+#undef TS_LAUNCH_BUILD8
+    return launch_status();
+  }
+  const bool half = layout->kv_format == TS_KV_FP16;
 #define TS_LAUNCH_BUILD(DD, HH)                                                                 \
   do {                                                                                          \
     if (p.S == 4) build_page_meta_kernel<DD, HH, 4><<<grid, kThreads, 0, s>>>(p);               \

@@ -198,32 +198,127 @@ __device__ __forceinline__ void i8_chunk_box(const uint4& c, float scale, uint4&
   hi = make_uint4(h[0], h[1], h[2], h[3]);
 }
 
-// One thread per (page, channel): kThreads / D pages per workgroup.  Set-up
-// work (a page is summarised once; appends keep it current), kept plain.
-template <int D>
+// The same for a value known as its nearest fp32 f, where f is no bf16 number (its lower
+// half is not zero): the exact value then lies between the same two bf16 numbers as f.
+__device__ __forceinline__ uint32_t bf16_directed_off_grid(float f, bool up) {
+  const uint32_t b = __float_as_uint(f);
+  return (b >> 16) + (((b >> 31) != 0u) != up ? 1u : 0u);
+}
+
+// Bulk rebuild for the INT8 cache, laid out like build_page_meta_kernel: the eight
+// consecutive lanes of a page each own sixteen channels and walk down the page's tokens, a
+// wave-wide load takes 128 contiguous bytes of each of eight pages (one token row with
+// D = 128, two with D = 64), NI of them in flight, and the tokens' scales come in fours.
+// Bound by memory, as long as the arithmetic stays in fp32: code * scale is one fused
+// multiply-add with ONE rounding (u * s - 128 * s for the biased code u), rounding keeps the
+// order, and so the smallest rounded product is the rounded smallest product.  From that
+// the bf16 below it follows without the exact value, unless the rounded one is itself a bf16
+// number (about one in 65536, or scales with few bits); those channels are worked out
+// again in fp64.  (One thread per channel with a byte load and three fp64 operations per
+// token, each page waiting for its own look-ups, ran at 0.9 TB/s.)
+// Slots past the sequence's last token repeat that token.
+template <int D, int NI>
 __global__ __launch_bounds__(kThreads) void build_page_meta_i8_kernel(MetaParams p) {
-  constexpr int PPB = kThreads / D;
-  const int c = threadIdx.x % D;
-  const int j = blockIdx.x * PPB + threadIdx.x / D;
-  const int h = blockIdx.y, b = blockIdx.z;
+  constexpr int R = 128 / D;     // token rows per load
+  constexpr int NS = NI * R;     // tokens per round
+  static_assert(NS % 4 == 0, "scales are fetched in fours");
+  const int lane = lane_id(), li = lane & 7;
+  // (with two rows the second row's chunks run backwards, so that the lane with the same
+  // channels is the mirror image within the eight)
+  const int r = R == 2 ? li >> 2 : 0, cg = r ? 7 - li : li;
+  const int first = (blockIdx.y * kWaves + wave_id()) * 8, j = first + lane / 8;
+  const int h = blockIdx.x, b = blockIdx.z;
   const int L = p.seq_lens[b];
-  const int Pb = (L + p.S - 1) / p.S;
-  if (j >= Pb || j >= p.Pmax) return;
-  const int phys = p.block_table[(size_t)b * p.Pmax + j];
-  if (phys < 0 || phys >= p.n_phys) return;
-  const int valid = min(p.S, L - j * p.S);
-  const int8_t* tile = reinterpret_cast<const int8_t*>(p.k_pool) +
-                       ((size_t)phys * p.Hkv + h) * (size_t)p.tile_stride;
-  const float* sc = p.k_scale + ((size_t)phys * p.Hkv + h) * (size_t)p.S;
-  double lo = INFINITY, hi = -INFINITY;
-  for (int t = 0; t < valid; ++t) {
-    const double k = static_cast<double>(tile[(size_t)t * D + c]) * static_cast<double>(sc[t]);
-    lo = fmin(lo, k);
-    hi = fmax(hi, k);
+  const int Pb = min((L + p.S - 1) / p.S, p.Pmax);
+  if (uniform(first) >= Pb) return;   // the whole group is past the end
+  const int phys = p.block_table[(size_t)b * p.Pmax + min(j, Pb - 1)];
+  const bool on = j < Pb && phys >= 0 && phys < p.n_phys;
+  const int last = on ? min(p.S, L - j * p.S) - 1 : 0;   // the page's last token
+  const size_t tile_id = (size_t)(on ? phys : 0) * p.Hkv + h;
+  const uint8_t* tile = reinterpret_cast<const uint8_t*>(p.k_pool) + tile_id * (size_t)p.tile_stride + cg * 16;
+  const float* sc = p.k_scale + tile_id * (size_t)p.S;
+  const float s_last = sc[last];
+  float lo[16], hi[16];
+#pragma unroll
+  for (int i = 0; i < 16; ++i) { lo[i] = INFINITY; hi[i] = -INFINITY; }
+  for (int t0 = 0; t0 < p.S; t0 += NS) {
+    uint4 w[NI];
+    float4 s4[NS / 4];
+#pragma unroll
+    for (int i = 0; i < NI; ++i) w[i] = load_stream16(tile + (size_t)min(t0 + i * R + r, last) * D);
+#pragma unroll
+    for (int q = 0; q < NS / 4; ++q) s4[q] = *reinterpret_cast<const float4*>(sc + t0 + 4 * q);
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      const float4 q = s4[i * R / 4];
+      const int e = i * R % 4;
+      float s = e == 0 ? q.x : e == 1 ? q.y : e == 2 ? q.z : q.w;
+      if (R == 2) s = r ? (e == 0 ? q.y : q.w) : s;
+      s = t0 + i * R + r <= last ? s : s_last;
+      const float bias = -128.0f * s;
+      const uint32_t x[4] = {w[i].x ^ 0x80808080u, w[i].y ^ 0x80808080u, w[i].z ^ 0x80808080u,
+                             w[i].w ^ 0x80808080u};
+#pragma unroll
+      for (int c = 0; c < 16; ++c) {
+        const float v = fmaf(static_cast<float>((x[c >> 2] >> (8 * (c & 3))) & 0xffu), s, bias);
+        lo[c] = fminf(lo[c], v);
+        hi[c] = fmaxf(hi[c], v);
+      }
+    }
   }
-  const size_t row = (((size_t)b * p.Hkv + h) * p.Pmax + j) * D + c;
-  p.page_min[row] = bf16_directed(lo, false);
-  p.page_max[row] = bf16_directed(hi, true);
+  // the lane's channels: all sixteen, or with two rows the half that it takes over from (and
+  // the other half that it leaves to) the lane of the other row
+  constexpr int NC = 16 / R;
+  const int c0 = cg * 16 + r * 8;
+  float klo[NC], khi[NC];
+  if constexpr (R == 2) {
+    auto mirror = [](float v) {
+      return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), kDppHalfMirror, 0xf, 0xf, true));
+    };
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+      klo[c] = fminf(r ? lo[8 + c] : lo[c], mirror(r ? lo[c] : lo[8 + c]));
+      khi[c] = fmaxf(r ? hi[8 + c] : hi[c], mirror(r ? hi[c] : hi[8 + c]));
+    }
+  } else {
+#pragma unroll
+    for (int c = 0; c < NC; ++c) { klo[c] = lo[c]; khi[c] = hi[c]; }
+  }
+  uint32_t mn[NC], mx[NC];
+  uint32_t redo = 0;   // channels with an extreme that is a bf16 number (zeros of either sign too)
+#pragma unroll
+  for (int c = 0; c < NC; ++c) {
+    mn[c] = bf16_directed_off_grid(klo[c], false);
+    mx[c] = bf16_directed_off_grid(khi[c], true);
+    if ((__float_as_uint(klo[c]) & 0xffffu) == 0u || (__float_as_uint(khi[c]) & 0xffffu) == 0u) redo |= 1u << c;
+  }
+  if (!on) return;
+  if (redo != 0u) {
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      if ((redo >> c) & 1u) {
+        double dlo = INFINITY, dhi = -INFINITY;
+        for (int t = 0; t <= last; ++t) {
+          const int8_t code = static_cast<int8_t>(tile[(size_t)t * D + r * 8 + c]);
+          const double k = static_cast<double>(code) * static_cast<double>(sc[t]);
+          dlo = fmin(dlo, k);
+          dhi = fmax(dhi, k);
+        }
+        mn[c] = bf16_directed(dlo, false);
+        mx[c] = bf16_directed(dhi, true);
+      }
+    }
+  }
+  const size_t row = (((size_t)b * p.Hkv + h) * p.Pmax + j) * D + c0;
+#pragma unroll
+  for (int q = 0; q < NC / 8; ++q) {
+    auto pack = [&](const uint32_t (&m)[NC]) {
+      return make_uint4(m[8 * q] | (m[8 * q + 1] << 16), m[8 * q + 2] | (m[8 * q + 3] << 16),
+                        m[8 * q + 4] | (m[8 * q + 5] << 16), m[8 * q + 6] | (m[8 * q + 7] << 16));
+    };
+    *reinterpret_cast<uint4*>(p.page_min + row + 8 * q) = pack(mn);
+    *reinterpret_cast<uint4*>(p.page_max + row + 8 * q) = pack(mx);
+  }
 }
 
 // Append to the INT8 cache: one workgroup per sequence, a wave per KV head at a

@@ -112,6 +112,39 @@ def splits(request):
     ts.set_tuning(0, 0, 0)
 
 
+@pytest.mark.parametrize("scales", ["as drawn", "powers of two", "few bits", "tiny"])
+@pytest.mark.parametrize("name", list(REDUCED8))
+def test_int8_metadata_is_rounded_outwards_exactly(oracle, name, scales):
+    """Every box of every page, bit for bit, on every (head_dim, page size) instance of the
+    bulk rebuild.  With scales of few significant bits most products code * scale are
+    themselves bf16 numbers, or round to one in fp32 from either side: there the rebuild has
+    to go back to the exact products."""
+    w = wl.make_workload(REDUCED8[name], DEV, seed=57, n_q=1, n_new=1)
+    print(f"[case] int8 metadata {name} {scales}", flush=True)
+    if scales != "as drawn":
+        k = w.k_scale
+        bits = k.view(torch.int32)
+        if scales == "powers of two":
+            k.copy_(torch.where(k.isnan(), k, (bits & 0x7f800000).view(torch.float32)))
+        elif scales == "few bits":   # 1 + j/4 or one unit in the last place beside it
+            near = (bits & 0x7fe00000) + (torch.arange(k.numel(), device=DEV).view(k.shape) % 3 - 1)
+            k.copy_(torch.where(k.isnan(), k, near.to(torch.int32).view(torch.float32)))
+        else:
+            k.mul_(2.0 ** -126)
+    sess = Session8(w)
+    ts.build_page_meta(sess.layout)
+    torch.cuda.synchronize()
+    lens = w.seq_lens.cpu()
+    Kq, ks, _, _ = wl.logical_kv_i8(w)
+    omin, omax = oracle.build_page_meta_i8(Kq.cpu().numpy(), ks.cpu().numpy(), lens.numpy().astype(np.int32),
+                                           w.spec.S, w.P_max)
+    for b in range(w.spec.B):
+        Pb = int(oracle.num_pages(int(lens[b]), w.spec.S))
+        assert np.array_equal(wl.bits(sess.page_min[b, :, :Pb]), omin[b, :, :Pb]), f"page_min of {b}"
+        assert np.array_equal(wl.bits(sess.page_max[b, :, :Pb]), omax[b, :, :Pb]), f"page_max of {b}"
+        assert torch.isnan(sess.page_min[b, :, Pb:].float()).all(), "rows past the last page"
+
+
 @pytest.mark.parametrize("name", list(REDUCED8))
 @pytest.mark.parametrize("splits", [0, 3], indirect=True)
 def test_int8_reduced_all_units(oracle, name, splits):
