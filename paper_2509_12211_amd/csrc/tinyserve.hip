@@ -390,18 +390,16 @@ int ts_build_page_meta(const ts_layout* layout, void* stream) {
   if ((p.Pmax + pages_per_wg - 1) / pages_per_wg > 65535) return TS_ERR_UNSUPPORTED;
   dim3 grid(p.Hkv, (p.Pmax + pages_per_wg - 1) / pages_per_wg, p.B);
   hipStream_t s = (hipStream_t)stream;
-  if (int8) {   // (128 bytes of a page per load; up to sixteen loads in flight)
+  if (int8) {   // (128 bytes of a page per load; up to eight loads in flight)
 #define TS_LAUNCH_BUILD8(DD, NN) build_page_meta_i8_kernel<DD, NN><<<grid, kThreads, 0, s>>>(p)
     const int loads = p.S * layout->head_dim / 128;
     if (layout->head_dim == 64) {
       if (loads == 2) TS_LAUNCH_BUILD8(64, 2);
       else if (loads == 4) TS_LAUNCH_BUILD8(64, 4);
-      else if (loads == 8) TS_LAUNCH_BUILD8(64, 8);
-      else TS_LAUNCH_BUILD8(64, 16);
+      else TS_LAUNCH_BUILD8(64, 8);
     } else {
       if (loads == 4) TS_LAUNCH_BUILD8(128, 4);
-      else if (loads == 8) TS_LAUNCH_BUILD8(128, 8);
-      else TS_LAUNCH_BUILD8(128, 16);
+      else TS_LAUNCH_BUILD8(128, 8);
     }
 #undef TS_LAUNCH_BUILD8
     return launch_status();
