@@ -24,6 +24,11 @@ static std::atomic<int> g_tune_splits{0}, g_tune_wg_per_cu{0};
 // query-aware path is latency-bound and wants one per compute unit; the dense
 // baseline streams the whole cache and wants several.
 constexpr int kDenseTargetWorkgroups = 1024;
+// Up to this many bytes of metadata and selected pages the units of a large batch count as
+// small (small_units_decode_kernel).  Beyond it a unit is bound by its data, and a whole
+// compute unit's waves on one unit get through them sooner: at 2.4 MB the two builds are
+// equal, at 4.7 MB and 15 MB the small one is 6 % and 18 % behind.
+constexpr size_t kSmallUnitBytes = 2 << 20;
 
 static Plan make_plan(const ts_layout* L, int max_topk, int target_workgroups = kTargetWorkgroups) {
   Plan pl;
@@ -70,8 +75,12 @@ static Plan make_plan(const ts_layout* L, int max_topk, int target_workgroups = 
   pl.total = off;
   // fused kernel LDS: select scratch (keys, bins), the unit's block-table row,
   // this workgroup's selected pages; the wave-merge area aliases the keys
-  const size_t lds_sel = select_lds_bytes(Pmax);
-  const size_t lds_att = (size_t)kWaves * G * (L->head_dim + 2) * 4;
+  pl.small_units = target_workgroups == kTargetWorkgroups && pl.g == 1 &&
+                   pl.units > kTargetWorkgroups &&
+                   ((size_t)Pmax + (size_t)max_topk * L->page_size) * 4 * L->head_dim <= kSmallUnitBytes;
+  const int waves = pl.small_units ? kSmallWaves : kWaves;
+  const size_t lds_sel = select_lds_bytes(Pmax, waves);
+  const size_t lds_att = (size_t)waves * G * (L->head_dim + 2) * 4;
   // ... and, in an area of its own, the query staging: a wave that is done
   // scoring starts the selection (which clears the bins) while another may not
   // have picked up its query sums yet, so the two must not share memory
@@ -115,13 +124,13 @@ __global__ __launch_bounds__(kThreads) void select_topk_kernel(const float* scor
   const int K = topk_per_seq ? topk_per_seq[b] : topk;
   const int Kb = uniform(max(0, min(min(K, Pb), Kmax)));
   if (h == 0 && threadIdx.x == 0) sel_count[b] = Kb;
-  const SelectLds L = carve_select(smem, Pmax);
+  const SelectLds L = carve_select<kWaves>(smem, Pmax);
   const float* srow = scores + (size_t)u * Pmax;
   int32_t* row = sel + (size_t)u * Kmax;
   for (int i = Kb + threadIdx.x; i < Kmax; i += kThreads) row[i] = -1;
   // eight loads per thread in flight per round (a plain loop would pay one
   // memory round trip per iteration); the key range is gathered on the way
-  const KeyLayout kl = KeyLayout::make(Pb);
+  const KeyLayout kl = KeyLayout::make<kWaves>(Pb);
   const ForcedPages fp = ForcedPages::make(keep_first, keep_last, Pb);
   uint32_t tmin = 0xffffffffu, tmax = 0u;
   for (int j0 = threadIdx.x; j0 < Pb; j0 += kThreads * 8) {
@@ -139,10 +148,10 @@ __global__ __launch_bounds__(kThreads) void select_topk_kernel(const float* scor
       }
     }
   }
-  select_begin(L, tmin, tmax);
+  select_begin<kWaves>(L, tmin, tmax);
   __syncthreads();
   TS_MARK(1);
-  select_topk_lds(L, kl, Pb, Kb, fp, [&](int rank, int page) { row[rank] = page; });
+  select_topk_lds<kWaves>(L, kl, Pb, Kb, fp, [&](int rank, int page) { row[rank] = page; });
   TS_MARK(5);
 }
 
@@ -480,7 +489,7 @@ int ts_select_topk_pages(const ts_layout* layout, const float* scores, int32_t t
   if (!scores || !sel || !sel_count || !layout->seq_lens) return TS_ERR_NULL;
   if (max_topk < 1 || (!topk_per_seq && (topk < 1 || max_topk < topk))) return TS_ERR_SHAPE;
   const int units = layout->num_seqs * layout->num_kv_heads;
-  const size_t lds = select_lds_bytes(layout->max_pages_per_seq);
+  const size_t lds = select_lds_bytes(layout->max_pages_per_seq, kWaves);
   if ((st = allow_lds(select_topk_kernel, lds)) != TS_OK) return st;
   select_topk_kernel<<<units, kThreads, lds, (hipStream_t)stream>>>(
       scores, layout->seq_lens, topk, topk_per_seq, sel, sel_count, layout->num_kv_heads,

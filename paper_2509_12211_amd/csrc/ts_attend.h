@@ -694,9 +694,9 @@ __device__ __forceinline__ bool merge_tagged(const uint64_t* part, int G, int g,
 
 // The workgroup attends `count` selected pages of unit (b, h): entry i of its
 // list is page sel_at(i), stored in physical page phys_at(page).  The list is
-// cut into fragments (PageGeom<S>); wave w takes fragments w, w + kWaves, ...
+// cut into fragments (PageGeom<S>); wave w takes fragments w, w + NW, ...
 // The waves' states are merged through LDS
-// (lds: kWaves * G * (D + 2) floats).  With n_split == 1 the normalised result
+// (lds: NW * G * (D + 2) floats).  With n_split == 1 the normalised result
 // goes to `out`; otherwise the unnormalised partial (o[D], m, l per head) is
 // handed to the combining workgroup through agent-scope stores.
 // Ends with a barrier after which `lds` may be reused; on return (n_split > 1)
@@ -713,7 +713,7 @@ __device__ __forceinline__ bool merge_tagged(const uint64_t* part, int G, int g,
 // split keeps its own partial in registers, polls for the others (bounded by
 // spin_limit polls per thread) and writes the unit's output; the function
 // returns false if that wait expired.
-template <int D, int S, bool kLatency, bool kPatch, bool kInt8, bool kHalf, bool kHaveQ = false,
+template <int NW, int D, int S, bool kLatency, bool kPatch, bool kInt8, bool kHalf, bool kHaveQ = false,
           typename SelAt, typename PhysAt>
 __device__ __forceinline__ bool attend_split(const AttendParams& p, int b, int h, int split,
                                              int count, int L, const NewToken& nt, SelAt sel_at,
@@ -721,6 +721,7 @@ __device__ __forceinline__ bool attend_split(const AttendParams& p, int b, int h
                                              const uint16_t* q_rows = nullptr, int spin_limit = 0,
                                              const QOperand<D, kInt8>* q_ready = nullptr) {
   using Geo = PageGeom<S>;
+  constexpr int NT = NW * kWave;
   constexpr int F = Geo::F, NS = Geo::NS, NH = Geo::NH;
   static_assert(!(kHalf && kInt8), "the INT8 cache goes with bf16 queries");
   using Frag = std::conditional_t<kInt8, PageFrag8<D, F>, PageFrag<D, F>>;
@@ -756,15 +757,15 @@ __device__ __forceinline__ bool attend_split(const AttendParams& p, int b, int h
       splice_x = nt.slot % F;
     }
   }
-  const bool splice = kPatch && splice_item >= 0 && wave == splice_item % kWaves;
+  const bool splice = kPatch && splice_item >= 0 && wave == splice_item % NW;
   if (splice) patch.load(nt);
   WaveAcc<D> acc;
   acc.init();
   TS_MARK(27);
 
-  for (int batch = wave; batch < n_items; batch += kWave * kWaves) {
+  for (int batch = wave; batch < n_items; batch += kWave * NW) {
     // lane x holds the page ids of this wave's x-th fragment of the batch
-    const int my_item = batch + lane * kWaves;
+    const int my_item = batch + lane * NW;
     int my_j[NS], my_phys[NS];
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
@@ -776,7 +777,7 @@ __device__ __forceinline__ bool attend_split(const AttendParams& p, int b, int h
         if (my_j[s] >= 0 && my_j[s] < p.Pmax) my_phys[s] = phys_at(my_j[s]);
       }
     }
-    const int n = min(kWave, (n_items - batch + kWaves - 1) / kWaves);
+    const int n = min(kWave, (n_items - batch + NW - 1) / NW);
     TS_MARK(28);
     // A ring of NBUF fragment buffers: up to NBUF fragments of this wave are in
     // flight (2 KiB - 8 KiB each) before the first is consumed.
@@ -789,7 +790,7 @@ __device__ __forceinline__ bool attend_split(const AttendParams& p, int b, int h
     // single cache line of it) and has no valid token: no branch around the loads.
     auto issue = [&](Frag& fr, int& it, int x) -> uint32_t {
       const int xc = min(x, n - 1);
-      it = batch + xc * kWaves;
+      it = batch + xc * NW;
       if constexpr (S >= 16) {
         const int j = __builtin_amdgcn_readlane(my_j[0], xc);
         const int phys = __builtin_amdgcn_readlane(my_phys[0], xc);
@@ -943,17 +944,17 @@ __device__ __forceinline__ bool attend_split(const AttendParams& p, int b, int h
   int spins = 0;
   // one thread per (head, channel); the thread of channel 0 also hands on the
   // head's running max and sum
-  for (int idx = threadIdx.x; idx < G * D; idx += kThreads) {
+  for (int idx = threadIdx.x; idx < G * D; idx += NT) {
     const int g = idx / D, c = idx % D;
-    float mw[kWaves], M = -INFINITY;
+    float mw[NW], M = -INFINITY;
 #pragma unroll
-    for (int w = 0; w < kWaves; ++w) {
+    for (int w = 0; w < NW; ++w) {
       mw[w] = lds[((size_t)w * G + g) * RS + D];
       M = fmaxf(M, mw[w]);
     }
     float Lsum = 0.f, O = 0.f;
 #pragma unroll
-    for (int w = 0; w < kWaves; ++w) {
+    for (int w = 0; w < NW; ++w) {
       const float* row = lds + ((size_t)w * G + g) * RS;
       const float wgt = __builtin_amdgcn_exp2f(mw[w] - M);
       Lsum += row[D + 1] * wgt;

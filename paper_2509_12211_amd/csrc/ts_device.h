@@ -7,8 +7,10 @@
 namespace ts {
 
 constexpr int kWave = 64;
-constexpr int kThreads = 512;            // every kernel here runs 8 wavefronts per workgroup
-constexpr int kWaves = kThreads / kWave;
+// Wavefronts per workgroup of every kernel but the fused one for many small units, which
+// has four (the code shared by both takes the number as the template parameter NW).
+constexpr int kWaves = 8;
+constexpr int kThreads = kWaves * kWave;
 
 typedef short short4_t __attribute__((ext_vector_type(4)));
 typedef float float4_t __attribute__((ext_vector_type(4)));

@@ -19,8 +19,9 @@ namespace ts {
 // Lane layout: a metadata row (D bf16) is read as D/8 chunks of 16 bytes, so
 // one wave-wide 16-byte load covers 64 / (D/8) consecutive pages; each lane
 // keeps Qp / Qn for its 8 channels.
-template <int D, bool kHalf = false>
+template <int D, bool kHalf = false, int NW = kWaves>
 struct ScoreLanes {
+  static constexpr int NT = NW * kWave;     // threads of the workgroup
   static constexpr int LPR = D / 8;         // lanes per metadata row
   static constexpr int PPW = kWave / LPR;   // pages per wave-wide load
   static constexpr int U = 4;               // wave-wide loads of min (and of max) in flight
@@ -35,7 +36,7 @@ struct ScoreLanes {
   // and its first use (loads return in issue order: what is needed first is
   // issued first).  stage: LDS scratch of query_stage_bytes(G) bytes.
   static constexpr size_t query_stage_bytes(int G) { return (size_t)G * D * 2 + 2 * D * 8; }
-  static constexpr int kQueryLoads = 16 * D / 8 / kThreads > 0 ? 16 * D / 8 / kThreads : 1;
+  static constexpr int kQueryLoads = 16 * D / 8 / NT > 0 ? 16 * D / 8 / NT : 1;
 
   struct QueryRegs { uint4 w[kQueryLoads]; };
 
@@ -49,7 +50,7 @@ struct ScoreLanes {
     const int n16 = G * D / 8;
 #pragma unroll
     for (int k = 0; k < kQueryLoads; ++k)
-      r.w[k] = reinterpret_cast<const uint4*>(q_group)[min((int)threadIdx.x + k * kThreads, n16 - 1)];
+      r.w[k] = reinterpret_cast<const uint4*>(q_group)[min((int)threadIdx.x + k * NT, n16 - 1)];
   }
 
   // Two barriers.
@@ -59,7 +60,7 @@ struct ScoreLanes {
     const int n16 = G * D / 8;
 #pragma unroll
     for (int k = 0; k < kQueryLoads; ++k) {
-      raw[min((int)threadIdx.x + k * kThreads, n16 - 1)] = r.w[k];
+      raw[min((int)threadIdx.x + k * NT, n16 - 1)] = r.w[k];
     }
     TS_MARK(20);
     __syncthreads();
@@ -102,9 +103,9 @@ struct ScoreLanes {
 // (rstep = PPW: the pages [base, base + PPI); larger when the groups of PPW pages
 // are dealt out in turn to several workgroups).  Rows up to Pmax are always
 // readable (whatever they hold), so the loads do not wait for the sequence length.
-template <int D, bool kHalf = false>
+template <int D, bool kHalf = false, int NW = kWaves>
 struct MetaTile {
-  static constexpr int U = ScoreLanes<D, kHalf>::U;
+  static constexpr int U = ScoreLanes<D, kHalf, NW>::U;
   uint4 mn[U], mx[U];
 
   // Plimit >= 1.  Pages at or past Plimit read row Plimit - 1 instead (no branch
@@ -125,7 +126,7 @@ struct MetaTile {
   // one page of the tile); pages >= Pb get -inf.  patch(min_row, max_row, page) may first
   // amend the row chunks this lane holds (a token appended in the same launch).
   template <typename Patch, typename Sink>
-  __device__ __forceinline__ void reduce(const ScoreLanes<D, kHalf>& ql, int base, int Pb, int Pmax,
+  __device__ __forceinline__ void reduce(const ScoreLanes<D, kHalf, NW>& ql, int base, int Pb, int Pmax,
                                          int rstep, Patch patch, Sink sink) {
     constexpr int LPR = ScoreLanes<D, kHalf>::LPR;
     static_assert(U == 4, "group_sum4_f64 folds four rows");
@@ -152,18 +153,18 @@ struct MetaTile {
 // in general the sequence's groups of PPW pages are dealt out in turn to gs
 // parties, and the caller, party goff, gets the groups (it * U + u) * gs + goff:
 // its share is then spread as evenly as can be over the whole sequence.
-template <int D, bool kHalf = false>
+template <int D, bool kHalf = false, int NW = kWaves>
 struct ScanRegs {
-  typename ScoreLanes<D, kHalf>::QueryRegs q;
-  MetaTile<D, kHalf> tile;
+  typename ScoreLanes<D, kHalf, NW>::QueryRegs q;
+  MetaTile<D, kHalf, NW> tile;
 };
 
-template <int D, bool kHalf>
-__device__ __forceinline__ void scan_issue_query(ScanRegs<D, kHalf>& r, const uint16_t* q_group, int G) {
-  ScoreLanes<D, kHalf>::issue_query(r.q, q_group, G);
+template <int D, bool kHalf, int NW>
+__device__ __forceinline__ void scan_issue_query(ScanRegs<D, kHalf, NW>& r, const uint16_t* q_group, int G) {
+  ScoreLanes<D, kHalf, NW>::issue_query(r.q, q_group, G);
 }
-template <int D, bool kHalf>
-__device__ __forceinline__ void scan_issue_tile(ScanRegs<D, kHalf>& r, const uint16_t* pmin_u,
+template <int D, bool kHalf, int NW>
+__device__ __forceinline__ void scan_issue_tile(ScanRegs<D, kHalf, NW>& r, const uint16_t* pmin_u,
                                                 const uint16_t* pmax_u, int Pmax, int first_iter,
                                                 int gs = 1, int goff = 0) {
   constexpr int PPW = ScoreLanes<D, kHalf>::PPW, PPI = ScoreLanes<D, kHalf>::PPI;
@@ -187,8 +188,8 @@ __device__ __forceinline__ void scan_issue_tile(ScanRegs<D, kHalf>& r, const uin
 // fetch AND the reduction it overlaps with, two copies of the reduction, so that
 // no load is issued where there is no next tile, measured 0.7 us slower on the
 // 16-sequence configuration.)
-template <int D, bool kBranchless, bool kHalf, typename AfterQuery, typename Patch, typename Sink>
-__device__ __forceinline__ void scan_finish(ScanRegs<D, kHalf>& r, const uint16_t* pmin_u,
+template <int D, bool kBranchless, bool kHalf, int NW, typename AfterQuery, typename Patch, typename Sink>
+__device__ __forceinline__ void scan_finish(ScanRegs<D, kHalf, NW>& r, const uint16_t* pmin_u,
                                             const uint16_t* pmax_u, int G, int Pmax, int first_iter,
                                             int iter_stride, unsigned char* q_stage,
                                             AfterQuery after_query, Patch patch, Sink sink,
@@ -196,7 +197,7 @@ __device__ __forceinline__ void scan_finish(ScanRegs<D, kHalf>& r, const uint16_
   constexpr int PPW = ScoreLanes<D, kHalf>::PPW, PPI = ScoreLanes<D, kHalf>::PPI;
   const int rstep = PPW * gs;
   TS_MARK(19);
-  ScoreLanes<D, kHalf> ql;
+  ScoreLanes<D, kHalf, NW> ql;
   ql.finish_query(r.q, G, q_stage);
   TS_MARK(16);
   const int Pb = after_query();
@@ -213,7 +214,7 @@ __device__ __forceinline__ void scan_finish(ScanRegs<D, kHalf>& r, const uint16_
     // of the barrier that follows (measured, with the arrival count below: 0.3-0.5 us).
     do {
       const int next = base + iter_stride * PPI * gs;
-      MetaTile<D, kHalf> cur = r.tile;
+      MetaTile<D, kHalf, NW> cur = r.tile;
       r.tile.load(pmin_u, pmax_u, next, max(Pb, 1), rstep);
       cur.reduce(ql, base, Pb, min(Pmax, limit), rstep, patch, sink);
       base = next;
@@ -221,7 +222,7 @@ __device__ __forceinline__ void scan_finish(ScanRegs<D, kHalf>& r, const uint16_
   } else {
     while (base < limit) {
       const int next = base + iter_stride * PPI * gs;
-      MetaTile<D, kHalf> cur = r.tile;
+      MetaTile<D, kHalf, NW> cur = r.tile;
       if (next < Pb) r.tile.load(pmin_u, pmax_u, next, Pb, rstep);
       cur.reduce(ql, base, Pb, Pmax, rstep, patch, sink);
       base = next;
@@ -239,10 +240,10 @@ __device__ __forceinline__ void score_pages_waves(const uint16_t* pmin_u, const 
                                                   unsigned char* q_stage, IssueExtra issue_extra,
                                                   AfterQuery after_query, Sink sink) {
   ScanRegs<D, kHalf> r;
-  scan_issue_query<D, kHalf>(r, q_group, G);
+  scan_issue_query(r, q_group, G);
   issue_extra();
-  scan_issue_tile<D, kHalf>(r, pmin_u, pmax_u, Pmax, first_iter);
-  scan_finish<D, true, kHalf>(r, pmin_u, pmax_u, G, Pmax, first_iter, iter_stride, q_stage, after_query,
+  scan_issue_tile(r, pmin_u, pmax_u, Pmax, first_iter);
+  scan_finish<D, true>(r, pmin_u, pmax_u, G, Pmax, first_iter, iter_stride, q_stage, after_query,
                        [](uint4&, uint4&, int) {}, sink);
 }
 

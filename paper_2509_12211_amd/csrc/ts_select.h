@@ -47,18 +47,20 @@ struct ForcedPages {
 
 constexpr int kRadixBits = 11;
 constexpr int kRadixBins = 1 << kRadixBits;
-static_assert(TS_MAX_PAGES_PER_SEQ / kThreads <= 64, "a thread's chunk must fit a 64-bit mask");
 
 // Keys live in LDS thread-chunked: thread t owns pages t*C .. t*C+C-1 (C =
-// ceil(Pb / kThreads)), stored at t*stride + i with an odd stride, so that both
+// ceil(Pb / threads)), stored at t*stride + i with an odd stride, so that both
 // "every thread reads its i-th key" and "consecutive lanes write consecutive
 // pages" are free of bank conflicts.
 struct KeyLayout {
   int C, stride;
   uint32_t magic;  // ceil(2^32 / C): j / C == umulhi(j, magic) for j < 2^20
+  template <int NW>
   __device__ __forceinline__ static KeyLayout make(int Pb) {
+    constexpr int NT = NW * kWave;
+    static_assert(TS_MAX_PAGES_PER_SEQ / NT <= 64, "a thread's chunk must fit a 64-bit mask");
     KeyLayout k;
-    k.C = max(1, (Pb + kThreads - 1) / kThreads);
+    k.C = max(1, (Pb + NT - 1) / NT);
     k.stride = k.C | 1;
     // (= ceil(2^32 / C) for every C >= 2, with a 32-bit division)
     k.magic = k.C == 1 ? 0u : 0xffffffffu / (uint32_t)k.C + 1u;
@@ -77,17 +79,19 @@ struct SelectLds {
   uint32_t* cand;  // [2 * kMaxCandidates]  (key, page) of the pages in the cut-off bin
 };
 constexpr int kMaxCandidates = 32;
-constexpr size_t select_key_words(int Pmax) {
-  // kThreads chunks of (C | 1) words, C = ceil(Pmax / kThreads), padded to 16 bytes
-  return (size_t)((kThreads * ((((Pmax + kThreads - 1) / kThreads)) | 1) + 3) / 4 * 4);
+constexpr size_t select_key_words(int Pmax, int NW) {
+  // a chunk of (C | 1) words per thread, C = ceil(Pmax / threads), padded to 16 bytes
+  const int NT = NW * kWave;
+  return (size_t)((NT * ((((Pmax + NT - 1) / NT)) | 1) + 3) / 4 * 4);
 }
-constexpr size_t select_lds_bytes(int Pmax) {
-  return select_key_words(Pmax) * 4 + kRadixBins * 4 + 64 * 4 + 2 * kMaxCandidates * 4;
+constexpr size_t select_lds_bytes(int Pmax, int NW) {
+  return select_key_words(Pmax, NW) * 4 + kRadixBins * 4 + 64 * 4 + 2 * kMaxCandidates * 4;
 }
+template <int NW>
 __device__ __forceinline__ SelectLds carve_select(unsigned char* smem, int Pmax) {
   SelectLds L;
   L.keys = reinterpret_cast<uint32_t*>(smem);
-  L.hist = L.keys + select_key_words(Pmax);
+  L.hist = L.keys + select_key_words(Pmax, NW);
   L.red = reinterpret_cast<int*>(L.hist + kRadixBins);
   L.cand = reinterpret_cast<uint32_t*>(L.red + 64);
   return L;
@@ -104,19 +108,27 @@ __device__ __forceinline__ int bin_slot_index(int k) {
 }
 static_assert(kRadixBins == 64 * 32, "slot layout written for 64 lanes x 32 slots");
 
-// Clears the bins and the candidate count; all threads, a barrier before the
-// first count.
+// Clears the bins (16-byte stores; all threads, a barrier before the next count).
+template <int NW>
+__device__ __forceinline__ void clear_bins(const SelectLds& L) {
+  static_assert(kRadixBins % (4 * NW * kWave) == 0, "whole rounds of the workgroup");
+#pragma unroll
+  for (int i = 0; i < kRadixBins / 4; i += NW * kWave)
+    reinterpret_cast<uint4*>(L.hist)[i + threadIdx.x] = make_uint4(0, 0, 0, 0);
+}
+// The bins and the candidate count.
+template <int NW>
 __device__ __forceinline__ void select_clear(const SelectLds& L) {
-  reinterpret_cast<uint4*>(L.hist)[threadIdx.x] = make_uint4(0, 0, 0, 0);
-  static_assert(kRadixBins == 4 * kThreads, "one 16-byte store per thread clears the bins");
+  clear_bins<NW>(L);
   if (threadIdx.x == 0) L.red[40] = 0;
 }
 // First half of the selection, to be called by all threads BEFORE the barrier
 // that makes the keys visible: clears the bins and deposits each wave's share
 // of the key range.  tmin / tmax: this thread's share of the min / max over ALL
 // keys (any partition over the threads; 0xffffffff / 0 if it saw none).
+template <int NW>
 __device__ __forceinline__ void select_begin(const SelectLds& L, uint32_t tmin, uint32_t tmax) {
-  select_clear(L);
+  select_clear<NW>(L);
   const uint32_t a = wave_min_u32(tmin), b = wave_max_u32(tmax);
   if (lane_id() == 0) {
     L.red[16 + wave_id()] = (int)a;
@@ -166,12 +178,13 @@ struct BinMap {
 };
 
 // The key range the waves deposited with select_begin (a barrier in between).
+template <int NW>
 __device__ __forceinline__ void select_deposited_range(const SelectLds& L, uint32_t& kmin,
                                                        uint32_t& kmax) {
   kmin = 0xffffffffu;
   kmax = 0u;
 #pragma unroll
-  for (int w = 0; w < kWaves; ++w) {
+  for (int w = 0; w < NW; ++w) {
     kmin = min(kmin, (uint32_t)L.red[16 + w]);
     kmax = max(kmax, (uint32_t)L.red[24 + w]);
   }
@@ -181,7 +194,7 @@ __device__ __forceinline__ void select_deposited_range(const SelectLds& L, uint3
 
 // Second half: keeps the Kb largest of the Pb keys in L.keys (ties: lower page
 // first) and calls emit(rank, page) for every kept page, rank = its position in
-// ascending page order.  All kThreads threads must call; Pb, Kb
+// ascending page order.  All threads must call; Pb, Kb
 // workgroup-uniform; select_begin and a barrier must precede the call.
 //
 // Stage 1 spreads the pages over the 2048 bins LINEARLY in score,
@@ -206,28 +219,29 @@ __device__ __forceinline__ void select_deposited_range(const SelectLds& L, uint3
 // key kForcedKey itself.  The map may come from an estimate of the range: if the
 // cut then falls into an end bin crowded with the keys outside the estimate,
 // stage 2b's exact passes resolve it like any other crowded bin.
-template <bool kCounted = false, typename Emit>
+template <int NW, bool kCounted = false, typename Emit>
 __device__ __forceinline__ void select_topk_lds(const SelectLds& L, const KeyLayout& kl, int Pb,
                                                 int Kb, const ForcedPages& fp, Emit emit,
                                                 const BinMap counted = BinMap{0.f, 0.f}) {
   const int tid = threadIdx.x, lane = lane_id(), wave = wave_id();
-  static_assert(kWaves <= 8, "red[] layout holds 8 wave slots");
+  static_assert(NW <= 8, "red[] layout holds 8 wave slots");
+  constexpr int NT = NW * kWave;
   constexpr int kBatch = 8;  // LDS reads issued together
   Pb = uniform(Pb);
   Kb = uniform(Kb);
   if (Kb <= 0) return;
   if (Kb >= Pb) {  // everything is kept
-    for (int j = tid; j < Pb; j += kThreads) emit(j, j);
+    for (int j = tid; j < Pb; j += NT) emit(j, j);
     return;
   }
   if (fp.count >= Kb) {  // the always-kept pages fill the budget: the Kb lowest ids of them
-    for (int r = tid; r < Kb; r += kThreads) emit(r, r < fp.first ? r : fp.last_begin + (r - fp.first));
+    for (int r = tid; r < Kb; r += NT) emit(r, r < fp.first ? r : fp.last_begin + (r - fp.first));
     return;
   }
   const bool any_forced = !kCounted && uniform(fp.count) != 0;
   if (any_forced) {   // (uniform) the keys of the always-kept pages, over what the caller wrote
-    for (int j = tid; j < fp.first; j += kThreads) L.keys[kl.at(j)] = kForcedKey;
-    for (int j = fp.last_begin + tid; j < Pb; j += kThreads) L.keys[kl.at(j)] = kForcedKey;
+    for (int j = tid; j < fp.first; j += NT) L.keys[kl.at(j)] = kForcedKey;
+    for (int j = fp.last_begin + tid; j < Pb; j += NT) L.keys[kl.at(j)] = kForcedKey;
     __syncthreads();
   }
   const int C = kl.C;
@@ -235,9 +249,6 @@ __device__ __forceinline__ void select_topk_lds(const SelectLds& L, const KeyLay
   const int my_n = max(0, min(C, Pb - my_first));     // pages in it
   const uint32_t* my_keys = L.keys + tid * kl.stride;
 
-  auto clear_bins = [&] {
-    reinterpret_cast<uint4*>(L.hist)[tid] = make_uint4(0, 0, 0, 0);
-  };
   // Block-wide min / max from per-thread partials; one barrier.
   auto block_range = [&](uint32_t& lo, uint32_t& hi) {
     uint32_t a = wave_min_u32(lo), b = wave_max_u32(hi);
@@ -245,7 +256,7 @@ __device__ __forceinline__ void select_topk_lds(const SelectLds& L, const KeyLay
     if (lane == 0) { L.red[16 + wave] = (int)a; L.red[24 + wave] = (int)b; }
     __syncthreads();
 #pragma unroll
-    for (int w = 0; w < kWaves; ++w) {
+    for (int w = 0; w < NW; ++w) {
       a = min(a, (uint32_t)L.red[16 + w]);
       b = max(b, (uint32_t)L.red[24 + w]);
     }
@@ -301,7 +312,7 @@ __device__ __forceinline__ void select_topk_lds(const SelectLds& L, const KeyLay
   // ---- stage 1: linear bins over [s_min, s_max] ------------------------------
   // (counted by the caller: the keys' range is not known here, and need not be)
   uint32_t kmin = 0u, kmax = 0xffffffffu;
-  if (!kCounted) select_deposited_range(L, kmin, kmax);
+  if (!kCounted) select_deposited_range<NW>(L, kmin, kmax);
   TS_MARK(10);
   const BinMap bins = kCounted ? counted : BinMap::exact(kmin, kmax);
   auto linear_slot = [&](uint32_t k) { return bins.template slot<kCounted>(k); };
@@ -344,7 +355,7 @@ __device__ __forceinline__ void select_topk_lds(const SelectLds& L, const KeyLay
       if (lane == kWave - 1) L.red[wave] = incl;   // slots 0..7 are used by nothing else
       __syncthreads();
 #pragma unroll
-      for (int w = 0; w < kWaves; ++w) {
+      for (int w = 0; w < NW; ++w) {
         const int t = uniform(L.red[w]);
         if (w < wave) incl += t;
       }
@@ -388,7 +399,7 @@ __device__ __forceinline__ void select_topk_lds(const SelectLds& L, const KeyLay
     } else {
       // ---- stage 2b: exact radix passes on the keys of the cut-off bin ----------
       __syncthreads();  // every wave has read the stage-1 counts
-      clear_bins();
+      clear_bins<NW>(L);
       clo = 0xffffffffu;
       chi = 0u;
       for_my_keys([&](uint32_t k, int) {
@@ -411,7 +422,7 @@ __device__ __forceinline__ void select_topk_lds(const SelectLds& L, const KeyLay
         bits = s;
         if (cnt2 == need || bits == 0) break;
         __syncthreads();  // every wave has read the counts
-        clear_bins();
+        clear_bins<NW>(L);
         __syncthreads();
       }
     }
@@ -438,7 +449,7 @@ __device__ __forceinline__ void select_topk_lds(const SelectLds& L, const KeyLay
   if (lane == kWave - 1) L.red[wave] = incl;   // slots 0..7 are used by nothing else
   __syncthreads();
 #pragma unroll
-  for (int w = 0; w < kWaves; ++w) {
+  for (int w = 0; w < NW; ++w) {
     const int t = uniform(L.red[w]);
     if (w < wave) incl += t;
   }

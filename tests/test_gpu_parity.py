@@ -457,6 +457,35 @@ def test_many_units_loop_build(oracle, built, name, fmt):
         sess.sel.fill_(-7)
 
 
+@pytest.mark.parametrize("name", list(MANY_UNITS))
+@pytest.mark.parametrize("fmt", FORMATS)
+def test_many_large_units_loop_build(oracle, built, name, fmt):
+    """Batches of more units than compute units whose units may be large (room for enough
+    selected pages in the list) go through the looping build, whatever they hold; the same
+    layouts with a short list (above) run one small workgroup per unit."""
+    spec = wl.scaled(MANY_UNITS[name], kv=fmt)
+    print(f"[case] many large units {name} {fmt}", flush=True)
+    w = wl.make_workload(spec, DEV, seed=405, n_q=2, n_new=2)
+    topk = w.topk
+    w.K_max = (2 << 20) // (spec.S * 4 * spec.d) + 3
+    sess = Session(w)
+    ts.build_page_meta(sess.layout)
+    scale = 1.0 / math.sqrt(spec.d)
+    n_units = spec.B * spec.Hkv
+    rng = np.random.default_rng(11)
+    picks = sorted(set(rng.integers(0, n_units, 10).tolist()) | {0, 255, 256, n_units - 1})
+    units = [(u // spec.Hkv, u % spec.Hkv) for u in picks]
+    for i in range(2):
+        call = (lambda *a, **k: ts.append_and_decode(sess.layout, w.k_new[i], w.v_new[i], *a, **k)) if i else \
+               (lambda *a, **k: ts.query_aware_decode(sess.layout, *a, **k))
+        call(w.q[i], topk, w.K_max, scale, sess.out, sess.ws, topk_per_seq=w.topk_per_seq,
+             scores_out=sess.scores, sel_out=sess.sel, sel_count_out=sess.sel_count)
+        compare_units(oracle, sess, units, scale, q_idx=i, what=f"{name} launch {i}")
+        assert torch.isfinite(sess.out).all() and int(sess.sel[:, :, 0].min()) >= 0
+        sess.out.fill_(float("nan"))
+        sess.sel.fill_(-7)
+
+
 CLUSTER_LOOP = {
     # 129 to 255 units in clusters of two or more workgroups (forced: the library's own
     # plan keeps a launch resident and would give these batches one workgroup per unit):
