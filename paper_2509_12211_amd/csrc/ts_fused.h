@@ -32,8 +32,6 @@ namespace ts {
 // waves) per compute unit; with thousands of units g = 1 and nothing is exchanged
 // between workgroups at all.
 constexpr int kCtrlWords = 64;   // control words at the head of the workspace
-constexpr int kCtrlTicket = 0;   // next unit (fused kernel, g == 1, more units than workgroups)
-constexpr int kCtrlExit = 1;     // workgroups that have finished taking tickets
 constexpr int kCtrlError = 2;    // sticky: a bounded wait expired
 constexpr int kCtrlEpoch = 16;   // launches of the fused kernel with clusters so far (own 64-byte line)
 constexpr int kCtrlArrive = 32;  // workgroups of the current launch that have read the epoch (own line)
@@ -177,8 +175,8 @@ __global__ __launch_bounds__(kThreads) void sparse_attention_kernel(AttendParams
 // steers a branch around a barrier is pinned uniform.
 // ---------------------------------------------------------------------------
 //
-// kLoop = false is the build for launches in which every cluster has exactly one
-// unit (units * g workgroups all resident: every latency-bound shape).  Without
+// kLoop = false is the build for launches in which every workgroup has exactly one
+// unit (all but clusters of a forced size that do not fit the device).  Without
 // the loop around the body the compiler has nothing to hoist: with it, every
 // unit-independent value of the whole body (several hundred instructions, most
 // of them spilled at once) is computed ahead of the first unit, that is ahead of
@@ -195,15 +193,19 @@ __global__ __launch_bounds__(kThreads) void sparse_attention_kernel(AttendParams
 // registers of that occupancy instead of saving registers for waves that never
 // come (measured: 0.5 us of 26 on the 16-sequence configuration).
 //
+// NW: waves per workgroup.  kCounted: how the attention's ring of fragments waits (see
+// attend_split).
+//
 // kCluster says whether a unit is shared by several workgroups (p.g > 1): the
 // build for one workgroup per unit carries nothing of the exchange, the build
 // for clusters nothing of the selection's stand-alone first stages.
-template <int NW, int D, int S, bool kLoop, bool kApp, bool kInt8, bool kHalf, bool kCluster>
+template <int NW, int D, int S, bool kLoop, bool kApp, bool kInt8, bool kHalf, bool kCluster,
+          bool kCounted = !kLoop>
 __device__ __forceinline__ void decode_units(const FusedParams& p) {
   constexpr int NT = NW * kWave;
   static_assert(!(kLoop && kApp), "the append is folded only into the loop-free build");
+  static_assert(!kLoop || kCluster, "a single workgroup per unit needs no loop");
   extern __shared__ __align__(16) unsigned char smem[];
-  __shared__ int s_flag;
   TS_MARK_INIT();
   TS_MARK(22);
   const AttendParams& at = p.at;
@@ -233,19 +235,7 @@ __device__ __forceinline__ void decode_units(const FusedParams& p) {
   unsigned char* q_stage = reinterpret_cast<unsigned char*>(bt_lds) +
                            ((size_t)Pmax * 4 + (size_t)at.chunk * 4 + 15) / 16 * 16;
   constexpr bool exchange = kCluster;
-  // With one workgroup per unit and more units than workgroups (long ragged
-  // batches) the units are handed out from a counter as workgroups become
-  // free: a unit then takes tens of microseconds, so the counter is not
-  // contended, and the spread of sequence lengths no longer decides the finish
-  // time.  Nothing ever waits on a ticket holder.
-  const bool dynamic = kLoop && !exchange && p.units > (int)gridDim.x;
   int u = padding ? 0 : where.cluster;
-  if (dynamic) {
-    if (threadIdx.x == 0) s_flag = atomic_add_agent(&p.ctrl[kCtrlTicket], 1);
-    __syncthreads();
-    u = uniform(s_flag);
-    __syncthreads();
-  }
 
   // The first loads of a unit (sequence length, K, query rows, block-table row,
   // first metadata tile) are sent out ahead of everything else: for the first
@@ -393,9 +383,8 @@ __device__ __forceinline__ void decode_units(const FusedParams& p) {
     // the sequence length.  The count's value is not asked for: an atomic that
     // returns one would hold this wave, and with it the barrier below, for a trip
     // to memory and back.
-    if (!kLoop || exchange) {
-      if (!counted && threadIdx.x == 0 && (exchange || app))
-        (void)atomic_add_agent(&p.ctrl[kCtrlArrive], 1);
+    if (exchange || app) {
+      if (!counted && threadIdx.x == 0) (void)atomic_add_agent(&p.ctrl[kCtrlArrive], 1);
       counted = true;
     }
 
@@ -543,22 +532,14 @@ __device__ __forceinline__ void decode_units(const FusedParams& p) {
     // words; the cluster's last member (its chunk of the list is the one that
     // can be short) keeps its own in registers, polls for the others and writes
     // the output.  Nobody else waits for anything.
-    const bool merged = attend_split<NW, D, S, !kLoop, kApp, kInt8, kHalf, true>(
+    const bool merged = attend_split<NW, D, S, kCounted, kApp, kInt8, kHalf, true>(
         at, b, h, member, count, L, nt, [&](int i) { return my_sel[i]; },
         [&](int j) { return bt_lds[j]; }, reinterpret_cast<float*>(smem), exchange ? tag : 0u,
         nullptr, p.spin_limit, &qop);
     TS_MARK(6);
     if (!merged) atomic_store_agent(&p.ctrl[kCtrlError], 1);
     if (!kLoop) break;
-    if (dynamic) {
-      __syncthreads();
-      if (threadIdx.x == 0) s_flag = atomic_add_agent(&p.ctrl[kCtrlTicket], 1);
-      __syncthreads();
-      u = uniform(s_flag);
-      __syncthreads();
-    } else {
-      u += n_clusters;
-    }
+    u += n_clusters;
     if (u >= p.units) break;
     issue_unit(u);
   }
@@ -566,7 +547,7 @@ __device__ __forceinline__ void decode_units(const FusedParams& p) {
   // the count shows that every workgroup has read the epoch word and, with one unit per
   // workgroup, its sequence length (all of them did so microseconds ago), its first
   // wave re-arms the count, advances the epoch and (append mode) the lengths.
-  if ((!kLoop || exchange) && (exchange || app) && blockIdx.x == 0 && wave_id() == 0) {
+  if ((exchange || app) && blockIdx.x == 0 && wave_id() == 0) {
     if (!wait_at_least(&p.ctrl[kCtrlArrive], p.n_arrive, p.spin_limit))
       atomic_store_agent(&p.ctrl[kCtrlError], 1);
     if (lane_id() == 0) {
@@ -581,13 +562,6 @@ __device__ __forceinline__ void decode_units(const FusedParams& p) {
       }
     }
   }
-  if (dynamic) {  // the last workgroup out re-arms the counters for the next launch
-    __syncthreads();
-    if (threadIdx.x == 0 && atomic_add_agent(&p.ctrl[kCtrlExit], 1) == (int)gridDim.x - 1) {
-      atomic_store_agent(&p.ctrl[kCtrlTicket], 0);
-      atomic_store_agent(&p.ctrl[kCtrlExit], 0);
-    }
-  }
 }
 
 template <int D, int S, bool kLoop, bool kApp, bool kInt8, bool kHalf, bool kCluster>
@@ -596,15 +570,32 @@ query_aware_decode_kernel(FusedParams p) {
   decode_units<kWaves, D, S, kLoop, kApp, kInt8, kHalf, kCluster>(p);
 }
 
+// Batches of more units than compute units whose units are not small: one workgroup of eight
+// waves per unit, one resident per compute unit, the next one handed out by the hardware as
+// one ends, so that the spread of sequence lengths does not decide the finish time and
+// workgroups are in different phases at any time.  (Workgroups that stayed and took the
+// units from a counter, the looping build, needed all unit-independent values of the body
+// ahead of the loop and spilled with 128 channels and pages of 32 and 64: 80 layouts of
+// 272-900 units 4 % slower on average and up to 20 %, the 64-sequence batch 890 against
+// 880 us.)  Bound by HBM: 6.3 TB/s on the 64-sequence batch.
+// With 128 channels of 16 bits and small pages the ring waits for everything in flight
+// before each fragment (see attend_split).
+template <int D, int S, bool kInt8, bool kHalf>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void
+many_units_decode_kernel(FusedParams p) {
+  constexpr bool kCounted = kInt8 || D == 64 || S > 16;
+  decode_units<kWaves, D, S, false, false, kInt8, kHalf, false, kCounted>(p);
+}
+
 // Batches of more units than compute units, as long as a unit is small (kSmallUnitBytes): one
 // workgroup of four waves per unit, two of them resident per compute unit, handed out by the
 // hardware.  Such a unit is bound by the chain of its phases, 10-13 us of which little is
 // data: two half-size workgroups run two such chains side by side on a compute unit, where
-// the looping build runs the units of a compute unit one after the other, and the loop-free
-// code starts its first loads 1 us earlier.  40 layouts of 264 to 1568 units: 1.0 to 2.4
+// workgroups of eight waves run them one after the other.  Against the looping build that
+// did so, 40 layouts of 264 to 1568 units: 1.0 to 2.4
 // times faster, geometric mean 1.52 (504 units of 176 pages, 6 kept: 35.2 -> 15.7 us).
-// An append runs as a kernel of its own in front, as for the looping build: folding it in
-// gained 3 % here and would make the first workgroup wait for ones not yet resident.
+// An append runs as a kernel of its own in front: folding it in gained 3 % here and would
+// make the first workgroup wait for ones not yet resident.
 constexpr int kSmallWaves = 4;
 template <int D, int S, bool kInt8, bool kHalf>
 __global__ __launch_bounds__(kSmallWaves * kWave) __attribute__((amdgpu_waves_per_eu(2, 2))) void
@@ -677,64 +668,77 @@ static int resident_capacity(KernelT kernel, size_t lds) {
     default: CALL(DD, 64); break;     \
   }
 
-// One unit per cluster and everything resident: the loop-free build, which
-// also exists with the append folded in.  Otherwise (thousands of
-// units, bound by bandwidth) the looping build; an append then runs as a launch
-// of its own in front of it: the looping build has no registers to spare for
-// it, and against hundreds of microseconds the extra launch does not count.
-// max_resident: workgroups the launch may count on being resident together.
-// Many small units (pl.small_units): a workgroup of half the size per unit, all launched at
-// once; as many as fit are resident and none waits for another.
+// The launches below: max_resident is the number of workgroups the launch may count on being
+// resident together.  An append is folded into the launch where all units are worked on at
+// once; otherwise it runs as a kernel of its own in front: those launches are bound by
+// bandwidth or have the latency of one unit hidden behind others.
+
+// One workgroup per unit (pl.g == 1); no workgroup waits for another unit's.
 template <int D, int S, int kFmt>
-static int launch_small_units(const ts_layout* layout, FusedParams& p, const Plan& pl,
-                              const void* k_new, const void* v_new, void* stream) {
+static int launch_single(const ts_layout* layout, FusedParams& p, const Plan& pl, const void* k_new,
+                         const void* v_new, int max_resident, void* stream) {
   constexpr bool kInt8 = kFmt == TS_KV_INT8, kHalf = kFmt == TS_KV_FP16;
-  auto kernel = small_units_decode_kernel<D, S, kInt8, kHalf>;
+  hipStream_t s = (hipStream_t)stream;
+  auto one_kernel = query_aware_decode_kernel<D, S, false, false, kInt8, kHalf, false>;
+  auto app_kernel = query_aware_decode_kernel<D, S, false, true, kInt8, kHalf, false>;
+  auto small_kernel = small_units_decode_kernel<D, S, kInt8, kHalf>;
+  auto many_kernel = many_units_decode_kernel<D, S, kInt8, kHalf>;
+  const unsigned grid = (unsigned)pl.units;
   int st;
+  p.xcds = 0;
+  p.n_arrive = pl.units;
+  if (!pl.small_units) {
+    auto kernel = k_new ? app_kernel : one_kernel;
+    if ((st = allow_lds(kernel, pl.lds_fused)) != TS_OK) return st;
+    int cap = resident_capacity(kernel, pl.lds_fused);
+    if (cap > max_resident) cap = max_resident;
+    if (pl.units <= cap) {
+      kernel<<<grid, kThreads, pl.lds_fused, s>>>(p);
+      return TS_OK;
+    }
+  }
   if (k_new) {
     if ((st = ts_append_token_meta(layout, k_new, v_new, 1, stream)) != TS_OK) return st;
     p.k_new = p.v_new = nullptr;
   }
+  auto kernel = pl.small_units ? small_kernel : many_kernel;
   if ((st = allow_lds(kernel, pl.lds_fused)) != TS_OK) return st;
-  p.xcds = 0;
-  p.n_arrive = 0;
-  kernel<<<(unsigned)pl.units, kSmallWaves * kWave, pl.lds_fused, (hipStream_t)stream>>>(p);
+  kernel<<<grid, pl.small_units ? kSmallWaves * kWave : kThreads, pl.lds_fused, s>>>(p);
   return TS_OK;
 }
 
-// kCluster: pl.g > 1.
-template <int D, int S, int kFmt, bool kCluster>
-static int launch_fused_shape(const ts_layout* layout, FusedParams& p, const Plan& pl,
-                              const void* k_new, const void* v_new, int max_resident,
-                              void* stream) {
+// A cluster of pl.g > 1 workgroups per unit: the loop-free build where all clusters are
+// resident at once, otherwise (a forced cluster size) the looping one, each cluster taking
+// several units in turn.
+template <int D, int S, int kFmt>
+static int launch_clusters(const ts_layout* layout, FusedParams& p, const Plan& pl,
+                           const void* k_new, const void* v_new, int max_resident, void* stream) {
   hipStream_t s = (hipStream_t)stream;
   constexpr bool kInt8 = kFmt == TS_KV_INT8, kHalf = kFmt == TS_KV_FP16;
-  auto loop_kernel = query_aware_decode_kernel<D, S, true, false, kInt8, kHalf, kCluster>;
-  auto one_kernel = query_aware_decode_kernel<D, S, false, false, kInt8, kHalf, kCluster>;
-  auto app_kernel = query_aware_decode_kernel<D, S, false, true, kInt8, kHalf, kCluster>;
+  auto loop_kernel = query_aware_decode_kernel<D, S, true, false, kInt8, kHalf, true>;
+  auto one_kernel = query_aware_decode_kernel<D, S, false, false, kInt8, kHalf, true>;
+  auto app_kernel = query_aware_decode_kernel<D, S, false, true, kInt8, kHalf, true>;
   int st;
   if ((st = allow_lds(loop_kernel, pl.lds_fused)) != TS_OK ||
       (st = allow_lds(one_kernel, pl.lds_fused)) != TS_OK ||
       (st = allow_lds(app_kernel, pl.lds_fused)) != TS_OK)
     return st;
-  const bool fold_append = k_new != nullptr;
-  int cap1 = resident_capacity(fold_append ? app_kernel : one_kernel, pl.lds_fused);
+  int cap1 = resident_capacity(k_new ? app_kernel : one_kernel, pl.lds_fused);
   if (cap1 > max_resident) cap1 = max_resident;
   const bool one_unit_each = pl.units * pl.g <= cap1;
-  if (k_new && !(one_unit_each && fold_append)) {
+  if (k_new && !one_unit_each) {
     if ((st = ts_append_token_meta(layout, k_new, v_new, 1, stream)) != TS_OK) return st;
     p.k_new = p.v_new = nullptr;
   }
   const int xcds = num_xcds();
   p.xcds = 0;
-  p.n_arrive = 0;
   if (one_unit_each) {
     unsigned grid = (unsigned)(pl.units * pl.g);
     p.n_arrive = (int)grid;
     // clusters one per XCD: the grid is padded to whole rounds of the XCDs if the
     // padded launch is still resident at once
     const unsigned padded = (unsigned)((pl.units + xcds - 1) / xcds * xcds * pl.g);
-    if (kCluster && xcds > 1 && (int)padded <= cap1) {
+    if (xcds > 1 && (int)padded <= cap1) {
       grid = padded;
       p.xcds = xcds;
       p.div_xcds = make_fast_div(xcds);
@@ -750,7 +754,7 @@ static int launch_fused_shape(const ts_layout* layout, FusedParams& p, const Pla
   int clusters = cap / pl.g;
   if (clusters < 1) return TS_ERR_DEVICE;   // a cluster must be co-resident
   if (clusters > pl.units) clusters = pl.units;
-  if (kCluster && xcds > 1 && clusters >= xcds) {
+  if (xcds > 1 && clusters >= xcds) {
     clusters = clusters / xcds * xcds;
     p.xcds = xcds;
     p.div_xcds = make_fast_div(xcds);
@@ -766,11 +770,9 @@ int launch_fused_format(const ts_layout* layout, FusedParams& p, const Plan& pl,
                         const void* v_new, int max_resident, void* stream) {
   int st = TS_ERR_UNSUPPORTED;
 #define TS_LAUNCH_FUSED(DD, SS)                                                                     \
-  st = pl.small_units ? launch_small_units<DD, SS, kFmt>(layout, p, pl, k_new, v_new, stream)       \
-       : pl.g > 1 ? launch_fused_shape<DD, SS, kFmt, true>(layout, p, pl, k_new, v_new, max_resident, \
-                                                         stream)                                    \
-                : launch_fused_shape<DD, SS, kFmt, false>(layout, p, pl, k_new, v_new,              \
-                                                          max_resident, stream)
+  st = pl.g > 1                                                                                   \
+           ? launch_clusters<DD, SS, kFmt>(layout, p, pl, k_new, v_new, max_resident, stream)       \
+           : launch_single<DD, SS, kFmt>(layout, p, pl, k_new, v_new, max_resident, stream)
   TS_DISPATCH_PAGE(kD, layout->page_size, TS_LAUNCH_FUSED)
 #undef TS_LAUNCH_FUSED
   return st;
