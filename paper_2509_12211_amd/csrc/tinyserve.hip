@@ -30,7 +30,18 @@ constexpr int kDenseTargetWorkgroups = 1024;
 // equal, at 4.7 MB and 15 MB the small one is 6 % and 18 % behind.
 constexpr size_t kSmallUnitBytes = 2 << 20;
 
-static Plan make_plan(const ts_layout* L, int max_topk, int target_workgroups = kTargetWorkgroups) {
+// From this many bytes per workgroup that even shares would save the longest sequence (a
+// guess from how much smaller the pool is than what B full-length sequences would need:
+// the lengths themselves are on the device), a launch goes by shares in proportion to the
+// work.  Working the shares out costs 1 us at the head of the kernel, and where one workgroup
+// per unit would have had nothing to exchange, the exchange 2 us more: twice the bytes there.
+// 140 ragged layouts, line against 0 / 20 / 80 / 200 KB: 0.99 / 1.01 / 1.016 / 1.01 times as
+// fast as without; 24 sequences x 8 KV heads of 512-8192 tokens 45.6 -> 40.5 us, 7 x 8 of
+// 4-50 K 38 -> 31 us, 21 x 8 of 38 K at the longest 137 -> 102 us.
+constexpr int kBalanceBytes = 80 << 10;
+
+static Plan make_plan(const ts_layout* L, int max_topk, int target_workgroups = kTargetWorkgroups,
+                      bool may_balance = true) {
   Plan pl;
   const int G = L->num_q_heads / L->num_kv_heads;
   const int Pmax = L->max_pages_per_seq;
@@ -49,9 +60,10 @@ static Plan make_plan(const ts_layout* L, int max_topk, int target_workgroups = 
   if (g > kMaxCluster) g = kMaxCluster;
   // (Even the shortest configurations measured, 256 pages with 32 kept, are
   // faster spread over a cluster than on one workgroup: 12.5 against 14.0 us.)
+  int forced = 0;
   if (target_workgroups == kTargetWorkgroups) {
     const int tuned = g_tune_splits.load(std::memory_order_relaxed);
-    const int forced = L->cluster_size > 0 ? L->cluster_size : tuned;
+    forced = L->cluster_size > 0 ? L->cluster_size : tuned;
     if (forced > 0) g = forced < kMaxCluster ? forced : kMaxCluster;
   }
   if (g > max_topk) g = max_topk;
@@ -61,32 +73,44 @@ static Plan make_plan(const ts_layout* L, int max_topk, int target_workgroups = 
   // groups per workgroup
   if (L->page_size < 16) pl.chunk = (pl.chunk + 3) / 4 * 4;
   pl.g = (max_topk + pl.chunk - 1) / pl.chunk;
+  const size_t unit_bytes = ((size_t)Pmax + (size_t)max_topk * L->page_size) * 4 * L->head_dim;
+  // The INT8 cache keeps the same partition of a unit over waves and workgroups everywhere: its
+  // operands carry a bias that cancels out of the output, so that with thousands of tokens of
+  // like weight the order of the sums shows in the fourth digit.
+  const bool int8 = L->kv_format == TS_KV_INT8;
+  pl.per_head = kTargetWorkgroups / L->num_kv_heads;
+  pl.balanced = may_balance && !int8 && target_workgroups == kTargetWorkgroups && forced == 0 && L->num_seqs > 1 &&
+                L->num_seqs <= kBalanceSeqs && pl.per_head > L->num_seqs &&
+                (double)unit_bytes / pl.g * (1.0 - (double)L->num_phys_pages / ((double)L->num_seqs * Pmax)) >=
+                    (double)(pl.g > 1 ? kBalanceBytes : 2 * kBalanceBytes);
   size_t off = kCtrlWords * sizeof(int32_t);
   pl.off_unit = off;
   pl.cstride = pl.units <= kCounterPadUnits ? kCounterPadStride : 1;
   off = align_up(off + 2 * (size_t)pl.units * pl.cstride * sizeof(int32_t), 256);
   // (one workgroup per unit exchanges nothing: its scores never leave LDS and its
   // result goes straight to the output)
+  const bool exchange = pl.g > 1 || pl.balanced;
+  size_t parts = (size_t)pl.units * pl.g;
+  if (pl.balanced && parts < (size_t)pl.per_head * L->num_kv_heads) parts = (size_t)pl.per_head * L->num_kv_heads;
   pl.off_scores = off;
-  if (pl.g > 1) off = align_up(off + (size_t)pl.units * Pmax * sizeof(uint64_t), 256);
+  if (exchange) off = align_up(off + (size_t)pl.units * Pmax * sizeof(uint64_t), 256);
   pl.off_part = off;
-  if (pl.g > 1)
-    off = align_up(off + (size_t)pl.units * pl.g * G * (L->head_dim + 2) * sizeof(uint64_t), 256);
+  if (exchange) off = align_up(off + parts * G * (L->head_dim + 2) * sizeof(uint64_t), 256);
   pl.total = off;
   // fused kernel LDS: select scratch (keys, bins), the unit's block-table row,
   // this workgroup's selected pages; the wave-merge area aliases the keys
-  pl.small_units = target_workgroups == kTargetWorkgroups && pl.g == 1 &&
-                   pl.units > kTargetWorkgroups &&
-                   ((size_t)Pmax + (size_t)max_topk * L->page_size) * 4 * L->head_dim <= kSmallUnitBytes;
+  pl.small_units = !int8 && target_workgroups == kTargetWorkgroups && pl.g == 1 &&
+                   pl.units > kTargetWorkgroups && unit_bytes <= kSmallUnitBytes;
   const int waves = pl.small_units ? kSmallWaves : kWaves;
   const size_t lds_sel = select_lds_bytes(Pmax, waves);
+  pl.list = pl.balanced ? (max_topk + 3) / 4 * 4 : pl.chunk;   // (a cluster of one holds the whole list)
   const size_t lds_att = (size_t)waves * G * (L->head_dim + 2) * 4;
   // ... and, in an area of its own, the query staging: a wave that is done
   // scoring starts the selection (which clears the bins) while another may not
   // have picked up its query sums yet, so the two must not share memory
   const size_t lds_query = (size_t)G * L->head_dim * 2 + 2 * (size_t)L->head_dim * 8;
   pl.lds_fused = (lds_sel > lds_att ? lds_sel : lds_att) +
-                 align_up((size_t)Pmax * 4 + (size_t)pl.chunk * 4, 16) + lds_query;
+                 align_up((size_t)Pmax * 4 + (size_t)pl.list * 4, 16) + lds_query;
   return pl;
 }
 
@@ -264,19 +288,24 @@ static int launch_fused(const ts_layout* layout, const void* k_new, const void* 
                         const void* q, int32_t topk, const int32_t* topk_per_seq,
                         int32_t max_topk, float softmax_scale, void* out, float* scores_out,
                         int32_t* sel_out, int32_t* sel_count_out, void* workspace,
-                        size_t workspace_bytes, void* stream) {
+                        size_t workspace_bytes, void* stream, bool may_balance = true) {
   int st = check_layout(layout);
   if (st != TS_OK) return st;
   if (!q || !out || !workspace || !layout->page_min || !layout->page_max) return TS_ERR_NULL;
   if ((st = check_pool(layout)) != TS_OK) return st;
   if (max_topk < 1 || (!topk_per_seq && (topk < 1 || max_topk < topk))) return TS_ERR_SHAPE;
-  Plan pl = make_plan(layout, max_topk);
+  Plan pl = make_plan(layout, max_topk, kTargetWorkgroups, may_balance);
   if (workspace_bytes < pl.total) return TS_ERR_WORKSPACE;
   const int cus = num_compute_units();
   if (cus <= 0) return TS_ERR_DEVICE;
+  const int tuned_per_cu = g_tune_wg_per_cu.load(std::memory_order_relaxed);
+  const int max_resident = cus * (tuned_per_cu > 0 ? tuned_per_cu : 1);
+  if (pl.balanced && pl.per_head * layout->num_kv_heads > max_resident)   // (a part of a device)
+    pl = make_plan(layout, max_topk, kTargetWorkgroups, false);
   unsigned char* ws = static_cast<unsigned char*>(workspace);
   FusedParams p;
   p.at = attend_params(layout, pl, q, out, ws, max_topk, softmax_scale);
+  p.at.chunk = pl.list;
   p.page_min = static_cast<const uint16_t*>(layout->page_min);
   p.page_max = static_cast<const uint16_t*>(layout->page_max);
   p.scores = reinterpret_cast<uint64_t*>(ws + pl.off_scores);
@@ -299,10 +328,8 @@ static int launch_fused(const ts_layout* layout, const void* k_new, const void* 
   p.div_hkv = make_fast_div(layout->num_kv_heads);
   p.div_xcds = make_fast_div(1);
   p.spin_limit = layout->wait_limit > 0 ? layout->wait_limit : kSpinLimit;
-  const int tuned_per_cu = g_tune_wg_per_cu.load(std::memory_order_relaxed);
-  const int per_cu = tuned_per_cu > 0 ? tuned_per_cu : 1;
 #define TS_CALL(FMT, DD) \
-  st = launch_fused_format<FMT, DD>(layout, p, pl, k_new, v_new, cus * per_cu, stream)
+  st = launch_fused_format<FMT, DD>(layout, p, pl, k_new, v_new, max_resident, stream)
   TS_DISPATCH_FORMAT(layout, TS_CALL);
 #undef TS_CALL
   if (st != TS_OK) return st;
@@ -610,13 +637,17 @@ int ts_query_aware_decode_static(const ts_layout* layout, const void* q, int32_t
   const int st = check_layout(layout);
   if (st != TS_OK) return st;
   if (max_topk < 1) return TS_ERR_SHAPE;
-  if (make_plan(layout, max_topk).total > (size_t)TS_STATIC_WORKSPACE_BYTES) return TS_ERR_WORKSPACE;
+  // (shares in proportion to the work need an exchange area for every unit: where it does not
+  // fit the region, clusters of one size)
+  const bool balance = make_plan(layout, max_topk).total <= (size_t)TS_STATIC_WORKSPACE_BYTES;
+  if (!balance && make_plan(layout, max_topk, kTargetWorkgroups, false).total > (size_t)TS_STATIC_WORKSPACE_BYTES)
+    return TS_ERR_WORKSPACE;
   void* ws = nullptr;
   const int sw = static_scratch(&ws);
   if (sw != TS_OK) return sw;
   return launch_fused(layout, nullptr, nullptr, q, topk, topk_per_seq, max_topk, softmax_scale, out,
                       scores_out, sel_out, sel_count_out, ws, (size_t)TS_STATIC_WORKSPACE_BYTES,
-                      stream);
+                      stream, balance);
 }
 
 int ts_append_and_decode(const ts_layout* layout, const void* k_new, const void* v_new,

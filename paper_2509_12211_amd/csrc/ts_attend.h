@@ -699,6 +699,8 @@ __device__ __forceinline__ bool merge_tagged(const uint64_t* part, int G, int g,
 // (lds: NW * G * (D + 2) floats).  With n_split == 1 the normalised result
 // goes to `out`; otherwise the unnormalised partial (o[D], m, l per head) is
 // handed to the combining workgroup through agent-scope stores.
+// The workgroup is part `split` of n_split on the unit; the unit's partials are rows
+// part_row .. part_row + n_split - 1 of the partial area.
 // Ends with a barrier after which `lds` may be reused; on return (n_split > 1)
 // the caller still has to wait for its stores and count its arrival.
 // kLatency: the launch is bound by the latency of its single pass (every workgroup has
@@ -715,8 +717,8 @@ __device__ __forceinline__ bool merge_tagged(const uint64_t* part, int G, int g,
 // returns false if that wait expired.
 template <int NW, int D, int S, bool kLatency, bool kPatch, bool kInt8, bool kHalf, bool kHaveQ = false,
           typename SelAt, typename PhysAt>
-__device__ __forceinline__ bool attend_split(const AttendParams& p, int b, int h, int split,
-                                             int count, int L, const NewToken& nt, SelAt sel_at,
+__device__ __forceinline__ bool attend_split(const AttendParams& p, int b, int h, int n_split,
+                                             size_t part_row, int split, int count, int L, const NewToken& nt, SelAt sel_at,
                                              PhysAt phys_at, float* lds, uint32_t tag = 0u,
                                              const uint16_t* q_rows = nullptr, int spin_limit = 0,
                                              const QOperand<D, kInt8>* q_ready = nullptr) {
@@ -939,7 +941,7 @@ __device__ __forceinline__ bool attend_split(const AttendParams& p, int b, int h
   }
   __syncthreads();
   TS_MARK(24);
-  float* part = p.partials + (((size_t)b * p.Hkv + h) * p.n_split + split) * (size_t)G * RS;
+  float* part = p.partials + (part_row + split) * (size_t)G * RS;
   bool ok = true;
   int spins = 0;
   // one thread per (head, channel); the thread of channel 0 also hands on the
@@ -960,15 +962,14 @@ __device__ __forceinline__ bool attend_split(const AttendParams& p, int b, int h
       Lsum += row[D + 1] * wgt;
       O += row[c] * wgt;
     }
-    if (p.n_split == 1) {
+    if (n_split == 1) {
       store_out(p, ((size_t)b * p.Hq + (size_t)h * G + g) * D + c, Lsum > 0.f ? O / Lsum : 0.f);
       if (c == 0 && p.lse) p.lse[(size_t)b * p.Hq + (size_t)h * G + g] = log_sum_exp(M, Lsum);
     } else if (tag != 0u) {
-      uint64_t* unit64 = reinterpret_cast<uint64_t*>(p.partials) +
-                         ((size_t)b * p.Hkv + h) * p.n_split * (size_t)G * RS;
-      if (split == p.n_split - 1) {   // (uniform) the merging split: its own partial never leaves
+      uint64_t* unit64 = reinterpret_cast<uint64_t*>(p.partials) + part_row * (size_t)G * RS;
+      if (split == n_split - 1) {   // (uniform) the merging split: its own partial never leaves
         // (small clusters take the partials four at a time, large ones sixteen)
-        const int others = p.n_split - 1;
+        const int others = n_split - 1;
         ok = (others <= 4 ? merge_tagged<D, 4>(unit64, G, g, c, others, tag, spin_limit, spins, M, Lsum, O)
                           : merge_tagged<D, 16>(unit64, G, g, c, others, tag, spin_limit, spins, M, Lsum, O)) && ok;
         store_out(p, ((size_t)b * p.Hq + (size_t)h * G + g) * D + c, Lsum > 0.f ? O / Lsum : 0.f);

@@ -51,6 +51,7 @@ struct Plan {
   int units;          // B * Hkv
   int g;              // workgroups per unit (= attention splits = score slices)
   int chunk;          // selected pages per workgroup
+  int list;           // entries of a workgroup's list of selected pages in LDS
   size_t off_unit;    // int32 [2][units * cstride]: [1] = arrival counters of the staged attention ([0] unused)
   int cstride;        // words between the counters of consecutive units
   size_t off_scores;  // {fp32 score, uint32 launch tag} [units][Pmax]
@@ -58,6 +59,8 @@ struct Plan {
   size_t total;
   size_t lds_fused;   // dynamic LDS of the fused kernel
   bool small_units;   // many small units: small_units_decode_kernel
+  bool balanced;      // a ragged batch: balanced_decode_kernel, per_head workgroups per KV head
+  int per_head;
 };
 
 static size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
@@ -84,6 +87,8 @@ struct FusedParams {
   int xcds;                    // > 1: clusters laid out one per XCD over that many XCDs (see cluster_of)
   int n_arrive;                // workgroups of the launch that work on a unit
   FastDiv div_g, div_xcds, div_hkv;   // divisions by g, xcds and the number of KV heads
+  // (last: what stands in front of these is fetched in few loads, see decode_units)
+  int per_head;                // balanced launches: workgroups per KV head
 };
 
 // Which cluster a workgroup belongs to, and as which member.  The hardware deals
@@ -137,7 +142,7 @@ __global__ __launch_bounds__(kThreads) void sparse_attention_kernel(AttendParams
   const int32_t* bt_row = p.block_table + (size_t)b * p.Pmax;
   const NewToken none{-1, 0, p.q, p.q};
   attend_split<kWaves, D, S, true, false, kInt8, kHalf>(
-      p, b, h, split, count, p.seq_lens[b], none,
+      p, b, h, p.n_split, (size_t)u * p.n_split, split, count, p.seq_lens[b], none,
       [&](int i) { return sel_row ? sel_row[i] : c0 + i; },
       [&](int j) { return bt_row[j]; }, reinterpret_cast<float*>(smem));
   if (p.n_split == 1) return;
@@ -148,6 +153,93 @@ __global__ __launch_bounds__(kThreads) void sparse_attention_kernel(AttendParams
   if (!uniform(s_last)) return;
   combine_splits<D>(p, b, h);
   if (threadIdx.x == 0) atomic_store_agent(&unit_done[u * cstride], 0);
+}
+
+// ---------------------------------------------------------------------------
+// Shares in proportion to the work (ragged batches).
+//
+// With clusters of one size a launch over sequences of different lengths ends with the
+// longest one, while the workgroups of the short ones have long left.  Here the workgroups
+// of a launch, N per KV head, are dealt out to the sequences by the bytes each has to
+// read: every wave works the same shares out for itself from the lengths, a lane per
+// sequence, and finds the one that belongs to its workgroup.
+// ---------------------------------------------------------------------------
+constexpr int kBalanceSeqs = kWave;   // a lane per sequence
+constexpr int kBalanceTryAll = 12;    // sequences up to which trying all shares at once is the quicker way
+constexpr int kBalanceMembers = 32;   // most members of a cluster (more only lengthen its merge)
+
+struct UnitShare {
+  int b, h, member, g;   // g == 0: nothing to do
+  int chunk;             // selected pages per member
+  int part_row;          // the cluster's first row of the partial area
+  int L, K;              // the sequence's length and page budget as given
+};
+
+template <int S, bool kApp>
+__device__ __forceinline__ UnitShare balanced_share(const FusedParams& p) {
+  const AttendParams& at = p.at;
+  const int lane = lane_id(), N = p.per_head;
+  const int L = at.seq_lens[min(lane, p.B - 1)];
+  const int K = p.topk_per_seq ? p.topk_per_seq[min(lane, p.B - 1)] : p.topk;
+  const int len = L + (kApp && L / S < at.Pmax ? 1 : 0);
+  const int P = min(pages_of(len, S), at.Pmax), Kb = max(0, min(min(K, P), at.Kmax));
+  const bool on = lane < p.B;
+  // in metadata rows (a token's K and V are as long as a page's box); at least one, so that an empty sequence has its workgroup too
+  const float work = on ? fmaxf((float)P + (float)(Kb * S), 1.f) : 0.f;
+  const float most = on ? (float)min((Kb + 3) / 4, kBalanceMembers) : 0.f;   // a page per wave at the least
+  // The smallest share t (work per workgroup) with which sum ceil(work / t) fits into N:
+  // t = total / N would if the parts came out even, t = total / (N - B) does in any case (and
+  // so does one workgroup each, t = the largest).
+  const float total = wave_sum_f32(work), largest = wave_max_f32(work);
+  const float lo = total * __builtin_amdgcn_rcpf((float)N);
+  const float hi = 1.001f * fminf(largest, total * __builtin_amdgcn_rcpf((float)max(N - p.B, 1)));
+  auto members = [](float w, float m, float i) { return fmaxf(fminf(ceilf(w * i), m), 1.f); };
+  float inv_t = 0.f;   // (0: one workgroup each)
+  if (p.B <= kBalanceTryAll) {   // 64 values of t at once, a lane each
+    const float inv = __builtin_amdgcn_rcpf(fmaf(fmaxf(hi - lo, 0.f), (float)lane * (1.f / 63.f), lo));
+    float n = 0.f;
+    for (int s = 0; s < p.B; ++s) {
+      const float w = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(work), s));
+      const float m = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(most), s));
+      n += members(w, m, inv);
+    }
+    const uint64_t fits = __ballot(n <= (float)N);
+    if (fits) inv_t = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(inv), __builtin_ctzll(fits)));
+  } else {                       // halving, a lane per sequence
+    float a = lo, z = hi;
+#pragma unroll
+    for (int i = 0; i < 6; ++i) {
+      const float mid = i == 0 ? z : 0.5f * (a + z), inv = __builtin_amdgcn_rcpf(mid);
+      if (wave_sum_f32(on ? members(work, most, inv) : 0.f) <= (float)N) {
+        z = mid;
+        inv_t = inv;
+      } else {
+        a = mid;
+      }
+    }
+  }
+  const int gl = on ? (int)members(work, most, inv_t) : 0;
+  const int incl = wave_inclusive_sum(gl);
+  // workgroup x: KV head x mod Hkv (so that with eight heads or a multiple a cluster stays on
+  // one XCD), place x / Hkv among the head's N
+  const int place = fast_div(blockIdx.x, p.div_hkv);
+  UnitShare u{};
+  u.h = (int)blockIdx.x - place * at.Hkv;
+  const uint64_t after = __ballot(incl > place);
+  if (after == 0ull) return u;   // more workgroups than members
+  const int s = __builtin_ctzll(after);
+  const int first = __builtin_amdgcn_readlane(incl - gl, s);
+  u.b = s;
+  u.g = __builtin_amdgcn_readlane(gl, s);
+  u.member = place - first;
+  u.part_row = u.h * N + first;
+  u.L = __builtin_amdgcn_readlane(L, s);
+  u.K = __builtin_amdgcn_readlane(K, s);
+  const int kept = __builtin_amdgcn_readlane(Kb, s);
+  u.chunk = max((int)ceilf((float)kept * __builtin_amdgcn_rcpf((float)u.g) - 1e-3f), 1);
+  if (u.chunk * u.g < kept) ++u.chunk;   // (the reciprocal is a bit short)
+  if (S < 16) u.chunk = (u.chunk + 3) / 4 * 4;   // whole groups of small pages
+  return u;
 }
 
 // ---------------------------------------------------------------------------
@@ -200,11 +292,12 @@ __global__ __launch_bounds__(kThreads) void sparse_attention_kernel(AttendParams
 // build for one workgroup per unit carries nothing of the exchange, the build
 // for clusters nothing of the selection's stand-alone first stages.
 template <int NW, int D, int S, bool kLoop, bool kApp, bool kInt8, bool kHalf, bool kCluster,
-          bool kCounted = !kLoop>
+          bool kCounted = !kLoop, bool kBalance = false>
 __device__ __forceinline__ void decode_units(const FusedParams& p) {
   constexpr int NT = NW * kWave;
   static_assert(!(kLoop && kApp), "the append is folded only into the loop-free build");
   static_assert(!kLoop || kCluster, "a single workgroup per unit needs no loop");
+  static_assert(!kBalance || (kCluster && !kLoop), "shares are worked out once, at the head");
   extern __shared__ __align__(16) unsigned char smem[];
   TS_MARK_INIT();
   TS_MARK(22);
@@ -219,14 +312,31 @@ __device__ __forceinline__ void decode_units(const FusedParams& p) {
                "s"(p.div_xcds.magic), "s"(at.q), "s"(at.block_table), "s"(at.seq_lens), "s"(at.Hq),
                "s"(at.Hkv), "s"(at.G), "s"(at.Pmax), "s"(at.chunk), "s"(at.lse), "s"(at.k_scale),
                "s"(at.v_scale));
-  const int g = kCluster ? p.g : 1, G = at.G, Pmax = at.Pmax;
-  const ClusterSlot where = kCluster ? cluster_of(blockIdx.x, p.div_g, p.div_xcds, p.xcds > 1)
-                                     : ClusterSlot{(int)blockIdx.x, 0};
+  const int G = at.G, Pmax = at.Pmax;
+  // which unit this workgroup works on, as which of how many members, and the size of a
+  // member's chunk of the selected pages
+  int epoch_raw, L_raw, K_raw;
+  UnitShare share{};
+  if constexpr (kBalance) {
+    epoch_raw = p.ctrl[kCtrlEpoch];
+    share = balanced_share<S, kApp>(p);
+    if (share.g == 0) {   // a workgroup too many: it leaves once all its waves have read the
+      asm volatile("" ::"v"(epoch_raw));   // lengths and the epoch
+      __syncthreads();
+      if (threadIdx.x == 0) (void)atomic_add_agent(&p.ctrl[kCtrlArrive], 1);
+      return;
+    }
+  }
+  const int g = kBalance ? share.g : kCluster ? p.g : 1;
+  const ClusterSlot where = kBalance   ? ClusterSlot{share.b * at.Hkv + share.h, share.member}
+                            : kCluster ? cluster_of(blockIdx.x, p.div_g, p.div_xcds, p.xcds > 1)
+                                       : ClusterSlot{(int)blockIdx.x, 0};
   const int member = kCluster ? where.member : 0;
+  const int chunk = kBalance ? share.chunk : at.chunk;
   const int n_clusters = kCluster ? fast_div(gridDim.x, p.div_g) : (int)gridDim.x;
   // (a launch laid out by XCD is padded to whole rounds of the XCDs: clusters past
   // the last unit leave before any barrier, see below, and are not counted in)
-  const bool padding = kCluster && !kLoop && where.cluster >= p.units;
+  const bool padding = kCluster && !kLoop && !kBalance && where.cluster >= p.units;
   const SelectLds sl = carve_select<NW>(smem, Pmax);
   const size_t sel_bytes = select_lds_bytes(Pmax, NW);
   const size_t att_bytes = (size_t)NW * G * (D + 2) * 4;
@@ -249,7 +359,7 @@ __device__ __forceinline__ void decode_units(const FusedParams& p) {
   // the 16-sequence configuration, but where the scores vary smoothly along the
   // sequence the few pages that matter then lie in tiles most members never see.
   constexpr int kBtRegs = 8;  // block-table entries per thread fetched through registers
-  int L_raw, K_raw, epoch_raw, bt_regs[kBtRegs];
+  int bt_regs[kBtRegs];
   ScanRegs<D, kHalf, NW> scan;
   // Append mode: the new token's key / value rows of this unit, as the 16-byte
   // chunk (channels 8 * (lane % (D/8)) .. + 7) every lane needs for the box update
@@ -258,10 +368,15 @@ __device__ __forceinline__ void decode_units(const FusedParams& p) {
   constexpr int LPR = ScoreLanes<D, kHalf>::LPR;
   uint4 kn16 = make_uint4(0, 0, 0, 0), vn16 = make_uint4(0, 0, 0, 0);
   auto issue_unit = [&](int uu) {
-    const int b = fast_div(uu, p.div_hkv), h = uu - b * at.Hkv;
-    epoch_raw = p.ctrl[kCtrlEpoch];
-    L_raw = at.seq_lens[b];
-    K_raw = p.topk_per_seq ? p.topk_per_seq[b] : p.topk;
+    const int b = kBalance ? share.b : fast_div(uu, p.div_hkv), h = uu - b * at.Hkv;
+    if constexpr (kBalance) {
+      L_raw = share.L;
+      K_raw = share.K;
+    } else {
+      epoch_raw = p.ctrl[kCtrlEpoch];
+      L_raw = at.seq_lens[b];
+      K_raw = p.topk_per_seq ? p.topk_per_seq[b] : p.topk;
+    }
     scan_issue_query(scan, at.q + ((size_t)b * at.Hq + (size_t)h * G) * D, G);
     if (app) {  // behind the query (needed first), ahead of the metadata (needed with it)
       const size_t row = ((size_t)b * at.Hkv + h) * D + (lane_id() % LPR) * 8;
@@ -290,7 +405,7 @@ __device__ __forceinline__ void decode_units(const FusedParams& p) {
   bool counted = false;
   while (kLoop ? u < p.units : true) {
     TS_MARK(0);
-    const int b = fast_div(u, p.div_hkv), h = u - b * at.Hkv;
+    const int b = kBalance ? share.b : fast_div(u, p.div_hkv), h = u - b * at.Hkv;
     const int32_t* bt_row = at.block_table + (size_t)b * Pmax;
     uint64_t* srow = p.scores + (size_t)u * Pmax;
     float* srow_out = p.scores_out ? p.scores_out + (size_t)u * Pmax : nullptr;
@@ -512,7 +627,7 @@ __device__ __forceinline__ void decode_units(const FusedParams& p) {
     if (kApp && !exchange) store_new_token();
 
     // 3. select; keep my own chunk of the ascending list
-    const int c0 = min(member * at.chunk, Kb), count = min(c0 + at.chunk, Kb) - c0;
+    const int c0 = min(member * chunk, Kb), count = min(c0 + chunk, Kb) - c0;
     int32_t* sel_row = (p.sel_out && member == 0) ? p.sel_out + (size_t)u * at.Kmax : nullptr;
     if (sel_row)
       for (int i = Kb + threadIdx.x; i < at.Kmax; i += NT) sel_row[i] = -1;
@@ -533,7 +648,8 @@ __device__ __forceinline__ void decode_units(const FusedParams& p) {
     // can be short) keeps its own in registers, polls for the others and writes
     // the output.  Nobody else waits for anything.
     const bool merged = attend_split<NW, D, S, kCounted, kApp, kInt8, kHalf, true>(
-        at, b, h, member, count, L, nt, [&](int i) { return my_sel[i]; },
+        at, b, h, kBalance ? g : at.n_split,
+        kBalance ? (size_t)share.part_row : ((size_t)b * at.Hkv + h) * at.n_split, member, count, L, nt, [&](int i) { return my_sel[i]; },
         [&](int j) { return bt_lds[j]; }, reinterpret_cast<float*>(smem), exchange ? tag : 0u,
         nullptr, p.spin_limit, &qop);
     TS_MARK(6);
@@ -570,6 +686,13 @@ query_aware_decode_kernel(FusedParams p) {
   decode_units<kWaves, D, S, kLoop, kApp, kInt8, kHalf, kCluster>(p);
 }
 
+// Ragged batches: see balanced_share.
+template <int D, int S, bool kApp, bool kHalf>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void
+balanced_decode_kernel(FusedParams p) {
+  decode_units<kWaves, D, S, false, kApp, false, kHalf, true, true, true>(p);
+}
+
 // Batches of more units than compute units whose units are not small: one workgroup of eight
 // waves per unit, one resident per compute unit, the next one handed out by the hardware as
 // one ends, so that the spread of sequence lengths does not decide the finish time and
@@ -597,10 +720,10 @@ many_units_decode_kernel(FusedParams p) {
 // An append runs as a kernel of its own in front: folding it in gained 3 % here and would
 // make the first workgroup wait for ones not yet resident.
 constexpr int kSmallWaves = 4;
-template <int D, int S, bool kInt8, bool kHalf>
+template <int D, int S, bool kHalf>
 __global__ __launch_bounds__(kSmallWaves * kWave) __attribute__((amdgpu_waves_per_eu(2, 2))) void
 small_units_decode_kernel(FusedParams p) {
-  decode_units<kSmallWaves, D, S, false, false, kInt8, kHalf, false>(p);
+  decode_units<kSmallWaves, D, S, false, false, false, kHalf, false>(p);
 }
 
 // ---------------------------------------------------------------------------
@@ -681,7 +804,6 @@ static int launch_single(const ts_layout* layout, FusedParams& p, const Plan& pl
   hipStream_t s = (hipStream_t)stream;
   auto one_kernel = query_aware_decode_kernel<D, S, false, false, kInt8, kHalf, false>;
   auto app_kernel = query_aware_decode_kernel<D, S, false, true, kInt8, kHalf, false>;
-  auto small_kernel = small_units_decode_kernel<D, S, kInt8, kHalf>;
   auto many_kernel = many_units_decode_kernel<D, S, kInt8, kHalf>;
   const unsigned grid = (unsigned)pl.units;
   int st;
@@ -701,9 +823,34 @@ static int launch_single(const ts_layout* layout, FusedParams& p, const Plan& pl
     if ((st = ts_append_token_meta(layout, k_new, v_new, 1, stream)) != TS_OK) return st;
     p.k_new = p.v_new = nullptr;
   }
-  auto kernel = pl.small_units ? small_kernel : many_kernel;
+  if constexpr (!kInt8) {
+    if (pl.small_units) {
+      auto small_kernel = small_units_decode_kernel<D, S, kHalf>;
+      if ((st = allow_lds(small_kernel, pl.lds_fused)) != TS_OK) return st;
+      small_kernel<<<grid, kSmallWaves * kWave, pl.lds_fused, s>>>(p);
+      return TS_OK;
+    }
+  }
+  if ((st = allow_lds(many_kernel, pl.lds_fused)) != TS_OK) return st;
+  many_kernel<<<grid, kThreads, pl.lds_fused, s>>>(p);
+  return TS_OK;
+}
+
+// Clusters in proportion to the work (pl.balanced); the plan has seen to it that all
+// workgroups are resident at once.
+template <int D, int S, int kFmt>
+static int launch_balanced(const ts_layout* layout, FusedParams& p, const Plan& pl,
+                           const void* k_new, const void* v_new, void* stream) {
+  constexpr bool kHalf = kFmt == TS_KV_FP16;
+  auto kernel = k_new ? balanced_decode_kernel<D, S, true, kHalf> : balanced_decode_kernel<D, S, false, kHalf>;
+  int st;
   if ((st = allow_lds(kernel, pl.lds_fused)) != TS_OK) return st;
-  kernel<<<grid, pl.small_units ? kSmallWaves * kWave : kThreads, pl.lds_fused, s>>>(p);
+  const unsigned grid = (unsigned)(pl.per_head * layout->num_kv_heads);
+  if (resident_capacity(kernel, pl.lds_fused) < (int)grid) return TS_ERR_DEVICE;   // they wait for each other
+  p.xcds = 0;
+  p.n_arrive = (int)grid;
+  p.per_head = pl.per_head;
+  kernel<<<grid, kThreads, pl.lds_fused, (hipStream_t)stream>>>(p);
   return TS_OK;
 }
 
@@ -770,7 +917,10 @@ int launch_fused_format(const ts_layout* layout, FusedParams& p, const Plan& pl,
                         const void* v_new, int max_resident, void* stream) {
   int st = TS_ERR_UNSUPPORTED;
 #define TS_LAUNCH_FUSED(DD, SS)                                                                     \
-  st = pl.g > 1                                                                                   \
+  if constexpr (kFmt != TS_KV_INT8) {                                                              \
+    if (pl.balanced) return launch_balanced<DD, SS, kFmt>(layout, p, pl, k_new, v_new, stream);    \
+  }                                                                                                \
+  st = pl.g > 1                                                                                    \
            ? launch_clusters<DD, SS, kFmt>(layout, p, pl, k_new, v_new, max_resident, stream)       \
            : launch_single<DD, SS, kFmt>(layout, p, pl, k_new, v_new, max_resident, stream)
   TS_DISPATCH_PAGE(kD, layout->page_size, TS_LAUNCH_FUSED)

@@ -533,6 +533,67 @@ def test_clusters_that_work_through_several_units(oracle, built, name, splits, f
         sess.sel.fill_(-7)
 
 
+BALANCED = {
+    # ragged batches of up to 255 units in a pool too small for B sequences of the full length:
+    # workgroups dealt out to the sequences by their work.  Both ways the shares are worked out
+    # (up to 12 sequences, more), 255 as well as 256 workgroups, one head and many
+    "d64_s16": wl.WorkloadSpec("ba1", 5, 8, 4, 64, 16, 3000, 0, L_min=1, budget_frac=0.2, headroom=16),
+    "d128_s32": wl.WorkloadSpec("ba2", 13, 16, 8, 128, 32, 2500, 0, L_min=40, budget_frac=0.3, headroom=16),
+    "d64_s4": wl.WorkloadSpec("ba3", 33, 4, 2, 64, 4, 900, 0, L_min=1, budget_frac=0.25, headroom=16),
+    "d128_s8": wl.WorkloadSpec("ba4", 64, 8, 1, 128, 8, 900, 0, L_min=1, budget_frac=0.4, headroom=16),
+    "d64_s64": wl.WorkloadSpec("ba5", 2, 32, 16, 64, 64, 9000, 0, L_min=300, budget_frac=0.5, headroom=16),
+    "d128_s16": wl.WorkloadSpec("ba6", 19, 12, 12, 128, 16, 1200, 0, L_min=1, budget_frac=0.3, headroom=16),
+    "d64_s8": wl.WorkloadSpec("ba7", 12, 6, 3, 64, 8, 2000, 30, L_min=1, headroom=16),
+    "d128_s4": wl.WorkloadSpec("ba8", 3, 2, 2, 128, 4, 1500, 90, L_min=1, headroom=16),
+    "d64_s32": wl.WorkloadSpec("ba9", 31, 8, 8, 64, 32, 1500, 0, L_min=1, budget_frac=0.5, headroom=16),
+    "d128_s64": wl.WorkloadSpec("ba10", 7, 16, 4, 128, 64, 4000, 9, L_min=1, headroom=16),
+}
+
+
+@pytest.mark.parametrize("name", list(BALANCED))
+@pytest.mark.parametrize("fmt", FORMATS)
+def test_shares_in_proportion_to_the_work(oracle, built, name, fmt):
+    """A room in the list of selected pages that makes the launch a large one (nothing else
+    does: the sequences are short) brings the balanced build; an empty sequence and one of a
+    single token among them, with and without the append, the lengths changing in between."""
+    spec = wl.scaled(BALANCED[name], kv=fmt)
+    print(f"[case] balanced {name} {fmt}", flush=True)
+    w = wl.make_workload(spec, DEV, seed=606, n_q=4, n_new=4)
+    topk = w.topk
+    g = max(1, 256 // (spec.B * spec.Hkv))
+    w.K_max = max(w.K_max, g * (640 << 10) // (spec.S * 4 * spec.d))
+    sess = Session(w)
+    full = ts.make_layout(spec.B, spec.Hq, spec.Hkv, spec.d, spec.S, w.P_max, w.k_pool, w.v_pool,
+                          w.block_table, sess.seq_lens, sess.page_min, sess.page_max)
+    full.num_phys_pages = spec.B * w.P_max
+    assert ts.workspace_bytes(sess.layout, w.K_max) >= ts.workspace_bytes(full, w.K_max)
+    sess.seq_lens[0] = 0
+    sess.seq_lens[1] = 1
+    ts.build_page_meta(sess.layout)
+    scale = 1.0 / math.sqrt(spec.d)
+    units = [(b, h) for b in range(spec.B) for h in range(spec.Hkv)]
+    rng = np.random.default_rng(12)
+    if len(units) > 40:
+        units = [units[i] for i in sorted(set(rng.integers(0, len(units), 24).tolist()) | {0, spec.Hkv, len(units) - 1})]
+    for i in range(4):
+        if i % 2:
+            ts.append_and_decode(sess.layout, w.k_new[i], w.v_new[i], w.q[i], topk, w.K_max, scale, sess.out,
+                                 sess.ws, topk_per_seq=w.topk_per_seq, scores_out=sess.scores,
+                                 sel_out=sess.sel, sel_count_out=sess.sel_count)
+        else:
+            ts.query_aware_decode(sess.layout, w.q[i], topk, w.K_max, scale, sess.out, sess.ws,
+                                  topk_per_seq=w.topk_per_seq, scores_out=sess.scores,
+                                  sel_out=sess.sel, sel_count_out=sess.sel_count)
+        compare_units(oracle, sess, units, scale, q_idx=i, what=f"{name} launch {i}")
+        assert torch.isfinite(sess.out).all()
+        sess.out.fill_(float("nan"))
+        sess.sel.fill_(-7)
+        if i == 1:      # other lengths: the shares of the next launch are other ones
+            sess.seq_lens.copy_(torch.roll(sess.seq_lens, 1))
+            sess.seq_lens.copy_(torch.minimum(sess.seq_lens, w.seq_lens))
+            ts.build_page_meta(sess.layout)
+
+
 def test_query_sums_read_back_through_one_hot_boxes(built):
     """Boxes are overwritten so that page c has max = unit vector c and min = 0: the
     score of page c then equals Qp_c = sum over the group's heads of max(q_c, 0), read
