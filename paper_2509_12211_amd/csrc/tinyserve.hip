@@ -39,6 +39,7 @@ constexpr size_t kSmallUnitBytes = 2 << 20;
 // fast as without; 24 sequences x 8 KV heads of 512-8192 tokens 45.6 -> 40.5 us, 7 x 8 of
 // 4-50 K 38 -> 31 us, 21 x 8 of 38 K at the longest 137 -> 102 us.
 constexpr int kBalanceBytes = 80 << 10;
+constexpr size_t kLdsBytes = 160 << 10;   // of a compute unit
 
 static Plan make_plan(const ts_layout* L, int max_topk, int target_workgroups = kTargetWorkgroups,
                       bool may_balance = true) {
@@ -111,6 +112,9 @@ static Plan make_plan(const ts_layout* L, int max_topk, int target_workgroups = 
   const size_t lds_query = (size_t)G * L->head_dim * 2 + 2 * (size_t)L->head_dim * 8;
   pl.lds_fused = (lds_sel > lds_att ? lds_sel : lds_att) +
                  align_up((size_t)Pmax * 4 + (size_t)pl.list * 4, 16) + lds_query;
+  // (a list of all selected pages may not fit where a cluster's share of it does: the longest
+  // block tables with more than about 5000 pages selected)
+  if (pl.balanced && pl.lds_fused > kLdsBytes) return make_plan(L, max_topk, target_workgroups, false);
   return pl;
 }
 
@@ -288,13 +292,17 @@ static int launch_fused(const ts_layout* layout, const void* k_new, const void* 
                         const void* q, int32_t topk, const int32_t* topk_per_seq,
                         int32_t max_topk, float softmax_scale, void* out, float* scores_out,
                         int32_t* sel_out, int32_t* sel_count_out, void* workspace,
-                        size_t workspace_bytes, void* stream, bool may_balance = true) {
+                        size_t workspace_bytes, void* stream) {
   int st = check_layout(layout);
   if (st != TS_OK) return st;
   if (!q || !out || !workspace || !layout->page_min || !layout->page_max) return TS_ERR_NULL;
   if ((st = check_pool(layout)) != TS_OK) return st;
   if (max_topk < 1 || (!topk_per_seq && (topk < 1 || max_topk < topk))) return TS_ERR_SHAPE;
-  Plan pl = make_plan(layout, max_topk, kTargetWorkgroups, may_balance);
+  Plan pl = make_plan(layout, max_topk);
+  // (shares in proportion to the work need an exchange area for every unit: a workspace
+  // without room for it, one sized for a larger pool for instance, gets clusters of one size)
+  if (pl.balanced && workspace_bytes < pl.total)
+    pl = make_plan(layout, max_topk, kTargetWorkgroups, false);
   if (workspace_bytes < pl.total) return TS_ERR_WORKSPACE;
   const int cus = num_compute_units();
   if (cus <= 0) return TS_ERR_DEVICE;
@@ -637,17 +645,14 @@ int ts_query_aware_decode_static(const ts_layout* layout, const void* q, int32_t
   const int st = check_layout(layout);
   if (st != TS_OK) return st;
   if (max_topk < 1) return TS_ERR_SHAPE;
-  // (shares in proportion to the work need an exchange area for every unit: where it does not
-  // fit the region, clusters of one size)
-  const bool balance = make_plan(layout, max_topk).total <= (size_t)TS_STATIC_WORKSPACE_BYTES;
-  if (!balance && make_plan(layout, max_topk, kTargetWorkgroups, false).total > (size_t)TS_STATIC_WORKSPACE_BYTES)
+  if (make_plan(layout, max_topk, kTargetWorkgroups, false).total > (size_t)TS_STATIC_WORKSPACE_BYTES)
     return TS_ERR_WORKSPACE;
   void* ws = nullptr;
   const int sw = static_scratch(&ws);
   if (sw != TS_OK) return sw;
   return launch_fused(layout, nullptr, nullptr, q, topk, topk_per_seq, max_topk, softmax_scale, out,
                       scores_out, sel_out, sel_count_out, ws, (size_t)TS_STATIC_WORKSPACE_BYTES,
-                      stream, balance);
+                      stream);
 }
 
 int ts_append_and_decode(const ts_layout* layout, const void* k_new, const void* v_new,

@@ -77,6 +77,16 @@ def test_workspace_bytes_is_host_only_and_monotone():
     assert ts.workspace_bytes(_layout(head_dim=96), 8) == 0
 
 
+def test_ragged_plan_only_where_its_list_fits_the_lds():
+    """A pool too small for sequences of the full length asks for shares in proportion to the
+    work, which need an exchange area of their own; not with a list of pages that fits the
+    160 KB of LDS only in shares (such a launch would be refused)."""
+    for topk, shares in ((1024, True), (8192, False)):
+        full, ragged = (ts.workspace_bytes(_layout(num_seqs=3, page_size=4, max_pages_per_seq=16384,
+                                                   num_phys_pages=n), topk) for n in (3 * 16384, 20000))
+        assert (ragged > full) == shares and ragged >= full > 0
+
+
 @pytest.mark.parametrize("kw,code", [
     (dict(num_seqs=0), ts.TS_ERR_SHAPE),
     (dict(num_q_heads=7), ts.TS_ERR_SHAPE),

@@ -594,6 +594,43 @@ def test_shares_in_proportion_to_the_work(oracle, built, name, fmt):
             ts.build_page_meta(sess.layout)
 
 
+@pytest.mark.parametrize("name", ["d64_s16", "d128_s16"])
+def test_workspace_without_room_for_shares(oracle, built, name):
+    """A workspace with room for clusters of one size and not for shares in proportion to the
+    work (a caller's own, sized for a larger pool) serves a ragged batch all the same."""
+    spec = BALANCED[name]
+    print(f"[case] small workspace {name}", flush=True)
+    w = wl.make_workload(spec, DEV, seed=31, n_q=1, n_new=1)
+    g = max(1, 256 // (spec.B * spec.Hkv))
+    w.K_max = max(w.K_max, g * (640 << 10) // (spec.S * 4 * spec.d))
+    sess = Session(w)
+    n_phys = sess.layout.num_phys_pages
+    sess.layout.num_phys_pages = spec.B * w.P_max
+    plain = ts.workspace_bytes(sess.layout, w.K_max)
+    sess.layout.num_phys_pages = n_phys
+    assert plain < ts.workspace_bytes(sess.layout, w.K_max)
+    sess.ws = torch.zeros(plain, dtype=torch.uint8, device=DEV)
+    ts.workspace_init(sess.ws)
+    ts.build_page_meta(sess.layout)
+    scale = 1.0 / math.sqrt(spec.d)
+    sess.fused(scale)
+    units = [(b, h) for b in range(spec.B) for h in range(0, spec.Hkv, 3)]
+    compare_units(oracle, sess, units, scale, what=name)
+
+
+def test_ragged_batch_with_a_list_longer_than_the_lds(oracle, built):
+    """The longest block tables and a list of pages that only fits the LDS in shares."""
+    spec = wl.WorkloadSpec("long_list", 3, 4, 2, 64, 4, 65000, 0, L_min=500, budget_frac=0.4, headroom=32)
+    print("[case] long list", flush=True)
+    w = wl.make_workload(spec, DEV, seed=443, n_q=1, n_new=1)
+    assert w.K_max > 5300 and sum(-(-int(n) // spec.S) for n in w.seq_lens) < 0.6 * spec.B * w.P_max
+    sess = Session(w)
+    ts.build_page_meta(sess.layout)
+    scale = 1.0 / math.sqrt(spec.d)
+    sess.fused(scale)
+    compare_units(oracle, sess, [(b, h) for b in range(3) for h in range(2)], scale, what="long list")
+
+
 def test_query_sums_read_back_through_one_hot_boxes(built):
     """Boxes are overwritten so that page c has max = unit vector c and min = 0: the
     score of page c then equals Qp_c = sum over the group's heads of max(q_c, 0), read
