@@ -21,8 +21,10 @@ TS_FORMAT_FUNCTIONS(extern, TS_KV_INT8, 128)
 static std::atomic<int> g_tune_splits{0}, g_tune_wg_per_cu{0};
 
 // target_workgroups: about how many workgroups a launch should have.  The
-// query-aware path is latency-bound and wants one per compute unit; the dense
-// baseline streams the whole cache and wants several.
+// query-aware path is latency-bound and wants one per compute unit; the full-cache path
+// with clusters of one size (the INT8 cache, more than 256 units) wants several rounds of
+// them, so that the short sequences' workgroups make room for the long ones' (one round
+// dealt out by the lengths is the better way where there is one: see make_plan).
 constexpr int kDenseTargetWorkgroups = 1024;
 // Up to this many bytes of metadata and selected pages the units of a large batch count as
 // small (small_units_decode_kernel).  Beyond it a unit is bound by its data, and a whole
@@ -92,6 +94,13 @@ static Plan make_plan(const ts_layout* L, int max_topk, int target_workgroups = 
   // result goes straight to the output)
   const bool exchange = pl.g > 1 || pl.balanced;
   size_t parts = (size_t)pl.units * pl.g;
+  // Every cached token: one round of workgroups in proportion to the lengths (dense_shares_kernel)
+  // wherever there is one for every unit and clusters of one size would not fit one round
+  // anyway (a few short sequences: working the shares out costs 0.3 us there and gains
+  // nothing).  Its partial results, at most 256 in fp32, have room in the area of these.
+  if (target_workgroups == kDenseTargetWorkgroups)
+    pl.balanced = !int8 && L->num_seqs <= kBalanceSeqs && pl.per_head >= L->num_seqs &&
+                  parts > (size_t)kTargetWorkgroups;
   if (pl.balanced && parts < (size_t)pl.per_head * L->num_kv_heads) parts = (size_t)pl.per_head * L->num_kv_heads;
   pl.off_scores = off;
   if (exchange) off = align_up(off + (size_t)pl.units * Pmax * sizeof(uint64_t), 256);
@@ -114,7 +123,7 @@ static Plan make_plan(const ts_layout* L, int max_topk, int target_workgroups = 
                  align_up((size_t)Pmax * 4 + (size_t)pl.list * 4, 16) + lds_query;
   // (a list of all selected pages may not fit where a cluster's share of it does: the longest
   // block tables with more than about 5000 pages selected)
-  if (pl.balanced && pl.lds_fused > kLdsBytes) return make_plan(L, max_topk, target_workgroups, false);
+  if (target_workgroups == kTargetWorkgroups && pl.balanced && pl.lds_fused > kLdsBytes) return make_plan(L, max_topk, target_workgroups, false);
   return pl;
 }
 

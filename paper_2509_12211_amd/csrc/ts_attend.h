@@ -995,23 +995,24 @@ __device__ __forceinline__ bool attend_split(const AttendParams& p, int b, int h
   return ok;
 }
 
-// Merge the n_split partials of unit (b, h) and write the normalised output.
+// Merge the n_split partials of unit (b, h), rows part_row .. of the partial area, and write
+// the normalised output.
 // The caller has observed every producer's arrival; the partials are read with
 // agent-scope loads.
 template <int D>
-__device__ __forceinline__ void combine_splits(const AttendParams& p, int b, int h) {
+__device__ __forceinline__ void combine_splits(const AttendParams& p, int b, int h, size_t part_row, int n_split) {
   constexpr int RS = D + 2;
   const int G = p.G;
-  const float* part = p.partials + ((size_t)b * p.Hkv + h) * p.n_split * (size_t)G * RS;
+  const float* part = p.partials + part_row * G * RS;
   for (int idx = threadIdx.x; idx < G * D; idx += kThreads) {
     const int g = idx / D, c = idx % D;
     // online merge, 8 partials per round with all their loads in flight together
     float M = -1e30f, Lsum = 0.f, O = 0.f;
-    for (int s0 = 0; s0 < p.n_split; s0 += 8) {
+    for (int s0 = 0; s0 < n_split; s0 += 8) {
       float o[8], m[8], l[8];
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
-        const bool on = s0 + i < p.n_split;  // rows past the end re-read row 0, unused
+        const bool on = s0 + i < n_split;  // rows past the end re-read row 0, unused
         const float* row = part + ((size_t)(on ? s0 + i : 0) * G + g) * RS;
         const float ov = load_agent(row + c), mv = load_agent(row + D), lv = load_agent(row + D + 1);
         o[i] = on ? ov : 0.f;

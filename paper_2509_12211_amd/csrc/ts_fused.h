@@ -151,7 +151,7 @@ __global__ __launch_bounds__(kThreads) void sparse_attention_kernel(AttendParams
   if (threadIdx.x == 0) s_last = atomic_add_agent(&unit_done[u * cstride], 1) == p.n_split - 1;
   __syncthreads();
   if (!uniform(s_last)) return;
-  combine_splits<D>(p, b, h);
+  combine_splits<D>(p, b, h, (size_t)u * p.n_split, p.n_split);
   if (threadIdx.x == 0) atomic_store_agent(&unit_done[u * cstride], 0);
 }
 
@@ -175,30 +175,25 @@ struct UnitShare {
   int L, K;              // the sequence's length and page budget as given
 };
 
-template <int S, bool kApp>
-__device__ __forceinline__ UnitShare balanced_share(const FusedParams& p) {
-  const AttendParams& at = p.at;
-  const int lane = lane_id(), N = p.per_head;
-  const int L = at.seq_lens[min(lane, p.B - 1)];
-  const int K = p.topk_per_seq ? p.topk_per_seq[min(lane, p.B - 1)] : p.topk;
-  const int len = L + (kApp && L / S < at.Pmax ? 1 : 0);
-  const int P = min(pages_of(len, S), at.Pmax), Kb = max(0, min(min(K, P), at.Kmax));
-  const bool on = lane < p.B;
-  // in metadata rows (a token's K and V are as long as a page's box); at least one, so that an empty sequence has its workgroup too
-  const float work = on ? fmaxf((float)P + (float)(Kb * S), 1.f) : 0.f;
-  const float most = on ? (float)min((Kb + 3) / 4, kBalanceMembers) : 0.f;   // a page per wave at the least
+// The share of workgroup blockIdx.x.  Lane s < B comes with sequence s: its work, the most
+// members its clusters may have, the pages Kb to deal out to them; L and K are handed through.
+template <int S>
+__device__ __forceinline__ UnitShare deal_shares(int B, int N, int Hkv, const FastDiv& div_hkv, float work,
+                                                 float most, int Kb, int L, int K) {
+  const int lane = lane_id();
+  const bool on = lane < B;
   // The smallest share t (work per workgroup) with which sum ceil(work / t) fits into N:
   // t = total / N would if the parts came out even, t = total / (N - B) does in any case (and
   // so does one workgroup each, t = the largest).
   const float total = wave_sum_f32(work), largest = wave_max_f32(work);
   const float lo = total * __builtin_amdgcn_rcpf((float)N);
-  const float hi = 1.001f * fminf(largest, total * __builtin_amdgcn_rcpf((float)max(N - p.B, 1)));
+  const float hi = 1.001f * fminf(largest, total * __builtin_amdgcn_rcpf((float)max(N - B, 1)));
   auto members = [](float w, float m, float i) { return fmaxf(fminf(ceilf(w * i), m), 1.f); };
   float inv_t = 0.f;   // (0: one workgroup each)
-  if (p.B <= kBalanceTryAll) {   // 64 values of t at once, a lane each
+  if (B <= kBalanceTryAll) {   // 64 values of t at once, a lane each
     const float inv = __builtin_amdgcn_rcpf(fmaf(fmaxf(hi - lo, 0.f), (float)lane * (1.f / 63.f), lo));
     float n = 0.f;
-    for (int s = 0; s < p.B; ++s) {
+    for (int s = 0; s < B; ++s) {
       const float w = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(work), s));
       const float m = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(most), s));
       n += members(w, m, inv);
@@ -222,9 +217,9 @@ __device__ __forceinline__ UnitShare balanced_share(const FusedParams& p) {
   const int incl = wave_inclusive_sum(gl);
   // workgroup x: KV head x mod Hkv (so that with eight heads or a multiple a cluster stays on
   // one XCD), place x / Hkv among the head's N
-  const int place = fast_div(blockIdx.x, p.div_hkv);
+  const int place = fast_div(blockIdx.x, div_hkv);
   UnitShare u{};
-  u.h = (int)blockIdx.x - place * at.Hkv;
+  u.h = (int)blockIdx.x - place * Hkv;
   const uint64_t after = __ballot(incl > place);
   if (after == 0ull) return u;   // more workgroups than members
   const int s = __builtin_ctzll(after);
@@ -240,6 +235,61 @@ __device__ __forceinline__ UnitShare balanced_share(const FusedParams& p) {
   if (u.chunk * u.g < kept) ++u.chunk;   // (the reciprocal is a bit short)
   if (S < 16) u.chunk = (u.chunk + 3) / 4 * 4;   // whole groups of small pages
   return u;
+}
+
+template <int S, bool kApp>
+__device__ __forceinline__ UnitShare balanced_share(const FusedParams& p) {
+  const AttendParams& at = p.at;
+  const int lane = lane_id();
+  const int L = at.seq_lens[min(lane, p.B - 1)];
+  const int K = p.topk_per_seq ? p.topk_per_seq[min(lane, p.B - 1)] : p.topk;
+  const int len = L + (kApp && L / S < at.Pmax ? 1 : 0);
+  const int P = min(pages_of(len, S), at.Pmax), Kb = max(0, min(min(K, P), at.Kmax));
+  const bool on = lane < p.B;
+  // in metadata rows (a token's K and V are as long as a page's box); at least one, so that an empty sequence has its workgroup too
+  const float work = on ? fmaxf((float)P + (float)(Kb * S), 1.f) : 0.f;
+  const float most = on ? (float)min((Kb + 3) / 4, kBalanceMembers) : 0.f;   // a page per wave at the least
+  return deal_shares<S>(p.B, p.per_head, at.Hkv, p.div_hkv, work, most, Kb, L, K);
+}
+
+// Attention over every cached token, the sequences' workgroups in proportion to their pages.
+// Bound by HBM, and by how the work divides over the compute units: the attention's registers
+// leave room for one workgroup of eight waves each, so a launch runs in rounds of 256, and
+// every round past the first pays another start (1.5-5 us) and ends with a partial one.
+// Clusters of one size over the longest possible sequence, four rounds of them, also left
+// the work of a ragged batch where the round-robin over the XCDs put it.  One round, dealt
+// out by the lengths on the device, against four (bf16): 16 sequences x 4 KV heads of 16 K
+// tokens, 64 channels, 56.3 -> 48.0 us (5.6 TB/s); 4 x 4 of 128 K 118 -> 93 (5.8); 3 x 8 of
+// 16 K, 128 channels, 67 -> 43; 7 x 8 of 4-50 K 156 -> 132; 24 x 8 of 512-8192 109 -> 94;
+// 24 layouts of 12 to 256 units 1.03 to 1.9 times faster.
+template <int D, int S, bool kHalf>
+__global__ __launch_bounds__(kThreads) void dense_shares_kernel(AttendParams p, int32_t* unit_done,
+                                                                int cstride, int B, int per_head,
+                                                                FastDiv div_hkv) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  __shared__ int s_last;
+  const int lane = lane_id(), len = p.seq_lens[min(lane, B - 1)];
+  const int pages = lane < B ? max(0, min(pages_of(len, S), p.Pmax)) : 0;
+  const UnitShare share =
+      deal_shares<S>(B, per_head, p.Hkv, div_hkv, lane < B ? fmaxf((float)pages, 1.f) : 0.f,
+                     (float)min((pages + 3) / 4, kMaxCluster), pages, len, pages);
+  const int g = uniform(share.g);
+  if (g == 0) return;   // a workgroup too many
+  const int b = share.b, h = share.h, u = b * p.Hkv + h;
+  const int c0 = min(share.member * share.chunk, share.K), count = min(c0 + share.chunk, share.K) - c0;
+  const int32_t* bt_row = p.block_table + (size_t)b * p.Pmax;
+  const NewToken none{-1, 0, p.q, p.q};
+  attend_split<kWaves, D, S, true, false, false, kHalf>(
+      p, b, h, g, (size_t)share.part_row, share.member, count, share.L, none,
+      [&](int i) { return c0 + i; }, [&](int j) { return bt_row[j]; }, reinterpret_cast<float*>(smem));
+  if (g == 1) return;
+  stores_complete();
+  __syncthreads();
+  if (threadIdx.x == 0) s_last = atomic_add_agent(&unit_done[u * cstride], 1) == g - 1;
+  __syncthreads();
+  if (!uniform(s_last)) return;
+  combine_splits<D>(p, b, h, (size_t)share.part_row, g);
+  if (threadIdx.x == 0) atomic_store_agent(&unit_done[u * cstride], 0);
 }
 
 // ---------------------------------------------------------------------------
@@ -937,6 +987,17 @@ int launch_attention_format(const ts_layout* layout, const AttendParams& a, cons
   const size_t lds = (size_t)kWaves * a.G * (layout->head_dim + 2) * 4;
   dim3 grid(pl.g, pl.units);
   hipStream_t s = (hipStream_t)stream;
+  if constexpr (!kInt8) {
+    if (!sel && pl.balanced) {
+      const FastDiv div_hkv = make_fast_div(a.Hkv);
+#define TS_LAUNCH_DENSE(DD, SS)                                                  \
+  dense_shares_kernel<DD, SS, kHalf><<<pl.per_head * a.Hkv, kThreads, lds, s>>>( \
+      a, unit_done, pl.cstride, layout->num_seqs, pl.per_head, div_hkv)
+      TS_DISPATCH_PAGE(kD, layout->page_size, TS_LAUNCH_DENSE)
+#undef TS_LAUNCH_DENSE
+      return launch_status();
+    }
+  }
 #define TS_LAUNCH_ATTENTION(DD, SS)              \
   sparse_attention_kernel<DD, SS, kInt8, kHalf> \
       <<<grid, kThreads, lds, s>>>(a, sel, sel_count, unit_done, pl.cstride)

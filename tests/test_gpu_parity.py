@@ -696,6 +696,46 @@ def test_dense_baseline_matches_oracle(oracle, built, name, fmt):
     assert torch.equal(first, sess.out)
 
 
+@pytest.mark.parametrize("shape", [(2, 16, 8, 64, 16, 1500), (12, 8, 2, 128, 8, 900), (13, 6, 3, 64, 4, 700),
+                                   (64, 4, 4, 128, 16, 300), (31, 8, 8, 64, 32, 1000), (7, 5, 5, 128, 64, 3000),
+                                   (64, 16, 1, 64, 64, 1500), (5, 12, 12, 128, 4, 400), (9, 28, 28, 64, 8, 200),
+                                   (3, 8, 4, 128, 32, 3000), (20, 4, 2, 64, 16, 1200), (6, 32, 2, 128, 16, 2000)])
+@pytest.mark.parametrize("fmt", ["bf16", "fp16"])
+def test_dense_shares(oracle, built, shape, fmt):
+    """The full-cache path with its workgroups dealt out by the lengths: as many sequences as
+    there are workgroups per head and few, an empty sequence, one of a single token, one page
+    less and more than a share, other lengths in the next call."""
+    B, Hq, Hkv, d, S, L = shape
+    print(f"[case] dense shares {shape} {fmt}", flush=True)
+    w = wl.make_workload(wl.WorkloadSpec("dense", B, Hq, Hkv, d, S, L, 4, L_min=2, headroom=S, kv=fmt), DEV,
+                         seed=17, n_q=2)
+    units = B * Hkv
+    assert units * min(-(-1024 // units), 64, (w.P_max + 3) // 4) > 256 and B <= 256 // Hkv
+    sess = Session(w)
+    scale = 1.0 / math.sqrt(d)
+    ws = ts.new_dense_workspace(sess.layout, DEV)
+    K, V = (wl.bits(x) for x in wl.logical_kv(w))
+    for call in range(2):
+        if call:
+            sess.seq_lens.copy_(w.seq_lens)
+        else:
+            sess.seq_lens[0] = 0
+            sess.seq_lens[B // 2] = 1
+        sess.out.fill_(float("nan"))
+        lse = torch.full((B, Hq), float("nan"), dtype=torch.float32, device=DEV)
+        ts.dense_decode_attention(sess.layout, w.q[call], scale, sess.out, ws, lse_out=lse)
+        torch.cuda.synchronize()
+        lens = sess.seq_lens.cpu().numpy()
+        with oracle.element_format(fmt):
+            ref, ref_lse = oracle.dense_decode_attention(wl.bits(w.q[call]), K, V, lens, scale, return_lse=True)
+        err = np.abs(sess.out.cpu().numpy().astype(np.float64) - ref).max()
+        assert err <= 2e-3, f"dense attention off by {err}"
+        some = lens > 0
+        err = np.abs(lse.cpu().numpy().astype(np.float64) - ref_lse)[some].max()
+        assert err <= LSE_ATOL, f"dense log-denominator off by {err}"
+        assert not sess.out[torch.from_numpy(~some).to(DEV)].any()
+
+
 @pytest.mark.parametrize("name", ["gqa8_d64_s16_offset", "gqa8_d64_s32_walk", "mha_d128_s16_ragged",
                                   "gqa2_d128_s4", "mha_d64_s8_ragged", "gqa4_d64_s64"])
 @pytest.mark.parametrize("splits", [0, 3], indirect=True)
