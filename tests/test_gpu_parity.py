@@ -736,6 +736,25 @@ def test_dense_shares(oracle, built, shape, fmt):
         assert not sess.out[torch.from_numpy(~some).to(DEV)].any()
 
 
+@pytest.mark.parametrize("shape", [(64, 8, 64, 16, 200, 1), (64, 8, 128, 8, 90, 0), (65, 8, 64, 32, 300, 0),
+                                   (65, 8, 128, 16, 150, 1), (79, 9, 64, 4, 60, 0)])
+def test_dense_two_rounds_of_units(oracle, built, shape):
+    """The full-cache path with one workgroup per unit (whole rounds of them, ragged ones) and
+    with several (520 even units)."""
+    B, Hkv, d, S, L, L_min = shape
+    print(f"[case] dense rounds {shape}", flush=True)
+    w = wl.make_workload(wl.WorkloadSpec("rounds", B, Hkv, Hkv, d, S, L, 4, L_min=L_min, headroom=1), DEV, seed=19)
+    sess = Session(w)
+    scale = 1.0 / math.sqrt(d)
+    ws = ts.new_dense_workspace(sess.layout, DEV)
+    ts.dense_decode_attention(sess.layout, w.q[0], scale, sess.out, ws)
+    torch.cuda.synchronize()
+    K, V = (wl.bits(x) for x in wl.logical_kv(w))
+    ref = oracle.dense_decode_attention(wl.bits(w.q[0]), K, V, w.seq_lens.cpu().numpy(), scale)
+    err = np.abs(sess.out.cpu().numpy().astype(np.float64) - ref).max()
+    assert err <= 2e-3, f"dense attention off by {err}"
+
+
 @pytest.mark.parametrize("name", ["gqa8_d64_s16_offset", "gqa8_d64_s32_walk", "mha_d128_s16_ragged",
                                   "gqa2_d128_s4", "mha_d64_s8_ragged", "gqa4_d64_s64"])
 @pytest.mark.parametrize("splits", [0, 3], indirect=True)
