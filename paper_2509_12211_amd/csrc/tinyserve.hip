@@ -586,7 +586,8 @@ int ts_sparse_decode_attention(const ts_layout* layout, const void* q, const int
   if (!q || !sel || !sel_count || !out || !workspace) return TS_ERR_NULL;
   if ((st = check_pool(layout)) != TS_OK) return st;
   if (max_topk < 1) return TS_ERR_SHAPE;
-  const Plan pl = make_plan(layout, max_topk);
+  // (clusters of one size: this call has no use for the exchange area of the fused ones)
+  const Plan pl = make_plan(layout, max_topk, kTargetWorkgroups, false);
   if (workspace_bytes < pl.total) return TS_ERR_WORKSPACE;
   return launch_attention(layout, pl, q, sel, sel_count, max_topk, softmax_scale, out, lse_out,
                           workspace, stream);

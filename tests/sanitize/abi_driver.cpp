@@ -96,6 +96,13 @@ int main() {
   { ts_layout x = good(); x.page_min = NULL; EXPECT(ts_score_pages(&x, p, pf, NULL), TS_ERR_NULL); }
   { ts_layout x = good(); x.num_seqs = 8; x.num_kv_heads = 4; x.num_q_heads = 16; x.max_pages_per_seq = 16384;
     EXPECT(ts_query_aware_decode_static(&x, p, 512, NULL, 512, 1.0f, p, NULL, NULL, NULL, NULL), TS_ERR_WORKSPACE); }
+  // a workspace sized for a large pool serves the staged attention of the same layout with a
+  // smaller one: past the workspace check, the stand-in for the launch says "unsupported"
+  { ts_layout x = good(); x.num_seqs = 24; x.num_q_heads = 32; x.num_kv_heads = 8; x.head_dim = 128;
+    x.max_pages_per_seq = 514; x.num_phys_pages = 24 * 514;
+    const size_t n = ts_workspace_bytes(&x, 130);
+    x.num_phys_pages = 12 * 514;
+    EXPECT(ts_sparse_decode_attention(&x, p, pi, pi, 130, 1.0f, p, NULL, p, n, NULL), TS_ERR_UNSUPPORTED); }
   if (failures == 0) puts("ok");
   return failures != 0;
 }
