@@ -19,6 +19,7 @@
 #include "ts_meta.h"
 #include "ts_score.h"
 #include "ts_select.h"
+#include "ts_shares.h"
 
 namespace ts {
 
@@ -166,7 +167,6 @@ __global__ __launch_bounds__(kThreads) void sparse_attention_kernel(AttendParams
 // ---------------------------------------------------------------------------
 constexpr int kBalanceSeqs = kWave;   // a lane per sequence
 constexpr int kBalanceTryAll = 12;    // sequences up to which trying all shares at once is the quicker way
-constexpr int kBalanceMembers = 32;   // most members of a cluster (more only lengthen its merge)
 
 struct UnitShare {
   int b, h, member, g;   // g == 0: nothing to do
@@ -175,28 +175,29 @@ struct UnitShare {
   int L, K;              // the sequence's length and page budget as given
 };
 
-// The share of workgroup blockIdx.x.  Lane s < B comes with sequence s: its work, the most
-// members its clusters may have, the pages Kb to deal out to them; L and K are handed through.
+// The share of workgroup blockIdx.x.  Lane s < B comes with sequence s: its work (0 in the other
+// lanes), the pages Kb to deal out to its members; L and K are handed through.
 template <int S>
-__device__ __forceinline__ UnitShare deal_shares(int B, int N, int Hkv, const FastDiv& div_hkv, float work,
-                                                 float most, int Kb, int L, int K) {
+__device__ __forceinline__ UnitShare deal_shares(int B, int N, int Hkv, const FastDiv& div_hkv, const SeqWork& w,
+                                                 int Kb, int L, int K) {
   const int lane = lane_id();
   const bool on = lane < B;
+  const float work = w.rows;
   // The smallest share t (work per workgroup) with which sum ceil(work / t) fits into N:
   // t = total / N would if the parts came out even, t = total / (N - B) does in any case (and
   // so does one workgroup each, t = the largest).
   const float total = wave_sum_f32(work), largest = wave_max_f32(work);
   const float lo = total * __builtin_amdgcn_rcpf((float)N);
   const float hi = 1.001f * fminf(largest, total * __builtin_amdgcn_rcpf((float)max(N - B, 1)));
-  auto members = [](float w, float m, float i) { return fmaxf(fminf(ceilf(w * i), m), 1.f); };
   float inv_t = 0.f;   // (0: one workgroup each)
   if (B <= kBalanceTryAll) {   // 64 values of t at once, a lane each
     const float inv = __builtin_amdgcn_rcpf(fmaf(fmaxf(hi - lo, 0.f), (float)lane * (1.f / 63.f), lo));
     float n = 0.f;
     for (int s = 0; s < B; ++s) {
-      const float w = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(work), s));
-      const float m = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(most), s));
-      n += members(w, m, inv);
+      SeqWork ws;
+      ws.rows = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(work), s));
+      ws.most = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(w.most), s));
+      n += members_of(ws, inv);
     }
     const uint64_t fits = __ballot(n <= (float)N);
     if (fits) inv_t = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(inv), __builtin_ctzll(fits)));
@@ -205,7 +206,7 @@ __device__ __forceinline__ UnitShare deal_shares(int B, int N, int Hkv, const Fa
 #pragma unroll
     for (int i = 0; i < 6; ++i) {
       const float mid = i == 0 ? z : 0.5f * (a + z), inv = __builtin_amdgcn_rcpf(mid);
-      if (wave_sum_f32(on ? members(work, most, inv) : 0.f) <= (float)N) {
+      if (wave_sum_f32(on ? members_of(w, inv) : 0.f) <= (float)N) {
         z = mid;
         inv_t = inv;
       } else {
@@ -213,7 +214,7 @@ __device__ __forceinline__ UnitShare deal_shares(int B, int N, int Hkv, const Fa
       }
     }
   }
-  const int gl = on ? (int)members(work, most, inv_t) : 0;
+  const int gl = on ? (int)members_of(w, inv_t) : 0;
   const int incl = wave_inclusive_sum(gl);
   // workgroup x: KV head x mod Hkv (so that with eight heads or a multiple a cluster stays on
   // one XCD), place x / Hkv among the head's N
@@ -245,11 +246,9 @@ __device__ __forceinline__ UnitShare balanced_share(const FusedParams& p) {
   const int K = p.topk_per_seq ? p.topk_per_seq[min(lane, p.B - 1)] : p.topk;
   const int len = L + (kApp && L / S < at.Pmax ? 1 : 0);
   const int P = min(pages_of(len, S), at.Pmax), Kb = max(0, min(min(K, P), at.Kmax));
-  const bool on = lane < p.B;
-  // in metadata rows (a token's K and V are as long as a page's box); at least one, so that an empty sequence has its workgroup too
-  const float work = on ? fmaxf((float)P + (float)(Kb * S), 1.f) : 0.f;
-  const float most = on ? (float)min((Kb + 3) / 4, kBalanceMembers) : 0.f;   // a page per wave at the least
-  return deal_shares<S>(p.B, p.per_head, at.Hkv, p.div_hkv, work, most, Kb, L, K);
+  SeqWork w = seq_work(P, Kb, at.Kmax, S);
+  if (lane >= p.B) w = SeqWork{0.f, 0.f};
+  return deal_shares<S>(p.B, p.per_head, at.Hkv, p.div_hkv, w, Kb, L, K);
 }
 
 // Attention over every cached token, the sequences' workgroups in proportion to their pages.
@@ -271,8 +270,10 @@ __global__ __launch_bounds__(kThreads) void dense_shares_kernel(AttendParams p, 
   const int lane = lane_id(), len = p.seq_lens[min(lane, B - 1)];
   const int pages = lane < B ? max(0, min(pages_of(len, S), p.Pmax)) : 0;
   const UnitShare share =
-      deal_shares<S>(B, per_head, p.Hkv, div_hkv, lane < B ? fmaxf((float)pages, 1.f) : 0.f,
-                     (float)min((pages + 3) / 4, kMaxCluster), pages, len, pages);
+      deal_shares<S>(B, per_head, p.Hkv, div_hkv,
+                     lane < B ? SeqWork{fmaxf((float)pages, 1.f), (float)min((pages + 3) / 4, kMaxCluster)}
+                              : SeqWork{0.f, 0.f},
+                     pages, len, pages);
   const int g = uniform(share.g);
   if (g == 0) return;   // a workgroup too many
   const int b = share.b, h = share.h, u = b * p.Hkv + h;

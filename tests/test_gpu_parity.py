@@ -631,6 +631,32 @@ def test_ragged_batch_with_a_list_longer_than_the_lds(oracle, built):
     compare_units(oracle, sess, [(b, h) for b in range(3) for h in range(2)], scale, what="long list")
 
 
+def test_long_sequence_with_a_small_budget(oracle, built):
+    """One sequence of some 6000 pages that keeps four of them beside three short ones that keep
+    sixty: its members score it together, and most of them have no page to attend, the one
+    that merges among them."""
+    print("[case] small budget", flush=True)
+    w = wl.make_workload(wl.WorkloadSpec("small_budget", 4, 8, 4, 128, 16, 100000, 60, L_min=4000, headroom=16),
+                         DEV, seed=91, n_q=2, n_new=2)
+    longest = int(w.seq_lens.argmax())
+    keep = int(w.seq_lens[longest])
+    assert keep > 60000
+    w.seq_lens.clamp_(max=3000)
+    w.seq_lens[longest] = keep
+    w.topk_per_seq = torch.full((4,), 60, dtype=torch.int32, device=DEV)
+    w.topk_per_seq[longest] = 4
+    sess = Session(w)
+    ts.build_page_meta(sess.layout)
+    scale = 1.0 / math.sqrt(128)
+    units = [(b, h) for b in range(4) for h in (0, 3)]
+    sess.fused(scale)
+    compare_units(oracle, sess, units, scale, what="small budget")
+    ts.append_and_decode(sess.layout, w.k_new[0], w.v_new[0], w.q[1], w.topk, w.K_max, scale, sess.out, sess.ws,
+                         topk_per_seq=w.topk_per_seq, scores_out=sess.scores, sel_out=sess.sel,
+                         sel_count_out=sess.sel_count)
+    compare_units(oracle, sess, units, scale, q_idx=1, what="small budget, append")
+
+
 def test_query_sums_read_back_through_one_hot_boxes(built):
     """Boxes are overwritten so that page c has max = unit vector c and min = 0: the
     score of page c then equals Qp_c = sum over the group's heads of max(q_c, 0), read
