@@ -108,7 +108,7 @@ static Plan make_plan(const ts_layout* L, int max_topk, int target_workgroups = 
   size_t off = kCtrlWords * sizeof(int32_t);
   pl.off_unit = off;
   pl.cstride = pl.units <= kCounterPadUnits ? kCounterPadStride : 1;
-  off = align_up(off + 2 * (size_t)pl.units * pl.cstride * sizeof(int32_t), 256);
+  off = align_up(off + (size_t)pl.units * pl.cstride * sizeof(int32_t), 256);
   // (one workgroup per unit exchanges nothing: its scores never leave LDS and its
   // result goes straight to the output)
   const bool exchange = room > 1 || pl.balanced;
@@ -568,7 +568,7 @@ static int launch_attention(const ts_layout* layout, const Plan& pl, const void*
   unsigned char* ws = static_cast<unsigned char*>(workspace);
   AttendParams a = attend_params(layout, pl, q, out, ws, max_topk, softmax_scale);
   a.lse = lse_out;
-  int32_t* unit_done = reinterpret_cast<int32_t*>(ws + pl.off_unit) + (size_t)pl.units * pl.cstride;
+  int32_t* unit_done = reinterpret_cast<int32_t*>(ws + pl.off_unit);
   int st = TS_ERR_UNSUPPORTED;
 #define TS_CALL(FMT, DD) \
   st = launch_attention_format<FMT, DD>(layout, a, pl, sel, sel_count, unit_done, stream)

@@ -53,7 +53,7 @@ struct Plan {
   int g;              // workgroups per unit (= attention splits = score slices)
   int chunk;          // selected pages per workgroup
   int list;           // entries of a workgroup's list of selected pages in LDS
-  size_t off_unit;    // int32 [2][units * cstride]: [1] = arrival counters of the staged attention ([0] unused)
+  size_t off_unit;    // int32 [units * cstride]: arrival counters of the staged attention
   int cstride;        // words between the counters of consecutive units
   size_t off_scores;  // {fp32 score, uint32 launch tag} [units][Pmax]
   size_t off_part;    // [units][g][G][d+2]: {fp32, launch tag} words (fused) or fp32 (staged attention)

@@ -77,6 +77,13 @@ def test_workspace_bytes_is_host_only_and_monotone():
     assert ts.workspace_bytes(_layout(head_dim=96), 8) == 0
 
 
+def test_one_workgroup_per_unit_needs_a_counter_each_and_no_more():
+    """Control words and one 256-byte slot per unit: nothing is exchanged."""
+    for units in (8, 512):
+        lay = _layout(num_seqs=units // 2, num_phys_pages=64 * units, cluster_size=1)
+        assert ts.workspace_bytes(lay, 64) == 256 + 256 * units
+
+
 def test_ragged_plan_only_where_its_list_fits_the_lds():
     """A pool too small for sequences of the full length asks for shares in proportion to the
     work, which need an exchange area of their own; not with a list of pages that fits the
