@@ -130,10 +130,11 @@ typedef struct ts_layout {
   int32_t kv_format;
   /* How the fused calls (ts_query_aware_decode, ts_append_and_decode) spread one
    * (sequence, KV head) over workgroups.  0 (the default): automatic, about one
-   * workgroup per compute unit in all; with few units a unit is then shared by a
-   * cluster of workgroups that wait for each other inside the launch, which needs
+   * workgroup per compute unit in all; with up to 128 units a unit is then shared by
+   * a cluster of workgroups that wait for each other inside the launch, which needs
    * the whole launch resident at once, i.e. a device that runs nothing else at the
-   * same time.  1: one workgroup per unit; no workgroup ever waits for another, so
+   * same time (with more units nothing waits for a partner; up to 256, an append's
+   * first workgroup waits until all others have started).  1: one workgroup per unit; no workgroup ever waits for another, so
    * the launch is safe beside kernels of other streams (slower for small batches).
    * A serving engine that overlaps other work with the decode step on the same
    * device should set 1; one that runs the step alone should leave 0.  n > 1: that

@@ -105,7 +105,7 @@ static Plan make_plan(const ts_layout* L, int max_topk, int target_workgroups = 
                 L->num_seqs <= kBalanceSeqs && pl.per_head > L->num_seqs &&
                 (double)unit_bytes / pl.g * (1.0 - (double)L->num_phys_pages / ((double)L->num_seqs * Pmax)) >=
                     (double)(pl.g > 1 ? kBalanceBytes : 2 * kBalanceBytes);
-  size_t off = kCtrlWords * sizeof(int32_t);
+  size_t off = kCtrlArea * sizeof(int32_t);
   pl.off_unit = off;
   pl.cstride = pl.units <= kCounterPadUnits ? kCounterPadStride : 1;
   off = align_up(off + (size_t)pl.units * pl.cstride * sizeof(int32_t), 256);
@@ -122,7 +122,7 @@ static Plan make_plan(const ts_layout* L, int max_topk, int target_workgroups = 
                   parts > (size_t)kTargetWorkgroups;
   if (pl.balanced && parts < (size_t)pl.per_head * L->num_kv_heads) parts = (size_t)pl.per_head * L->num_kv_heads;
   pl.off_scores = off;
-  if (exchange) off = align_up(off + (size_t)pl.units * Pmax * sizeof(uint64_t), 256);
+  if (room > 1) off = align_up(off + (size_t)pl.units * Pmax * sizeof(uint64_t), 256);
   pl.off_part = off;
   if (exchange) off = align_up(off + parts * G * (L->head_dim + 2) * sizeof(uint64_t), 256);
   pl.total = off;

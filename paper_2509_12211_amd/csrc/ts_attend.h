@@ -715,8 +715,10 @@ __device__ __forceinline__ bool merge_tagged(const uint64_t* part, int G, int g,
 // split keeps its own partial in registers, polls for the others (bounded by
 // spin_limit polls per thread) and writes the unit's output; the function
 // returns false if that wait expired.
+// kWords (tag == 0): the partial is handed on as such words too, with the tag 0 that no launch
+// has; for callers whose workspace other launches read tagged words from.
 template <int NW, int D, int S, bool kLatency, bool kPatch, bool kInt8, bool kHalf, bool kHaveQ = false,
-          typename SelAt, typename PhysAt>
+          bool kWords = false, typename SelAt, typename PhysAt>
 __device__ __forceinline__ bool attend_split(const AttendParams& p, int b, int h, int n_split,
                                              size_t part_row, int split, int count, int L, const NewToken& nt, SelAt sel_at,
                                              PhysAt phys_at, float* lds, uint32_t tag = 0u,
@@ -982,6 +984,13 @@ __device__ __forceinline__ bool attend_split(const AttendParams& p, int b, int h
           store_agent_tagged(part64 + g * RS + D + 1, Lsum, tag);
         }
       }
+    } else if constexpr (kWords) {
+      uint64_t* part64 = reinterpret_cast<uint64_t*>(p.partials) + (part_row + split) * (size_t)G * RS;
+      store_agent_tagged(part64 + g * RS + c, O, 0u);
+      if (c == 0) {
+        store_agent_tagged(part64 + g * RS + D, M, 0u);
+        store_agent_tagged(part64 + g * RS + D + 1, Lsum, 0u);
+      }
     } else {
       store_agent(part + g * RS + c, O);
       if (c == 0) {
@@ -998,12 +1007,13 @@ __device__ __forceinline__ bool attend_split(const AttendParams& p, int b, int h
 // Merge the n_split partials of unit (b, h), rows part_row .. of the partial area, and write
 // the normalised output.
 // The caller has observed every producer's arrival; the partials are read with
-// agent-scope loads.
-template <int D>
+// agent-scope loads.  kWords: they are words of 8 bytes (see attend_split).
+template <int D, bool kWords = false>
 __device__ __forceinline__ void combine_splits(const AttendParams& p, int b, int h, size_t part_row, int n_split) {
   constexpr int RS = D + 2;
   const int G = p.G;
-  const float* part = p.partials + part_row * G * RS;
+  constexpr int W = kWords ? 2 : 1;   // floats per value
+  const float* part = p.partials + part_row * G * RS * W;
   for (int idx = threadIdx.x; idx < G * D; idx += kThreads) {
     const int g = idx / D, c = idx % D;
     // online merge, 8 partials per round with all their loads in flight together
@@ -1013,8 +1023,8 @@ __device__ __forceinline__ void combine_splits(const AttendParams& p, int b, int
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
         const bool on = s0 + i < n_split;  // rows past the end re-read row 0, unused
-        const float* row = part + ((size_t)(on ? s0 + i : 0) * G + g) * RS;
-        const float ov = load_agent(row + c), mv = load_agent(row + D), lv = load_agent(row + D + 1);
+        const float* row = part + ((size_t)(on ? s0 + i : 0) * G + g) * RS * W;
+        const float ov = load_agent(row + c * W), mv = load_agent(row + D * W), lv = load_agent(row + (D + 1) * W);
         o[i] = on ? ov : 0.f;
         m[i] = on ? mv : -1e30f;
         l[i] = on ? lv : 0.f;

@@ -36,6 +36,11 @@ constexpr int kCtrlWords = 64;   // control words at the head of the workspace
 constexpr int kCtrlError = 2;    // sticky: a bounded wait expired
 constexpr int kCtrlEpoch = 16;   // launches of the fused kernel with clusters so far (own 64-byte line)
 constexpr int kCtrlArrive = 32;  // workgroups of the current launch that have read the epoch (own line)
+// Behind them, for launches of up to 256 workgroups whose units may be shared without waiting:
+// members of a unit that have handed on their partial, zero between launches.  (At the front of
+// the workspace like the control words: layouts that use the same memory in turn find it zero.)
+constexpr int kCtrlDone = kCtrlWords;
+constexpr int kCtrlArea = kCtrlWords + 256;
 constexpr int kSpinLimit = 1 << 20;  // polls (a few hundred ns each) before a wait gives up
 constexpr int kTargetWorkgroups = 256;
 constexpr int kMaxCluster = 64;
@@ -182,39 +187,40 @@ __device__ __forceinline__ UnitShare deal_shares(int B, int N, int Hkv, const Fa
                                                  int Kb, int L, int K) {
   const int lane = lane_id();
   const bool on = lane < B;
-  const float work = w.rows;
-  // The smallest share t (work per workgroup) with which sum ceil(work / t) fits into N:
-  // t = total / N would if the parts came out even, t = total / (N - B) does in any case (and
-  // so does one workgroup each, t = the largest).
-  const float total = wave_sum_f32(work), largest = wave_max_f32(work);
-  const float lo = total * __builtin_amdgcn_rcpf((float)N);
-  const float hi = 1.001f * fminf(largest, total * __builtin_amdgcn_rcpf((float)max(N - B, 1)));
-  float inv_t = 0.f;   // (0: one workgroup each)
+  // The smallest share t (rows per workgroup) with which the members fit into N.  Not below
+  // total / N nor below what a member reads in full; total / (N - B) on top of the latter does
+  // in any case, and so does one workgroup each, t = the largest.
+  const float total = wave_sum_f32(w.rows), largest = wave_max_f32(w.whole + w.rows);
+  const float floor_t = wave_max_f32(w.whole);
+  const float lo = fmaxf(total * __builtin_amdgcn_rcpf((float)N), floor_t);
+  const float hi = 1.001f * fminf(largest, floor_t + total * __builtin_amdgcn_rcpf((float)max(N - B, 1)));
+  float best = INFINITY;   // (one workgroup each)
   if (B <= kBalanceTryAll) {   // 64 values of t at once, a lane each
-    const float inv = __builtin_amdgcn_rcpf(fmaf(fmaxf(hi - lo, 0.f), (float)lane * (1.f / 63.f), lo));
+    const float t = fmaf(fmaxf(hi - lo, 0.f), (float)lane * (1.f / 63.f), lo);
     float n = 0.f;
     for (int s = 0; s < B; ++s) {
       SeqWork ws;
-      ws.rows = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(work), s));
+      ws.whole = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(w.whole), s));
+      ws.rows = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(w.rows), s));
       ws.most = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(w.most), s));
-      n += members_of(ws, inv);
+      n += members_of(ws, __builtin_amdgcn_rcpf(t - ws.whole));
     }
     const uint64_t fits = __ballot(n <= (float)N);
-    if (fits) inv_t = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(inv), __builtin_ctzll(fits)));
+    if (fits) best = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(t), __builtin_ctzll(fits)));
   } else {                       // halving, a lane per sequence
     float a = lo, z = hi;
 #pragma unroll
     for (int i = 0; i < 6; ++i) {
-      const float mid = i == 0 ? z : 0.5f * (a + z), inv = __builtin_amdgcn_rcpf(mid);
-      if (wave_sum_f32(on ? members_of(w, inv) : 0.f) <= (float)N) {
+      const float mid = i == 0 ? z : 0.5f * (a + z);
+      if (wave_sum_f32(on ? members_of(w, __builtin_amdgcn_rcpf(mid - w.whole)) : 0.f) <= (float)N) {
         z = mid;
-        inv_t = inv;
+        best = mid;
       } else {
         a = mid;
       }
     }
   }
-  const int gl = on ? (int)members_of(w, inv_t) : 0;
+  const int gl = on ? (int)members_of(w, __builtin_amdgcn_rcpf(best - w.whole)) : 0;
   const int incl = wave_inclusive_sum(gl);
   // workgroup x: KV head x mod Hkv (so that with eight heads or a multiple a cluster stays on
   // one XCD), place x / Hkv among the head's N
@@ -238,7 +244,7 @@ __device__ __forceinline__ UnitShare deal_shares(int B, int N, int Hkv, const Fa
   return u;
 }
 
-template <int S, bool kApp>
+template <int S, bool kApp, bool kExchange>
 __device__ __forceinline__ UnitShare balanced_share(const FusedParams& p) {
   const AttendParams& at = p.at;
   const int lane = lane_id();
@@ -246,8 +252,8 @@ __device__ __forceinline__ UnitShare balanced_share(const FusedParams& p) {
   const int K = p.topk_per_seq ? p.topk_per_seq[min(lane, p.B - 1)] : p.topk;
   const int len = L + (kApp && L / S < at.Pmax ? 1 : 0);
   const int P = min(pages_of(len, S), at.Pmax), Kb = max(0, min(min(K, P), at.Kmax));
-  SeqWork w = seq_work(P, Kb, at.Kmax, S);
-  if (lane >= p.B) w = SeqWork{0.f, 0.f};
+  SeqWork w = seq_work(P, Kb, at.Kmax, S, kExchange);
+  if (lane >= p.B) w = SeqWork{0.f, 0.f, 0.f};
   return deal_shares<S>(p.B, p.per_head, at.Hkv, p.div_hkv, w, Kb, L, K);
 }
 
@@ -271,8 +277,8 @@ __global__ __launch_bounds__(kThreads) void dense_shares_kernel(AttendParams p, 
   const int pages = lane < B ? max(0, min(pages_of(len, S), p.Pmax)) : 0;
   const UnitShare share =
       deal_shares<S>(B, per_head, p.Hkv, div_hkv,
-                     lane < B ? SeqWork{fmaxf((float)pages, 1.f), (float)min((pages + 3) / 4, kMaxCluster)}
-                              : SeqWork{0.f, 0.f},
+                     lane < B ? SeqWork{0.f, fmaxf((float)pages, 1.f), (float)min((pages + 3) / 4, kMaxCluster)}
+                              : SeqWork{0.f, 0.f, 0.f},
                      pages, len, pages);
   const int g = uniform(share.g);
   if (g == 0) return;   // a workgroup too many
@@ -348,7 +354,7 @@ __device__ __forceinline__ void decode_units(const FusedParams& p) {
   constexpr int NT = NW * kWave;
   static_assert(!(kLoop && kApp), "the append is folded only into the loop-free build");
   static_assert(!kLoop || kCluster, "a single workgroup per unit needs no loop");
-  static_assert(!kBalance || (kCluster && !kLoop), "shares are worked out once, at the head");
+  static_assert(!kBalance || !kLoop, "shares are worked out once, at the head");
   extern __shared__ __align__(16) unsigned char smem[];
   TS_MARK_INIT();
   TS_MARK(22);
@@ -370,11 +376,11 @@ __device__ __forceinline__ void decode_units(const FusedParams& p) {
   UnitShare share{};
   if constexpr (kBalance) {
     epoch_raw = p.ctrl[kCtrlEpoch];
-    share = balanced_share<S, kApp>(p);
+    share = balanced_share<S, kApp, kCluster>(p);
     if (share.g == 0) {   // a workgroup too many: it leaves once all its waves have read the
       asm volatile("" ::"v"(epoch_raw));   // lengths and the epoch
       __syncthreads();
-      if (threadIdx.x == 0) (void)atomic_add_agent(&p.ctrl[kCtrlArrive], 1);
+      if ((kCluster || kApp) && threadIdx.x == 0) (void)atomic_add_agent(&p.ctrl[kCtrlArrive], 1);
       return;
     }
   }
@@ -382,7 +388,9 @@ __device__ __forceinline__ void decode_units(const FusedParams& p) {
   const ClusterSlot where = kBalance   ? ClusterSlot{share.b * at.Hkv + share.h, share.member}
                             : kCluster ? cluster_of(blockIdx.x, p.div_g, p.div_xcds, p.xcds > 1)
                                        : ClusterSlot{(int)blockIdx.x, 0};
-  const int member = kCluster ? where.member : 0;
+  const int member = kCluster || kBalance ? where.member : 0;
+  // (who shares the scoring: without an exchange every member scores all pages)
+  const int scan_g = kCluster ? g : 1, scan_member = kCluster ? member : 0;
   const int chunk = kBalance ? share.chunk : at.chunk;
   const int n_clusters = kCluster ? fast_div(gridDim.x, p.div_g) : (int)gridDim.x;
   // (a launch laid out by XCD is padded to whole rounds of the XCDs: clusters past
@@ -439,7 +447,7 @@ __device__ __forceinline__ void decode_units(const FusedParams& p) {
     for (int k = 0; k < kBtRegs; ++k)   // no branch around the loads
       bt_regs[k] = bt_row[min((int)threadIdx.x + k * NT, Pmax - 1)];
     scan_issue_tile(scan, p.page_min + (size_t)uu * Pmax * D, p.page_max + (size_t)uu * Pmax * D,
-                       Pmax, wave_id(), g, member);
+                       Pmax, wave_id(), scan_g, scan_member);
   };
   if (kLoop ? u < p.units : true) issue_unit(u);   // the host launches no idle cluster
   // (a padding workgroup leaves only here, behind the loads of unit 0, whose results it
@@ -459,7 +467,7 @@ __device__ __forceinline__ void decode_units(const FusedParams& p) {
     const int b = kBalance ? share.b : fast_div(u, p.div_hkv), h = u - b * at.Hkv;
     const int32_t* bt_row = at.block_table + (size_t)b * Pmax;
     uint64_t* srow = p.scores + (size_t)u * Pmax;
-    float* srow_out = p.scores_out ? p.scores_out + (size_t)u * Pmax : nullptr;
+    float* srow_out = p.scores_out && (exchange || member == 0) ? p.scores_out + (size_t)u * Pmax : nullptr;
 
     // 1. score my share of the pages; the unit's block-table row is parked in LDS
     KeyLayout kl;
@@ -524,9 +532,14 @@ __device__ __forceinline__ void decode_units(const FusedParams& p) {
           } else if (__ballot(pg == j_new) != 0ull && pg == j_new) {
             mn = slot_new == 0 ? kn16 : widen_box<kHalf>(mn, kn16, true);
             mx = slot_new == 0 ? kn16 : widen_box<kHalf>(mx, kn16, false);
-            const size_t row = ((size_t)u * Pmax + pg) * D + (lane_id() % LPR) * 8;
-            *reinterpret_cast<uint4*>(const_cast<uint16_t*>(p.page_min) + row) = mn;
-            *reinterpret_cast<uint4*>(const_cast<uint16_t*>(p.page_max) + row) = mx;
+            // (where every member scores the page, each widens it for itself and the first writes
+            // it back; a member that reads the row behind that write widens it once more, to the
+            // same box)
+            if (exchange || member == 0) {
+              const size_t row = ((size_t)u * Pmax + pg) * D + (lane_id() % LPR) * 8;
+              *reinterpret_cast<uint4*>(const_cast<uint16_t*>(p.page_min) + row) = mn;
+              *reinterpret_cast<uint4*>(const_cast<uint16_t*>(p.page_max) + row) = mx;
+            }
           }
         },
         [&](int pg, float s) {
@@ -539,7 +552,7 @@ __device__ __forceinline__ void decode_units(const FusedParams& p) {
           }
           if (srow_out) srow_out[pg] = s;
         },
-        g, member, srow_out != nullptr);
+        scan_g, scan_member, srow_out != nullptr);
     TS_MARK_WAVE(32);
     const int L = uniform(L_unit);
     const int Pb = uniform(min(pages_of(L, S), Pmax));
@@ -698,11 +711,25 @@ __device__ __forceinline__ void decode_units(const FusedParams& p) {
     // words; the cluster's last member (its chunk of the list is the one that
     // can be short) keeps its own in registers, polls for the others and writes
     // the output.  Nobody else waits for anything.
-    const bool merged = attend_split<NW, D, S, kCounted, kApp, kInt8, kHalf, true>(
+    // Shares without an exchange wait for nothing at all: the member that finds itself the
+    // last to have handed on its partial merges them.
+    constexpr bool apart = kBalance && !kCluster;
+    const bool merged = attend_split<NW, D, S, kCounted, kApp, kInt8, kHalf, true, apart>(
         at, b, h, kBalance ? g : at.n_split,
         kBalance ? (size_t)share.part_row : ((size_t)b * at.Hkv + h) * at.n_split, member, count, L, nt, [&](int i) { return my_sel[i]; },
         [&](int j) { return bt_lds[j]; }, reinterpret_cast<float*>(smem), exchange ? tag : 0u,
         nullptr, p.spin_limit, &qop);
+    if (apart && g > 1) {
+      int* last = reinterpret_cast<int*>(smem);   // (free behind the barrier that ends the attention)
+      stores_complete();
+      __syncthreads();
+      if (threadIdx.x == 0) *last = atomic_add_agent(&p.ctrl[kCtrlDone + u], 1) == g - 1;
+      __syncthreads();
+      if (uniform(*last)) {
+        combine_splits<D, true>(at, b, h, (size_t)share.part_row, g);
+        if (threadIdx.x == 0) atomic_store_agent(&p.ctrl[kCtrlDone + u], 0);
+      }
+    }
     TS_MARK(6);
     if (!merged) atomic_store_agent(&p.ctrl[kCtrlError], 1);
     if (!kLoop) break;
@@ -737,11 +764,16 @@ query_aware_decode_kernel(FusedParams p) {
   decode_units<kWaves, D, S, kLoop, kApp, kInt8, kHalf, kCluster>(p);
 }
 
-// Ragged batches: see balanced_share.
-template <int D, int S, bool kApp, bool kHalf>
+// Ragged batches: see balanced_share.  kExchange: the members of a cluster divide the scoring and
+// wait for each other's scores and partials, as in launches with clusters of one size.  Batches
+// that would have one workgroup per unit otherwise (129 to 255 units) do not: their launches
+// never waited, so that several streams could run them side by side, and must not start to.
+// Every member scores all pages, the pages kept are divided, and the last member to finish
+// merges the partials.
+template <int D, int S, bool kApp, bool kHalf, bool kExchange>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void
 balanced_decode_kernel(FusedParams p) {
-  decode_units<kWaves, D, S, false, kApp, false, kHalf, true, true, true>(p);
+  decode_units<kWaves, D, S, false, kApp, false, kHalf, kExchange, true, true>(p);
 }
 
 // Batches of more units than compute units whose units are not small: one workgroup of eight
@@ -889,15 +921,17 @@ static int launch_single(const ts_layout* layout, FusedParams& p, const Plan& pl
 
 // Clusters in proportion to the work (pl.balanced); the plan has seen to it that all
 // workgroups are resident at once.
-template <int D, int S, int kFmt>
+template <int D, int S, int kFmt, bool kExchange>
 static int launch_balanced(const ts_layout* layout, FusedParams& p, const Plan& pl,
                            const void* k_new, const void* v_new, void* stream) {
   constexpr bool kHalf = kFmt == TS_KV_FP16;
-  auto kernel = k_new ? balanced_decode_kernel<D, S, true, kHalf> : balanced_decode_kernel<D, S, false, kHalf>;
+  auto kernel = k_new ? balanced_decode_kernel<D, S, true, kHalf, kExchange>
+                      : balanced_decode_kernel<D, S, false, kHalf, kExchange>;
   int st;
   if ((st = allow_lds(kernel, pl.lds_fused)) != TS_OK) return st;
   const unsigned grid = (unsigned)(pl.per_head * layout->num_kv_heads);
-  if (resident_capacity(kernel, pl.lds_fused) < (int)grid) return TS_ERR_DEVICE;   // they wait for each other
+  if (kExchange && resident_capacity(kernel, pl.lds_fused) < (int)grid)
+    return TS_ERR_DEVICE;   // they wait for each other
   p.xcds = 0;
   p.n_arrive = (int)grid;
   p.per_head = pl.per_head;
@@ -969,7 +1003,9 @@ int launch_fused_format(const ts_layout* layout, FusedParams& p, const Plan& pl,
   int st = TS_ERR_UNSUPPORTED;
 #define TS_LAUNCH_FUSED(DD, SS)                                                                     \
   if constexpr (kFmt != TS_KV_INT8) {                                                              \
-    if (pl.balanced) return launch_balanced<DD, SS, kFmt>(layout, p, pl, k_new, v_new, stream);    \
+    if (pl.balanced)                                                                               \
+      return pl.g > 1 ? launch_balanced<DD, SS, kFmt, true>(layout, p, pl, k_new, v_new, stream)   \
+                      : launch_balanced<DD, SS, kFmt, false>(layout, p, pl, k_new, v_new, stream); \
   }                                                                                                \
   st = pl.g > 1                                                                                    \
            ? launch_clusters<DD, SS, kFmt>(layout, p, pl, k_new, v_new, max_resident, stream)       \

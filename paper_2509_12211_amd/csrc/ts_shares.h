@@ -11,28 +11,33 @@ namespace ts {
 constexpr int kBalanceMembers = 32;   // most members of a cluster (more only lengthen its merge)
 
 // What a sequence asks of the workgroups that share one of its KV heads, in metadata rows (a
-// token's K and V are as long as a page's box), and the most members it may have.
+// token's K and V are as long as a page's box): rows every member reads in full, rows divided
+// among them, and the most members it may have.
 struct SeqWork {
-  float rows, most;
+  float whole, rows, most;
 };
 
 // P pages, Kb of them kept, of at most Kmax that any sequence keeps.  At least one row, so that
-// an empty sequence has its workgroup too.  The limit goes by the longest list (a page per wave
-// of every member at the least there, as with clusters of one size), not by the sequence's own:
-// one that keeps 4 pages of 8000 has 8000 to score, and on one workgroup did so for the whole
-// launch (one of 128 K tokens and five of 1600, 8 KV heads of 128 channels: 116 us; 28.9 now,
-// 42 with even clusters).
-TS_BOTH SeqWork seq_work(int P, int Kb, int Kmax, int S) {
+// an empty sequence has its workgroup too.
+// exchange: the members divide the scoring as well and hand each other the scores.  The limit
+// then goes by the longest list (a page per wave of every member at the least there, as with
+// clusters of one size), not by the sequence's own: one that keeps 4 pages of 8000 has 8000 to
+// score, and on one workgroup did so for the whole launch (one of 128 K tokens and five of
+// 1600, 8 KV heads of 128 channels: 116 us; 28.9 now, 42 with even clusters).
+// Otherwise every member scores all pages, and there is no use for one without pages to attend.
+TS_BOTH SeqWork seq_work(int P, int Kb, int Kmax, int S, bool exchange) {
   SeqWork w;
-  w.rows = fmaxf((float)P + (float)(Kb * S), 1.f);
-  const int most = (Kmax + 3) / 4;
+  w.whole = exchange ? 0.f : (float)P;
+  w.rows = fmaxf((float)(Kb * S) + (exchange ? (float)P : 0.f), 1.f);
+  const int most = ((exchange ? Kmax : Kb) + 3) / 4;
   w.most = (float)(most < kBalanceMembers ? most : kBalanceMembers);
   return w;
 }
 
-// Members of a cluster at `inv_t`, the reciprocal of the rows per workgroup (0: one).
-TS_BOTH float members_of(const SeqWork& w, float inv_t) {
-  return fmaxf(fminf(ceilf(w.rows * inv_t), w.most), 1.f);
+// Members of a cluster at `inv`, the reciprocal of how many divided rows a member may take (the
+// rows per workgroup less those read in full; 0: no limit).
+TS_BOTH float members_of(const SeqWork& w, float inv) {
+  return fmaxf(fminf(ceilf(w.rows * inv), w.most), 1.f);
 }
 
 }  // namespace ts

@@ -78,10 +78,10 @@ def test_workspace_bytes_is_host_only_and_monotone():
 
 
 def test_one_workgroup_per_unit_needs_a_counter_each_and_no_more():
-    """Control words and one 256-byte slot per unit: nothing is exchanged."""
-    for units in (8, 512):
-        lay = _layout(num_seqs=units // 2, num_phys_pages=64 * units, cluster_size=1)
-        assert ts.workspace_bytes(lay, 64) == 256 + 256 * units
+    """One 256-byte slot per unit beside what every workspace has: nothing is exchanged."""
+    small, large = (ts.workspace_bytes(_layout(num_seqs=units // 2, num_phys_pages=64 * units, cluster_size=1), 64)
+                    for units in (8, 512))
+    assert large - small == 256 * (512 - 8)
 
 
 def test_ragged_plan_only_where_its_list_fits_the_lds():

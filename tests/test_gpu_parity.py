@@ -618,6 +618,61 @@ def test_workspace_without_room_for_shares(oracle, built, name):
     compare_units(oracle, sess, units, scale, what=name)
 
 
+RAGGED_UNITS = {
+    # 129 to 255 units of very different lengths and budgets: workgroups dealt out by the work,
+    # the members of a unit without any waiting for each other
+    "d128_s16": wl.WorkloadSpec("ru1", 20, 16, 8, 128, 16, 6000, 0, L_min=1, budget_frac=0.5, headroom=16),
+    "d64_s32": wl.WorkloadSpec("ru2", 18, 8, 8, 64, 32, 16000, 0, L_min=300, budget_frac=0.4, headroom=64),
+    "d64_s4": wl.WorkloadSpec("ru3", 11, 12, 12, 64, 4, 9000, 0, L_min=1, budget_frac=0.5, headroom=16),
+    "d128_s8": wl.WorkloadSpec("ru4", 50, 12, 4, 128, 8, 5000, 0, L_min=1, budget_frac=0.5, headroom=16),
+    "d128_s64": wl.WorkloadSpec("ru5", 3, 64, 64, 128, 64, 9000, 0, L_min=60, budget_frac=0.5, headroom=64),
+    "d64_s8": wl.WorkloadSpec("ru6", 43, 3, 3, 64, 8, 9000, 0, L_min=1, budget_frac=0.5, headroom=16),
+    "d128_s4": wl.WorkloadSpec("ru7", 24, 8, 8, 128, 4, 4000, 0, L_min=1, budget_frac=0.5, headroom=16),
+    "d64_s16": wl.WorkloadSpec("ru8", 24, 32, 8, 64, 16, 16000, 0, L_min=1, budget_frac=0.5, headroom=32),
+    "d128_s32": wl.WorkloadSpec("ru9", 24, 32, 8, 128, 32, 8000, 0, L_min=1, budget_frac=0.5, headroom=32),
+    "d64_s64": wl.WorkloadSpec("ru10", 63, 3, 3, 64, 64, 16000, 0, L_min=1, budget_frac=0.5, headroom=64),
+}
+
+
+@pytest.mark.parametrize("name", list(RAGGED_UNITS))
+@pytest.mark.parametrize("fmt", FORMATS)
+def test_ragged_units_wait_for_nobody(oracle, built, name, fmt):
+    """Launches over more units than half the compute units have never waited inside, so that
+    several streams could run them side by side: with waits limited to one poll the results
+    are right and no wait expires.  An empty sequence and one of a single token among them;
+    with the append (whose first workgroup does wait until the others have started, so that the
+    limit is the default one) and other lengths in between."""
+    spec = wl.scaled(RAGGED_UNITS[name], kv=fmt)
+    print(f"[case] ragged units {name} {fmt}", flush=True)
+    w = wl.make_workload(spec, DEV, seed=717, n_q=4, n_new=4)
+    sess = Session(w)
+    n_units = spec.B * spec.Hkv
+    assert 128 < n_units < 256
+    sess.seq_lens[0] = 0
+    sess.seq_lens[1] = 1
+    ts.build_page_meta(sess.layout)
+    scale = 1.0 / math.sqrt(spec.d)
+    lens = w.seq_lens.cpu().tolist()
+    order = sorted(range(spec.B), key=lambda b: lens[b])
+    units = [(b, h) for b in {0, 1, order[-1], order[-2], order[spec.B // 2], order[spec.B // 3]}
+             for h in {0, spec.Hkv - 1}]
+    for i in range(4):
+        sess.layout.wait_limit = 0 if i % 2 else 1
+        if i % 2:
+            ts.append_and_decode(sess.layout, w.k_new[i], w.v_new[i], w.q[i], w.topk, w.K_max, scale, sess.out,
+                                 sess.ws, topk_per_seq=w.topk_per_seq, scores_out=sess.scores,
+                                 sel_out=sess.sel, sel_count_out=sess.sel_count)
+        else:
+            sess.fused(scale, q_idx=i)
+        compare_units(oracle, sess, units, scale, q_idx=i, what=f"{name} launch {i}")
+        assert torch.isfinite(sess.out).all()
+        sess.out.fill_(float("nan"))
+        sess.sel.fill_(-7)
+        if i == 1:
+            sess.seq_lens.copy_(torch.minimum(torch.roll(sess.seq_lens, 1), w.seq_lens))
+            ts.build_page_meta(sess.layout)
+
+
 def test_ragged_batch_with_a_list_longer_than_the_lds(oracle, built):
     """The longest block tables and a list of pages that only fits the LDS in shares."""
     spec = wl.WorkloadSpec("long_list", 3, 4, 2, 64, 4, 65000, 0, L_min=500, budget_frac=0.4, headroom=32)

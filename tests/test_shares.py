@@ -13,8 +13,9 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 SRC = """
 #include <hip/hip_runtime.h>
 #include "ts_shares.h"
-extern "C" float members(int P, int Kb, int Kmax, int S, float t) {
-  return ts::members_of(ts::seq_work(P, Kb, Kmax, S), 1.f / t);
+extern "C" float members(int P, int Kb, int Kmax, int S, int exchange, float t) {
+  const ts::SeqWork w = ts::seq_work(P, Kb, Kmax, S, exchange != 0);
+  return ts::members_of(w, t > w.whole ? 1.f / (t - w.whole) : INFINITY);
 }
 """
 
@@ -31,20 +32,20 @@ def lib(tmp_path_factory):
                     "-Wno-unknown-warning-option", "-Xclang", "-target-feature", "-Xclang",
                     "-packed-fp32-ops", "-I", CSRC, src, "-o", so], check=True, capture_output=True)
     L = ctypes.CDLL(so)
-    L.members.argtypes = [ctypes.c_int] * 4 + [ctypes.c_float]
+    L.members.argtypes = [ctypes.c_int] * 5 + [ctypes.c_float]
     L.members.restype = ctypes.c_float
     return L
 
 
-def deal(lib, seqs, n, S):
+def deal(lib, seqs, n, S, exchange=1):
     """Members of each (pages, kept) sequence: the smallest share with which they fit into n."""
     kmax = max(k for _, k in seqs)
     lo, hi = 1.0, float(max(p + k * S for p, k in seqs))
     for _ in range(40):
         t = 0.5 * (lo + hi)
-        fits = sum(lib.members(p, k, kmax, S, t) for p, k in seqs) <= n
+        fits = sum(lib.members(p, k, kmax, S, exchange, t) for p, k in seqs) <= n
         lo, hi = (lo, t) if fits else (t, hi)
-    return [int(lib.members(p, k, kmax, S, hi)) for p, k in seqs]
+    return [int(lib.members(p, k, kmax, S, exchange, hi)) for p, k in seqs]
 
 
 def test_a_long_sequence_with_a_small_budget_is_scored_by_many(lib):
@@ -54,7 +55,16 @@ def test_a_long_sequence_with_a_small_budget_is_scored_by_many(lib):
 
 
 def test_no_more_members_than_the_longest_list_has_pages_for(lib):
-    assert lib.members(8000, 4, 4, 16, 100.0) == 1       # four pages at most: one page per wave
-    assert lib.members(8000, 4, 40, 16, 100.0) == 10
-    assert lib.members(8000, 4, 4000, 16, 100.0) == 32   # (a limit of its own)
-    assert lib.members(0, 0, 40, 16, 100.0) == 1         # an empty sequence has its workgroup
+    assert lib.members(8000, 4, 4, 16, 1, 100.0) == 1       # four pages at most: one page per wave
+    assert lib.members(8000, 4, 40, 16, 1, 100.0) == 10
+    assert lib.members(8000, 4, 4000, 16, 1, 100.0) == 32   # (a limit of its own)
+    assert lib.members(0, 0, 40, 16, 1, 100.0) == 1         # an empty sequence has its workgroup
+
+
+def test_members_that_each_score_everything_divide_only_the_pages_kept(lib):
+    assert lib.members(8000, 4, 4000, 16, 0, 100.0) == 1      # nothing to attend for a second one
+    assert lib.members(500, 100, 4000, 16, 0, 900.0) == 4     # 1600 rows of tokens, 400 a member
+    assert lib.members(500, 100, 4000, 16, 0, 400.0) == 25    # (less than the scoring: the limit)
+    assert lib.members(0, 0, 4000, 16, 0, 100.0) == 1
+    got = deal(lib, [(512, 128)] * 4 + [(64, 16)] * 12, 32, 16, exchange=0)
+    assert got == [5] * 4 + [1] * 12 and sum(got) <= 32       # 512 + 2048 / 5 rows each
