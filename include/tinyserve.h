@@ -267,7 +267,11 @@ int ts_append_and_decode(const ts_layout* layout, const void* k_new, const void*
 int ts_append_and_decode_launches(const ts_layout* layout, int32_t max_topk);
 
 /* Host-only: bytes of workspace the three calls above need for this layout and
- * max_topk (0 on invalid arguments).  Reads only the scalar fields. */
+ * max_topk (0 on invalid arguments).  Reads only the scalar fields, and not
+ * num_phys_pages.  With cluster_size 0 and 2 to 64 sequences on at most 255 units
+ * it includes room for 256 partial results (0.13 to 4.1 MiB) of workgroups dealt
+ * out by the lengths; a workspace without that room is accepted and gets clusters
+ * of one size, whose sums come in another order. */
 size_t ts_workspace_bytes(const ts_layout* layout, int32_t max_topk);
 
 /* The comparison the paper measures against (the FullCache rows of its latency

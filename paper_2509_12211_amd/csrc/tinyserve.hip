@@ -32,19 +32,24 @@ constexpr int kDenseTargetWorkgroups = 1024;
 // equal, at 4.7 MB and 15 MB the small one is 6 % and 18 % behind.
 constexpr size_t kSmallUnitBytes = 2 << 20;
 
-// From this many bytes per workgroup that even shares would save the longest sequence (a
-// guess from how much smaller the pool is than what B full-length sequences would need:
-// the lengths themselves are on the device), a launch goes by shares in proportion to the
-// work.  Working the shares out costs 1 us at the head of the kernel, and where one workgroup
-// per unit would have had nothing to exchange, the exchange 2 us more: twice the bytes there.
-// 140 ragged layouts, line against 0 / 20 / 80 / 200 KB: 0.99 / 1.01 / 1.016 / 1.01 times as
-// fast as without; 24 sequences x 8 KV heads of 512-8192 tokens 45.6 -> 40.5 us, 7 x 8 of
-// 4-50 K 38 -> 31 us, 21 x 8 of 38 K at the longest 137 -> 102 us.
-constexpr int kBalanceBytes = 80 << 10;
+// A launch over up to 255 units goes by shares in proportion to the work where the lengths and
+// budgets say that this saves its busiest workgroup kShareBytes (kShareBytesSingle where a unit has
+// one workgroup otherwise and handing partials on is new).  They are on the device, so that the
+// kernel looks at them ahead of its first loads, which costs 0.2-0.5 us where the lengths turn
+// out alike (TinyLLaMA-shaped 19.8 -> 20.0, GPT2-345M-shaped 18.7 -> 19.1 us), and working
+// the shares out another 0.4.  A launch that has little to win whatever the lengths are is spared
+// even that: one whose even clusters read less than this per workgroup and, where all sequences
+// have the same budget, so that only their metadata differ (or, with one workgroup a unit, short
+// ones are left out at best), one with less than kShareBytesUniform per workgroup of what could
+// be divided.  24 sequences x 8 KV heads of 512-8192 tokens, a quarter kept: 45.9 -> 39.9 us (equal
+// lengths 56.2 -> 56.8); 7 x 8 of 4-50 K, a tenth kept: 35.2 -> 29.6; one budget, 12 x 8 of 2-32 K,
+// 64 of 2000 pages kept: 33.9 -> 30.3; 10 x 4 of 2-64 K, pages of 8: 43.4 -> 38.1.
+constexpr int kShareBytes = 80 << 10, kShareBytesSingle = 160 << 10;
+constexpr int kShareBytesUniform = 160 << 10, kShareBytesUniformSingle = 320 << 10;
 constexpr size_t kLdsBytes = 160 << 10;   // of a compute unit
 
 static Plan make_plan(const ts_layout* L, int max_topk, int target_workgroups = kTargetWorkgroups,
-                      bool may_balance = true) {
+                      bool may_share = true) {
   Plan pl;
   const int G = L->num_q_heads / L->num_kv_heads;
   const int Pmax = L->max_pages_per_seq;
@@ -101,48 +106,56 @@ static Plan make_plan(const ts_layout* L, int max_topk, int target_workgroups = 
   // like weight the order of the sums shows in the fourth digit.
   const bool int8 = L->kv_format == TS_KV_INT8;
   pl.per_head = kTargetWorkgroups / L->num_kv_heads;
-  pl.balanced = may_balance && !int8 && target_workgroups == kTargetWorkgroups && forced == 0 && L->num_seqs > 1 &&
-                L->num_seqs <= kBalanceSeqs && pl.per_head > L->num_seqs &&
-                (double)unit_bytes / pl.g * (1.0 - (double)L->num_phys_pages / ((double)L->num_seqs * Pmax)) >=
-                    (double)(pl.g > 1 ? kBalanceBytes : 2 * kBalanceBytes);
+  // (the area for the partials of shares goes by the shape of the batch alone, so that the
+  // workspace for the longest list serves shorter ones, with and without shares)
+  const bool room_for_shares = may_share && !int8 && target_workgroups == kTargetWorkgroups && forced == 0 &&
+                               L->num_seqs > 1 && L->num_seqs <= kBalanceSeqs && pl.per_head > L->num_seqs;
+  const float row_bytes = 4.f * (float)L->head_dim, inv_g = 1.f / (float)pl.g;
+  pl.min_rows = (float)(pl.g > 1 ? kShareBytes : kShareBytesSingle) / row_bytes;
+  // (what shares can save at most: without an exchange they divide only the kept pages)
+  const float kept = (float)(pl.chunk < max_topk ? pl.chunk : max_topk) * (float)L->page_size;
+  const float meta = (float)Pmax * inv_g;
+  pl.shares = room_for_shares && (pl.g > 1 ? meta + kept : kept) >= pl.min_rows;
+  pl.shares_uniform = pl.shares && (pl.g > 1 ? meta * row_bytes >= (float)kShareBytesUniform
+                                             : kept * row_bytes >= (float)kShareBytesUniformSingle);
   size_t off = kCtrlArea * sizeof(int32_t);
   pl.off_unit = off;
   pl.cstride = pl.units <= kCounterPadUnits ? kCounterPadStride : 1;
   off = align_up(off + (size_t)pl.units * pl.cstride * sizeof(int32_t), 256);
   // (one workgroup per unit exchanges nothing: its scores never leave LDS and its
   // result goes straight to the output)
-  const bool exchange = room > 1 || pl.balanced;
+  const bool exchange = room > 1 || room_for_shares;
   size_t parts = (size_t)pl.units * room;
   // Every cached token: one round of workgroups in proportion to the lengths (dense_shares_kernel)
   // wherever there is one for every unit and clusters of one size would not fit one round
   // anyway (a few short sequences: working the shares out costs 0.3 us there and gains
   // nothing).  Its partial results, at most 256 in fp32, have room in the area of these.
   if (target_workgroups == kDenseTargetWorkgroups)
-    pl.balanced = !int8 && L->num_seqs <= kBalanceSeqs && pl.per_head >= L->num_seqs &&
-                  parts > (size_t)kTargetWorkgroups;
-  if (pl.balanced && parts < (size_t)pl.per_head * L->num_kv_heads) parts = (size_t)pl.per_head * L->num_kv_heads;
+    pl.shares = !int8 && L->num_seqs <= kBalanceSeqs && pl.per_head >= L->num_seqs &&
+                parts > (size_t)kTargetWorkgroups;
+  if (room_for_shares && parts < (size_t)pl.per_head * L->num_kv_heads) parts = (size_t)pl.per_head * L->num_kv_heads;
   pl.off_scores = off;
   if (room > 1) off = align_up(off + (size_t)pl.units * Pmax * sizeof(uint64_t), 256);
   pl.off_part = off;
   if (exchange) off = align_up(off + parts * G * (L->head_dim + 2) * sizeof(uint64_t), 256);
   pl.total = off;
-  // fused kernel LDS: select scratch (keys, bins), the unit's block-table row,
+  // fused kernel LDS: select scratch (keys, bins), the query, the unit's block-table row,
   // this workgroup's selected pages; the wave-merge area aliases the keys
   pl.small_units = !int8 && target_workgroups == kTargetWorkgroups && pl.g == 1 &&
                    pl.units > kTargetWorkgroups && unit_bytes <= kSmallUnitBytes;
   const int waves = pl.small_units ? kSmallWaves : kWaves;
   const size_t lds_sel = select_lds_bytes(Pmax, waves);
-  pl.list = pl.balanced ? (max_topk + 3) / 4 * 4 : pl.chunk;   // (a cluster of one holds the whole list)
   const size_t lds_att = (size_t)waves * G * (L->head_dim + 2) * 4;
   // ... and, in an area of its own, the query staging: a wave that is done
   // scoring starts the selection (which clears the bins) while another may not
   // have picked up its query sums yet, so the two must not share memory
   const size_t lds_query = (size_t)G * L->head_dim * 2 + 2 * (size_t)L->head_dim * 8;
-  pl.lds_fused = (lds_sel > lds_att ? lds_sel : lds_att) +
-                 align_up((size_t)Pmax * 4 + (size_t)pl.list * 4, 16) + lds_query;
-  // (a list of all selected pages may not fit where a cluster's share of it does: the longest
-  // block tables with more than about 5000 pages selected)
-  if (target_workgroups == kTargetWorkgroups && pl.balanced && pl.lds_fused > kLdsBytes) return make_plan(L, max_topk, target_workgroups, false);
+  const size_t lds = (lds_sel > lds_att ? lds_sel : lds_att) + lds_query + (size_t)Pmax * 4;
+  // (by shares, a cluster of one holds the whole list.  That may not fit where an even cluster's
+  // share of it does: the longest block tables with more than about 5000 pages selected)
+  const size_t lds_shares = lds + kShareWords * 4 + (size_t)max_topk * 4;
+  if (target_workgroups == kTargetWorkgroups && lds_shares > kLdsBytes) pl.shares = pl.shares_uniform = false;
+  pl.lds_fused = pl.shares ? lds_shares : lds + (size_t)pl.chunk * 4;
   return pl;
 }
 
@@ -327,21 +340,18 @@ static int launch_fused(const ts_layout* layout, const void* k_new, const void* 
   if ((st = check_pool(layout)) != TS_OK) return st;
   if (max_topk < 1 || (!topk_per_seq && (topk < 1 || max_topk < topk))) return TS_ERR_SHAPE;
   Plan pl = make_plan(layout, max_topk);
-  // (shares in proportion to the work need an exchange area for every unit: a workspace
-  // without room for it, one sized for a larger pool for instance, gets clusters of one size)
-  if (pl.balanced && workspace_bytes < pl.total)
+  // (a workspace without room for the partials of shares gets clusters of one size)
+  if (workspace_bytes < pl.total)
     pl = make_plan(layout, max_topk, kTargetWorkgroups, false);
   if (workspace_bytes < pl.total) return TS_ERR_WORKSPACE;
+  if (!topk_per_seq) pl.shares = pl.shares_uniform;
   const int cus = num_compute_units();
   if (cus <= 0) return TS_ERR_DEVICE;
   const int tuned_per_cu = g_tune_wg_per_cu.load(std::memory_order_relaxed);
   const int max_resident = cus * (tuned_per_cu > 0 ? tuned_per_cu : 1);
-  if (pl.balanced && pl.per_head * layout->num_kv_heads > max_resident)   // (a part of a device)
-    pl = make_plan(layout, max_topk, kTargetWorkgroups, false);
   unsigned char* ws = static_cast<unsigned char*>(workspace);
   FusedParams p;
   p.at = attend_params(layout, pl, q, out, ws, max_topk, softmax_scale);
-  p.at.chunk = pl.list;
   p.page_min = static_cast<const uint16_t*>(layout->page_min);
   p.page_max = static_cast<const uint16_t*>(layout->page_max);
   p.scores = reinterpret_cast<uint64_t*>(ws + pl.off_scores);

@@ -131,7 +131,11 @@ __device__ __forceinline__ int tile_token(int t, int r) {
 // and 0 for a placeholder fetch: with 0 every lane reads the first bytes of the
 // tile, so the instruction touches one cache line instead of the whole tile
 // (the data is never used).
-template <int D, int S>
+// kTogether: the loads of a K tile, which come back to the same lines, go out with nothing in
+// between; where the scheduler happened to put other loads there, 24 sequences x 8 KV heads of
+// 8192 tokens took 52.8 instead of 52.3 us.
+constexpr int kAluMayCross = 0xc;   // scalar and matrix instructions (sched_barrier's mask)
+template <int D, int S, bool kTogether = false>
 __device__ __forceinline__ void load_page(PageFrag<D, PageGeom<S>::F>& f, const uint16_t* ktile,
                                           const uint16_t* vtile, int hoff, int spread) {
   constexpr int F = PageGeom<S>::F;
@@ -141,9 +145,13 @@ __device__ __forceinline__ void load_page(PageFrag<D, PageGeom<S>::F>& f, const 
 #pragma unroll
   for (int t = 0; t < PageFrag<D, F>::NT; ++t) {
     const uint16_t* krow = ktile + (hoff + tile_token<F>(t, r)) * D * spread + kb * (D / 4);
+    const uint16_t* at[PageFrag<D, F>::KQ];
 #pragma unroll
-    for (int i = 0; i < PageFrag<D, F>::KQ; ++i)
-      f.k[t][i] = *reinterpret_cast<const uint4*>(krow + i * 8 * spread);
+    for (int i = 0; i < PageFrag<D, F>::KQ; ++i) at[i] = krow + i * 8 * spread;
+    if (kTogether) __builtin_amdgcn_sched_barrier(kAluMayCross);
+#pragma unroll
+    for (int i = 0; i < PageFrag<D, F>::KQ; ++i) f.k[t][i] = *reinterpret_cast<const uint4*>(at[i]);
+    if (kTogether) __builtin_amdgcn_sched_barrier(kAluMayCross);
   }
 #pragma unroll
   for (int cb = 0; cb < PageFrag<D, F>::NCB; ++cb) {
@@ -692,6 +700,8 @@ __device__ __forceinline__ bool merge_tagged(const uint64_t* part, int G, int g,
   return ok;
 }
 
+struct SplitPlace { int n_split, split; size_t part_row; };
+
 // The workgroup attends `count` selected pages of unit (b, h): entry i of its
 // list is page sel_at(i), stored in physical page phys_at(page).  The list is
 // cut into fragments (PageGeom<S>); wave w takes fragments w, w + NW, ...
@@ -699,8 +709,10 @@ __device__ __forceinline__ bool merge_tagged(const uint64_t* part, int G, int g,
 // (lds: NW * G * (D + 2) floats).  With n_split == 1 the normalised result
 // goes to `out`; otherwise the unnormalised partial (o[D], m, l per head) is
 // handed to the combining workgroup through agent-scope stores.
-// The workgroup is part `split` of n_split on the unit; the unit's partials are rows
-// part_row .. part_row + n_split - 1 of the partial area.
+// place() says which part `split` of n_split on the unit the workgroup is; the unit's partials are
+// rows part_row .. part_row + n_split - 1 of the partial area.  It is asked behind the last
+// fragment: three scalars held across the ring of fragments were three more to spill there
+// (24 sequences x 8 KV heads of 8192 tokens: 51.4 -> 53.5 us).
 // Ends with a barrier after which `lds` may be reused; on return (n_split > 1)
 // the caller still has to wait for its stores and count its arrival.
 // kLatency: the launch is bound by the latency of its single pass (every workgroup has
@@ -718,9 +730,9 @@ __device__ __forceinline__ bool merge_tagged(const uint64_t* part, int G, int g,
 // kWords (tag == 0): the partial is handed on as such words too, with the tag 0 that no launch
 // has; for callers whose workspace other launches read tagged words from.
 template <int NW, int D, int S, bool kLatency, bool kPatch, bool kInt8, bool kHalf, bool kHaveQ = false,
-          bool kWords = false, typename SelAt, typename PhysAt>
-__device__ __forceinline__ bool attend_split(const AttendParams& p, int b, int h, int n_split,
-                                             size_t part_row, int split, int count, int L, const NewToken& nt, SelAt sel_at,
+          bool kWords = false, typename PlaceOf, typename SelAt, typename PhysAt>
+__device__ __forceinline__ bool attend_split(const AttendParams& p, int b, int h, PlaceOf place,
+                                             int count, int L, const NewToken& nt, SelAt sel_at,
                                              PhysAt phys_at, float* lds, uint32_t tag = 0u,
                                              const uint16_t* q_rows = nullptr, int spin_limit = 0,
                                              const QOperand<D, kInt8>* q_ready = nullptr) {
@@ -806,7 +818,7 @@ __device__ __forceinline__ bool attend_split(const AttendParams& p, int b, int h
           load_page8<D, S>(fr, k_pool8 + tile, v_pool8 + tile, p.k_scale + so, p.v_scale + so, hoff,
                            good ? 1 : 0);
         } else {
-          load_page<D, S>(fr, p.k_pool + tile, p.v_pool + tile, hoff, good ? 1 : 0);
+          load_page<D, S, kWords>(fr, p.k_pool + tile, p.v_pool + tile, hoff, good ? 1 : 0);
         }
         const int valid = good ? max(0, min(F, L - j * S - hoff)) : 0;
         return valid >= 32 ? 0xffffffffu : (1u << valid) - 1u;
@@ -943,6 +955,9 @@ __device__ __forceinline__ bool attend_split(const AttendParams& p, int b, int h
   }
   __syncthreads();
   TS_MARK(24);
+  const SplitPlace at = place();
+  const int n_split = at.n_split, split = at.split;
+  const size_t part_row = at.part_row;
   float* part = p.partials + (part_row + split) * (size_t)G * RS;
   bool ok = true;
   int spins = 0;

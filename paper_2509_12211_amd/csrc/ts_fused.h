@@ -57,7 +57,6 @@ struct Plan {
   int units;          // B * Hkv
   int g;              // workgroups per unit (= attention splits = score slices)
   int chunk;          // selected pages per workgroup
-  int list;           // entries of a workgroup's list of selected pages in LDS
   size_t off_unit;    // int32 [units * cstride]: arrival counters of the staged attention
   int cstride;        // words between the counters of consecutive units
   size_t off_scores;  // {fp32 score, uint32 launch tag} [units][Pmax]
@@ -65,8 +64,10 @@ struct Plan {
   size_t total;
   size_t lds_fused;   // dynamic LDS of the fused kernel
   bool small_units;   // many small units: small_units_decode_kernel
-  bool balanced;      // a ragged batch: balanced_decode_kernel, per_head workgroups per KV head
-  int per_head;
+  bool shares;        // workgroups by the work if the lengths ask for it, per_head of them per KV head:
+  int per_head;       // shares_decode_kernel (query-aware), dense_shares_kernel (every token)
+  bool shares_uniform;   // ... also where all sequences have the same budget
+  float min_rows;     // ... that is, if it saves the busiest workgroup that many metadata rows
 };
 
 static size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
@@ -91,10 +92,11 @@ struct FusedParams {
   int keep_first, keep_last;   // pages kept whatever their score (0, 0: the paper's selection)
   int spin_limit;              // polls before a cross-workgroup wait gives up
   int xcds;                    // > 1: clusters laid out one per XCD over that many XCDs (see cluster_of)
-  int n_arrive;                // workgroups of the launch that work on a unit
+  int n_arrive;                // workgroups of the launch that count themselves in
   FastDiv div_g, div_xcds, div_hkv;   // divisions by g, xcds and the number of KV heads
   // (last: what stands in front of these is fetched in few loads, see decode_units)
-  int per_head;                // balanced launches: workgroups per KV head
+  int per_head;                // shares: workgroups per KV head
+  float inv_g, min_rows;       // ... see Plan
 };
 
 // Which cluster a workgroup belongs to, and as which member.  The hardware deals
@@ -148,7 +150,7 @@ __global__ __launch_bounds__(kThreads) void sparse_attention_kernel(AttendParams
   const int32_t* bt_row = p.block_table + (size_t)b * p.Pmax;
   const NewToken none{-1, 0, p.q, p.q};
   attend_split<kWaves, D, S, true, false, kInt8, kHalf>(
-      p, b, h, p.n_split, (size_t)u * p.n_split, split, count, p.seq_lens[b], none,
+      p, b, h, [&] { return SplitPlace{p.n_split, split, (size_t)u * p.n_split}; }, count, p.seq_lens[b], none,
       [&](int i) { return sel_row ? sel_row[i] : c0 + i; },
       [&](int j) { return bt_row[j]; }, reinterpret_cast<float*>(smem));
   if (p.n_split == 1) return;
@@ -171,6 +173,7 @@ __global__ __launch_bounds__(kThreads) void sparse_attention_kernel(AttendParams
 // sequence, and finds the one that belongs to its workgroup.
 // ---------------------------------------------------------------------------
 constexpr int kBalanceSeqs = kWave;   // a lane per sequence
+constexpr int kShareWords = 8;        // of LDS, in which a workgroup's place in its unit waits until it is needed
 constexpr int kBalanceTryAll = 12;    // sequences up to which trying all shares at once is the quicker way
 
 struct UnitShare {
@@ -180,21 +183,19 @@ struct UnitShare {
   int L, K;              // the sequence's length and page budget as given
 };
 
-// The share of workgroup blockIdx.x.  Lane s < B comes with sequence s: its work (0 in the other
-// lanes), the pages Kb to deal out to its members; L and K are handed through.
-template <int S>
-__device__ __forceinline__ UnitShare deal_shares(int B, int N, int Hkv, const FastDiv& div_hkv, const SeqWork& w,
-                                                 int Kb, int L, int K) {
+// The smallest share t (rows per workgroup) with which the members of all sequences fit into N
+// workgroups.  Lane s < B comes with sequence s, the other lanes with nothing.  INFINITY: one
+// workgroup each.  Not below total / N nor below what a member reads in full (`lo`); total /
+// (N - B) on top of the latter does in any case, and so does one workgroup each.
+__device__ __forceinline__ float share_floor(int N, const SeqWork& w) {
+  return fmaxf(wave_sum_f32(w.rows) * __builtin_amdgcn_rcpf((float)N), wave_max_f32(w.whole));
+}
+__device__ __forceinline__ float smallest_share(int B, int N, const SeqWork& w, float lo) {
   const int lane = lane_id();
   const bool on = lane < B;
-  // The smallest share t (rows per workgroup) with which the members fit into N.  Not below
-  // total / N nor below what a member reads in full; total / (N - B) on top of the latter does
-  // in any case, and so does one workgroup each, t = the largest.
-  const float total = wave_sum_f32(w.rows), largest = wave_max_f32(w.whole + w.rows);
-  const float floor_t = wave_max_f32(w.whole);
-  const float lo = fmaxf(total * __builtin_amdgcn_rcpf((float)N), floor_t);
-  const float hi = 1.001f * fminf(largest, floor_t + total * __builtin_amdgcn_rcpf((float)max(N - B, 1)));
-  float best = INFINITY;   // (one workgroup each)
+  const float spread = wave_max_f32(w.whole) + wave_sum_f32(w.rows) * __builtin_amdgcn_rcpf((float)max(N - B, 1));
+  const float hi = 1.001f * fminf(wave_max_f32(w.whole + w.rows), spread);
+  float best = INFINITY;
   if (B <= kBalanceTryAll) {   // 64 values of t at once, a lane each
     const float t = fmaf(fmaxf(hi - lo, 0.f), (float)lane * (1.f / 63.f), lo);
     float n = 0.f;
@@ -220,7 +221,15 @@ __device__ __forceinline__ UnitShare deal_shares(int B, int N, int Hkv, const Fa
       }
     }
   }
-  const int gl = on ? (int)members_of(w, __builtin_amdgcn_rcpf(best - w.whole)) : 0;
+  return best;
+}
+
+// The share of workgroup blockIdx.x at t rows per workgroup.  Lane s < B comes with sequence s:
+// its work, the pages Kb to deal out to its members; L and K are handed through.
+template <int S>
+__device__ __forceinline__ UnitShare take_share(int B, int N, int Hkv, const FastDiv& div_hkv, const SeqWork& w,
+                                                float t, int Kb, int L, int K) {
+  const int gl = lane_id() < B ? (int)members_of(w, __builtin_amdgcn_rcpf(t - w.whole)) : 0;
   const int incl = wave_inclusive_sum(gl);
   // workgroup x: KV head x mod Hkv (so that with eight heads or a multiple a cluster stays on
   // one XCD), place x / Hkv among the head's N
@@ -244,17 +253,28 @@ __device__ __forceinline__ UnitShare deal_shares(int B, int N, int Hkv, const Fa
   return u;
 }
 
+// Whether the batch goes by shares, and this workgroup's if so.  Lane s < B comes with the
+// length L and the budget K of sequence s (the lanes past them with the last one's).  Every wave
+// of the launch works it out from the same numbers by the same operations.
+// Batches of one length leave at the first test: there is nothing to gain, whatever the block
+// tables and the pool have room for.  The next one asks what shares could save at the very
+// best, and only then they are worked out.
 template <int S, bool kApp, bool kExchange>
-__device__ __forceinline__ UnitShare balanced_share(const FusedParams& p) {
+__device__ __forceinline__ bool by_shares(const FusedParams& p, int L, int K, UnitShare& share) {
   const AttendParams& at = p.at;
-  const int lane = lane_id();
-  const int L = at.seq_lens[min(lane, p.B - 1)];
-  const int K = p.topk_per_seq ? p.topk_per_seq[min(lane, p.B - 1)] : p.topk;
+  if (__ballot(((L ^ uniform(L)) | (K ^ uniform(K))) != 0) == 0ull) return false;
+  const bool on = lane_id() < p.B;
   const int len = L + (kApp && L / S < at.Pmax ? 1 : 0);
   const int P = min(pages_of(len, S), at.Pmax), Kb = max(0, min(min(K, P), at.Kmax));
   SeqWork w = seq_work(P, Kb, at.Kmax, S, kExchange);
-  if (lane >= p.B) w = SeqWork{0.f, 0.f, 0.f};
-  return deal_shares<S>(p.B, p.per_head, at.Hkv, p.div_hkv, w, Kb, L, K);
+  if (!on) w = SeqWork{0.f, 0.f, 0.f};
+  const float even = wave_max_f32(even_rows(P, Kb, at.chunk, S, p.inv_g));
+  const float lo = share_floor(p.per_head, w);
+  if (even - lo < p.min_rows) return false;
+  const float t = smallest_share(p.B, p.per_head, w, lo);
+  if (even - t < p.min_rows) return false;
+  share = take_share<S>(p.B, p.per_head, at.Hkv, p.div_hkv, w, t, Kb, L, K);
+  return true;
 }
 
 // Attention over every cached token, the sequences' workgroups in proportion to their pages.
@@ -275,11 +295,10 @@ __global__ __launch_bounds__(kThreads) void dense_shares_kernel(AttendParams p, 
   __shared__ int s_last;
   const int lane = lane_id(), len = p.seq_lens[min(lane, B - 1)];
   const int pages = lane < B ? max(0, min(pages_of(len, S), p.Pmax)) : 0;
-  const UnitShare share =
-      deal_shares<S>(B, per_head, p.Hkv, div_hkv,
-                     lane < B ? SeqWork{0.f, fmaxf((float)pages, 1.f), (float)min((pages + 3) / 4, kMaxCluster)}
-                              : SeqWork{0.f, 0.f, 0.f},
-                     pages, len, pages);
+  const SeqWork w = lane < B ? SeqWork{0.f, fmaxf((float)pages, 1.f), (float)min((pages + 3) / 4, kMaxCluster)}
+                             : SeqWork{0.f, 0.f, 0.f};
+  const float t = smallest_share(B, per_head, w, share_floor(per_head, w));
+  const UnitShare share = take_share<S>(B, per_head, p.Hkv, div_hkv, w, t, pages, len, pages);
   const int g = uniform(share.g);
   if (g == 0) return;   // a workgroup too many
   const int b = share.b, h = share.h, u = b * p.Hkv + h;
@@ -287,7 +306,7 @@ __global__ __launch_bounds__(kThreads) void dense_shares_kernel(AttendParams p, 
   const int32_t* bt_row = p.block_table + (size_t)b * p.Pmax;
   const NewToken none{-1, 0, p.q, p.q};
   attend_split<kWaves, D, S, true, false, false, kHalf>(
-      p, b, h, g, (size_t)share.part_row, share.member, count, share.L, none,
+      p, b, h, [&] { return SplitPlace{g, share.member, (size_t)share.part_row}; }, count, share.L, none,
       [&](int i) { return c0 + i; }, [&](int j) { return bt_row[j]; }, reinterpret_cast<float*>(smem));
   if (g == 1) return;
   stores_complete();
@@ -348,13 +367,16 @@ __global__ __launch_bounds__(kThreads) void dense_shares_kernel(AttendParams p, 
 // kCluster says whether a unit is shared by several workgroups (p.g > 1): the
 // build for one workgroup per unit carries nothing of the exchange, the build
 // for clusters nothing of the selection's stand-alone first stages.
+//
+// kDecide: the lengths decide between clusters of one size and shares in proportion to the
+// work (see by_shares), ahead of the first loads.
 template <int NW, int D, int S, bool kLoop, bool kApp, bool kInt8, bool kHalf, bool kCluster,
-          bool kCounted = !kLoop, bool kBalance = false>
+          bool kCounted = !kLoop, bool kDecide = false>
 __device__ __forceinline__ void decode_units(const FusedParams& p) {
   constexpr int NT = NW * kWave;
   static_assert(!(kLoop && kApp), "the append is folded only into the loop-free build");
   static_assert(!kLoop || kCluster, "a single workgroup per unit needs no loop");
-  static_assert(!kBalance || !kLoop, "shares are worked out once, at the head");
+  static_assert(!(kDecide && kLoop), "shares are worked out once, at the head");
   extern __shared__ __align__(16) unsigned char smem[];
   TS_MARK_INIT();
   TS_MARK(22);
@@ -367,44 +389,30 @@ __device__ __forceinline__ void decode_units(const FusedParams& p) {
                "s"(p.v_new), "s"(p.topk), "s"(p.units), "s"(p.g), "s"(p.xcds), "s"(p.div_hkv.d),
                "s"(p.div_hkv.magic), "s"(p.div_g.d), "s"(p.div_g.magic), "s"(p.div_xcds.d),
                "s"(p.div_xcds.magic), "s"(at.q), "s"(at.block_table), "s"(at.seq_lens), "s"(at.Hq),
-               "s"(at.Hkv), "s"(at.G), "s"(at.Pmax), "s"(at.chunk), "s"(at.lse), "s"(at.k_scale),
+               "s"(at.Hkv), "s"(at.G), "s"(at.Pmax), "s"(at.lse), "s"(at.k_scale),
                "s"(at.v_scale));
   const int G = at.G, Pmax = at.Pmax;
   // which unit this workgroup works on, as which of how many members, and the size of a
   // member's chunk of the selected pages
   int epoch_raw, L_raw, K_raw;
-  UnitShare share{};
-  if constexpr (kBalance) {
-    epoch_raw = p.ctrl[kCtrlEpoch];
-    share = balanced_share<S, kApp, kCluster>(p);
-    if (share.g == 0) {   // a workgroup too many: it leaves once all its waves have read the
-      asm volatile("" ::"v"(epoch_raw));   // lengths and the epoch
-      __syncthreads();
-      if ((kCluster || kApp) && threadIdx.x == 0) (void)atomic_add_agent(&p.ctrl[kCtrlArrive], 1);
-      return;
-    }
-  }
-  const int g = kBalance ? share.g : kCluster ? p.g : 1;
-  const ClusterSlot where = kBalance   ? ClusterSlot{share.b * at.Hkv + share.h, share.member}
-                            : kCluster ? cluster_of(blockIdx.x, p.div_g, p.div_xcds, p.xcds > 1)
-                                       : ClusterSlot{(int)blockIdx.x, 0};
-  const int member = kCluster || kBalance ? where.member : 0;
-  // (who shares the scoring: without an exchange every member scores all pages)
-  const int scan_g = kCluster ? g : 1, scan_member = kCluster ? member : 0;
-  const int chunk = kBalance ? share.chunk : at.chunk;
+  const ClusterSlot where = kCluster ? cluster_of(blockIdx.x, p.div_g, p.div_xcds, p.xcds > 1)
+                                     : ClusterSlot{(int)blockIdx.x, 0};
+  int g = kCluster ? p.g : 1, member = kCluster ? where.member : 0;
+  int chunk = at.chunk;
   const int n_clusters = kCluster ? fast_div(gridDim.x, p.div_g) : (int)gridDim.x;
   // (a launch laid out by XCD is padded to whole rounds of the XCDs: clusters past
   // the last unit leave before any barrier, see below, and are not counted in)
-  const bool padding = kCluster && !kLoop && !kBalance && where.cluster >= p.units;
+  const bool padding = (kCluster || kDecide) && !kLoop && where.cluster >= p.units;
   const SelectLds sl = carve_select<NW>(smem, Pmax);
-  const size_t sel_bytes = select_lds_bytes(Pmax, NW);
-  const size_t att_bytes = (size_t)NW * G * (D + 2) * 4;
-  int32_t* bt_lds = reinterpret_cast<int32_t*>(smem + (sel_bytes > att_bytes ? sel_bytes : att_bytes));
-  int32_t* my_sel = bt_lds + Pmax;  // [chunk]
-  unsigned char* q_stage = reinterpret_cast<unsigned char*>(bt_lds) +
-                           ((size_t)Pmax * 4 + (size_t)at.chunk * 4 + 15) / 16 * 16;
+  const uint32_t sel_bytes = (uint32_t)select_lds_bytes(Pmax, NW), att_bytes = (uint32_t)(NW * G * (D + 2) * 4);
+  const uint32_t q_off = sel_bytes > att_bytes ? sel_bytes : att_bytes;
   constexpr bool exchange = kCluster;
+  unsigned char* q_stage = smem + q_off;
+  int32_t* words = reinterpret_cast<int32_t*>(q_stage + ScoreLanes<D, kHalf, NW>::query_stage_bytes(G));
+  int32_t* bt_lds = words + (kDecide ? kShareWords : 0);
+  int32_t* my_sel = bt_lds + Pmax;  // [chunk]
   int u = padding ? 0 : where.cluster;
+  int b = fast_div(u, p.div_hkv), h = u - b * at.Hkv;
 
   // The first loads of a unit (sequence length, K, query rows, block-table row,
   // first metadata tile) are sent out ahead of everything else: for the first
@@ -426,12 +434,36 @@ __device__ __forceinline__ void decode_units(const FusedParams& p) {
   constexpr bool app = kApp;
   constexpr int LPR = ScoreLanes<D, kHalf>::LPR;
   uint4 kn16 = make_uint4(0, 0, 0, 0), vn16 = make_uint4(0, 0, 0, 0);
+  bool leave = padding;
+  if constexpr (kDecide) {
+    const int lane = min(lane_id(), p.B - 1);
+    epoch_raw = p.ctrl[kCtrlEpoch];
+    const int L_lane = at.seq_lens[lane], K_lane = (p.topk_per_seq ? p.topk_per_seq : at.seq_lens)[lane];
+    UnitShare share{b, h, member, g, chunk, u * at.n_split};
+    if (uniform(by_shares<S, kApp, kCluster>(p, L_lane, p.topk_per_seq ? K_lane : p.topk, share))) {
+      leave = share.g == 0;
+      g = share.g;
+      member = share.member;
+      chunk = share.chunk;
+      b = share.b;
+      h = share.h;
+      u = b * at.Hkv + h;
+    }
+    L_raw = __builtin_amdgcn_readlane(L_lane, b);
+    K_raw = p.topk_per_seq ? __builtin_amdgcn_readlane(K_lane, b) : p.topk;
+    // What only the end of the attention needs waits for it in LDS: in scalar registers it was
+    // spilled in the ring of fragments (24 sequences x 8 KV heads of 8192 tokens: 50.6 -> 50.0 us).
+    if (threadIdx.x == 0) {
+      words[0] = g;
+      words[1] = member;
+      words[2] = share.part_row;
+      *reinterpret_cast<int32_t**>(words + 4) = &p.ctrl[kCtrlDone + u];   // (no cluster: u < 256)
+    }
+  }
   auto issue_unit = [&](int uu) {
-    const int b = kBalance ? share.b : fast_div(uu, p.div_hkv), h = uu - b * at.Hkv;
-    if constexpr (kBalance) {
-      L_raw = share.L;
-      K_raw = share.K;
-    } else {
+    if constexpr (!kDecide) {
+      b = fast_div(uu, p.div_hkv);
+      h = uu - b * at.Hkv;
       epoch_raw = p.ctrl[kCtrlEpoch];
       L_raw = at.seq_lens[b];
       K_raw = p.topk_per_seq ? p.topk_per_seq[b] : p.topk;
@@ -447,13 +479,27 @@ __device__ __forceinline__ void decode_units(const FusedParams& p) {
     for (int k = 0; k < kBtRegs; ++k)   // no branch around the loads
       bt_regs[k] = bt_row[min((int)threadIdx.x + k * NT, Pmax - 1)];
     scan_issue_tile(scan, p.page_min + (size_t)uu * Pmax * D, p.page_max + (size_t)uu * Pmax * D,
-                       Pmax, wave_id(), scan_g, scan_member);
+                       Pmax, wave_id(), kCluster ? g : 1, kCluster ? member : 0);
   };
   if (kLoop ? u < p.units : true) issue_unit(u);   // the host launches no idle cluster
+  // (The empty asm keeps the loads where they are: in front of anything that waits for one of
+  // them, in the order of their use.  Left to the scheduler, the query's went out last and was waited
+  // for with everything else.)
+  if (!kLoop) asm volatile("" : : "s"(q_off) : "memory");
   // (a padding workgroup leaves only here, behind the loads of unit 0, whose results it
   // drops: with an exit ahead of them the kernel's arguments would be fetched in two
   // dependent trips, the second one behind the test)
-  if (padding) return;
+  if (leave) {
+    // A workgroup too many counts itself in like the others, once all its waves have read the
+    // lengths and the epoch: lengths advanced while it still looks at them could send it
+    // another way.
+    if (kDecide && (kCluster || kApp)) {
+      asm volatile("" ::"v"(epoch_raw));
+      __syncthreads();
+      if (threadIdx.x == 0) (void)atomic_add_agent(&p.ctrl[kCtrlArrive], 1);
+    }
+    return;
+  }
   TS_MARK(23);
 
   // Launch tag of the score exchange.  The epoch word is read by every
@@ -464,7 +510,6 @@ __device__ __forceinline__ void decode_units(const FusedParams& p) {
   bool counted = false;
   while (kLoop ? u < p.units : true) {
     TS_MARK(0);
-    const int b = kBalance ? share.b : fast_div(u, p.div_hkv), h = u - b * at.Hkv;
     const int32_t* bt_row = at.block_table + (size_t)b * Pmax;
     uint64_t* srow = p.scores + (size_t)u * Pmax;
     float* srow_out = p.scores_out && (exchange || member == 0) ? p.scores_out + (size_t)u * Pmax : nullptr;
@@ -529,7 +574,7 @@ __device__ __forceinline__ void decode_units(const FusedParams& p) {
                 *reinterpret_cast<uint4*>(const_cast<uint16_t*>(p.page_max) + row) = mx;
               }
             }
-          } else if (__ballot(pg == j_new) != 0ull && pg == j_new) {
+          } else if (kApp && __ballot(pg == j_new) != 0ull && pg == j_new) {
             mn = slot_new == 0 ? kn16 : widen_box<kHalf>(mn, kn16, true);
             mx = slot_new == 0 ? kn16 : widen_box<kHalf>(mx, kn16, false);
             // (where every member scores the page, each widens it for itself and the first writes
@@ -552,7 +597,7 @@ __device__ __forceinline__ void decode_units(const FusedParams& p) {
           }
           if (srow_out) srow_out[pg] = s;
         },
-        scan_g, scan_member, srow_out != nullptr);
+        kCluster ? g : 1, kCluster ? member : 0, srow_out != nullptr);
     TS_MARK_WAVE(32);
     const int L = uniform(L_unit);
     const int Pb = uniform(min(pages_of(L, S), Pmax));
@@ -713,21 +758,28 @@ __device__ __forceinline__ void decode_units(const FusedParams& p) {
     // the output.  Nobody else waits for anything.
     // Shares without an exchange wait for nothing at all: the member that finds itself the
     // last to have handed on its partial merges them.
-    constexpr bool apart = kBalance && !kCluster;
+    constexpr bool apart = kDecide && !kCluster;
     const bool merged = attend_split<NW, D, S, kCounted, kApp, kInt8, kHalf, true, apart>(
-        at, b, h, kBalance ? g : at.n_split,
-        kBalance ? (size_t)share.part_row : ((size_t)b * at.Hkv + h) * at.n_split, member, count, L, nt, [&](int i) { return my_sel[i]; },
-        [&](int j) { return bt_lds[j]; }, reinterpret_cast<float*>(smem), exchange ? tag : 0u,
-        nullptr, p.spin_limit, &qop);
-    if (apart && g > 1) {
+        at, b, h,
+        [&] {
+          if constexpr (kDecide) {
+            return SplitPlace{uniform(words[0]), uniform(words[1]), (size_t)uniform(words[2])};
+          } else {
+            return SplitPlace{at.n_split, member, (size_t)u * at.n_split};
+          }
+        },
+        count, L, nt, [&](int i) { return my_sel[i]; }, [&](int j) { return bt_lds[j]; },
+        reinterpret_cast<float*>(smem), exchange ? tag : 0u, nullptr, p.spin_limit, &qop);
+    if (apart && uniform(words[0]) > 1) {
       int* last = reinterpret_cast<int*>(smem);   // (free behind the barrier that ends the attention)
       stores_complete();
       __syncthreads();
-      if (threadIdx.x == 0) *last = atomic_add_agent(&p.ctrl[kCtrlDone + u], 1) == g - 1;
+      int32_t* done = *reinterpret_cast<int32_t**>(words + 4);
+      if (threadIdx.x == 0) *last = atomic_add_agent(done, 1) == words[0] - 1;
       __syncthreads();
       if (uniform(*last)) {
-        combine_splits<D, true>(at, b, h, (size_t)share.part_row, g);
-        if (threadIdx.x == 0) atomic_store_agent(&p.ctrl[kCtrlDone + u], 0);
+        combine_splits<D, true>(at, b, h, (size_t)uniform(words[2]), uniform(words[0]));
+        if (threadIdx.x == 0) atomic_store_agent(done, 0);
       }
     }
     TS_MARK(6);
@@ -764,16 +816,16 @@ query_aware_decode_kernel(FusedParams p) {
   decode_units<kWaves, D, S, kLoop, kApp, kInt8, kHalf, kCluster>(p);
 }
 
-// Ragged batches: see balanced_share.  kExchange: the members of a cluster divide the scoring and
-// wait for each other's scores and partials, as in launches with clusters of one size.  Batches
-// that would have one workgroup per unit otherwise (129 to 255 units) do not: their launches
-// never waited, so that several streams could run them side by side, and must not start to.
-// Every member scores all pages, the pages kept are divided, and the last member to finish
-// merges the partials.
-template <int D, int S, bool kApp, bool kHalf, bool kExchange>
+// Up to 255 units of batches that may be ragged: see by_shares.  kCluster: the members of a
+// cluster divide the scoring and wait for each other's scores and partials, by shares as with
+// clusters of one size.  Batches that have one workgroup per unit otherwise (129 to 255 units) do
+// not: their launches never waited, so that several streams could run them side by side, and
+// must not start to.  Every member scores all pages, the pages kept are divided, and the last
+// member to finish merges the partials.
+template <int D, int S, bool kApp, bool kHalf, bool kCluster>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void
-balanced_decode_kernel(FusedParams p) {
-  decode_units<kWaves, D, S, false, kApp, false, kHalf, kExchange, true, true>(p);
+shares_decode_kernel(FusedParams p) {
+  decode_units<kWaves, D, S, false, kApp, false, kHalf, kCluster, true, true>(p);
 }
 
 // Batches of more units than compute units whose units are not small: one workgroup of eight
@@ -919,24 +971,40 @@ static int launch_single(const ts_layout* layout, FusedParams& p, const Plan& pl
   return TS_OK;
 }
 
-// Clusters in proportion to the work (pl.balanced); the plan has seen to it that all
-// workgroups are resident at once.
-template <int D, int S, int kFmt, bool kExchange>
-static int launch_balanced(const ts_layout* layout, FusedParams& p, const Plan& pl,
-                           const void* k_new, const void* v_new, void* stream) {
-  constexpr bool kHalf = kFmt == TS_KV_FP16;
-  auto kernel = k_new ? balanced_decode_kernel<D, S, true, kHalf, kExchange>
-                      : balanced_decode_kernel<D, S, false, kHalf, kExchange>;
-  int st;
-  if ((st = allow_lds(kernel, pl.lds_fused)) != TS_OK) return st;
-  const unsigned grid = (unsigned)(pl.per_head * layout->num_kv_heads);
-  if (kExchange && resident_capacity(kernel, pl.lds_fused) < (int)grid)
-    return TS_ERR_DEVICE;   // they wait for each other
+// A grid whose clusters of pl.g workgroups lie one per XCD is padded to whole rounds of the XCDs,
+// where that many can be resident at once: the number of workgroups, p.xcds and p.div_xcds.
+static unsigned cluster_grid(FusedParams& p, const Plan& pl, int cap) {
+  const int xcds = num_xcds();
+  const unsigned padded = (unsigned)((pl.units + xcds - 1) / xcds * xcds * pl.g);
   p.xcds = 0;
+  if (xcds <= 1 || (int)padded > cap) return (unsigned)(pl.units * pl.g);
+  p.xcds = xcds;
+  p.div_xcds = make_fast_div(xcds);
+  return padded;
+}
+
+// Up to 255 units of a batch that may be ragged (pl.shares): clusters of one size or in
+// proportion to the work, as the lengths have it.  False: not all workgroups fit the
+// device at once (a part of one).
+template <int D, int S, int kFmt, bool kCluster>
+static bool launch_shares(const ts_layout* layout, FusedParams& p, const Plan& pl, const void* k_new,
+                          int max_resident, void* stream, int& st) {
+  constexpr bool kHalf = kFmt == TS_KV_FP16;
+  auto kernel = k_new ? shares_decode_kernel<D, S, true, kHalf, kCluster>
+                      : shares_decode_kernel<D, S, false, kHalf, kCluster>;
+  if ((st = allow_lds(kernel, pl.lds_fused)) != TS_OK) return true;
+  int cap = resident_capacity(kernel, pl.lds_fused);
+  if (cap > max_resident) cap = max_resident;
+  unsigned grid = kCluster ? cluster_grid(p, pl, cap) : (unsigned)pl.units;
+  if (!kCluster) p.xcds = 0;
+  if (grid < (unsigned)(pl.per_head * layout->num_kv_heads)) grid = (unsigned)(pl.per_head * layout->num_kv_heads);
+  if ((int)grid > cap) return false;
   p.n_arrive = (int)grid;
   p.per_head = pl.per_head;
+  p.inv_g = 1.f / (float)pl.g;
+  p.min_rows = pl.min_rows;
   kernel<<<grid, kThreads, pl.lds_fused, (hipStream_t)stream>>>(p);
-  return TS_OK;
+  return true;
 }
 
 // A cluster of pl.g > 1 workgroups per unit: the loop-free build where all clusters are
@@ -965,16 +1033,8 @@ static int launch_clusters(const ts_layout* layout, FusedParams& p, const Plan& 
   const int xcds = num_xcds();
   p.xcds = 0;
   if (one_unit_each) {
-    unsigned grid = (unsigned)(pl.units * pl.g);
-    p.n_arrive = (int)grid;
-    // clusters one per XCD: the grid is padded to whole rounds of the XCDs if the
-    // padded launch is still resident at once
-    const unsigned padded = (unsigned)((pl.units + xcds - 1) / xcds * xcds * pl.g);
-    if (xcds > 1 && (int)padded <= cap1) {
-      grid = padded;
-      p.xcds = xcds;
-      p.div_xcds = make_fast_div(xcds);
-    }
+    const unsigned grid = cluster_grid(p, pl, cap1);
+    p.n_arrive = pl.units * pl.g;
     if (p.k_new)
       app_kernel<<<grid, kThreads, pl.lds_fused, s>>>(p);
     else
@@ -1003,9 +1063,10 @@ int launch_fused_format(const ts_layout* layout, FusedParams& p, const Plan& pl,
   int st = TS_ERR_UNSUPPORTED;
 #define TS_LAUNCH_FUSED(DD, SS)                                                                     \
   if constexpr (kFmt != TS_KV_INT8) {                                                              \
-    if (pl.balanced)                                                                               \
-      return pl.g > 1 ? launch_balanced<DD, SS, kFmt, true>(layout, p, pl, k_new, v_new, stream)   \
-                      : launch_balanced<DD, SS, kFmt, false>(layout, p, pl, k_new, v_new, stream); \
+    if (pl.shares &&                                                                               \
+        (pl.g > 1 ? launch_shares<DD, SS, kFmt, true>(layout, p, pl, k_new, max_resident, stream, st)  \
+                  : launch_shares<DD, SS, kFmt, false>(layout, p, pl, k_new, max_resident, stream, st))) \
+      return st;                                                                                   \
   }                                                                                                \
   st = pl.g > 1                                                                                    \
            ? launch_clusters<DD, SS, kFmt>(layout, p, pl, k_new, v_new, max_resident, stream)       \
@@ -1025,7 +1086,7 @@ int launch_attention_format(const ts_layout* layout, const AttendParams& a, cons
   dim3 grid(pl.g, pl.units);
   hipStream_t s = (hipStream_t)stream;
   if constexpr (!kInt8) {
-    if (!sel && pl.balanced) {
+    if (!sel && pl.shares) {
       const FastDiv div_hkv = make_fast_div(a.Hkv);
 #define TS_LAUNCH_DENSE(DD, SS)                                                  \
   dense_shares_kernel<DD, SS, kHalf><<<pl.per_head * a.Hkv, kThreads, lds, s>>>( \

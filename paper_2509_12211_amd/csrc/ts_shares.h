@@ -34,6 +34,12 @@ TS_BOTH SeqWork seq_work(int P, int Kb, int Kmax, int S, bool exchange) {
   return w;
 }
 
+// Rows the busiest workgroup of a sequence reads with a cluster of g workgroups, which divide the
+// scoring evenly and the pages kept in pieces of `chunk`.
+TS_BOTH float even_rows(int P, int Kb, int chunk, int S, float inv_g) {
+  return (float)P * inv_g + (float)((Kb < chunk ? Kb : chunk) * S);
+}
+
 // Members of a cluster at `inv`, the reciprocal of how many divided rows a member may take (the
 // rows per workgroup less those read in full; 0: no limit).
 TS_BOTH float members_of(const SeqWork& w, float inv) {

@@ -2,6 +2,8 @@
 workload and compares HIP results against it with the stated tolerances."""
 from __future__ import annotations
 
+import math
+
 import numpy as np
 import torch
 
@@ -163,3 +165,44 @@ def unit_samples(w, n, seed=0):
     while len(picks) < min(n, B * Hkv):
         picks.add((int(rng.integers(B)), int(rng.integers(Hkv))))
     return sorted(picks)
+
+
+SHARE_BYTES = {False: 80 << 10, True: 160 << 10}     # by whether a unit has one workgroup otherwise
+SHARE_BYTES_UNIFORM = {False: 160 << 10, True: 320 << 10}
+
+
+def goes_by_shares(spec, P_max, K_max, lens, budgets, grow=0):
+    """Whether a fused launch deals its workgroups out by the work, and the members each sequence
+    gets: the host's rule (csrc/tinyserve.hip) and the kernel's (csrc/ts_shares.h, by_shares in
+    csrc/ts_fused.h) once more, so that a test can say which way its case takes.  budgets: one
+    number for all sequences, or a list."""
+    B, S, row_bytes = spec.B, spec.S, 4.0 * spec.d
+    uniform = not hasattr(budgets, "__len__")
+    budgets = [int(budgets)] * B if uniform else [int(k) for k in budgets]
+    n = 256 // spec.Hkv
+    g = min(max(1, 256 // (B * spec.Hkv)), (K_max + 3) // 4, 64)
+    chunk = -(-K_max // g)
+    if S < 16:
+        chunk = -(-chunk // 4) * 4
+    g = -(-K_max // chunk)
+    min_rows = SHARE_BYTES[g == 1] / row_bytes
+    meta, kept = P_max / g, min(K_max, chunk) * S
+    if spec.kv == "int8" or not 1 < B <= 64 or n <= B or (meta if g > 1 else 0) + kept < min_rows:
+        return False, None
+    if uniform and (meta if g > 1 else kept) * row_bytes < SHARE_BYTES_UNIFORM[g == 1]:
+        return False, None
+    pages = [min(-(-(int(L) + (grow if int(L) // S < P_max else 0)) // S), P_max) for L in lens]
+    kept = [max(0, min(k, p, K_max)) for k, p in zip(budgets, pages)]
+    whole = [0.0 if g > 1 else float(p) for p in pages]
+    rows = [max(k * S + (p if g > 1 else 0), 1.0) for p, k in zip(pages, kept)]
+    most = [min(((K_max if g > 1 else k) + 3) // 4, 32) for k in kept]
+    even = max(p / g + min(k, chunk) * S for p, k in zip(pages, kept))
+
+    def members(t):
+        return [max(1, min(m, math.ceil(r / (t - w)) if t > w else m)) for w, r, m in zip(whole, rows, most)]
+
+    lo, hi = max(sum(rows) / n, max(whole)), max(w + r for w, r in zip(whole, rows))
+    for _ in range(60):
+        t = 0.5 * (lo + hi)
+        lo, hi = (lo, t) if sum(members(t)) <= n else (t, hi)
+    return len({(int(L), k) for L, k in zip(lens, budgets)}) > 1 and even - hi >= min_rows, members(hi)

@@ -84,14 +84,17 @@ def test_one_workgroup_per_unit_needs_a_counter_each_and_no_more():
     assert large - small == 256 * (512 - 8)
 
 
-def test_ragged_plan_only_where_its_list_fits_the_lds():
-    """A pool too small for sequences of the full length asks for shares in proportion to the
-    work, which need an exchange area of their own; not with a list of pages that fits the
-    160 KB of LDS only in shares (such a launch would be refused)."""
-    for topk, shares in ((1024, True), (8192, False)):
-        full, ragged = (ts.workspace_bytes(_layout(num_seqs=3, page_size=4, max_pages_per_seq=16384,
-                                                   num_phys_pages=n), topk) for n in (3 * 16384, 20000))
-        assert (ragged > full) == shares and ragged >= full > 0
+def test_workspace_goes_by_the_shape_alone():
+    """The size does not move with the pool, and a longer list never needs less, also across the
+    lengths where a cluster of one can no longer hold the whole of it in LDS."""
+    for B, Hkv, S, Pmax in ((3, 2, 4, 16384), (24, 8, 16, 514), (16, 4, 16, 1024), (2, 1, 16, 4000)):
+        def size(topk, n):
+            return ts.workspace_bytes(_layout(num_seqs=B, num_q_heads=Hkv * 4, num_kv_heads=Hkv, page_size=S,
+                                              max_pages_per_seq=Pmax, num_phys_pages=n), topk)
+        sizes = [size(topk, B * Pmax) for topk in (1, 4, 5, 30, 31, 128, 255, 256, 257, 1024, 5000, 6000, 16000)]
+        assert sizes == sorted(sizes) and sizes[0] > 0
+        for n in (1, B * Pmax // 3, 5 * B * Pmax):
+            assert [size(topk, n) for topk in (5, 1024)] == [size(topk, B * Pmax) for topk in (5, 1024)]
 
 
 @pytest.mark.parametrize("kw,code", [

@@ -12,7 +12,8 @@ from paper_2509_12211_amd import tinyserve as ts
 from paper_2509_12211_amd import workloads as wl
 
 from helpers import (assert_out_close, assert_scores_close, attention_on_set, by_sequence,
-                     check_selection, full_size_units, head_view, oracle_sequence, unit_samples)
+                     check_selection, full_size_units, goes_by_shares, head_view, oracle_sequence,
+                     unit_samples)
 
 pytestmark = pytest.mark.gpu
 
@@ -534,56 +535,58 @@ def test_clusters_that_work_through_several_units(oracle, built, name, splits, f
 
 
 BALANCED = {
-    # ragged batches of up to 255 units in a pool too small for B sequences of the full length:
+    # ragged batches of up to 128 units, long and unlike enough for the lengths to ask for shares:
     # workgroups dealt out to the sequences by their work.  Both ways the shares are worked out
-    # (up to 12 sequences, more), 255 as well as 256 workgroups, one head and many
-    "d64_s16": wl.WorkloadSpec("ba1", 5, 8, 4, 64, 16, 3000, 0, L_min=1, budget_frac=0.2, headroom=16),
-    "d128_s32": wl.WorkloadSpec("ba2", 13, 16, 8, 128, 32, 2500, 0, L_min=40, budget_frac=0.3, headroom=16),
-    "d64_s4": wl.WorkloadSpec("ba3", 33, 4, 2, 64, 4, 900, 0, L_min=1, budget_frac=0.25, headroom=16),
-    "d128_s8": wl.WorkloadSpec("ba4", 64, 8, 1, 128, 8, 900, 0, L_min=1, budget_frac=0.4, headroom=16),
-    "d64_s64": wl.WorkloadSpec("ba5", 2, 32, 16, 64, 64, 9000, 0, L_min=300, budget_frac=0.5, headroom=16),
-    "d128_s16": wl.WorkloadSpec("ba6", 19, 12, 12, 128, 16, 1200, 0, L_min=1, budget_frac=0.3, headroom=16),
-    "d64_s8": wl.WorkloadSpec("ba7", 12, 6, 3, 64, 8, 2000, 30, L_min=1, headroom=16),
-    "d128_s4": wl.WorkloadSpec("ba8", 3, 2, 2, 128, 4, 1500, 90, L_min=1, headroom=16),
-    "d64_s32": wl.WorkloadSpec("ba9", 31, 8, 8, 64, 32, 1500, 0, L_min=1, budget_frac=0.5, headroom=16),
-    "d128_s64": wl.WorkloadSpec("ba10", 7, 16, 4, 128, 64, 4000, 9, L_min=1, headroom=16),
+    # (up to 12 sequences, more), 252 as well as 256 workgroups, one head and many, one budget
+    # for all sequences (d64_s8)
+    "d64_s16": wl.WorkloadSpec("ba1", 5, 8, 4, 64, 16, 30000, 0, L_min=1, budget_frac=0.4, headroom=16),
+    "d128_s32": wl.WorkloadSpec("ba2", 13, 16, 8, 128, 32, 3500, 0, L_min=40, budget_frac=0.3, headroom=16),
+    "d64_s4": wl.WorkloadSpec("ba3", 33, 4, 2, 64, 4, 9000, 0, L_min=1, budget_frac=0.3, headroom=16),
+    "d128_s8": wl.WorkloadSpec("ba4", 64, 8, 1, 128, 8, 9000, 0, L_min=1, budget_frac=0.4, headroom=16),
+    "d64_s64": wl.WorkloadSpec("ba5", 3, 32, 16, 64, 64, 30000, 0, L_min=300, budget_frac=0.5, headroom=16),
+    "d128_s16": wl.WorkloadSpec("ba6", 10, 12, 12, 128, 16, 3000, 0, L_min=1, budget_frac=0.3, headroom=16),
+    "d64_s8": wl.WorkloadSpec("ba7", 12, 6, 3, 64, 8, 48000, 100, L_min=1, headroom=16),
+    "d128_s4": wl.WorkloadSpec("ba8", 3, 2, 2, 128, 4, 50000, 300, L_min=1, headroom=16),
+    "d64_s32": wl.WorkloadSpec("ba9", 15, 8, 8, 64, 32, 6000, 0, L_min=1, budget_frac=0.5, headroom=16),
+    "d128_s64": wl.WorkloadSpec("ba10", 7, 16, 4, 128, 64, 12000, 0, L_min=1, budget_frac=0.4, headroom=16),
 }
 
 
+def _by_shares(sess, grow=0):
+    w = sess.w
+    budgets = w.topk if w.topk_per_seq is None else w.topk_per_seq.tolist()
+    return goes_by_shares(w.spec, w.P_max, w.K_max, sess.seq_lens.tolist(), budgets, grow)
+
+
+@pytest.mark.parametrize("roomy", [False, True])
 @pytest.mark.parametrize("name", list(BALANCED))
 @pytest.mark.parametrize("fmt", FORMATS)
-def test_shares_in_proportion_to_the_work(oracle, built, name, fmt):
-    """A room in the list of selected pages that makes the launch a large one (nothing else
-    does: the sequences are short) brings the balanced build; an empty sequence and one of a
+def test_shares_in_proportion_to_the_work(oracle, built, name, fmt, roomy):
+    """Workgroups dealt out by the lengths and budgets, whatever the pool has room for (roomy:
+    one that could hold every sequence at its full length); an empty sequence and one of a
     single token among them, with and without the append, the lengths changing in between."""
     spec = wl.scaled(BALANCED[name], kv=fmt)
-    print(f"[case] balanced {name} {fmt}", flush=True)
+    print(f"[case] balanced {name} {fmt} roomy={roomy}", flush=True)
     w = wl.make_workload(spec, DEV, seed=606, n_q=4, n_new=4)
-    topk = w.topk
-    g = max(1, 256 // (spec.B * spec.Hkv))
-    w.K_max = max(w.K_max, g * (640 << 10) // (spec.S * 4 * spec.d))
     sess = Session(w)
-    full = ts.make_layout(spec.B, spec.Hq, spec.Hkv, spec.d, spec.S, w.P_max, w.k_pool, w.v_pool,
-                          w.block_table, sess.seq_lens, sess.page_min, sess.page_max)
-    full.num_phys_pages = spec.B * w.P_max
-    assert ts.workspace_bytes(sess.layout, w.K_max) >= ts.workspace_bytes(full, w.K_max)
+    if roomy:       # (the kernels never look past the pages the table names)
+        sess.layout.num_phys_pages = max(w.k_pool.shape[0], spec.B * w.P_max)
     sess.seq_lens[0] = 0
     sess.seq_lens[1] = 1
+    went, members = _by_shares(sess)
+    assert went and max(members) > 1, members
     ts.build_page_meta(sess.layout)
     scale = 1.0 / math.sqrt(spec.d)
-    units = [(b, h) for b in range(spec.B) for h in range(spec.Hkv)]
-    rng = np.random.default_rng(12)
-    if len(units) > 40:
-        units = [units[i] for i in sorted(set(rng.integers(0, len(units), 24).tolist()) | {0, spec.Hkv, len(units) - 1})]
+    order = sorted(range(spec.B), key=lambda b: int(sess.seq_lens[b]))
+    units = [(b, h) for b in {0, 1, order[-1], order[-2], order[spec.B // 2], order[spec.B // 3]}
+             for h in {0, spec.Hkv - 1}]
     for i in range(4):
         if i % 2:
-            ts.append_and_decode(sess.layout, w.k_new[i], w.v_new[i], w.q[i], topk, w.K_max, scale, sess.out,
+            ts.append_and_decode(sess.layout, w.k_new[i], w.v_new[i], w.q[i], w.topk, w.K_max, scale, sess.out,
                                  sess.ws, topk_per_seq=w.topk_per_seq, scores_out=sess.scores,
                                  sel_out=sess.sel, sel_count_out=sess.sel_count)
         else:
-            ts.query_aware_decode(sess.layout, w.q[i], topk, w.K_max, scale, sess.out, sess.ws,
-                                  topk_per_seq=w.topk_per_seq, scores_out=sess.scores,
-                                  sel_out=sess.sel, sel_count_out=sess.sel_count)
+            sess.fused(scale, q_idx=i)
         compare_units(oracle, sess, units, scale, q_idx=i, what=f"{name} launch {i}")
         assert torch.isfinite(sess.out).all()
         sess.out.fill_(float("nan"))
@@ -592,30 +595,6 @@ def test_shares_in_proportion_to_the_work(oracle, built, name, fmt):
             sess.seq_lens.copy_(torch.roll(sess.seq_lens, 1))
             sess.seq_lens.copy_(torch.minimum(sess.seq_lens, w.seq_lens))
             ts.build_page_meta(sess.layout)
-
-
-@pytest.mark.parametrize("name", ["d64_s16", "d128_s16"])
-def test_workspace_without_room_for_shares(oracle, built, name):
-    """A workspace with room for clusters of one size and not for shares in proportion to the
-    work (a caller's own, sized for a larger pool) serves a ragged batch all the same."""
-    spec = BALANCED[name]
-    print(f"[case] small workspace {name}", flush=True)
-    w = wl.make_workload(spec, DEV, seed=31, n_q=1, n_new=1)
-    g = max(1, 256 // (spec.B * spec.Hkv))
-    w.K_max = max(w.K_max, g * (640 << 10) // (spec.S * 4 * spec.d))
-    sess = Session(w)
-    n_phys = sess.layout.num_phys_pages
-    sess.layout.num_phys_pages = spec.B * w.P_max
-    plain = ts.workspace_bytes(sess.layout, w.K_max)
-    sess.layout.num_phys_pages = n_phys
-    assert plain < ts.workspace_bytes(sess.layout, w.K_max)
-    sess.ws = torch.zeros(plain, dtype=torch.uint8, device=DEV)
-    ts.workspace_init(sess.ws)
-    ts.build_page_meta(sess.layout)
-    scale = 1.0 / math.sqrt(spec.d)
-    sess.fused(scale)
-    units = [(b, h) for b in range(spec.B) for h in range(0, spec.Hkv, 3)]
-    compare_units(oracle, sess, units, scale, what=name)
 
 
 RAGGED_UNITS = {
@@ -650,6 +629,8 @@ def test_ragged_units_wait_for_nobody(oracle, built, name, fmt):
     assert 128 < n_units < 256
     sess.seq_lens[0] = 0
     sess.seq_lens[1] = 1
+    went, members = _by_shares(sess)
+    assert went and max(members) > 1, members
     ts.build_page_meta(sess.layout)
     scale = 1.0 / math.sqrt(spec.d)
     lens = w.seq_lens.cpu().tolist()
@@ -673,13 +654,85 @@ def test_ragged_units_wait_for_nobody(oracle, built, name, fmt):
             ts.build_page_meta(sess.layout)
 
 
+@pytest.mark.parametrize("name", ["d64_s16", "d128_s16"])
+def test_workspace_without_room_for_shares(oracle, built, name):
+    """A workspace with room for clusters of one size and not for shares in proportion to the
+    work (a caller's own) serves a ragged batch all the same."""
+    spec = (BALANCED if name == "d64_s16" else RAGGED_UNITS)[name]
+    print(f"[case] small workspace {name}", flush=True)
+    w = wl.make_workload(spec, DEV, seed=31, n_q=1, n_new=1)
+    sess = Session(w)
+    sess.layout.cluster_size = max(1, 256 // (spec.B * spec.Hkv))     # what is chosen by itself
+    plain = ts.workspace_bytes(sess.layout, w.K_max)
+    sess.layout.cluster_size = 0
+    assert plain < ts.workspace_bytes(sess.layout, w.K_max)
+    sess.ws = torch.zeros(plain, dtype=torch.uint8, device=DEV)
+    ts.workspace_init(sess.ws)
+    ts.build_page_meta(sess.layout)
+    scale = 1.0 / math.sqrt(spec.d)
+    sess.fused(scale)
+    order = sorted(range(spec.B), key=lambda b: int(sess.seq_lens[b]))
+    units = [(b, h) for b in {order[0], order[-1], order[spec.B // 2]} for h in range(0, spec.Hkv, 3)]
+    compare_units(oracle, sess, units, scale, what=name)
+
+
+EQUAL = {
+    # batches of one length in tables with room for twice that, with a budget of its own per
+    # sequence: the kernel that looks at the lengths finds nothing to deal out.  Clusters, clusters
+    # in whole rounds of the XCDs, one workgroup per unit, more workgroups than members
+    "d64_s16": wl.WorkloadSpec("eq1", 5, 8, 4, 64, 16, 9000, 240, headroom=9000),
+    "d128_s32": wl.WorkloadSpec("eq2", 4, 16, 4, 128, 32, 7000, 90, headroom=7000),
+    "d128_s16": wl.WorkloadSpec("eq3", 20, 16, 8, 128, 16, 3000, 90, headroom=3000),
+    "d64_s4": wl.WorkloadSpec("eq4", 3, 6, 6, 64, 4, 5000, 600, headroom=5000),
+    "d64_s64": wl.WorkloadSpec("eq5", 13, 13, 13, 64, 64, 6000, 90, headroom=6000),
+    "d128_s8": wl.WorkloadSpec("eq6", 30, 8, 4, 128, 8, 3000, 200, headroom=3000),
+}
+
+
+@pytest.mark.parametrize("name", list(EQUAL))
+@pytest.mark.parametrize("fmt", FORMATS)
+def test_equal_lengths_in_the_kernel_that_asks_for_them(oracle, built, name, fmt):
+    """Results bit-equal to those of the same launch told to use clusters of that size, step
+    after step with the append (which advances the lengths the next launch looks at)."""
+    spec = wl.scaled(EQUAL[name], kv=fmt)
+    print(f"[case] equal {name} {fmt}", flush=True)
+    got = []
+    for forced in (0, max(1, min(256 // (spec.B * spec.Hkv), (spec.topk + 3) // 4))):
+        w = wl.make_workload(spec, DEV, seed=808, n_q=4, n_new=4)
+        w.topk_per_seq = torch.full((spec.B,), spec.topk, dtype=torch.int32, device=DEV)
+        sess = Session(w, cluster_size=forced)
+        went, members = _by_shares(sess)
+        assert not went and members is not None      # (asked, and answered no)
+        ts.build_page_meta(sess.layout)
+        scale = 1.0 / math.sqrt(spec.d)
+        for i in range(4):
+            if i % 2:
+                ts.append_and_decode(sess.layout, w.k_new[i], w.v_new[i], w.q[i], w.topk, w.K_max, scale, sess.out,
+                                     sess.ws, topk_per_seq=w.topk_per_seq, scores_out=sess.scores,
+                                     sel_out=sess.sel, sel_count_out=sess.sel_count)
+            else:
+                sess.fused(scale, q_idx=i)
+            torch.cuda.synchronize()
+            assert ts.workspace_status(sess.ws) == 0
+            if forced:
+                out, sel, scores = got.pop(0)
+                assert torch.equal(out, sess.out) and torch.equal(sel, sess.sel) and torch.equal(scores, sess.scores)
+            else:
+                got.append((sess.out.clone(), sess.sel.clone(), sess.scores.clone()))
+        if not forced:
+            lens = sess.seq_lens.clone()
+    assert torch.equal(lens, sess.seq_lens) and int(lens[0]) == spec.L + 2
+    compare_units(oracle, sess, [(0, 0), (spec.B - 1, spec.Hkv - 1)], scale, q_idx=3, what=name)
+
+
 def test_ragged_batch_with_a_list_longer_than_the_lds(oracle, built):
     """The longest block tables and a list of pages that only fits the LDS in shares."""
     spec = wl.WorkloadSpec("long_list", 3, 4, 2, 64, 4, 65000, 0, L_min=500, budget_frac=0.4, headroom=32)
     print("[case] long list", flush=True)
     w = wl.make_workload(spec, DEV, seed=443, n_q=1, n_new=1)
-    assert w.K_max > 5300 and sum(-(-int(n) // spec.S) for n in w.seq_lens) < 0.6 * spec.B * w.P_max
+    assert w.K_max > 5300
     sess = Session(w)
+    assert _by_shares(sess)[0]       # (what it would do if the list fitted)
     ts.build_page_meta(sess.layout)
     scale = 1.0 / math.sqrt(spec.d)
     sess.fused(scale)
@@ -701,6 +754,8 @@ def test_long_sequence_with_a_small_budget(oracle, built):
     w.topk_per_seq = torch.full((4,), 60, dtype=torch.int32, device=DEV)
     w.topk_per_seq[longest] = 4
     sess = Session(w)
+    went, members = _by_shares(sess)
+    assert went and members[longest] > 4, members
     ts.build_page_meta(sess.layout)
     scale = 1.0 / math.sqrt(128)
     units = [(b, h) for b in range(4) for h in (0, 3)]

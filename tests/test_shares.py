@@ -1,10 +1,15 @@
 """The arithmetic by which ragged batches are dealt out to workgroups (csrc/ts_shares.h), on the
 CPU: the header is compiled into a small library of its own and the dealing done in Python."""
 import ctypes
+import math
 import os
 import subprocess
 
 import pytest
+
+from paper_2509_12211_amd import workloads as wl
+
+from helpers import goes_by_shares
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2509_12211_amd", "csrc")
@@ -13,6 +18,7 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 SRC = """
 #include <hip/hip_runtime.h>
 #include "ts_shares.h"
+extern "C" float even(int P, int Kb, int chunk, int S, int g) { return ts::even_rows(P, Kb, chunk, S, 1.f / g); }
 extern "C" float members(int P, int Kb, int Kmax, int S, int exchange, float t) {
   const ts::SeqWork w = ts::seq_work(P, Kb, Kmax, S, exchange != 0);
   return ts::members_of(w, t > w.whole ? 1.f / (t - w.whole) : INFINITY);
@@ -32,14 +38,16 @@ def lib(tmp_path_factory):
                     "-Wno-unknown-warning-option", "-Xclang", "-target-feature", "-Xclang",
                     "-packed-fp32-ops", "-I", CSRC, src, "-o", so], check=True, capture_output=True)
     L = ctypes.CDLL(so)
+    L.even.argtypes = [ctypes.c_int] * 5
+    L.even.restype = ctypes.c_float
     L.members.argtypes = [ctypes.c_int] * 5 + [ctypes.c_float]
     L.members.restype = ctypes.c_float
     return L
 
 
-def deal(lib, seqs, n, S, exchange=1):
+def deal(lib, seqs, n, S, exchange=1, kmax=None):
     """Members of each (pages, kept) sequence: the smallest share with which they fit into n."""
-    kmax = max(k for _, k in seqs)
+    kmax = kmax or max(k for _, k in seqs)
     lo, hi = 1.0, float(max(p + k * S for p, k in seqs))
     for _ in range(40):
         t = 0.5 * (lo + hi)
@@ -68,3 +76,38 @@ def test_members_that_each_score_everything_divide_only_the_pages_kept(lib):
     assert lib.members(0, 0, 4000, 16, 0, 100.0) == 1
     got = deal(lib, [(512, 128)] * 4 + [(64, 16)] * 12, 32, 16, exchange=0)
     assert got == [5] * 4 + [1] * 12 and sum(got) <= 32       # 512 + 2048 / 5 rows each
+
+
+@pytest.mark.parametrize("B,Hkv,d,S,L,topk,frac", [(5, 4, 64, 16, 30000, 0, .4), (13, 8, 128, 32, 3500, 0, .3),
+                                                    (33, 2, 64, 4, 9000, 0, .3), (24, 8, 128, 16, 8192, 0, .25),
+                                                    (7, 8, 128, 32, 50001, 0, .1), (12, 8, 128, 16, 32000, 64, 0)])
+def test_model_of_the_rule_deals_like_the_header(lib, B, Hkv, d, S, L, topk, frac):
+    """helpers.goes_by_shares, which the GPU tests ask which way a case goes, against the header."""
+    spec = wl.WorkloadSpec("m", B, Hkv, Hkv, d, S, L, topk)
+    P_max = -(-L // S)
+    lens = [1 + (L - 1) * i // (B - 1) for i in range(B)]
+    K_max = topk if topk else math.ceil(frac * P_max) + 1
+    budgets = topk if topk else [max(1, math.ceil(frac * -(-n // S))) for n in lens]
+    went, members = goes_by_shares(spec, P_max, K_max, lens, budgets)
+    assert went
+    g = max(1, min(256 // (B * Hkv), (K_max + 3) // 4))
+    seqs = [(-(-n // S), min(k, -(-n // S))) for n, k in zip(lens, budgets if frac else [topk] * B)]
+    want = deal(lib, seqs, 256 // Hkv, S, 1 if g > 1 else 0, K_max)
+    assert members == want and sum(members) <= 256 // Hkv
+    # alike lengths, whatever the table has room for: nothing to deal out
+    same = [L // 2] * B
+    assert not goes_by_shares(spec, P_max, K_max, same, topk if topk else [K_max // 2] * B)[0]
+
+
+def test_rows_of_an_even_cluster(lib):
+    assert lib.even(1024, 128, 32, 16, 4) == 256 + 512      # a quarter of the scoring, 32 pages
+    assert lib.even(1024, 4, 32, 16, 4) == 256 + 64         # fewer kept than a member's piece
+    assert lib.even(512, 128, 128, 16, 1) == 512 + 2048
+
+
+def test_one_budget_for_all_needs_metadata_to_gain_by():
+    """The same kept pages everywhere: only the metadata differ, and short tables have little."""
+    spec = wl.WorkloadSpec("m", 16, 32, 4, 64, 16, 16384, 128)
+    lens = [1000 + 1000 * i for i in range(16)]
+    assert goes_by_shares(spec, 1026, 128, lens, 128) == (False, None)            # not even asked
+    assert goes_by_shares(spec, 1026, 128, lens, [128] * 16)[1] is not None
