@@ -81,30 +81,13 @@ static Plan make_plan(const ts_layout* L, int max_topk, int target_workgroups = 
   // groups per workgroup
   if (L->page_size < 16) pl.chunk = (pl.chunk + 3) / 4 * 4;
   pl.g = (max_topk + pl.chunk - 1) / pl.chunk;
-  const int room = pl.g;   // of the exchange area
-  // Full-cache path, two rounds of units and more: one workgroup each, unless their lengths look
-  // alike (a pool of nearly full sequences) and the last round would be more than half empty.
-  // 22 layouts of 512 to 992 units against two workgroups each: ragged ones 1.10-1.55 times
-  // faster (48 x 16 of 500-4096 tokens, page 32, 105.7 -> 80.9 us; 31 x 32 of 100-2000, 128
-  // channels, 137 -> 98), even ones 1.03-1.09 (64 x 8 of 4096, 128 channels, 189 -> 178), but
-  // 544 and 640 even units (2.1 and 2.5 rounds) 0.92 and 0.95.  A pool much smaller than the
-  // longest sequence suggests keeps two: a workgroup alone gets 35 GB/s of the 5800, so
-  // that a few long sequences would decide the finish time.  (The workspace is the same either
-  // way: it does not depend on the size of the pool.)
-  if (target_workgroups == kDenseTargetWorkgroups && L->kv_format != TS_KV_INT8 &&
-      pl.units >= 2 * kTargetWorkgroups) {
-    const int last = pl.units % kTargetWorkgroups;
-    const double fill = (double)L->num_phys_pages / ((double)L->num_seqs * Pmax);
-    if (fill >= 0.4 && (fill < 0.9 || last == 0 || last > kTargetWorkgroups * 5 / 8)) {
-      pl.g = 1;
-      pl.chunk = max_topk;
-    }
-  }
   const size_t unit_bytes = ((size_t)Pmax + (size_t)max_topk * L->page_size) * 4 * L->head_dim;
   // The INT8 cache keeps the same partition of a unit over waves and workgroups everywhere: its
   // operands carry a bias that cancels out of the output, so that with thousands of tokens of
   // like weight the order of the sums shows in the fourth digit.
   const bool int8 = L->kv_format == TS_KV_INT8;
+  // Full-cache path, two rounds of units and more: one workgroup or two each, by the lengths
+  pl.rounds = target_workgroups == kDenseTargetWorkgroups && !int8 && pl.units >= 2 * kTargetWorkgroups && pl.g == 2;
   pl.per_head = kTargetWorkgroups / L->num_kv_heads;
   // (the area for the partials of shares goes by the shape of the batch alone, so that the
   // workspace for the longest list serves shorter ones, with and without shares)
@@ -124,8 +107,8 @@ static Plan make_plan(const ts_layout* L, int max_topk, int target_workgroups = 
   off = align_up(off + (size_t)pl.units * pl.cstride * sizeof(int32_t), 256);
   // (one workgroup per unit exchanges nothing: its scores never leave LDS and its
   // result goes straight to the output)
-  const bool exchange = room > 1 || room_for_shares;
-  size_t parts = (size_t)pl.units * room;
+  const bool exchange = pl.g > 1 || room_for_shares;
+  size_t parts = (size_t)pl.units * pl.g;
   // Every cached token: one round of workgroups in proportion to the lengths (dense_shares_kernel)
   // wherever there is one for every unit and clusters of one size would not fit one round
   // anyway (a few short sequences: working the shares out costs 0.3 us there and gains
@@ -135,7 +118,7 @@ static Plan make_plan(const ts_layout* L, int max_topk, int target_workgroups = 
                 parts > (size_t)kTargetWorkgroups;
   if (room_for_shares && parts < (size_t)pl.per_head * L->num_kv_heads) parts = (size_t)pl.per_head * L->num_kv_heads;
   pl.off_scores = off;
-  if (room > 1) off = align_up(off + (size_t)pl.units * Pmax * sizeof(uint64_t), 256);
+  if (pl.g > 1) off = align_up(off + (size_t)pl.units * Pmax * sizeof(uint64_t), 256);
   pl.off_part = off;
   if (exchange) off = align_up(off + parts * G * (L->head_dim + 2) * sizeof(uint64_t), 256);
   pl.total = off;

@@ -66,6 +66,7 @@ struct Plan {
   bool small_units;   // many small units: small_units_decode_kernel
   bool shares;        // workgroups by the work if the lengths ask for it, per_head of them per KV head:
   int per_head;       // shares_decode_kernel (query-aware), dense_shares_kernel (every token)
+  bool rounds;        // every token, two rounds of units and more: dense_rounds_kernel
   bool shares_uniform;   // ... also where all sequences have the same budget
   float min_rows;     // ... that is, if it saves the busiest workgroup that many metadata rows
 };
@@ -315,6 +316,62 @@ __global__ __launch_bounds__(kThreads) void dense_shares_kernel(AttendParams p, 
   __syncthreads();
   if (!uniform(s_last)) return;
   combine_splits<D>(p, b, h, (size_t)share.part_row, g);
+  if (threadIdx.x == 0) atomic_store_agent(&unit_done[u * cstride], 0);
+}
+
+// Attention over every cached token, two rounds of units and more: one workgroup each, or the
+// sequences longer than half the longest in two parts, as the lengths have it (see
+// rounds_of).  A workgroup alone gets 35 GB/s of the 5800, so that a few sequences much
+// longer than the rest would decide the finish time.
+// Workgroup x < units has unit x or its first part, and workgroup units + x the second: those
+// with nothing to do come last, when the compute units run out of work anyway.  With a few
+// long sequences workgroups 2 u and 2 u + 1 have unit u, so that their second parts do not come last
+// (64 x 8 units, three of 16 K tokens and the rest of 800: 142 -> 117 us; 600 units of 300 tokens the
+// other way round, 21.6 against 20.4).
+// bf16, against two parts at half the table's width for all, split with its partials whatever
+// the length: 48 x 16 units of 500-4096 tokens, pages of 32, 105.4 -> 79.4 us; 31 x 32 of 100-2000,
+// 128 channels, 131 -> 97; 64 x 8 of 4096, 128 channels, 181 -> 173; 56 x 16 of 2-8 K 229 -> 210.
+template <int D, int S, bool kHalf>
+__global__ __launch_bounds__(kThreads) void dense_rounds_kernel(AttendParams p, int32_t* unit_done,
+                                                                int cstride, int B, int units,
+                                                                FastDiv div_hkv) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  __shared__ int s_last;
+  const int x = (int)blockIdx.x, u_far = x < units ? x : x - units, u_near = x >> 1;
+  const int len_far = p.seq_lens[fast_div(u_far, div_hkv)], len_near = p.seq_lens[fast_div(u_near, div_hkv)];
+  int total = 0, longest = 0;
+  for (int i = lane_id(); i < B; i += kWave) {
+    const int pages = max(0, min(pages_of(p.seq_lens[i], S), p.Pmax));
+    total += pages;
+    longest = max(longest, pages);
+  }
+  total = __builtin_amdgcn_readlane(wave_inclusive_sum(total), 63);
+  longest = (int)wave_max_u32((uint32_t)longest);
+  const Rounds way = (Rounds)uniform(rounds_of(total, longest, B, units));
+  const bool near = way == kFewLong;
+  const int split = near ? x & 1 : (int)(x >= units), u = near ? u_near : u_far;
+  const int b = fast_div(u, div_hkv), h = u - b * p.Hkv, len = uniform(near ? len_near : len_far);
+  const int pages = max(0, min(pages_of(len, S), p.Pmax));
+  int chunk = longest;
+  if (way != kWhole) {
+    chunk = (longest + 1) / 2;
+    if (S < 16) chunk = (chunk + 3) / 4 * 4;   // whole groups of small pages
+  }
+  const int n_split = pages > chunk ? 2 : 1;
+  if (split >= n_split) return;
+  const int c0 = split * chunk, count = min(chunk, pages - c0);
+  const int32_t* bt_row = p.block_table + (size_t)b * p.Pmax;
+  const NewToken none{-1, 0, p.q, p.q};
+  attend_split<kWaves, D, S, true, false, false, kHalf>(
+      p, b, h, [&] { return SplitPlace{n_split, split, (size_t)u * 2}; }, count, len, none,
+      [&](int i) { return c0 + i; }, [&](int j) { return bt_row[j]; }, reinterpret_cast<float*>(smem));
+  if (n_split == 1) return;
+  stores_complete();
+  __syncthreads();
+  if (threadIdx.x == 0) s_last = atomic_add_agent(&unit_done[u * cstride], 1) == 1;
+  __syncthreads();
+  if (!uniform(s_last)) return;
+  combine_splits<D>(p, b, h, (size_t)u * 2, 2);
   if (threadIdx.x == 0) atomic_store_agent(&unit_done[u * cstride], 0);
 }
 
@@ -1093,6 +1150,17 @@ int launch_attention_format(const ts_layout* layout, const AttendParams& a, cons
       a, unit_done, pl.cstride, layout->num_seqs, pl.per_head, div_hkv)
       TS_DISPATCH_PAGE(kD, layout->page_size, TS_LAUNCH_DENSE)
 #undef TS_LAUNCH_DENSE
+      return launch_status();
+    }
+  }
+  if constexpr (!kInt8) {
+    if (!sel && pl.rounds) {
+      const FastDiv div_hkv = make_fast_div(a.Hkv);
+#define TS_LAUNCH_ROUNDS(DD, SS)                                          \
+  dense_rounds_kernel<DD, SS, kHalf><<<2 * pl.units, kThreads, lds, s>>>( \
+      a, unit_done, pl.cstride, layout->num_seqs, pl.units, div_hkv)
+      TS_DISPATCH_PAGE(kD, layout->page_size, TS_LAUNCH_ROUNDS)
+#undef TS_LAUNCH_ROUNDS
       return launch_status();
     }
   }

@@ -46,4 +46,17 @@ TS_BOTH float members_of(const SeqWork& w, float inv) {
   return fmaxf(fminf(ceilf(w.rows * inv), w.most), 1.f);
 }
 
+// Every cached token, two rounds of units and more (of kRound at once): whether each unit is best
+// left to one workgroup (kWhole).  total, longest: pages of the B sequences.  A few sequences much
+// longer than the rest would decide the finish time (kFewLong); even lengths are divided where
+// they would leave the last round mostly empty (kHalves).
+constexpr int kRound = 256;
+enum Rounds { kWhole, kHalves, kFewLong };
+TS_BOTH Rounds rounds_of(int total, int longest, int B, int units) {
+  const float mean = (float)total / (float)B, most = (float)longest;
+  const int last = units % kRound;
+  if (mean < 0.4f * most) return kFewLong;
+  return mean < 0.9f * most || last == 0 || last > kRound * 5 / 8 ? kWhole : kHalves;
+}
+
 }  // namespace ts

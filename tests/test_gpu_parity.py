@@ -874,21 +874,37 @@ def test_dense_shares(oracle, built, shape, fmt):
 
 @pytest.mark.parametrize("shape", [(64, 8, 64, 16, 200, 1), (64, 8, 128, 8, 90, 0), (65, 8, 64, 32, 300, 0),
                                    (65, 8, 128, 16, 150, 1), (79, 9, 64, 4, 60, 0)])
-def test_dense_two_rounds_of_units(oracle, built, shape):
-    """The full-cache path with one workgroup per unit (whole rounds of them, ragged ones) and
-    with several (520 even units)."""
+@pytest.mark.parametrize("lengths", ["drawn", "few_long", "empty_and_one"])
+def test_dense_two_rounds_of_units(oracle, built, shape, lengths):
+    """The full-cache path with one workgroup per unit (whole rounds of them, ragged ones), with
+    halves (520 even units) and with a few long sequences in two parts beside whole short ones;
+    twice on one workspace, the log-denominators too."""
     B, Hkv, d, S, L, L_min = shape
-    print(f"[case] dense rounds {shape}", flush=True)
+    print(f"[case] dense rounds {shape} {lengths}", flush=True)
     w = wl.make_workload(wl.WorkloadSpec("rounds", B, Hkv, Hkv, d, S, L, 4, L_min=L_min, headroom=1), DEV, seed=19)
+    if lengths == "few_long":
+        longest = w.seq_lens.argsort(descending=True)[:3]
+        short = w.seq_lens.clamp(max=L // 4)
+        short[longest] = w.seq_lens[longest]
+        w.seq_lens.copy_(short)
+    elif lengths == "empty_and_one":
+        w.seq_lens[0], w.seq_lens[1], w.seq_lens[B - 1] = 0, 1, 0
     sess = Session(w)
     scale = 1.0 / math.sqrt(d)
     ws = ts.new_dense_workspace(sess.layout, DEV)
-    ts.dense_decode_attention(sess.layout, w.q[0], scale, sess.out, ws)
-    torch.cuda.synchronize()
-    K, V = (wl.bits(x) for x in wl.logical_kv(w))
-    ref = oracle.dense_decode_attention(wl.bits(w.q[0]), K, V, w.seq_lens.cpu().numpy(), scale)
-    err = np.abs(sess.out.cpu().numpy().astype(np.float64) - ref).max()
-    assert err <= 2e-3, f"dense attention off by {err}"
+    K, V = wl.logical_kv(w)
+    ref, ref_lse = oracle.dense_decode_attention(wl.bits(w.q[0]), wl.bits(K), wl.bits(V),
+                                                 w.seq_lens.cpu().numpy(), scale, return_lse=True)
+    some = w.seq_lens.cpu().numpy() > 0
+    lse = torch.full((B, Hkv), float("nan"), dtype=torch.float32, device=DEV)
+    for _ in range(2):
+        sess.out.fill_(float("nan"))
+        ts.dense_decode_attention(sess.layout, w.q[0], scale, sess.out, ws, lse_out=lse)
+        torch.cuda.synchronize()
+        err = np.abs(sess.out.cpu().numpy().astype(np.float64) - ref).max()
+        assert err <= 2e-3, f"dense attention off by {err}"
+        err = np.abs(lse.cpu().numpy().astype(np.float64)[some] - ref_lse[some]).max()
+        assert err <= LSE_ATOL, f"dense log-denominator off by {err}"
 
 
 @pytest.mark.parametrize("name", ["gqa8_d64_s16_offset", "gqa8_d64_s32_walk", "mha_d128_s16_ragged",

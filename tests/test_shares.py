@@ -19,6 +19,7 @@ SRC = """
 #include <hip/hip_runtime.h>
 #include "ts_shares.h"
 extern "C" float even(int P, int Kb, int chunk, int S, int g) { return ts::even_rows(P, Kb, chunk, S, 1.f / g); }
+extern "C" int rounds(int total, int longest, int B, int units) { return ts::rounds_of(total, longest, B, units); }
 extern "C" float members(int P, int Kb, int Kmax, int S, int exchange, float t) {
   const ts::SeqWork w = ts::seq_work(P, Kb, Kmax, S, exchange != 0);
   return ts::members_of(w, t > w.whole ? 1.f / (t - w.whole) : INFINITY);
@@ -111,3 +112,20 @@ def test_one_budget_for_all_needs_metadata_to_gain_by():
     lens = [1000 + 1000 * i for i in range(16)]
     assert goes_by_shares(spec, 1026, 128, lens, 128) == (False, None)            # not even asked
     assert goes_by_shares(spec, 1026, 128, lens, [128] * 16)[1] is not None
+
+
+WHOLE, HALVES, FEW_LONG = 0, 1, 2
+
+
+@pytest.mark.parametrize("pages,Hkv,want", [
+    ([256] * 64, 8, WHOLE),                      # even, two full rounds
+    ([125] * 68, 8, HALVES),                     # even, a last round of 32
+    ([125] * 75, 9, WHOLE),                      # even, a last round of 163
+    ([10 * i + 100 for i in range(68)], 8, WHOLE),   # ragged: the rounds do not end together anyway
+    ([1000] * 3 + [50] * 61, 8, FEW_LONG),
+    ([0] * 64, 8, WHOLE),                        # nothing cached at all
+])
+def test_rounds_of_whole_or_divided_units_go_by_the_lengths(lib, pages, Hkv, want):
+    """The full-cache path over two rounds of units and more; the pool and the table's width have
+    no say (a pool of B full tables let a few long sequences decide the finish time)."""
+    assert lib.rounds(sum(pages), max(pages), len(pages), len(pages) * Hkv) == want
