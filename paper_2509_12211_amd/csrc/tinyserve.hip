@@ -639,7 +639,8 @@ int ts_query_aware_decode(const ts_layout* layout, const void* q, int32_t topk,
 // array starts out zeroed, which is the state ts_workspace_init would leave; from
 // then on the launches keep it consistent themselves (launch tags only grow,
 // whatever layout the bytes were last used for: every exchange word is an aligned
-// 8-byte {value, tag} pair and the control words always sit at the front).
+// 8-byte {value, tag} pair, partials that nobody polls for carry the tag 0 that no launch
+// has, and the control words and counters always sit at the front).
 // ---------------------------------------------------------------------------
 static __device__ __align__(256) unsigned char scratch[TS_STATIC_WORKSPACE_BYTES];
 constexpr int kMaxDevices = 64;

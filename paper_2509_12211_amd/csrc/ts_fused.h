@@ -952,7 +952,8 @@ static int allow_lds(KernelT kernel, size_t bytes) {
              : TS_ERR_LAUNCH;
 }
 
-// Workgroups of `kernel` that can be resident on the whole device at once.  The
+// Workgroups of `kernel`, of eight waves (only such workgroups ever wait for each other, and
+// only of them anyone asks), that can be resident on the whole device at once.  The
 // runtime's answer is remembered per (device, kernel, LDS size): the query costs more
 // host time than the launch itself.
 template <typename KernelT>

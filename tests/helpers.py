@@ -145,8 +145,8 @@ def assert_out_close(gpu_out, oracle_out, what=""):
 def full_size_units(w, name):
     """Units compared at full size: every (sequence, KV head) of the small batches; of the
     ragged batch all KV heads of the 8 shortest and the 8 longest sequences and of the
-    sequences that hold the first unit, the units on either side of the first hand-out
-    of tickets beyond the resident workgroups (255, 256) and the last unit."""
+    sequences that hold the first unit, the units on either side of the end of the first
+    round of workgroups (255, 256) and the last unit."""
     B, Hkv = w.spec.B, w.spec.Hkv
     if name != "ragged":
         return [(b, h) for b in range(B) for h in range(Hkv)]

@@ -264,7 +264,8 @@ MANY8 = {
 
 
 @pytest.mark.parametrize("name", list(MANY8))
-def test_int8_many_units_loop_build(oracle, name):
+def test_int8_many_units(oracle, name):
+    """More units than compute units: one workgroup of eight waves each, whatever their size."""
     spec = MANY8[name]
     print(f"[case] int8 many units {name}", flush=True)
     w = wl.make_workload(spec, DEV, seed=404, n_q=2, n_new=1)

@@ -346,7 +346,7 @@ def test_append_matches_oracle_and_rebuild(oracle, built):
 APPEND_FUSED = {
     # clusters of two workgroups per unit
     "gqa4_d64_s16": wl.WorkloadSpec("af1", 4, 8, 2, 64, 16, 200, 6, L_min=1, headroom=48),
-    # more units than workgroups: one workgroup per unit, units handed out by ticket
+    # more units than compute units: one workgroup per unit, handed out by the hardware
     "mha_d128_s16_many": wl.WorkloadSpec("af2", 72, 4, 4, 128, 16, 300, 5, L_min=1, headroom=48),
     "gqa8_d64_s32": wl.WorkloadSpec("af3", 3, 16, 2, 64, 32, 700, 7, keys="walk", headroom=80),
     "gqa2_d128_s32": wl.WorkloadSpec("af4", 2, 4, 2, 128, 32, 500, 4, headroom=80),
@@ -409,8 +409,8 @@ def test_append_and_decode_equals_separate_calls(oracle, built, name, splits, fm
 
 
 MANY_UNITS = {
-    # more units than resident workgroups: the build of the fused kernel that loops over
-    # units (one workgroup per unit, units handed out by ticket), every (d, S) instance
+    # more units than compute units: one workgroup per unit, handed out by the hardware, every
+    # (d, S) instance
     "d64_s16": wl.WorkloadSpec("mu1", 80, 4, 4, 64, 16, 700, 9, L_min=1, headroom=32),
     "d64_s32": wl.WorkloadSpec("mu2", 40, 16, 8, 64, 32, 900, 6, L_min=1, headroom=64),
     "d128_s16": wl.WorkloadSpec("mu3", 70, 4, 4, 128, 16, 500, 0, L_min=1, budget_frac=0.3,
@@ -427,12 +427,19 @@ MANY_UNITS = {
 }
 
 
+def _unit_bytes(w):
+    """What a unit is taken to be worth at most: all of its metadata and the longest list's tiles."""
+    return (w.P_max + w.K_max * w.spec.S) * 4 * w.spec.d
+
+
 @pytest.mark.parametrize("name", list(MANY_UNITS))
 @pytest.mark.parametrize("fmt", FORMATS)
-def test_many_units_loop_build(oracle, built, name, fmt):
+def test_many_small_units(oracle, built, name, fmt):
+    """Units of up to 2 MB: workgroups of four waves, two to a compute unit."""
     spec = wl.scaled(MANY_UNITS[name], kv=fmt)
     print(f"[case] many units {name} {fmt}", flush=True)
     w = wl.make_workload(spec, DEV, seed=404, n_q=3, n_new=3)
+    assert _unit_bytes(w) <= 2 << 20
     sess = Session(w)
     ts.build_page_meta(sess.layout)
     scale = 1.0 / math.sqrt(spec.d)
@@ -451,8 +458,7 @@ def test_many_units_loop_build(oracle, built, name, fmt):
         else:
             sess.fused(scale, q_idx=i)
         compare_units(oracle, sess, units, scale, q_idx=i, what=f"{name} launch {i}")
-        # units are handed out longest sequence first: every one of them must have been
-        # (the buffers start out as NaN / -7)
+        # every unit must have had its workgroup (the buffers start out as NaN / -7)
         assert torch.isfinite(sess.out).all() and int(sess.sel[:, :, 0].min()) >= 0
         sess.out.fill_(float("nan"))
         sess.sel.fill_(-7)
@@ -460,15 +466,16 @@ def test_many_units_loop_build(oracle, built, name, fmt):
 
 @pytest.mark.parametrize("name", list(MANY_UNITS))
 @pytest.mark.parametrize("fmt", FORMATS)
-def test_many_large_units_loop_build(oracle, built, name, fmt):
+def test_many_large_units(oracle, built, name, fmt):
     """Batches of more units than compute units whose units may be large (room for enough
-    selected pages in the list) go through the looping build, whatever they hold; the same
-    layouts with a short list (above) run one small workgroup per unit."""
+    selected pages in the list), whatever they hold: one workgroup of eight waves per unit,
+    one to a compute unit, where the same layouts with a short list (above) run small ones."""
     spec = wl.scaled(MANY_UNITS[name], kv=fmt)
     print(f"[case] many large units {name} {fmt}", flush=True)
     w = wl.make_workload(spec, DEV, seed=405, n_q=2, n_new=2)
     topk = w.topk
     w.K_max = (2 << 20) // (spec.S * 4 * spec.d) + 3
+    assert _unit_bytes(w) > 2 << 20
     sess = Session(w)
     ts.build_page_meta(sess.layout)
     scale = 1.0 / math.sqrt(spec.d)
@@ -1410,7 +1417,7 @@ FULL = ["tiny", "gpt2_345m", "tinyllama", "longctx", "ragged"]
 def test_full_size_sampled(oracle, built, name):
     """The five benchmark workloads at full size, default launch shapes: EVERY unit of the four
     small batches, and of the ragged batch every KV head of 20 sequences (shortest, longest, the
-    ticket boundaries), against the oracle."""
+    ends of the first round of workgroups), against the oracle."""
     spec = wl.SPECS[name]
     print(f"[case] full {name}", flush=True)
     w = wl.make_workload(spec, DEV, seed=1000 + FULL.index(name), n_q=2, n_new=1)

@@ -28,6 +28,12 @@ KERNELS = {
     "page 16": "_ZN2ts25query_aware_decode_kernelILi64ELi16ELb0ELb1ELb0ELb0ELb1EEEvNS_11FusedParamsE",
     "page 32": "_ZN2ts25query_aware_decode_kernelILi64ELi32ELb0ELb1ELb0ELb0ELb1EEEvNS_11FusedParamsE",
 }
+# the builds that look at the lengths first: append folded in and not, clusters and one
+# workgroup per unit
+SHARES = {
+    "shares, append, clusters": "_ZN2ts20shares_decode_kernelILi64ELi16ELb1ELb0ELb1EEEvNS_11FusedParamsE",
+    "shares, single": "_ZN2ts20shares_decode_kernelILi64ELi16ELb0ELb0ELb0EEEvNS_11FusedParamsE",
+}
 
 
 @pytest.fixture(scope="module")
@@ -75,9 +81,9 @@ def test_arguments_arrive_in_one_trip(fused_asm, which):
     assert spills == 0, f"{spills} scalar registers parked in vector lanes ahead of the first load"
 
 
-@pytest.mark.parametrize("which", sorted(KERNELS))
+@pytest.mark.parametrize("which", sorted(KERNELS) + sorted(SHARES))
 def test_no_scratch_memory(fused_asm, which):
-    sym = KERNELS[which]
+    sym = KERNELS.get(which) or SHARES[which]
     m = re.search(r"\.amdhsa_kernel " + re.escape(sym) + r"\n(.*?)\.end_amdhsa_kernel", fused_asm, re.S)
     assert m, "kernel descriptor not found"
     size = re.search(r"\.amdhsa_private_segment_fixed_size (\d+)", m.group(1))
