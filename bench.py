@@ -633,7 +633,7 @@ def main():
         },
         "roofline": {
             "bound": "hbm",
-            "kernel": "query_aware_decode_kernel",
+            "kernel": "many_units_decode_kernel" if b.spec.B * b.spec.Hkv > 256 else "query_aware_decode_kernel",
             "achieved": round(achieved, 1),
             "peak": HBM_PEAK / 1e9,
             "unit": "GB/s",
