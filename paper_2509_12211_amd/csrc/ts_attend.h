@@ -117,6 +117,20 @@ struct PageFrag {
   uint2 v[NT][NCB];
 };
 
+// First channel of the i-th chunk of eight that quarter kb of the wave (its lanes 16 kb .. 16 kb
+// + 15) takes of a key or query row.  Which channels the four quarters contract is free as long
+// as both operands agree, so it goes by the memory: a wave-wide 16-byte load of keys touches
+// sixteen rows, and with 128 channels of 16 bits the quarters' chunks lie side by side, 64 bytes
+// of one line per row.  With 32 channels in a row for each quarter every load touched both lines
+// of all sixteen rows and came back to each four times instead of twice: 24 sequences x 8 KV
+// heads of 512-8192 tokens 38.8 -> 37.4 us, every token of 16 x 32 sequences of 1-8 K 233 -> 226,
+// 64 x 32 of 1-32 K 894 -> 889.  (Streaming loads on top: 3 % faster to 14 % slower by the
+// shape.)  With 64 channels a row is one line, and nothing changes either way.
+template <int D, bool kInt8>
+__device__ __forceinline__ int key_channel(int kb, int i) {
+  return D == 128 && !kInt8 ? 32 * i + 8 * kb : kb * (D / 4) + 8 * i;
+}
+
 // Fragment token held by MFMA row r of tile t.  For F = 32 the rows are permuted
 // so that the eight tokens a lane needs for the two P.V products are contiguous
 // in the channel-major V tile.
@@ -131,11 +145,11 @@ __device__ __forceinline__ int tile_token(int t, int r) {
 // and 0 for a placeholder fetch: with 0 every lane reads the first bytes of the
 // tile, so the instruction touches one cache line instead of the whole tile
 // (the data is never used).
-// kTogether: the loads of a K tile, which come back to the same lines, go out with nothing in
-// between; where the scheduler happened to put other loads there, 24 sequences x 8 KV heads of
-// 8192 tokens took 52.8 instead of 52.3 us.
+// The loads of a K tile, which come back to the same lines, go out with nothing in between:
+// where the scheduler happened to put other loads there, 24 sequences x 8 KV heads of 8192 tokens
+// took 52.8 instead of 52.3 us, and 64 x 32 of 1-32 K 912 instead of 909.
 constexpr int kAluMayCross = 0xc;   // scalar and matrix instructions (sched_barrier's mask)
-template <int D, int S, bool kTogether = false>
+template <int D, int S>
 __device__ __forceinline__ void load_page(PageFrag<D, PageGeom<S>::F>& f, const uint16_t* ktile,
                                           const uint16_t* vtile, int hoff, int spread) {
   constexpr int F = PageGeom<S>::F;
@@ -144,14 +158,14 @@ __device__ __forceinline__ void load_page(PageFrag<D, PageGeom<S>::F>& f, const 
   hoff *= spread;
 #pragma unroll
   for (int t = 0; t < PageFrag<D, F>::NT; ++t) {
-    const uint16_t* krow = ktile + (hoff + tile_token<F>(t, r)) * D * spread + kb * (D / 4);
+    const uint16_t* krow = ktile + (hoff + tile_token<F>(t, r)) * D * spread;
     const uint16_t* at[PageFrag<D, F>::KQ];
 #pragma unroll
-    for (int i = 0; i < PageFrag<D, F>::KQ; ++i) at[i] = krow + i * 8 * spread;
-    if (kTogether) __builtin_amdgcn_sched_barrier(kAluMayCross);
+    for (int i = 0; i < PageFrag<D, F>::KQ; ++i) at[i] = krow + key_channel<D, false>(kb, i) * spread;
+    __builtin_amdgcn_sched_barrier(kAluMayCross);
 #pragma unroll
     for (int i = 0; i < PageFrag<D, F>::KQ; ++i) f.k[t][i] = *reinterpret_cast<const uint4*>(at[i]);
-    if (kTogether) __builtin_amdgcn_sched_barrier(kAluMayCross);
+    __builtin_amdgcn_sched_barrier(kAluMayCross);
   }
 #pragma unroll
   for (int cb = 0; cb < PageFrag<D, F>::NCB; ++cb) {
@@ -186,10 +200,10 @@ __device__ __forceinline__ void load_small_pages(PageFrag<D, 16>& f, const uint1
     ok = sk == s ? toff[s] : ok;
     ov = sv == s ? toff[s] : ov;
   }
-  const uint16_t* krow = k_pool + ok + (r % S) * D + kb * (D / 4);
+  const uint16_t* krow = k_pool + ok + (r % S) * D;
 #pragma unroll
   for (int i = 0; i < PageFrag<D, 16>::KQ; ++i)
-    f.k[0][i] = *reinterpret_cast<const uint4*>(krow + i * 8 * spread);
+    f.k[0][i] = *reinterpret_cast<const uint4*>(krow + key_channel<D, false>(kb, i) * spread);
   const uint16_t* vbase = v_pool + ov + (4 * kb) % S;
 #pragma unroll
   for (int cb = 0; cb < PageFrag<D, 16>::NCB; ++cb)
@@ -358,7 +372,7 @@ struct NewToken {
   const uint16_t* v_row;
 };
 
-template <int D, int F>
+template <int D, int F, bool kInt8 = false>
 struct TokenPatch {
   uint4 k[PageFrag<D, F>::KQ];       // this lane's D/4 channels of the key
   uint32_t v[PageFrag<D, F>::NCB];   // value of channel 16 * cb + lane % 16
@@ -366,7 +380,7 @@ struct TokenPatch {
     const int lane = lane_id(), r = lane & 15, kb = lane >> 4;
 #pragma unroll
     for (int i = 0; i < PageFrag<D, F>::KQ; ++i)
-      k[i] = *reinterpret_cast<const uint4*>(nt.k_row + kb * (D / 4) + i * 8);
+      k[i] = *reinterpret_cast<const uint4*>(nt.k_row + key_channel<D, kInt8>(kb, i));
 #pragma unroll
     for (int cb = 0; cb < PageFrag<D, F>::NCB; ++cb) v[cb] = nt.v_row[16 * cb + r];
   }
@@ -400,13 +414,13 @@ struct TokenPatch {
 // the biased halves the expanded fragments hold and the two scales put where the
 // fragment keeps the token's.  To be called by a whole wave.
 template <int D, int F>
-struct TokenPatch8 : TokenPatch<D, F> {
+struct TokenPatch8 : TokenPatch<D, F, true> {
   float ksc, vsc;
   __device__ __forceinline__ static uint32_t code_half(float x, float scale) {
     return 0x6400u | (static_cast<uint32_t>(i8_code(x, scale) + 128) & 0xffu);   // half of code + kI8Bias
   }
   __device__ __forceinline__ void load(const NewToken& nt) {
-    TokenPatch<D, F>::load(nt);
+    TokenPatch<D, F, true>::load(nt);
     float ka = 0.f, va = 0.f;
 #pragma unroll
     for (int i = 0; i < PageFrag<D, F>::KQ; ++i) ka = fmaxf(ka, chunk_amax_bf16(this->k[i]));
@@ -467,8 +481,8 @@ struct WaveAcc {
   }
 };
 
-// Query operand: lane (head = lane%16, kb = lane/16) holds q[head][kb*D/4 .. +D/4).
-template <int D>
+// Query operand: lane (head = lane%16, kb = lane/16) holds a quarter of q[head] (key_channel).
+template <int D, bool kInt8>
 __device__ __forceinline__ void load_q_frag(short4_t (&qf)[D / 16], const uint16_t* q_group,
                                             int G) {
   const int lane = lane_id(), head = lane & 15, kb = lane >> 4;
@@ -478,7 +492,7 @@ __device__ __forceinline__ void load_q_frag(short4_t (&qf)[D / 16], const uint16
     // a redundant copy of it that nobody reads.  They are deliberately NOT zeroed:
     // overwriting the destination of a load in flight makes the wave wait for it,
     // two serial memory round trips at the start of every attention phase.
-    const uint4 w = *reinterpret_cast<const uint4*>(q_group + (size_t)min(head, G - 1) * D + kb * (D / 4) + i * 8);
+    const uint4 w = *reinterpret_cast<const uint4*>(q_group + (size_t)min(head, G - 1) * D + key_channel<D, kInt8>(kb, i));
     qf[2 * i] = as_short4(w.x, w.y);
     qf[2 * i + 1] = as_short4(w.z, w.w);
   }
@@ -580,7 +594,7 @@ struct QOperand {
   short4_t qf[D / 16];
   float qbias;   // INT8 cache: kI8Bias * sum over the channels of this lane's query row
   __device__ __forceinline__ void load(const uint16_t* rows, int G) {
-    load_q_frag<D>(qf, rows, G);
+    load_q_frag<D, kInt8>(qf, rows, G);
     qbias = 0.f;
     if constexpr (kInt8) {
       typedef __fp16 h2_t __attribute__((ext_vector_type(2)));
@@ -715,8 +729,6 @@ struct SplitPlace { int n_split, split; size_t part_row; };
 // (24 sequences x 8 KV heads of 8192 tokens: 51.4 -> 53.5 us).
 // Ends with a barrier after which `lds` may be reused; on return (n_split > 1)
 // the caller still has to wait for its stores and count its arrival.
-// kLatency: the launch is bound by the latency of its single pass (every workgroup has
-// one unit): the ring waits for each fragment by count (see below).
 // kPatch: a token appended in the same launch may have to be spliced in (nt).
 // kInt8: the cache holds int8 keys / values with per-token scales.
 // kHalf: queries, keys and values are IEEE half instead of bf16.
@@ -729,7 +741,7 @@ struct SplitPlace { int n_split, split; size_t part_row; };
 // returns false if that wait expired.
 // kWords (tag == 0): the partial is handed on as such words too, with the tag 0 that no launch
 // has; for callers whose workspace other launches read tagged words from.
-template <int NW, int D, int S, bool kLatency, bool kPatch, bool kInt8, bool kHalf, bool kHaveQ = false,
+template <int NW, int D, int S, bool kPatch, bool kInt8, bool kHalf, bool kHaveQ = false,
           bool kWords = false, typename PlaceOf, typename SelAt, typename PhysAt>
 __device__ __forceinline__ bool attend_split(const AttendParams& p, int b, int h, PlaceOf place,
                                              int count, int L, const NewToken& nt, SelAt sel_at,
@@ -818,7 +830,7 @@ __device__ __forceinline__ bool attend_split(const AttendParams& p, int b, int h
           load_page8<D, S>(fr, k_pool8 + tile, v_pool8 + tile, p.k_scale + so, p.v_scale + so, hoff,
                            good ? 1 : 0);
         } else {
-          load_page<D, S, kWords>(fr, p.k_pool + tile, p.v_pool + tile, hoff, good ? 1 : 0);
+          load_page<D, S>(fr, p.k_pool + tile, p.v_pool + tile, hoff, good ? 1 : 0);
         }
         const int valid = good ? max(0, min(F, L - j * S - hoff)) : 0;
         return valid >= 32 ? 0xffffffffu : (1u << valid) - 1u;
@@ -861,76 +873,55 @@ __device__ __forceinline__ bool attend_split(const AttendParams& p, int b, int h
         attend_page<D, F, false, kHalf>(f[i], qf, vmask[i], p.scale_log2, acc);
       }
     };
-    if constexpr (kLatency) {
-      // The ring.  A wait for a fragment can only count the loads sent out after it
-      // ("all but the newest k have arrived") where that number is the same on every path
-      // that leads to the wait; where paths with different numbers meet, the compiler falls
-      // back to waiting for everything in flight, which exposes a full memory latency per
-      // fragment.  So the code is laid out by how many buffers are in use:
-      //   - n >= NBUF: all buffers filled with no test in between; whole rounds (every
-      //     buffer consumed and refilled, no test) as long as a full ring lies ahead; one
-      //     round that consumes every buffer and refills the first `live` of them; then
-      //   - the last `live` < NBUF fragments (also the whole of a short list, fetched
-      //     under a test each): these are waited for together.
-      // No placeholder loads anywhere: a load with nothing to fetch would still queue
-      // behind the compute unit's outstanding misses.
-      int live;   // fragments in buffers 0 .. live - 1 once the rounds are through
-      if (n >= NBUF) {
-  #pragma unroll
-        for (int i = 0; i < NBUF; ++i) vmask[i] = issue(f[i], item[i], i);
-        TS_MARK(17);
-        TS_MARK_WAVE(48);
-        int x0 = 0;
-        for (; x0 + 2 * NBUF <= n; x0 += NBUF) {
-  #pragma unroll
-          for (int i = 0; i < NBUF; ++i) {
-            consume(i);
-            vmask[i] = issue(f[i], item[i], x0 + i + NBUF);
-          }
-        }
-        live = n - x0 - NBUF;
-  #pragma unroll
-        for (int i = 0; i < NBUF; ++i) {
-          consume(i);
-          if (i < live) vmask[i] = issue(f[i], item[i], x0 + i + NBUF);
-        }
-      } else {
-        live = n;
-  #pragma unroll
-        for (int i = 0; i < NBUF - 1; ++i)
-          if (i < live) vmask[i] = issue(f[i], item[i], i);
-        TS_MARK(17);
-        TS_MARK_WAVE(48);
-      }
-  #pragma unroll
-      for (int i = 0; i < NBUF - 1; ++i)
-        if (i < live) consume(i);
-    } else {
-      // Bandwidth-bound launches (thousands of units, other workgroups to hide a wave's
-      // waits): every buffer is filled at once (a slot past the end re-reads one cache
-      // line) and refilled under a test of its own, which makes the compiler wait for
-      // everything in flight before each fragment.  Measured on the 64-sequence batch,
-      // that is 2 % FASTER than the counted waits above: with fewer bytes of a wave in
-      // flight, the lines of a key tile, which four instructions come back to, are still
-      // in the L1 when the last of them arrives.
+    // The ring.  A wait for a fragment can only count the loads sent out after it
+    // ("all but the newest k have arrived") where that number is the same on every path
+    // that leads to the wait; where paths with different numbers meet, the compiler falls
+    // back to waiting for everything in flight, which exposes a full memory latency per
+    // fragment.  So the code is laid out by how many buffers are in use:
+    //   - n >= NBUF: all buffers filled with no test in between; whole rounds (every
+    //     buffer consumed and refilled, no test) as long as a full ring lies ahead; one
+    //     round that consumes every buffer and refills the first `live` of them; then
+    //   - the last `live` < NBUF fragments (also the whole of a short list, fetched
+    //     under a test each): these are waited for together.
+    // No placeholder loads anywhere: a load with nothing to fetch would still queue
+    // behind the compute unit's outstanding misses.
+    int live;   // fragments in buffers 0 .. live - 1 once the rounds are through
+    if (n >= NBUF) {
 #pragma unroll
       for (int i = 0; i < NBUF; ++i) vmask[i] = issue(f[i], item[i], i);
       TS_MARK(17);
       TS_MARK_WAVE(48);
-      for (int x0 = 0; x0 < n; x0 += NBUF) {
+      int x0 = 0;
+      for (; x0 + 2 * NBUF <= n; x0 += NBUF) {
 #pragma unroll
         for (int i = 0; i < NBUF; ++i) {
-          if (x0 + i < n) consume(i);
-          if (x0 + i + NBUF < n) vmask[i] = issue(f[i], item[i], x0 + i + NBUF);
+          consume(i);
+          vmask[i] = issue(f[i], item[i], x0 + i + NBUF);
         }
       }
+      live = n - x0 - NBUF;
+#pragma unroll
+      for (int i = 0; i < NBUF; ++i) {
+        consume(i);
+        if (i < live) vmask[i] = issue(f[i], item[i], x0 + i + NBUF);
+      }
+    } else {
+      live = n;
+#pragma unroll
+      for (int i = 0; i < NBUF - 1; ++i)
+        if (i < live) vmask[i] = issue(f[i], item[i], i);
+      TS_MARK(17);
+      TS_MARK_WAVE(48);
     }
+#pragma unroll
+    for (int i = 0; i < NBUF - 1; ++i)
+      if (i < live) consume(i);
     // Every fragment has been consumed, so nothing is in flight here; saying so (a wait
     // that never waits) keeps the compiler from assuming, where the loop over the batches
     // closes, that a buffer may still be waiting for a refill: it then drained the memory
     // pipeline in front of each buffer's first fill, so that the ring's fragments were
     // fetched one after the other (-0.3 us on the 16-sequence configuration).
-    if (kLatency) __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0), other counters untouched
+    __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0), other counters untouched
   }
 
   TS_MARK(18);

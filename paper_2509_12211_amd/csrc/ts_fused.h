@@ -150,7 +150,7 @@ __global__ __launch_bounds__(kThreads) void sparse_attention_kernel(AttendParams
   const int32_t* sel_row = sel ? sel + (size_t)u * p.Kmax + c0 : nullptr;
   const int32_t* bt_row = p.block_table + (size_t)b * p.Pmax;
   const NewToken none{-1, 0, p.q, p.q};
-  attend_split<kWaves, D, S, true, false, kInt8, kHalf>(
+  attend_split<kWaves, D, S, false, kInt8, kHalf>(
       p, b, h, [&] { return SplitPlace{p.n_split, split, (size_t)u * p.n_split}; }, count, p.seq_lens[b], none,
       [&](int i) { return sel_row ? sel_row[i] : c0 + i; },
       [&](int j) { return bt_row[j]; }, reinterpret_cast<float*>(smem));
@@ -306,7 +306,7 @@ __global__ __launch_bounds__(kThreads) void dense_shares_kernel(AttendParams p, 
   const int c0 = min(share.member * share.chunk, share.K), count = min(c0 + share.chunk, share.K) - c0;
   const int32_t* bt_row = p.block_table + (size_t)b * p.Pmax;
   const NewToken none{-1, 0, p.q, p.q};
-  attend_split<kWaves, D, S, true, false, false, kHalf>(
+  attend_split<kWaves, D, S, false, false, kHalf>(
       p, b, h, [&] { return SplitPlace{g, share.member, (size_t)share.part_row}; }, count, share.L, none,
       [&](int i) { return c0 + i; }, [&](int j) { return bt_row[j]; }, reinterpret_cast<float*>(smem));
   if (g == 1) return;
@@ -362,7 +362,7 @@ __global__ __launch_bounds__(kThreads) void dense_rounds_kernel(AttendParams p, 
   const int c0 = split * chunk, count = min(chunk, pages - c0);
   const int32_t* bt_row = p.block_table + (size_t)b * p.Pmax;
   const NewToken none{-1, 0, p.q, p.q};
-  attend_split<kWaves, D, S, true, false, false, kHalf>(
+  attend_split<kWaves, D, S, false, false, kHalf>(
       p, b, h, [&] { return SplitPlace{n_split, split, (size_t)u * 2}; }, count, len, none,
       [&](int i) { return c0 + i; }, [&](int j) { return bt_row[j]; }, reinterpret_cast<float*>(smem));
   if (n_split == 1) return;
@@ -418,8 +418,7 @@ __global__ __launch_bounds__(kThreads) void dense_rounds_kernel(AttendParams p, 
 // registers of that occupancy instead of saving registers for waves that never
 // come (measured: 0.5 us of 26 on the 16-sequence configuration).
 //
-// NW: waves per workgroup.  kCounted: how the attention's ring of fragments waits (see
-// attend_split).
+// NW: waves per workgroup.
 //
 // kCluster says whether a unit is shared by several workgroups (p.g > 1): the
 // build for one workgroup per unit carries nothing of the exchange, the build
@@ -428,7 +427,7 @@ __global__ __launch_bounds__(kThreads) void dense_rounds_kernel(AttendParams p, 
 // kDecide: the lengths decide between clusters of one size and shares in proportion to the
 // work (see by_shares), ahead of the first loads.
 template <int NW, int D, int S, bool kLoop, bool kApp, bool kInt8, bool kHalf, bool kCluster,
-          bool kCounted = !kLoop, bool kDecide = false>
+          bool kDecide = false>
 __device__ __forceinline__ void decode_units(const FusedParams& p) {
   constexpr int NT = NW * kWave;
   static_assert(!(kLoop && kApp), "the append is folded only into the loop-free build");
@@ -828,7 +827,7 @@ __device__ __forceinline__ void decode_units(const FusedParams& p) {
     // Shares without an exchange wait for nothing at all: the member that finds itself the
     // last to have handed on its partial merges them.
     constexpr bool apart = kDecide && !kCluster;
-    const bool merged = attend_split<NW, D, S, kCounted, kApp, kInt8, kHalf, true, apart>(
+    const bool merged = attend_split<NW, D, S, kApp, kInt8, kHalf, true, apart>(
         at, b, h,
         [&] {
           if constexpr (kDecide) {
@@ -894,7 +893,7 @@ query_aware_decode_kernel(FusedParams p) {
 template <int D, int S, bool kApp, bool kHalf, bool kCluster>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void
 shares_decode_kernel(FusedParams p) {
-  decode_units<kWaves, D, S, false, kApp, false, kHalf, kCluster, true, true>(p);
+  decode_units<kWaves, D, S, false, kApp, false, kHalf, kCluster, true>(p);
 }
 
 // Batches of more units than compute units whose units are not small: one workgroup of eight
@@ -905,13 +904,10 @@ shares_decode_kernel(FusedParams p) {
 // ahead of the loop and spilled with 128 channels and pages of 32 and 64: 80 layouts of
 // 272-900 units 4 % slower on average and up to 20 %, the 64-sequence batch 890 against
 // 880 us.)  Bound by HBM: 6.3 TB/s on the 64-sequence batch.
-// With 128 channels of 16 bits and small pages the ring waits for everything in flight
-// before each fragment (see attend_split).
 template <int D, int S, bool kInt8, bool kHalf>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void
 many_units_decode_kernel(FusedParams p) {
-  constexpr bool kCounted = kInt8 || D == 64 || S > 16;
-  decode_units<kWaves, D, S, false, false, kInt8, kHalf, false, kCounted>(p);
+  decode_units<kWaves, D, S, false, false, kInt8, kHalf, false>(p);
 }
 
 // Batches of more units than compute units, as long as a unit is small (kSmallUnitBytes): one
