@@ -16,6 +16,8 @@ HIPCC_FLAGS = [
     "-Wno-unused-function", "-Wno-unknown-warning-option",
     # packed-FP32 instruction selection is switched off for all device code
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    # the leading scalar arguments of a kernel arrive in registers
+    "-mllvm", "-amdgpu-kernarg-preload-count=14",
 ]
 
 

@@ -157,6 +157,33 @@ __device__ __forceinline__ double group_sum4_f64(const double (&v)[4], int lane_
   return k;
 }
 
+// One value per lane, summed over the group by the same additions: delivered to every lane.
+template <int N>
+__device__ __forceinline__ double group_sum1_f64(double k) {
+  static_assert(N == 8 || N == 16, "group of 8 or 16 lanes");
+  if (N == 16) k += dpp_move_f64<kDppMirror>(k);
+  k += dpp_move_f64<kDppHalfMirror>(k);
+  k += dpp_move_f64<kDppXor2>(k);
+  k += dpp_move_f64<kDppXor1>(k);
+  return k;
+}
+// Two: in lanes 0 - 3 of the group's first eight the sum of v[0], in lanes 4 - 7 that of v[1].
+template <int N>
+__device__ __forceinline__ double group_sum2_f64(const double (&v)[2], int lane_in_group) {
+  static_assert(N == 8 || N == 16, "group of 8 or 16 lanes");
+  double s[2] = {v[0], v[1]};
+  if (N == 16) {
+#pragma unroll
+    for (int u = 0; u < 2; ++u) s[u] += dpp_move_f64<kDppMirror>(s[u]);
+  }
+  const bool upper = (lane_in_group & 4) != 0;
+  double k = upper ? s[1] : s[0];
+  k += dpp_move_f64<kDppHalfMirror>(upper ? s[0] : s[1]);
+  k += dpp_move_f64<kDppXor2>(k);
+  k += dpp_move_f64<kDppXor1>(k);
+  return k;
+}
+
 // Combine a value over the four lanes {l, l^16, l^32, l^48} (the four rows of a
 // wave) with the gfx950 row-swap instructions.
 typedef unsigned uint2s_t __attribute__((ext_vector_type(2)));

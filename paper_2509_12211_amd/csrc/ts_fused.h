@@ -100,6 +100,27 @@ struct FusedParams {
   float inv_g, min_rows;       // ... see Plan
 };
 
+// What the first loads of a workgroup are addressed with, as kernel arguments of their own in front
+// of the struct: these fourteen words are in scalar registers when a wave starts (the flag
+// -amdgpu-kernarg-preload-count of the build), where the struct is a trip to memory away.  The
+// loads go out 0.6 us after the kernel's entry instead of 0.9, and with them ends a launch: 4 units
+// of 12 workgroups 10.0 -> 9.7 us, 16 of 16 (131072 tokens each) 19.6 -> 19.2.
+struct FirstArgs {
+  const uint16_t* q;
+  const uint16_t* page_min;
+  const uint16_t* page_max;
+  const uint16_t* k_new;
+  const uint16_t* v_new;
+  uint32_t shape;              // pages of a table row | g << 16 | (G - 1) << 24 | log2 of the XCDs << 28
+  uint32_t units;
+  uint32_t magic_g, magic_hkv; // FastDiv::magic
+  __device__ __forceinline__ int Pmax() const { return (int)(shape & 0xffffu); }
+  __device__ __forceinline__ int g() const { return (int)((shape >> 16) & 0xffu); }
+  __device__ __forceinline__ int G() const { return (int)((shape >> 24) & 15u) + 1; }
+  __device__ __forceinline__ int xcd_bits() const { return (int)(shape >> 28); }
+};
+static_assert(TS_MAX_PAGES_PER_SEQ <= 0xffff && kMaxCluster <= 0xff, "fields of FirstArgs::shape");
+
 // Which cluster a workgroup belongs to, and as which member.  The hardware deals
 // consecutive workgroup ids out to the XCDs in turn (on a part with eight of them,
 // ids congruent modulo 8 share a die; the first id of a launch goes wherever the
@@ -128,6 +149,13 @@ __device__ __forceinline__ ClusterSlot cluster_of(int wg, const FastDiv& g, cons
     c.member = wg - c.cluster * (int)g.d;
   }
   return c;
+}
+
+// The same from the first arguments: g >= 2, the number of XCDs a power of two (1: consecutive ids).
+__device__ __forceinline__ ClusterSlot cluster_of(int wg, const FirstArgs& f) {
+  const int bits = f.xcd_bits(), slot = wg >> bits, xcd = wg & ((1 << bits) - 1);
+  const int c = (int)__umulhi((uint32_t)slot, f.magic_g);
+  return ClusterSlot{(c << bits) + xcd, slot - c * f.g()};
 }
 
 __device__ __forceinline__ int pages_of(int len, int S) { return (len + S - 1) / S; }
@@ -424,11 +452,16 @@ __global__ __launch_bounds__(kThreads) void dense_rounds_kernel(AttendParams p, 
 // build for one workgroup per unit carries nothing of the exchange, the build
 // for clusters nothing of the selection's stand-alone first stages.
 //
+// kRound > 0: a wave scores its share of the pages in one round of at most that many groups (see
+// ScanRegs), and what the first loads need comes in the arguments in front (f).
+//
 // kDecide: the lengths decide between clusters of one size and shares in proportion to the
 // work (see by_shares), ahead of the first loads.
 template <int NW, int D, int S, bool kLoop, bool kApp, bool kInt8, bool kHalf, bool kCluster,
-          bool kDecide = false>
-__device__ __forceinline__ void decode_units(const FusedParams& p) {
+          bool kDecide = false, int kRound = 0>
+__device__ __forceinline__ void decode_units(const FusedParams& p, const FirstArgs& f = FirstArgs{}) {
+  constexpr bool kFirst = kRound > 0;
+  static_assert(!kFirst || (kCluster && !kLoop && !kDecide), "one round of scoring: clusters with one unit each");
   constexpr int NT = NW * kWave;
   static_assert(!(kLoop && kApp), "the append is folded only into the loop-free build");
   static_assert(!kLoop || kCluster, "a single workgroup per unit needs no loop");
@@ -441,24 +474,25 @@ __device__ __forceinline__ void decode_units(const FusedParams& p) {
   // first branch: the compiler fetches a kernel argument in the block that first uses it,
   // and arguments first used behind the tests below came in a second and a third trip to
   // memory, each waited for, before the first load could go out.
-  asm volatile("" ::"s"(p.ctrl), "s"(p.page_min), "s"(p.page_max), "s"(p.topk_per_seq), "s"(p.k_new),
+  if (!kFirst) asm volatile("" ::"s"(p.ctrl), "s"(p.page_min), "s"(p.page_max), "s"(p.topk_per_seq), "s"(p.k_new),
                "s"(p.v_new), "s"(p.topk), "s"(p.units), "s"(p.g), "s"(p.xcds), "s"(p.div_hkv.d),
                "s"(p.div_hkv.magic), "s"(p.div_g.d), "s"(p.div_g.magic), "s"(p.div_xcds.d),
                "s"(p.div_xcds.magic), "s"(at.q), "s"(at.block_table), "s"(at.seq_lens), "s"(at.Hq),
                "s"(at.Hkv), "s"(at.G), "s"(at.Pmax), "s"(at.lse), "s"(at.k_scale),
                "s"(at.v_scale));
-  const int G = at.G, Pmax = at.Pmax;
+  const int G = kFirst ? f.G() : at.G, Pmax = kFirst ? f.Pmax() : at.Pmax;
   // which unit this workgroup works on, as which of how many members, and the size of a
   // member's chunk of the selected pages
   int epoch_raw, L_raw, K_raw;
-  const ClusterSlot where = kCluster ? cluster_of(blockIdx.x, p.div_g, p.div_xcds, p.xcds > 1)
-                                     : ClusterSlot{(int)blockIdx.x, 0};
-  int g = kCluster ? p.g : 1, member = kCluster ? where.member : 0;
+  ClusterSlot where{(int)blockIdx.x, 0};
+  if constexpr (kFirst) where = cluster_of(blockIdx.x, f);
+  else if constexpr (kCluster) where = cluster_of(blockIdx.x, p.div_g, p.div_xcds, p.xcds > 1);
+  int g = kCluster ? (kFirst ? f.g() : p.g) : 1, member = kCluster ? where.member : 0;
   int chunk = at.chunk;
   const int n_clusters = kCluster ? fast_div(gridDim.x, p.div_g) : (int)gridDim.x;
   // (a launch laid out by XCD is padded to whole rounds of the XCDs: clusters past
   // the last unit leave before any barrier, see below, and are not counted in)
-  const bool padding = (kCluster || kDecide) && !kLoop && where.cluster >= p.units;
+  const bool padding = (kCluster || kDecide) && !kLoop && where.cluster >= (kFirst ? (int)f.units : p.units);
   const SelectLds sl = carve_select<NW>(smem, Pmax);
   const uint32_t sel_bytes = (uint32_t)select_lds_bytes(Pmax, NW), att_bytes = (uint32_t)(NW * G * (D + 2) * 4);
   const uint32_t q_off = sel_bytes > att_bytes ? sel_bytes : att_bytes;
@@ -468,7 +502,7 @@ __device__ __forceinline__ void decode_units(const FusedParams& p) {
   int32_t* bt_lds = words + (kDecide ? kShareWords : 0);
   int32_t* my_sel = bt_lds + Pmax;  // [chunk]
   int u = padding ? 0 : where.cluster;
-  int b = fast_div(u, p.div_hkv), h = u - b * at.Hkv;
+  int b = kFirst ? fast_div(u, FastDiv{1, f.magic_hkv}) : fast_div(u, p.div_hkv), h = u - b * at.Hkv;
 
   // The first loads of a unit (sequence length, K, query rows, block-table row,
   // first metadata tile) are sent out ahead of everything else: for the first
@@ -481,9 +515,9 @@ __device__ __forceinline__ void decode_units(const FusedParams& p) {
   // of the sequence; dealing out whole tiles of PPI pages reads 0.3 us faster on
   // the 16-sequence configuration, but where the scores vary smoothly along the
   // sequence the few pages that matter then lie in tiles most members never see.
-  constexpr int kBtRegs = 8;  // block-table entries per thread fetched through registers
+  constexpr int kBtRegs = kRound == 1 ? 4 : 8;  // block-table entries per thread fetched through registers
   int bt_regs[kBtRegs];
-  ScanRegs<D, kHalf, NW> scan;
+  ScanRegs<D, kHalf, NW, kRound> scan;
   // Append mode: the new token's key / value rows of this unit, as the 16-byte
   // chunk (channels 8 * (lane % (D/8)) .. + 7) every lane needs for the box update
   // and the pool write (bf16 also for the INT8 cache, which quantises them).
@@ -537,11 +571,32 @@ __device__ __forceinline__ void decode_units(const FusedParams& p) {
     scan_issue_tile(scan, p.page_min + (size_t)uu * Pmax * D, p.page_max + (size_t)uu * Pmax * D,
                        Pmax, wave_id(), kCluster ? g : 1, kCluster ? member : 0);
   };
-  if (kLoop ? u < p.units : true) issue_unit(u);   // the host launches no idle cluster
+  if constexpr (kFirst) {
+    // (the same loads; those whose addresses need the struct come last, and wait in registers
+    // until the scores are worked out)
+    scan_issue_query(scan, f.q + (size_t)u * G * D, G);
+    if (app) {
+      const size_t row = (size_t)u * D + (lane_id() % LPR) * 8;
+      kn16 = *reinterpret_cast<const uint4*>(f.k_new + row);
+      vn16 = *reinterpret_cast<const uint4*>(f.v_new + row);
+    }
+    scan_issue_tile(scan, f.page_min + (size_t)u * Pmax * D, f.page_max + (size_t)u * Pmax * D,
+                       Pmax, wave_id(), kCluster ? g : 1, kCluster ? member : 0);
+    __builtin_amdgcn_sched_barrier(0);
+    epoch_raw = p.ctrl[kCtrlEpoch];
+    L_raw = at.seq_lens[b];
+    K_raw = p.topk_per_seq ? p.topk_per_seq[b] : p.topk;
+    const int32_t* bt_row = at.block_table + (size_t)b * Pmax;
+#pragma unroll
+    for (int k = 0; k < kBtRegs; ++k)   // no branch around the loads
+      bt_regs[k] = bt_row[min((int)threadIdx.x + k * NT, Pmax - 1)];
+  } else {
+    if (kLoop ? u < p.units : true) issue_unit(u);   // the host launches no idle cluster
+  }
   // (The empty asm keeps the loads where they are: in front of anything that waits for one of
   // them, in the order of their use.  Left to the scheduler, the query's went out last and was waited
   // for with everything else.)
-  if (!kLoop) asm volatile("" : : "s"(q_off) : "memory");
+  if (!kLoop && !kFirst) asm volatile("" : : "s"(q_off) : "memory");
   // (a padding workgroup leaves only here, behind the loads of unit 0, whose results it
   // drops: with an exit ahead of them the kernel's arguments would be fetched in two
   // dependent trips, the second one behind the test)
@@ -578,20 +633,23 @@ __device__ __forceinline__ void decode_units(const FusedParams& p) {
     uint32_t tmin = 0xffffffffu, tmax = 0u;  // this thread's share of the key range
     uint4 box_lo = make_uint4(0, 0, 0, 0), box_hi = make_uint4(0, 0, 0, 0);   // this lane's chunk of the
     bool has_box = false;                    // new token's box, if it has to write it back
+    auto park_table = [&] {
+#pragma unroll
+      for (int k = 0; k < kBtRegs; ++k) {
+        const int j = threadIdx.x + k * NT;
+        if (j < Pmax) bt_lds[j] = bt_regs[k];
+      }
+      for (int j = threadIdx.x + kBtRegs * NT; j < Pmax; j += NT)
+        bt_lds[j] = bt_row[j];
+    };
     scan_finish<D, !kLoop>(
         scan, p.page_min + (size_t)u * Pmax * D, p.page_max + (size_t)u * Pmax * D, G, Pmax,
         wave_id(), NW, q_stage,
         [&] {
-#pragma unroll
-          for (int k = 0; k < kBtRegs; ++k) {
-            const int j = threadIdx.x + k * NT;
-            if (j < Pmax) bt_lds[j] = bt_regs[k];
-          }
-          for (int j = threadIdx.x + kBtRegs * NT; j < Pmax; j += NT)
-            bt_lds[j] = bt_row[j];
+          if (!kFirst) park_table();
           // (the empty asm pins the first use of the two values to this point:
           // using them earlier would put a memory round trip in front of the scan)
-          asm volatile("" : "+v"(L_raw), "+v"(K_raw), "+v"(epoch_raw));
+          if (!kFirst) asm volatile("" : "+v"(L_raw), "+v"(K_raw), "+v"(epoch_raw));
           // the tag is fixed by the first unit: the epoch word may already have
           // been advanced (by the launch's first workgroup, once it is through
           // with its own units) when a later unit's loads go out
@@ -599,7 +657,7 @@ __device__ __forceinline__ void decode_units(const FusedParams& p) {
           // ts_workspace_init, so the count skips it when it wraps)
           if (tag == 0u) tag = max((uint32_t)uniform(epoch_raw) + 1u, 1u);
           L_unit = uniform(L_raw);
-          K_unit = uniform(K_raw);
+          if (!kFirst) K_unit = uniform(K_raw);
           if (app && L_unit / S < Pmax) {  // a sequence with no room left is not extended
             j_new = L_unit / S;
             slot_new = L_unit % S;
@@ -657,7 +715,13 @@ __device__ __forceinline__ void decode_units(const FusedParams& p) {
           }
           if (srow_out) srow_out[pg] = s;
         },
-        kCluster ? g : 1, kCluster ? member : 0, srow_out != nullptr);
+        kCluster ? g : 1, kCluster ? member : 0, srow_out != nullptr,
+        [&] {
+          if constexpr (kFirst) {
+            park_table();
+            K_unit = uniform(K_raw);
+          }
+        });
     TS_MARK_WAVE(32);
     const int L = uniform(L_unit);
     const int Pb = uniform(min(pages_of(L, S), Pmax));
@@ -884,6 +948,23 @@ query_aware_decode_kernel(FusedParams p) {
   decode_units<kWaves, D, S, kLoop, kApp, kInt8, kHalf, kCluster>(p);
 }
 
+// Clusters with one unit each, as in query_aware_decode_kernel's loop-free build, whose waves score
+// their share of the pages in one round of at most R groups of 8 (64 channels) or 4 pages.  These
+// launches are bound by the chain of their phases, and scoring is one of its links: 300
+// instructions for the four groups of a tile and as many again for the next tile's loads, whose
+// pages mostly do not exist.  R = 1 (8 waves, a group each): 4 units of 12 workgroups with 188
+// pages 11.5 -> 10.3 us, 1 of 8 with 257 10.6 -> 9.8; R = 3: 128 of 2 with 257 16.8 -> 16.1, 4 of 32
+// with 4098 17.9 -> 17.0; R = 5: 16.. 128 units of 513-4097 pages -0.1 us, without an append 18.5 -> 17.9.
+// The first loads' arguments come ahead of the others (FirstArgs).
+template <int D, int S, bool kApp, bool kInt8, bool kHalf, int R>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void
+one_round_decode_kernel(const uint16_t* q, const uint16_t* page_min, const uint16_t* page_max,
+                        const uint16_t* k_new, const uint16_t* v_new, uint32_t shape, uint32_t units,
+                        uint32_t magic_g, uint32_t magic_hkv, FusedParams p) {
+  decode_units<kWaves, D, S, false, kApp, kInt8, kHalf, true, false, R>(
+      p, FirstArgs{q, page_min, page_max, k_new, v_new, shape, units, magic_g, magic_hkv});
+}
+
 // Up to 255 units of batches that may be ragged: see by_shares.  kCluster: the members of a
 // cluster divide the scoring and wait for each other's scores and partials, by shares as with
 // clusters of one size.  Batches that have one workgroup per unit otherwise (129 to 255 units) do
@@ -1073,7 +1154,24 @@ static bool launch_shares(const ts_layout* layout, FusedParams& p, const Plan& p
   return true;
 }
 
-// A cluster of pl.g > 1 workgroups per unit: the loop-free build where all clusters are
+// The build for clusters whose waves score their pages in one round, nullptr where that takes more
+// than five groups each: from 40 groups a member on the rounds of four follow each other without a
+// gap, and a longer tile would not fit the registers.
+using OneRound = void (*)(const uint16_t*, const uint16_t*, const uint16_t*, const uint16_t*, const uint16_t*,
+                          uint32_t, uint32_t, uint32_t, uint32_t, FusedParams);
+template <int D, int S, bool kApp, int kFmt>
+static OneRound one_round_kernel(const FusedParams& p) {
+  constexpr bool kInt8 = kFmt == TS_KV_INT8, kHalf = kFmt == TS_KV_FP16;
+  constexpr int group = ScoreLanes<D>::PPW;
+  const int groups = (p.at.Pmax + group - 1) / group;
+  const int rows = ((groups + p.g - 1) / p.g + kWaves - 1) / kWaves;
+  if (rows <= 1) return one_round_decode_kernel<D, S, kApp, kInt8, kHalf, 1>;
+  if (rows <= 3) return one_round_decode_kernel<D, S, kApp, kInt8, kHalf, 3>;
+  if (rows <= 5) return one_round_decode_kernel<D, S, kApp, kInt8, kHalf, 5>;
+  return nullptr;
+}
+
+// A cluster of pl.g > 1 workgroups per unit: the loop-free builds where all clusters are
 // resident at once, otherwise (a forced cluster size) the looping one, each cluster taking
 // several units in turn.
 template <int D, int S, int kFmt>
@@ -1085,6 +1183,23 @@ static int launch_clusters(const ts_layout* layout, FusedParams& p, const Plan& 
   auto one_kernel = query_aware_decode_kernel<D, S, false, false, kInt8, kHalf, true>;
   auto app_kernel = query_aware_decode_kernel<D, S, false, true, kInt8, kHalf, true>;
   int st;
+  const OneRound round_kernel = k_new ? one_round_kernel<D, S, true, kFmt>(p) : one_round_kernel<D, S, false, kFmt>(p);
+  if (round_kernel) {
+    if ((st = allow_lds(round_kernel, pl.lds_fused)) != TS_OK) return st;
+    int cap = resident_capacity(round_kernel, pl.lds_fused);
+    if (cap > max_resident) cap = max_resident;
+    const unsigned grid = cluster_grid(p, pl, cap);
+    int xcd_bits = 0;
+    while (p.xcds > 1 << xcd_bits) ++xcd_bits;
+    if (pl.units * pl.g <= cap && (p.xcds == 0 || p.xcds == 1 << xcd_bits)) {
+      p.n_arrive = pl.units * pl.g;
+      const uint32_t shape = (uint32_t)p.at.Pmax | (uint32_t)p.g << 16 | (uint32_t)(p.at.G - 1) << 24 |
+                             (uint32_t)xcd_bits << 28;
+      round_kernel<<<grid, kThreads, pl.lds_fused, s>>>(p.at.q, p.page_min, p.page_max, p.k_new, p.v_new, shape,
+                                                        (uint32_t)pl.units, p.div_g.magic, p.div_hkv.magic, p);
+      return TS_OK;
+    }
+  }
   if ((st = allow_lds(loop_kernel, pl.lds_fused)) != TS_OK ||
       (st = allow_lds(one_kernel, pl.lds_fused)) != TS_OK ||
       (st = allow_lds(app_kernel, pl.lds_fused)) != TS_OK)

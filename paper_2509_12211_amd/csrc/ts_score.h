@@ -24,8 +24,6 @@ struct ScoreLanes {
   static constexpr int NT = NW * kWave;     // threads of the workgroup
   static constexpr int LPR = D / 8;         // lanes per metadata row
   static constexpr int PPW = kWave / LPR;   // pages per wave-wide load
-  static constexpr int U = 4;               // wave-wide loads of min (and of max) in flight
-  static constexpr int PPI = PPW * U;       // pages one wave covers per iteration
   double qp[8], qn[8];
 
   // Qp / Qn of the unit, computed once per workgroup through LDS: the G query
@@ -103,9 +101,8 @@ struct ScoreLanes {
 // (rstep = PPW: the pages [base, base + PPI); larger when the groups of PPW pages
 // are dealt out in turn to several workgroups).  Rows up to Pmax are always
 // readable (whatever they hold), so the loads do not wait for the sequence length.
-template <int D, bool kHalf = false, int NW = kWaves>
+template <int D, bool kHalf = false, int NW = kWaves, int U = 4>
 struct MetaTile {
-  static constexpr int U = ScoreLanes<D, kHalf, NW>::U;
   uint4 mn[U], mx[U];
 
   // Plimit >= 1.  Pages at or past Plimit read row Plimit - 1 instead (no branch
@@ -122,14 +119,17 @@ struct MetaTile {
     }
   }
 
-  // sink(page, score) is called once per page < Pmax by one lane (a lane takes at most
-  // one page of the tile); pages >= Pb get -inf.  patch(min_row, max_row, page) may first
+  // The tile's scores: a lane ends up with at most one.  patch(min_row, max_row, page) may first
   // amend the row chunks this lane holds (a token appended in the same launch).
-  template <typename Patch, typename Sink>
-  __device__ __forceinline__ void reduce(const ScoreLanes<D, kHalf, NW>& ql, int base, int Pb, int Pmax,
-                                         int rstep, Patch patch, Sink sink) {
+  struct Score {
+    double s;
+    int page;    // of this lane's score
+    bool mine;   // it is this lane that reports it
+  };
+  template <typename Patch>
+  __device__ __forceinline__ Score scores(const ScoreLanes<D, kHalf, NW>& ql, int base, int rstep, Patch patch) {
     constexpr int LPR = ScoreLanes<D, kHalf>::LPR;
-    static_assert(U == 4, "group_sum4_f64 folds four rows");
+    static_assert(U == 4 || U == 2 || U == 1, "rows folded in one butterfly");
     const int lane = lane_id(), cg = lane % LPR, prow = lane / LPR;
     double part[U];
 #pragma unroll
@@ -137,10 +137,33 @@ struct MetaTile {
       patch(mn[u], mx[u], base + u * rstep + prow);
       part[u] = ql.row_partial(mn[u], mx[u]);
     }
-    const double s = group_sum4_f64<LPR>(part, cg);
-    // lanes 0, 2, 4, 6 of a page's lanes hold the sums of rows 0, 1, 2, 3
-    const int pg = base + (cg >> 1) * rstep + prow;
-    if ((cg & 1) == 0 && cg < 8 && pg < Pmax) sink(pg, pg < Pb ? static_cast<float>(s) : -INFINITY);
+    // of a page's first eight lanes, 8 / U at a time hold the sum of a row, and the first of
+    // those reports it
+    constexpr int LPS = 8 / U;
+    Score r;
+    if constexpr (U == 4) r.s = group_sum4_f64<LPR>(part, cg);
+    else if constexpr (U == 2) r.s = group_sum2_f64<LPR>(part, cg);
+    else r.s = group_sum1_f64<LPR>(part[0]);
+    r.page = base + cg / LPS * rstep + prow;
+    r.mine = cg % LPS == 0 && cg < 8;
+    return r;
+  }
+  // sink(page, score) is called once per page < Pmax by one lane; pages >= Pb get -inf.
+  template <typename Sink>
+  __device__ __forceinline__ static void report(const Score& r, int Pb, int Pmax, Sink sink) {
+    if (r.mine && r.page < Pmax) sink(r.page, r.page < Pb ? static_cast<float>(r.s) : -INFINITY);
+  }
+  template <typename Patch, typename Sink>
+  __device__ __forceinline__ void reduce(const ScoreLanes<D, kHalf, NW>& ql, int base, int Pb, int Pmax,
+                                         int rstep, Patch patch, Sink sink) {
+    report(scores(ql, base, rstep, patch), Pb, Pmax, sink);
+  }
+  // Everything of the tile has arrived (the first use of its registers, pinned to this place).
+  __device__ __forceinline__ void arrived() {
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      asm volatile("" : "+v"(mn[u].x), "+v"(mn[u].y), "+v"(mn[u].z), "+v"(mn[u].w), "+v"(mx[u].x),
+                   "+v"(mx[u].y), "+v"(mx[u].z), "+v"(mx[u].w));
   }
 };
 
@@ -153,22 +176,35 @@ struct MetaTile {
 // in general the sequence's groups of PPW pages are dealt out in turn to gs
 // parties, and the caller, party goff, gets the groups (it * U + u) * gs + goff:
 // its share is then spread as evenly as can be over the whole sequence.
-template <int D, bool kHalf = false, int NW = kWaves>
+//
+// R = 0: any number of iterations of U = 4.  R > 0: the build for launches in which a wave has at
+// most R groups of pages: one tile and, with more than one group, a last group of its own.
+template <int D, bool kHalf = false, int NW = kWaves, int R = 0>
 struct ScanRegs {
+  static constexpr int U = R == 0 ? 4 : (R == 1 ? 1 : R - 1);
+  static constexpr bool kTail = R > 1;
+  static constexpr int PPI = ScoreLanes<D, kHalf, NW>::PPW * U;   // pages one wave covers per iteration
   typename ScoreLanes<D, kHalf, NW>::QueryRegs q;
-  MetaTile<D, kHalf, NW> tile;
+  MetaTile<D, kHalf, NW, U> tile;
+  MetaTile<D, kHalf, NW, 1> tail;
 };
 
-template <int D, bool kHalf, int NW>
-__device__ __forceinline__ void scan_issue_query(ScanRegs<D, kHalf, NW>& r, const uint16_t* q_group, int G) {
+struct Nothing {
+  __device__ __forceinline__ void operator()() const {}
+};
+
+template <int D, bool kHalf, int NW, int R>
+__device__ __forceinline__ void scan_issue_query(ScanRegs<D, kHalf, NW, R>& r, const uint16_t* q_group, int G) {
   ScoreLanes<D, kHalf, NW>::issue_query(r.q, q_group, G);
 }
-template <int D, bool kHalf, int NW>
-__device__ __forceinline__ void scan_issue_tile(ScanRegs<D, kHalf, NW>& r, const uint16_t* pmin_u,
+template <int D, bool kHalf, int NW, int R>
+__device__ __forceinline__ void scan_issue_tile(ScanRegs<D, kHalf, NW, R>& r, const uint16_t* pmin_u,
                                                 const uint16_t* pmax_u, int Pmax, int first_iter,
                                                 int gs = 1, int goff = 0) {
-  constexpr int PPW = ScoreLanes<D, kHalf>::PPW, PPI = ScoreLanes<D, kHalf>::PPI;
+  constexpr int PPW = ScoreLanes<D, kHalf>::PPW, PPI = ScanRegs<D, kHalf, NW, R>::PPI;
   r.tile.load(pmin_u, pmax_u, first_iter * PPI * gs + goff * PPW, Pmax, PPW * gs);
+  if constexpr (ScanRegs<D, kHalf, NW, R>::kTail)
+    r.tail.load(pmin_u, pmax_u, (NW * PPI + first_iter * PPW) * gs + goff * PPW, Pmax, 0);
 }
 
 // `after_query` runs once the query is in registers and returns Pb.  Must be
@@ -188,13 +224,16 @@ __device__ __forceinline__ void scan_issue_tile(ScanRegs<D, kHalf, NW>& r, const
 // fetch AND the reduction it overlaps with, two copies of the reduction, so that
 // no load is issued where there is no next tile, measured 0.7 us slower on the
 // 16-sequence configuration.)
-template <int D, bool kBranchless, bool kHalf, int NW, typename AfterQuery, typename Patch, typename Sink>
-__device__ __forceinline__ void scan_finish(ScanRegs<D, kHalf, NW>& r, const uint16_t* pmin_u,
+template <int D, bool kBranchless, bool kHalf, int NW, int R, typename AfterQuery, typename Patch, typename Sink,
+          typename BeforeReport = Nothing>
+__device__ __forceinline__ void scan_finish(ScanRegs<D, kHalf, NW, R>& r, const uint16_t* pmin_u,
                                             const uint16_t* pmax_u, int G, int Pmax, int first_iter,
                                             int iter_stride, unsigned char* q_stage,
                                             AfterQuery after_query, Patch patch, Sink sink,
-                                            int gs = 1, int goff = 0, bool fill_to_pmax = true) {
-  constexpr int PPW = ScoreLanes<D, kHalf>::PPW, PPI = ScoreLanes<D, kHalf>::PPI;
+                                            int gs = 1, int goff = 0, bool fill_to_pmax = true,
+                                            BeforeReport before_report = BeforeReport{}) {
+  using Regs = ScanRegs<D, kHalf, NW, R>;
+  constexpr int PPW = ScoreLanes<D, kHalf>::PPW, PPI = Regs::PPI;
   const int rstep = PPW * gs;
   TS_MARK(19);
   ScoreLanes<D, kHalf, NW> ql;
@@ -205,7 +244,19 @@ __device__ __forceinline__ void scan_finish(ScanRegs<D, kHalf, NW>& r, const uin
   // only the first tile is fetched blind; later ones stop at the sequence's
   // last page (pages >= Pb still get their -inf through the sink)
   int base = first_iter * PPI * gs + goff * PPW;   // first page of the tile's first group
-  if (kBranchless) {
+  if constexpr (R > 0) {
+    const int end = min(Pmax, limit);
+    const auto s = r.tile.scores(ql, base, rstep, patch);
+    // (waited for here, ahead of the stores of the sink: behind them a wait would be one for
+    // their acknowledgement too)
+    if constexpr (Regs::kTail) r.tail.arrived();
+    before_report();
+    r.tile.report(s, Pb, end, sink);
+    if constexpr (Regs::kTail) {
+      const int last = (NW * PPI + first_iter * PPW) * gs + goff * PPW;
+      if (uniform(last) < end) r.tail.reduce(ql, last, Pb, end, 0, patch, sink);
+    }
+  } else if (kBranchless) {
     // The first tile is reduced whether or not it holds a page below the limit (the sink
     // sees no page at or past the limit).  With a path around the loop the tile's loads
     // would still be in flight where the two paths meet, and the compiler, which cannot
@@ -214,7 +265,7 @@ __device__ __forceinline__ void scan_finish(ScanRegs<D, kHalf, NW>& r, const uin
     // of the barrier that follows (measured, with the arrival count below: 0.3-0.5 us).
     do {
       const int next = base + iter_stride * PPI * gs;
-      MetaTile<D, kHalf, NW> cur = r.tile;
+      auto cur = r.tile;
       r.tile.load(pmin_u, pmax_u, next, max(Pb, 1), rstep);
       cur.reduce(ql, base, Pb, min(Pmax, limit), rstep, patch, sink);
       base = next;
@@ -222,7 +273,7 @@ __device__ __forceinline__ void scan_finish(ScanRegs<D, kHalf, NW>& r, const uin
   } else {
     while (base < limit) {
       const int next = base + iter_stride * PPI * gs;
-      MetaTile<D, kHalf, NW> cur = r.tile;
+      auto cur = r.tile;
       if (next < Pb) r.tile.load(pmin_u, pmax_u, next, Pb, rstep);
       cur.reduce(ql, base, Pb, Pmax, rstep, patch, sink);
       base = next;

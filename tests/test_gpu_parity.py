@@ -1312,6 +1312,32 @@ def test_cluster_merge_in_batches(oracle, built, cluster, shape):
         compare_units(oracle, sess, units, scale, what=f"merge/cluster={cluster}/{shape}/launch {step}")
 
 
+@pytest.mark.parametrize("groups", [1, 8, 9, 24, 25, 40, 41])
+@pytest.mark.parametrize("d,S", [(64, 16), (128, 8)])
+@pytest.mark.parametrize("opens", [False, True])
+def test_scoring_in_one_round_of_groups(oracle, built, groups, d, S, opens):
+    """The builds whose waves score at most one, three or five groups of pages, at the most groups
+    a member of the cluster may have for each and one more, the table exactly as wide as that:
+    the new token's page is the last row of the last group, opened by it or widened."""
+    print(f"[case] one round groups={groups} d={d} S={S} opens={opens}", flush=True)
+    g, per_group = 3, 512 // d
+    pages = groups * g * per_group
+    L = (pages - 1) * S + (0 if opens else S - 1)
+    spec = wl.WorkloadSpec("round", 2, 4, 2, d, S, L, max(3, min(pages // 3, 60)), headroom=pages * S - L)
+    w = wl.make_workload(spec, DEV, seed=900 + groups, n_q=2, n_new=1, poison=0.0)
+    assert w.P_max == pages
+    f = Session(w, poison_meta=False, cluster_size=g)
+    ts.build_page_meta(f.layout)
+    scale = 1.0 / math.sqrt(d)
+    units = [(b, h) for b in range(spec.B) for h in range(spec.Hkv)]
+    ts.append_and_decode(f.layout, w.k_new[0], w.v_new[0], w.q[0], w.topk, w.K_max, scale, f.out, f.ws,
+                         scores_out=f.scores, sel_out=f.sel, sel_count_out=f.sel_count)
+    compare_units(oracle, f, units, scale, what=f"one round {groups}/{d} append")
+    f.out.fill_(float("nan"))
+    f.fused(scale, q_idx=1)
+    compare_units(oracle, f, units, scale, q_idx=1, what=f"one round {groups}/{d}")
+
+
 def test_an_expired_wait_raises_the_sticky_word_and_the_launch_still_ends(oracle, built):
     """ts_layout.wait_limit = 1 lets a workgroup give up on its partners after two looks.  Such a
     launch must still run to its end (nothing hangs, nothing is read out of bounds) and
