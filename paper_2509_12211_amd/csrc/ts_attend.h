@@ -714,10 +714,28 @@ __device__ __forceinline__ bool merge_tagged(const uint64_t* part, int G, int g,
   return ok;
 }
 
+// The list entry that lane x of the wave looks up for page s of its x-th fragment, in a wave's first batch.
+template <int NW, int S>
+__device__ __forceinline__ int first_entry(int s) {
+  const int item = wave_id() + lane_id() * NW;
+  return S < 16 ? item * PageGeom<S>::NS + s : item / PageGeom<S>::NH;
+}
+
+// A wave's first batch of entries, looked up ahead of the call (those past the list may be anything).
+template <int S>
+struct FirstEntries {
+  static constexpr bool kAny = true;
+  int j[PageGeom<S>::NS], phys[PageGeom<S>::NS];
+};
+struct NoEntries {
+  static constexpr bool kAny = false;
+};
+
 struct SplitPlace { int n_split, split; size_t part_row; };
 
 // The workgroup attends `count` selected pages of unit (b, h): entry i of its
-// list is page sel_at(i), stored in physical page phys_at(page).  The list is
+// list is page sel_at(i), stored in physical page phys_at(page); a caller that has looked the
+// entries of the waves' first batches up already hands them over (ready).  The list is
 // cut into fragments (PageGeom<S>); wave w takes fragments w, w + NW, ...
 // The waves' states are merged through LDS
 // (lds: NW * G * (D + 2) floats).  With n_split == 1 the normalised result
@@ -742,12 +760,13 @@ struct SplitPlace { int n_split, split; size_t part_row; };
 // kWords (tag == 0): the partial is handed on as such words too, with the tag 0 that no launch
 // has; for callers whose workspace other launches read tagged words from.
 template <int NW, int D, int S, bool kPatch, bool kInt8, bool kHalf, bool kHaveQ = false,
-          bool kWords = false, typename PlaceOf, typename SelAt, typename PhysAt>
+          bool kWords = false, typename PlaceOf, typename SelAt, typename PhysAt, typename Ready = NoEntries>
 __device__ __forceinline__ bool attend_split(const AttendParams& p, int b, int h, PlaceOf place,
                                              int count, int L, const NewToken& nt, SelAt sel_at,
                                              PhysAt phys_at, float* lds, uint32_t tag = 0u,
                                              const uint16_t* q_rows = nullptr, int spin_limit = 0,
-                                             const QOperand<D, kInt8>* q_ready = nullptr) {
+                                             const QOperand<D, kInt8>* q_ready = nullptr,
+                                             Ready ready = Ready{}) {
   using Geo = PageGeom<S>;
   constexpr int NT = NW * kWave;
   constexpr int F = Geo::F, NS = Geo::NS, NH = Geo::NH;
@@ -791,10 +810,10 @@ __device__ __forceinline__ bool attend_split(const AttendParams& p, int b, int h
   acc.init();
   TS_MARK(27);
 
-  for (int batch = wave; batch < n_items; batch += kWave * NW) {
-    // lane x holds the page ids of this wave's x-th fragment of the batch
+  int my_j[NS], my_phys[NS];
+  // lane x holds the page ids of this wave's x-th fragment of the batch
+  auto look_up = [&](int batch) {
     const int my_item = batch + lane * NW;
-    int my_j[NS], my_phys[NS];
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
       my_j[s] = -1;
@@ -805,6 +824,17 @@ __device__ __forceinline__ bool attend_split(const AttendParams& p, int b, int h
         if (my_j[s] >= 0 && my_j[s] < p.Pmax) my_phys[s] = phys_at(my_j[s]);
       }
     }
+  };
+  if constexpr (Ready::kAny) {
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+      const bool on = first_entry<NW, S>(s) < count && ready.j[s] >= 0 && ready.j[s] < p.Pmax;
+      my_j[s] = ready.j[s];
+      my_phys[s] = on ? ready.phys[s] : -1;
+    }
+  }
+  for (int batch = wave; batch < n_items; batch += kWave * NW) {
+    if (!Ready::kAny || batch != wave) look_up(batch);
     const int n = min(kWave, (n_items - batch + NW - 1) / NW);
     TS_MARK(28);
     // A ring of NBUF fragment buffers: up to NBUF fragments of this wave are in

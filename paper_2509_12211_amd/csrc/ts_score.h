@@ -200,11 +200,11 @@ __device__ __forceinline__ void scan_issue_query(ScanRegs<D, kHalf, NW, R>& r, c
 template <int D, bool kHalf, int NW, int R>
 __device__ __forceinline__ void scan_issue_tile(ScanRegs<D, kHalf, NW, R>& r, const uint16_t* pmin_u,
                                                 const uint16_t* pmax_u, int Pmax, int first_iter,
-                                                int gs = 1, int goff = 0) {
+                                                int gs = 1, int goff = 0, int iter_stride = NW) {
   constexpr int PPW = ScoreLanes<D, kHalf>::PPW, PPI = ScanRegs<D, kHalf, NW, R>::PPI;
   r.tile.load(pmin_u, pmax_u, first_iter * PPI * gs + goff * PPW, Pmax, PPW * gs);
   if constexpr (ScanRegs<D, kHalf, NW, R>::kTail)
-    r.tail.load(pmin_u, pmax_u, (NW * PPI + first_iter * PPW) * gs + goff * PPW, Pmax, 0);
+    r.tail.load(pmin_u, pmax_u, (iter_stride * PPI + first_iter * PPW) * gs + goff * PPW, Pmax, 0);
 }
 
 // `after_query` runs once the query is in registers and returns Pb.  Must be
@@ -253,7 +253,7 @@ __device__ __forceinline__ void scan_finish(ScanRegs<D, kHalf, NW, R>& r, const 
     before_report();
     r.tile.report(s, Pb, end, sink);
     if constexpr (Regs::kTail) {
-      const int last = (NW * PPI + first_iter * PPW) * gs + goff * PPW;
+      const int last = (iter_stride * PPI + first_iter * PPW) * gs + goff * PPW;
       if (uniform(last) < end) r.tail.reduce(ql, last, Pb, end, 0, patch, sink);
     }
   } else if (kBranchless) {
@@ -279,23 +279,6 @@ __device__ __forceinline__ void scan_finish(ScanRegs<D, kHalf, NW, R>& r, const 
       base = next;
     }
   }
-}
-
-// Both halves back to back.  Loads go out in the order their data is needed:
-// the query rows, then whatever `issue_extra` loads, then the first metadata
-// tile; only then is anything waited for.
-template <int D, bool kHalf, typename IssueExtra, typename AfterQuery, typename Sink>
-__device__ __forceinline__ void score_pages_waves(const uint16_t* pmin_u, const uint16_t* pmax_u,
-                                                  const uint16_t* q_group, int G, int Pmax,
-                                                  int first_iter, int iter_stride,
-                                                  unsigned char* q_stage, IssueExtra issue_extra,
-                                                  AfterQuery after_query, Sink sink) {
-  ScanRegs<D, kHalf> r;
-  scan_issue_query(r, q_group, G);
-  issue_extra();
-  scan_issue_tile(r, pmin_u, pmax_u, Pmax, first_iter);
-  scan_finish<D, true>(r, pmin_u, pmax_u, G, Pmax, first_iter, iter_stride, q_stage, after_query,
-                       [](uint4&, uint4&, int) {}, sink);
 }
 
 }  // namespace ts

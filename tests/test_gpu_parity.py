@@ -1338,6 +1338,23 @@ def test_scoring_in_one_round_of_groups(oracle, built, groups, d, S, opens):
     compare_units(oracle, f, units, scale, q_idx=1, what=f"one round {groups}/{d}")
 
 
+@pytest.mark.parametrize("groups", [3, 64, 65, 192, 193, 320, 321])
+@pytest.mark.parametrize("d", [64, 128])
+def test_staged_scoring_in_one_round_of_groups(oracle, built, groups, d):
+    """ts_score_pages and the staged calls behind it with 64 units (eight workgroups each), at the
+    most groups of pages for which its waves score one, three and five of them and one more; the
+    table is a few rows wider than the longest sequence, the shortest is far from it."""
+    print(f"[case] staged round groups={groups} d={d}", flush=True)
+    pages = groups * (512 // d)
+    spec = wl.WorkloadSpec("staged", 16, 8, 4, d, 4, pages * 4 - 15, max(2, min(pages // 4, 40)),
+                           L_min=max(1, pages // 3), headroom=12)
+    w = wl.make_workload(spec, DEV, seed=1000 + groups, n_q=1, n_new=1)
+    sess = Session(w)
+    ts.build_page_meta(sess.layout)
+    sess.staged(1.0 / math.sqrt(d))
+    compare_units(oracle, sess, [(b, b % 4) for b in range(spec.B)], 1.0 / math.sqrt(d), what=f"staged {groups}/{d}")
+
+
 def test_an_expired_wait_raises_the_sticky_word_and_the_launch_still_ends(oracle, built):
     """ts_layout.wait_limit = 1 lets a workgroup give up on its partners after two looks.  Such a
     launch must still run to its end (nothing hangs, nothing is read out of bounds) and
