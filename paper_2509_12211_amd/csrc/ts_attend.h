@@ -532,7 +532,7 @@ __device__ __forceinline__ void attend_page(const PageFrag<D, F>& f, const short
 #pragma unroll
     for (int v = 0; v < 4; ++v)
       sc[t][v] = (kScaled ? (sc[t][v] - qbias) * kst[v] : sc[t][v]) * scale_log2;
-    if (partial) {   // (uniform) a fragment with all its tokens, the common case, masks nothing
+    if (TS_RARELY(partial)) {   // (uniform) a fragment with all its tokens, the common case, masks nothing
       const uint32_t mine = vmask >> tile_token<F>(t, 4 * kb);   // this lane's four tokens
 #pragma unroll
       for (int v = 0; v < 4; ++v)
@@ -573,7 +573,7 @@ __device__ __forceinline__ void attend_page(const PageFrag<D, F>& f, const short
 #pragma unroll
     for (int cb = 0; cb < NCB; ++cb) {
       uint32_t v0 = f.v[t][cb].x, v1 = f.v[t][cb].y;
-      if (partial && !kScaled) {  // slots that hold no token may hold anything: zero them
+      if (TS_RARELY(partial && !kScaled)) {  // slots that hold no token may hold anything: zero them
         if (!(mine & 1u)) v0 &= 0xffff0000u;
         if (!(mine & 2u)) v0 &= 0x0000ffffu;
         if (!(mine & 4u)) v1 &= 0xffff0000u;
@@ -805,7 +805,7 @@ __device__ __forceinline__ bool attend_split(const AttendParams& p, int b, int h
     }
   }
   const bool splice = kPatch && splice_item >= 0 && wave == splice_item % NW;
-  if (splice) patch.load(nt);
+  if (TS_RARELY(splice)) patch.load(nt);
   WaveAcc<D> acc;
   acc.init();
   TS_MARK(27);
@@ -892,14 +892,14 @@ __device__ __forceinline__ bool attend_split(const AttendParams& p, int b, int h
         PageFrag<D, F> fx;
         expand_frag<D, F>(f[i], fx);
         if constexpr (kPatch) {
-          if (splice && item[i] == splice_item) {
+          if (TS_RARELY(splice && item[i] == splice_item)) {
             patch.apply(fx, splice_x);
             patch.apply_scales(f[i].ks, f[i].vs, splice_x);
           }
         }
         attend_page<D, F, true>(fx, qf, vmask[i], p.scale_log2, acc, f[i].ks, f[i].vs, qbias);
       } else {
-        if (splice && item[i] == splice_item) patch.apply(f[i], splice_x);
+        if (TS_RARELY(splice && item[i] == splice_item)) patch.apply(f[i], splice_x);
         attend_page<D, F, false, kHalf>(f[i], qf, vmask[i], p.scale_log2, acc);
       }
     };
@@ -1002,7 +1002,7 @@ __device__ __forceinline__ bool attend_split(const AttendParams& p, int b, int h
     }
     if (n_split == 1) {
       store_out(p, ((size_t)b * p.Hq + (size_t)h * G + g) * D + c, Lsum > 0.f ? O / Lsum : 0.f);
-      if (c == 0 && p.lse) p.lse[(size_t)b * p.Hq + (size_t)h * G + g] = log_sum_exp(M, Lsum);
+      if (TS_RARELY(c == 0 && p.lse)) p.lse[(size_t)b * p.Hq + (size_t)h * G + g] = log_sum_exp(M, Lsum);
     } else if (tag != 0u) {
       uint64_t* unit64 = reinterpret_cast<uint64_t*>(p.partials) + part_row * (size_t)G * RS;
       if (split == n_split - 1) {   // (uniform) the merging split: its own partial never leaves
@@ -1011,7 +1011,7 @@ __device__ __forceinline__ bool attend_split(const AttendParams& p, int b, int h
         ok = (others <= 4 ? merge_tagged<D, 4>(unit64, G, g, c, others, tag, spin_limit, spins, M, Lsum, O)
                           : merge_tagged<D, 16>(unit64, G, g, c, others, tag, spin_limit, spins, M, Lsum, O)) && ok;
         store_out(p, ((size_t)b * p.Hq + (size_t)h * G + g) * D + c, Lsum > 0.f ? O / Lsum : 0.f);
-        if (c == 0 && p.lse) p.lse[(size_t)b * p.Hq + (size_t)h * G + g] = log_sum_exp(M, Lsum);
+        if (TS_RARELY(c == 0 && p.lse)) p.lse[(size_t)b * p.Hq + (size_t)h * G + g] = log_sum_exp(M, Lsum);
       } else {
         uint64_t* part64 = unit64 + (size_t)split * G * RS;
         store_agent_tagged(part64 + g * RS + c, O, tag);
@@ -1080,7 +1080,7 @@ __device__ __forceinline__ void combine_splits(const AttendParams& p, int b, int
       M = Mn;
     }
     store_out(p, ((size_t)b * p.Hq + (size_t)h * G + g) * D + c, Lsum > 0.f ? O / Lsum : 0.f);
-    if (c == 0 && p.lse) p.lse[(size_t)b * p.Hq + (size_t)h * G + g] = log_sum_exp(M, Lsum);
+    if (TS_RARELY(c == 0 && p.lse)) p.lse[(size_t)b * p.Hq + (size_t)h * G + g] = log_sum_exp(M, Lsum);
   }
 }
 

@@ -623,7 +623,7 @@ __device__ __forceinline__ void decode_units(const FusedParams& p, const FirstAr
   // (a padding workgroup leaves only here, behind the loads of unit 0, whose results it
   // drops: with an exit ahead of them the kernel's arguments would be fetched in two
   // dependent trips, the second one behind the test)
-  if (leave) {
+  if (TS_RARELY(leave)) {
     // A workgroup too many counts itself in like the others, once all its waves have read the
     // lengths and the epoch: lengths advanced while it still looks at them could send it
     // another way.
@@ -659,11 +659,11 @@ __device__ __forceinline__ void decode_units(const FusedParams& p, const FirstAr
     auto park_table = [&] {
 #pragma unroll
       for (int k = 0; k < kBtRegs; ++k) {
-        const int j = threadIdx.x + k * NT;
-        if (j < Pmax) bt_lds[j] = bt_regs[k];
+        // (threads past the row's end write its last entry once more: a test would be a branch each)
+        bt_lds[min((int)threadIdx.x + k * NT, Pmax - 1)] = bt_regs[k];
       }
-      for (int j = threadIdx.x + kBtRegs * NT; j < Pmax; j += NT)
-        bt_lds[j] = bt_row[j];
+      if (TS_RARELY(Pmax > kBtRegs * NT))
+        for (int j = threadIdx.x + kBtRegs * NT; j < Pmax; j += NT) bt_lds[j] = bt_row[j];
     };
     scan_finish<D, !kLoop>(
         scan, p.page_min + (size_t)u * Pmax * D, p.page_max + (size_t)u * Pmax * D, G, Pmax,
@@ -701,7 +701,7 @@ __device__ __forceinline__ void decode_units(const FusedParams& p, const FirstAr
             // INT8 cache: the box takes the dequantised key rounded outwards; the
             // whole wave works out the row's scale (the LPR lanes of a row each
             // hold one chunk of it), the page's lanes do the rest
-            if (kApp && __ballot(pg == j_new) != 0ull) {
+            if (kApp && TS_RARELY(__ballot(pg == j_new) != 0ull)) {
               float amax = chunk_amax_bf16(kn16);
 #pragma unroll
               for (int m = 1; m < LPR; m <<= 1) amax = fmaxf(amax, shfl_xor_f(amax, m));
@@ -715,7 +715,7 @@ __device__ __forceinline__ void decode_units(const FusedParams& p, const FirstAr
                 has_box = true;
               }
             }
-          } else if (kApp && __ballot(pg == j_new) != 0ull && pg == j_new) {
+          } else if (kApp && TS_RARELY(__ballot(pg == j_new) != 0ull) && pg == j_new) {
             mn = slot_new == 0 ? kn16 : widen_box<kHalf>(mn, kn16, true);
             mx = slot_new == 0 ? kn16 : widen_box<kHalf>(mx, kn16, false);
             // (where every member scores the page, each widens it for itself and the first writes
@@ -736,7 +736,7 @@ __device__ __forceinline__ void decode_units(const FusedParams& p, const FirstAr
             tmin = min(tmin, k);
             tmax = max(tmax, k);
           }
-          if (srow_out) srow_out[pg] = s;
+          if (TS_RARELY(srow_out != nullptr)) srow_out[pg] = s;
         },
         kCluster ? g : 1, kCluster ? member : 0, srow_out != nullptr,
         [&] {
@@ -776,13 +776,13 @@ __device__ __forceinline__ void decode_units(const FusedParams& p, const FirstAr
     // when the kernel is done.
     auto store_new_token = [&] {
       const int t = (int)threadIdx.x - (NT - kWave);
-      if (__ballot(has_box) != 0ull && has_box) {
+      if (TS_RARELY(__ballot(has_box) != 0ull) && has_box) {
         const size_t row = ((size_t)u * Pmax + j_new) * D + (lane_id() % LPR) * 8;
         store_through16(const_cast<uint16_t*>(p.page_min) + row, box_lo);
         store_through16(const_cast<uint16_t*>(p.page_max) + row, box_hi);
       }
       if constexpr (kInt8) {
-        if (j_new >= 0 && member == 0 && wave_id() == NW - 1) {   // (uniform) the whole last wave
+        if (TS_RARELY(j_new >= 0 && member == 0 && wave_id() == NW - 1)) {   // (uniform) the whole last wave
           float ka = chunk_amax_bf16(kn16), va = chunk_amax_bf16(vn16);
 #pragma unroll
           for (int m = 1; m < LPR; m <<= 1) {
@@ -810,7 +810,7 @@ __device__ __forceinline__ void decode_units(const FusedParams& p, const FirstAr
         }
         return;
       }
-      if (j_new >= 0 && member == 0 && t >= 0 && t < LPR) {
+      if (TS_RARELY(j_new >= 0 && member == 0 && wave_id() == NW - 1) && t < LPR) {
         const int phys = bt_lds[j_new];
         if (phys >= 0 && phys < at.n_phys) {
           const size_t tile = ((size_t)phys * at.Hkv + h) * (size_t)at.tile_stride;
@@ -880,7 +880,7 @@ __device__ __forceinline__ void decode_units(const FusedParams& p, const FirstAr
       else if (per_thread <= 2) poll(std::integral_constant<int, 2>{});
       else if (per_thread <= 4) poll(std::integral_constant<int, 4>{});
       else poll(std::integral_constant<int, 8>{});
-      if (expired) atomic_store_agent(&p.ctrl[kCtrlError], 1);
+      if (TS_RARELY(expired)) atomic_store_agent(&p.ctrl[kCtrlError], 1);
       TS_MARK(3);
       TS_MARK_WAVE(40);
     } else {
@@ -893,12 +893,12 @@ __device__ __forceinline__ void decode_units(const FusedParams& p, const FirstAr
     // 3. select; keep my own chunk of the ascending list
     const int c0 = min(member * chunk, Kb), count = min(c0 + chunk, Kb) - c0;
     int32_t* sel_row = (p.sel_out && member == 0) ? p.sel_out + (size_t)u * at.Kmax : nullptr;
-    if (sel_row)
+    if (TS_RARELY(sel_row != nullptr))
       for (int i = Kb + threadIdx.x; i < at.Kmax; i += NT) sel_row[i] = -1;
-    if (p.sel_count && member == 0 && h == 0 && threadIdx.x == 0) p.sel_count[b] = Kb;
+    if (TS_RARELY(p.sel_count && member == 0 && h == 0) && threadIdx.x == 0) p.sel_count[b] = Kb;
     auto keep_page = [&](int rank, int page) {
       if (rank >= c0 && rank < c0 + count) my_sel[rank - c0] = page;
-      if (sel_row) sel_row[rank] = page;
+      if (TS_RARELY(sel_row != nullptr)) sel_row[rank] = page;
     };
     if (exchange) select_topk_lds<NW, true>(sl, kl, Pb, Kb, forced, keep_page, bins);
     else select_topk_lds<NW, false>(sl, kl, Pb, Kb, forced, keep_page);
@@ -938,7 +938,7 @@ __device__ __forceinline__ void decode_units(const FusedParams& p, const FirstAr
       }
     }
     TS_MARK(6);
-    if (!merged) atomic_store_agent(&p.ctrl[kCtrlError], 1);
+    if (TS_RARELY(!merged)) atomic_store_agent(&p.ctrl[kCtrlError], 1);
     if (!kLoop) break;
     u += n_clusters;
     if (u >= p.units) break;
@@ -948,7 +948,7 @@ __device__ __forceinline__ void decode_units(const FusedParams& p, const FirstAr
   // the count shows that every workgroup has read the epoch word and, with one unit per
   // workgroup, its sequence length (all of them did so microseconds ago), its first
   // wave re-arms the count, advances the epoch and (append mode) the lengths.
-  if ((exchange || app) && blockIdx.x == 0 && wave_id() == 0) {
+  if ((exchange || app) && TS_RARELY(blockIdx.x == 0 && wave_id() == 0)) {
     if (!wait_at_least(&p.ctrl[kCtrlArrive], p.n_arrive, p.spin_limit))
       atomic_store_agent(&p.ctrl[kCtrlError], 1);
     if (lane_id() == 0) {

@@ -229,12 +229,12 @@ __device__ __forceinline__ void select_topk_lds(const SelectLds& L, const KeyLay
   constexpr int kBatch = 8;  // LDS reads issued together
   Pb = uniform(Pb);
   Kb = uniform(Kb);
-  if (Kb <= 0) return;
-  if (Kb >= Pb) {  // everything is kept
+  if (TS_RARELY(Kb <= 0)) return;
+  if (TS_RARELY(Kb >= Pb)) {  // everything is kept
     for (int j = tid; j < Pb; j += NT) emit(j, j);
     return;
   }
-  if (fp.count >= Kb) {  // the always-kept pages fill the budget: the Kb lowest ids of them
+  if (TS_RARELY(fp.count >= Kb)) {  // the always-kept pages fill the budget: the Kb lowest ids of them
     for (int r = tid; r < Kb; r += NT) emit(r, r < fp.first ? r : fp.last_begin + (r - fp.first));
     return;
   }
@@ -319,7 +319,7 @@ __device__ __forceinline__ void select_topk_lds(const SelectLds& L, const KeyLay
   int need = Kb, cut_slot = 0;
   uint32_t clo = kmin, chi = kmax, base = 0u;  // stage 2b: the keys still undecided are
   int bits = 0;                                // those k with k - clo in [base, base + 2^bits)
-  if (kmax > kmin) {
+  if (TS_USUALLY(kmax > kmin)) {
     if (!kCounted) {
       for_my_keys([&](uint32_t k, int) { atomicAdd(&L.hist[bin_slot_index(linear_slot(k))], 1u); });
       __syncthreads();
@@ -329,7 +329,7 @@ __device__ __forceinline__ void select_topk_lds(const SelectLds& L, const KeyLay
     find_cut(need, cut_slot, above, cnt);
     TS_MARK(12);
     need -= above;
-    if (cnt == need || cnt <= kMaxCandidates) {
+    if (TS_USUALLY(cnt == need || cnt <= kMaxCandidates)) {
       // ---- stage 2a, the usual case: the cut-off bin is kept whole, or holds few enough
       // pages to list them.  ONE pass over the keys and ONE barrier: every thread marks
       // the pages of its chunk that are kept for certain (above the cut-off bin), lists
