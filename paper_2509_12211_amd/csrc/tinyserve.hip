@@ -76,10 +76,7 @@ static Plan make_plan(const ts_layout* L, int max_topk, int target_workgroups = 
   }
   if (g > max_topk) g = max_topk;
   if (g < 1) g = 1;
-  pl.chunk = (max_topk + g - 1) / g;
-  // pages smaller than an MFMA tile are attended four / two at a time: whole
-  // groups per workgroup
-  if (L->page_size < 16) pl.chunk = (pl.chunk + 3) / 4 * 4;
+  pl.chunk = chunk_of(max_topk, g, L->page_size);
   pl.g = (max_topk + pl.chunk - 1) / pl.chunk;
   const size_t unit_bytes = ((size_t)Pmax + (size_t)max_topk * L->page_size) * 4 * L->head_dim;
   // The INT8 cache keeps the same partition of a unit over waves and workgroups everywhere: its
@@ -347,6 +344,17 @@ static int launch_fused(const ts_layout* layout, const void* k_new, const void* 
     pl = make_plan(layout, max_topk, kTargetWorkgroups, false);
   if (workspace_bytes < pl.total) return TS_ERR_WORKSPACE;
   if (!topk_per_seq) pl.shares = pl.shares_uniform;
+  // Clusters of one size: no more members than pay, out of those that fit the device (which the
+  // workspace has room for whatever the list's length).  Not the INT8 cache, see make_plan.
+  if (!pl.shares && pl.g > 2 && layout->kv_format != TS_KV_INT8 && layout->cluster_size == 0 &&
+      g_tune_splits.load(std::memory_order_relaxed) == 0) {
+    const int g = cluster_members(pl.units, pl.g, layout->max_pages_per_seq, max_topk, layout->page_size,
+                                  layout->head_dim);
+    const int chunk = chunk_of(max_topk, g, layout->page_size);
+    pl.lds_fused += (size_t)(chunk - pl.chunk) * 4;
+    pl.chunk = chunk;
+    pl.g = (max_topk + chunk - 1) / chunk;
+  }
   const int cus = num_compute_units();
   if (cus <= 0) return TS_ERR_DEVICE;
   const int tuned_per_cu = g_tune_wg_per_cu.load(std::memory_order_relaxed);

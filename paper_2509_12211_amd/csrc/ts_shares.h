@@ -46,6 +46,46 @@ TS_BOTH float members_of(const SeqWork& w, float inv) {
   return fmaxf(fminf(ceilf(w.rows * inv), w.most), 1.f);
 }
 
+// Kept pages of each member where K are divided among g: whole groups of pages that are smaller
+// than an MFMA tile.
+TS_BOTH int chunk_of(int K, int g, int S) {
+  const int c = (K + g - 1) / g;
+  return S < 16 ? (c + 3) / 4 * 4 : c;
+}
+
+// Members of a cluster in a launch of `units` of them, at most `most`, each with a table of P pages, K
+// kept, d channels: the number whose launch is worked out to be the shortest.  What it takes beyond
+// what all have in common, in us: a round of scoring with more than one group of pages a wave; the
+// member's rows and tiles at 100 B/ns; each fragment of a wave after the first; each sixteen partials
+// merged after the first; and, with more than 96 workgroups, every further one (their polls, arrivals
+// and dispatch).  Fitted to 49 layouts of 1 to 64 units with 100 to 8000 pages, timed at 4 to 8 sizes each: 0.3 %
+// above the best size on average, 4 % at the most, where as many members as fit the device with
+// four pages each were 6 % above it, 37 % at the most (4 units, 250 of 1000 pages: 63 members 17.5
+// us, 17 12.7; 16 units, 48 of 250: 12 11.5, 6 10.7; 8 units, 120 of 1000: 30 14.0, 16 12.5).
+TS_BOTH float cluster_us(int units, int g, int P, int K, int S, int d) {
+  const int chunk = chunk_of(K, g, S), members = (K + chunk - 1) / chunk;
+  const int group = 512 / d, groups = (P + group - 1) / group;
+  const int rows = ((groups + members - 1) / members + 7) / 8;
+  const int frags = S < 16 ? (chunk * S + 15) / 16 : chunk * (S > 32 ? S / 32 : 1);
+  const int rounds = (frags + 7) / 8, batches = members > 17 ? (members + 14) / 16 : 1, wgs = units * members;
+  const float scoring = rows <= 1 ? 0.f : rows <= 3 ? 0.5f : rows <= 5 ? 1.f : 1.f + 0.35f * (float)(rows - 5);
+  const float bytes = ((float)P / (float)members + (float)(chunk * S)) * 4.f * (float)d;
+  return scoring + bytes * 1e-5f + 0.3f * (float)(rounds - 1) + 0.7f * (float)(batches - 1) +
+         (wgs > 96 ? 0.012f * (float)(wgs - 96) : 0.f);
+}
+TS_BOTH int cluster_members(int units, int most, int P, int K, int S, int d) {
+  int best = most;
+  float least = cluster_us(units, most, P, K, S, d);
+  for (int g = most - 1; g >= 2; --g) {
+    const float us = cluster_us(units, g, P, K, S, d);
+    if (us < least) {
+      least = us;
+      best = g;
+    }
+  }
+  return best;
+}
+
 // Every cached token, two rounds of units and more (of kRound at once): whether each unit is best
 // left to one workgroup (kWhole).  total, longest: pages of the B sequences.  A few sequences much
 // longer than the rest would decide the finish time (kFewLong); even lengths are divided where

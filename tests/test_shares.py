@@ -20,6 +20,8 @@ SRC = """
 #include "ts_shares.h"
 extern "C" float even(int P, int Kb, int chunk, int S, int g) { return ts::even_rows(P, Kb, chunk, S, 1.f / g); }
 extern "C" int rounds(int total, int longest, int B, int units) { return ts::rounds_of(total, longest, B, units); }
+extern "C" int cluster(int units, int most, int P, int K, int S, int d) { return ts::cluster_members(units, most, P, K, S, d); }
+extern "C" int chunk(int K, int g, int S) { return ts::chunk_of(K, g, S); }
 extern "C" float members(int P, int Kb, int Kmax, int S, int exchange, float t) {
   const ts::SeqWork w = ts::seq_work(P, Kb, Kmax, S, exchange != 0);
   return ts::members_of(w, t > w.whole ? 1.f / (t - w.whole) : INFINITY);
@@ -129,3 +131,21 @@ def test_rounds_of_whole_or_divided_units_go_by_the_lengths(lib, pages, Hkv, wan
     """The full-cache path over two rounds of units and more; the pool and the table's width have
     no say (a pool of B full tables let a few long sequences decide the finish time)."""
     assert lib.rounds(sum(pages), max(pages), len(pages), len(pages) * Hkv) == want
+
+
+@pytest.mark.parametrize("S", [4, 8, 16, 32, 64])
+def test_members_of_clusters_of_one_size(lib, S):
+    """No more members than the plan has room for, never one, every kept page in somebody's chunk; a
+    short list leaves compute units alone, a long one over long rows takes all of them."""
+    for units in (1, 4, 16, 32, 64, 128):
+        for P in (1, 7, 250, 1000, 16384):
+            for K in (5, 48, 250, 2000):
+                most = min(256 // units, (K + 3) // 4, 64)
+                if most < 2:
+                    continue
+                for d in (64, 128):
+                    g = lib.cluster(units, most, P, K, S, d)
+                    chunk = lib.chunk(K, g, S)
+                    assert 2 <= g <= most and chunk * g >= K and (S >= 16 or chunk % 4 == 0)
+    assert lib.cluster(4, 63, 1000, 250, S, 64) < 40
+    assert lib.cluster(64, 4, 4000, 1000, S, 128) == 4
