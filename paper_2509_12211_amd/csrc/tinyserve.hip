@@ -344,10 +344,15 @@ static int launch_fused(const ts_layout* layout, const void* k_new, const void* 
     pl = make_plan(layout, max_topk, kTargetWorkgroups, false);
   if (workspace_bytes < pl.total) return TS_ERR_WORKSPACE;
   if (!topk_per_seq) pl.shares = pl.shares_uniform;
+  const int cus = num_compute_units();
+  if (cus <= 0) return TS_ERR_DEVICE;
+  const int tuned_per_cu = g_tune_wg_per_cu.load(std::memory_order_relaxed);
+  const int max_resident = cus * (tuned_per_cu > 0 ? tuned_per_cu : 1);
   // Clusters of one size: no more members than pay, out of those that fit the device (which the
-  // workspace has room for whatever the list's length).  Not the INT8 cache, see make_plan.
-  if (!pl.shares && pl.g > 2 && layout->kv_format != TS_KV_INT8 && layout->cluster_size == 0 &&
-      g_tune_splits.load(std::memory_order_relaxed) == 0) {
+  // workspace has room for whatever the list's length).  Not the INT8 cache, see make_plan; not where
+  // they do not fit, a part of a device, whose clusters take the units in turns.
+  if (!pl.shares && pl.g > 2 && pl.units * pl.g <= max_resident && layout->kv_format != TS_KV_INT8 &&
+      layout->cluster_size == 0 && g_tune_splits.load(std::memory_order_relaxed) == 0) {
     const int g = cluster_members(pl.units, pl.g, layout->max_pages_per_seq, max_topk, layout->page_size,
                                   layout->head_dim);
     const int chunk = chunk_of(max_topk, g, layout->page_size);
@@ -355,10 +360,6 @@ static int launch_fused(const ts_layout* layout, const void* k_new, const void* 
     pl.chunk = chunk;
     pl.g = (max_topk + chunk - 1) / chunk;
   }
-  const int cus = num_compute_units();
-  if (cus <= 0) return TS_ERR_DEVICE;
-  const int tuned_per_cu = g_tune_wg_per_cu.load(std::memory_order_relaxed);
-  const int max_resident = cus * (tuned_per_cu > 0 ? tuned_per_cu : 1);
   unsigned char* ws = static_cast<unsigned char*>(workspace);
   FusedParams p;
   p.at = attend_params(layout, pl, q, out, ws, max_topk, softmax_scale);
