@@ -478,10 +478,12 @@ __global__ __launch_bounds__(kThreads) void dense_rounds_kernel(AttendParams p, 
 // kRound > 0: a wave scores its share of the pages in one round of at most that many groups (see
 // ScanRegs), and what the first loads need comes in the arguments in front (f).
 //
+// kInRegs: what the first loads are addressed with is in registers already (see with_args).
+//
 // kDecide: the lengths decide between clusters of one size and shares in proportion to the
 // work (see by_shares), ahead of the first loads.
 template <int NW, int D, int S, bool kLoop, bool kApp, bool kInt8, bool kHalf, bool kCluster,
-          bool kDecide = false, int kRound = 0>
+          bool kDecide = false, int kRound = 0, bool kInRegs = false>
 __device__ __forceinline__ void decode_units(const FusedParams& p, const FirstArgs& f = FirstArgs{}) {
   constexpr bool kFirst = kRound > 0;
   static_assert(!kFirst || (kCluster && !kLoop && !kDecide), "one round of scoring: clusters with one unit each");
@@ -497,7 +499,7 @@ __device__ __forceinline__ void decode_units(const FusedParams& p, const FirstAr
   // first branch: the compiler fetches a kernel argument in the block that first uses it,
   // and arguments first used behind the tests below came in a second and a third trip to
   // memory, each waited for, before the first load could go out.
-  if (!kFirst) asm volatile("" ::"s"(p.ctrl), "s"(p.page_min), "s"(p.page_max), "s"(p.topk_per_seq), "s"(p.k_new),
+  if (!kFirst && !kInRegs) asm volatile("" ::"s"(p.ctrl), "s"(p.page_min), "s"(p.page_max), "s"(p.topk_per_seq), "s"(p.k_new),
                "s"(p.v_new), "s"(p.topk), "s"(p.units), "s"(p.g), "s"(p.xcds), "s"(p.div_hkv.d),
                "s"(p.div_hkv.magic), "s"(p.div_g.d), "s"(p.div_g.magic), "s"(p.div_xcds.d),
                "s"(p.div_xcds.magic), "s"(at.q), "s"(at.block_table), "s"(at.seq_lens), "s"(at.Hq),
@@ -581,7 +583,7 @@ __device__ __forceinline__ void decode_units(const FusedParams& p, const FirstAr
       L_raw = at.seq_lens[b];
       K_raw = p.topk_per_seq ? p.topk_per_seq[b] : p.topk;
     }
-    scan_issue_query(scan, at.q + ((size_t)b * at.Hq + (size_t)h * G) * D, G);
+    scan_issue_query(scan, at.q + (kInRegs ? (size_t)uu * G : (size_t)b * at.Hq + (size_t)h * G) * D, G);
     if (app) {  // behind the query (needed first), ahead of the metadata (needed with it)
       const size_t row = ((size_t)b * at.Hkv + h) * D + (lane_id() % LPR) * 8;
       kn16 = *reinterpret_cast<const uint4*>(p.k_new + row);
@@ -977,7 +979,7 @@ query_aware_decode_kernel(FusedParams p) {
 // instructions for the four groups of a tile and as many again for the next tile's loads, whose
 // pages mostly do not exist.  R = 1 (8 waves, a group each): 4 units of 12 workgroups with 188
 // pages 11.5 -> 10.3 us, 1 of 8 with 257 10.6 -> 9.8; R = 3: 128 of 2 with 257 16.8 -> 16.1, 4 of 32
-// with 4098 17.9 -> 17.0; R = 5: 16.. 128 units of 513-4097 pages -0.1 us, without an append 18.5 -> 17.9.
+// with 4098 17.9 -> 17.0; R = 5: 16 to 128 units of 513-4097 pages -0.1 us, without an append 18.5 -> 17.9.
 // The first loads' arguments come ahead of the others (FirstArgs).
 template <int D, int S, bool kApp, bool kInt8, bool kHalf, int R>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void
@@ -1014,6 +1016,27 @@ many_units_decode_kernel(FusedParams p) {
   decode_units<kWaves, D, S, false, false, kInt8, kHalf, false>(p);
 }
 
+// One workgroup per unit: the struct with what the unit's first loads are addressed with taken from
+// leading arguments, which are in registers when a wave starts (see FirstArgs): 504 units of 174 pages
+// 16.4 -> 16.1 us, 512 of 125 16.1 -> 15.9, 1280 of 94 37.8 -> 37.5.  Units that are not small do
+// not feel it.
+// shape: pages of a table row | G << 16.
+__device__ __forceinline__ FusedParams with_args(FusedParams p, const uint16_t* q, const uint16_t* page_min,
+                                                 const uint16_t* page_max, const int32_t* block_table,
+                                                 const int32_t* seq_lens, const int32_t* topk_per_seq, uint32_t shape,
+                                                 uint32_t magic_hkv) {
+  p.at.q = q;
+  p.page_min = page_min;
+  p.page_max = page_max;
+  p.at.block_table = block_table;
+  p.at.seq_lens = seq_lens;
+  p.topk_per_seq = topk_per_seq;
+  p.at.Pmax = (int)(shape & 0xffffu);
+  p.at.G = (int)(shape >> 16);
+  p.div_hkv.magic = magic_hkv;
+  return p;
+}
+
 // Batches of more units than compute units, as long as a unit is small (kSmallUnitBytes): one
 // workgroup of four waves per unit, two of them resident per compute unit, handed out by the
 // hardware.  Such a unit is bound by the chain of its phases, 10-13 us of which little is
@@ -1026,8 +1049,11 @@ many_units_decode_kernel(FusedParams p) {
 constexpr int kSmallWaves = 4;
 template <int D, int S, bool kHalf>
 __global__ __launch_bounds__(kSmallWaves * kWave) __attribute__((amdgpu_waves_per_eu(2, 2))) void
-small_units_decode_kernel(FusedParams p) {
-  decode_units<kSmallWaves, D, S, false, false, false, kHalf, false>(p);
+small_units_decode_kernel(const uint16_t* q, const uint16_t* page_min, const uint16_t* page_max,
+                          const int32_t* block_table, const int32_t* seq_lens, const int32_t* topk_per_seq,
+                          uint32_t shape, uint32_t magic_hkv, FusedParams p) {
+  decode_units<kSmallWaves, D, S, false, false, false, kHalf, false, false, 0, true>(
+      with_args(p, q, page_min, page_max, block_table, seq_lens, topk_per_seq, shape, magic_hkv));
 }
 
 // ---------------------------------------------------------------------------
@@ -1132,7 +1158,9 @@ static int launch_single(const ts_layout* layout, FusedParams& p, const Plan& pl
     if (pl.small_units) {
       auto small_kernel = small_units_decode_kernel<D, S, kHalf>;
       if ((st = allow_lds(small_kernel, pl.lds_fused)) != TS_OK) return st;
-      small_kernel<<<grid, kSmallWaves * kWave, pl.lds_fused, s>>>(p);
+      small_kernel<<<grid, kSmallWaves * kWave, pl.lds_fused, s>>>(
+          p.at.q, p.page_min, p.page_max, p.at.block_table, p.at.seq_lens, p.topk_per_seq,
+          (uint32_t)p.at.Pmax | (uint32_t)p.at.G << 16, p.div_hkv.magic, p);
       return TS_OK;
     }
   }
