@@ -624,8 +624,10 @@ __device__ __forceinline__ void decode_units(const FusedParams& p, const FirstAr
   if (!kLoop && !kFirst) asm volatile("" : : "s"(q_off) : "memory");
   // (a padding workgroup leaves only here, behind the loads of unit 0, whose results it
   // drops: with an exit ahead of them the kernel's arguments would be fetched in two
-  // dependent trips, the second one behind the test)
-  if (TS_RARELY(leave)) {
+  // dependent trips, the second one behind the test.  The expectation is for the builds it was
+  // measured on: in those that score in a loop over tiles the compiler, with the exit out of the
+  // way, parks 2 to 10 scalar registers in vector lanes ahead of the first load, none without it)
+  if (kFirst || kDecide ? TS_RARELY(leave) : leave) {
     // A workgroup too many counts itself in like the others, once all its waves have read the
     // lengths and the epoch: lengths advanced while it still looks at them could send it
     // another way.
