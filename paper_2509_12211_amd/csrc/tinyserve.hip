@@ -135,8 +135,26 @@ static Plan make_plan(const ts_layout* L, int max_topk, int target_workgroups = 
   // share of it does: the longest block tables with more than about 5000 pages selected)
   const size_t lds_shares = lds + kShareWords * 4 + (size_t)max_topk * 4;
   if (target_workgroups == kTargetWorkgroups && lds_shares > kLdsBytes) pl.shares = pl.shares_uniform = false;
+  pl.lds_list = lds;
   pl.lds_fused = pl.shares ? lds_shares : lds + (size_t)pl.chunk * 4;
   return pl;
+}
+
+// Clusters of one size: no more members than pay, out of those that fit the device (which the
+// workspace has room for whatever the list's length).  Not the INT8 cache, see make_plan; not where
+// they do not fit, a part of a device, whose clusters take the units in turns.  Fewer members hold
+// longer lists: no longer than the LDS has room for, sized for what is launched (the plan's may
+// still be that of shares, which are not asked for where all sequences have the same budget).
+static void fit_clusters(const ts_layout* L, int max_topk, int max_resident, Plan& pl) {
+  if (pl.shares || pl.g <= 2 || pl.units * pl.g > max_resident || L->kv_format == TS_KV_INT8 ||
+      L->cluster_size != 0 || g_tune_splits.load(std::memory_order_relaxed) != 0)
+    return;
+  const int g = cluster_members(pl.units, pl.g, L->max_pages_per_seq, max_topk, L->page_size, L->head_dim);
+  const int chunk = chunk_of(max_topk, g, L->page_size);
+  if (pl.lds_list + (size_t)chunk * 4 > kLdsBytes) return;
+  pl.lds_fused = pl.lds_list + (size_t)chunk * 4;
+  pl.chunk = chunk;
+  pl.g = (max_topk + chunk - 1) / chunk;
 }
 
 // ---------------------------------------------------------------------------
@@ -348,18 +366,7 @@ static int launch_fused(const ts_layout* layout, const void* k_new, const void* 
   if (cus <= 0) return TS_ERR_DEVICE;
   const int tuned_per_cu = g_tune_wg_per_cu.load(std::memory_order_relaxed);
   const int max_resident = cus * (tuned_per_cu > 0 ? tuned_per_cu : 1);
-  // Clusters of one size: no more members than pay, out of those that fit the device (which the
-  // workspace has room for whatever the list's length).  Not the INT8 cache, see make_plan; not where
-  // they do not fit, a part of a device, whose clusters take the units in turns.
-  if (!pl.shares && pl.g > 2 && pl.units * pl.g <= max_resident && layout->kv_format != TS_KV_INT8 &&
-      layout->cluster_size == 0 && g_tune_splits.load(std::memory_order_relaxed) == 0) {
-    const int g = cluster_members(pl.units, pl.g, layout->max_pages_per_seq, max_topk, layout->page_size,
-                                  layout->head_dim);
-    const int chunk = chunk_of(max_topk, g, layout->page_size);
-    pl.lds_fused += (size_t)(chunk - pl.chunk) * 4;
-    pl.chunk = chunk;
-    pl.g = (max_topk + chunk - 1) / chunk;
-  }
+  fit_clusters(layout, max_topk, max_resident, pl);
   unsigned char* ws = static_cast<unsigned char*>(workspace);
   FusedParams p;
   p.at = attend_params(layout, pl, q, out, ws, max_topk, softmax_scale);

@@ -63,6 +63,7 @@ struct Plan {
   size_t off_part;    // [units][g][G][d+2]: {fp32, launch tag} words (fused) or fp32 (staged attention)
   size_t total;
   size_t lds_fused;   // dynamic LDS of the fused kernel
+  size_t lds_list;    // ... in front of this workgroup's selected pages, which come last
   bool small_units;   // many small units: small_units_decode_kernel
   bool shares;        // workgroups by the work if the lengths ask for it, per_head of them per KV head:
   int per_head;       // shares_decode_kernel (query-aware), dense_shares_kernel (every token)
