@@ -500,12 +500,21 @@ __device__ __forceinline__ void decode_units(const FusedParams& p, const FirstAr
   // first branch: the compiler fetches a kernel argument in the block that first uses it,
   // and arguments first used behind the tests below came in a second and a third trip to
   // memory, each waited for, before the first load could go out.
-  if (!kFirst && !kInRegs) asm volatile("" ::"s"(p.ctrl), "s"(p.page_min), "s"(p.page_max), "s"(p.topk_per_seq), "s"(p.k_new),
-               "s"(p.v_new), "s"(p.topk), "s"(p.units), "s"(p.g), "s"(p.xcds), "s"(p.div_hkv.d),
-               "s"(p.div_hkv.magic), "s"(p.div_g.d), "s"(p.div_g.magic), "s"(p.div_xcds.d),
-               "s"(p.div_xcds.magic), "s"(at.q), "s"(at.block_table), "s"(at.seq_lens), "s"(at.Hq),
-               "s"(at.Hkv), "s"(at.G), "s"(at.Pmax), "s"(at.lse), "s"(at.k_scale),
-               "s"(at.v_scale));
+  // Nothing else, and of the cluster's arguments nothing in a build without one: fetched here and
+  // first used behind the rare blocks, which lie out of the way, they were parked in vector lanes
+  // (16 registers, and a second trip, with 128 channels, pages of 64, append, one workgroup per unit).
+  // 192 units of 4096 tokens with an append, 64 channels, pages of 16 15.8 -> 15.4 us, the INT8 cache
+  // with pages of 32 16.3 -> 15.7.  (lse and the scales go with the cluster's all the same: without
+  // them four registers are parked in the append build for 64 channels and pages of 16.)
+  if constexpr (!kFirst && !kInRegs) {
+    asm volatile("" ::"s"(p.ctrl), "s"(p.page_min), "s"(p.page_max), "s"(p.topk_per_seq), "s"(p.topk),
+                 "s"(p.div_hkv.d), "s"(p.div_hkv.magic), "s"(at.q), "s"(at.block_table), "s"(at.seq_lens),
+                 "s"(at.Hq), "s"(at.Hkv), "s"(at.G), "s"(at.Pmax));
+    if constexpr (kCluster)
+      asm volatile("" ::"s"(p.units), "s"(p.g), "s"(p.xcds), "s"(p.div_g.d), "s"(p.div_g.magic),
+                   "s"(p.div_xcds.d), "s"(p.div_xcds.magic), "s"(at.lse), "s"(at.k_scale), "s"(at.v_scale));
+    if constexpr (kApp || kLoop) asm volatile("" ::"s"(p.k_new), "s"(p.v_new));
+  }
   const int G = kFirst ? f.G() : at.G, Pmax = kFirst ? f.Pmax() : at.Pmax;
   // which unit this workgroup works on, as which of how many members, and the size of a
   // member's chunk of the selected pages
@@ -625,10 +634,10 @@ __device__ __forceinline__ void decode_units(const FusedParams& p, const FirstAr
   if (!kLoop && !kFirst) asm volatile("" : : "s"(q_off) : "memory");
   // (a padding workgroup leaves only here, behind the loads of unit 0, whose results it
   // drops: with an exit ahead of them the kernel's arguments would be fetched in two
-  // dependent trips, the second one behind the test.  The expectation is for the builds it was
-  // measured on: in those that score in a loop over tiles the compiler, with the exit out of the
+  // dependent trips, the second one behind the test.  The expectation is for the builds that score in
+  // one round: in those that score in a loop over tiles the compiler, with the exit out of the
   // way, parks 2 to 10 scalar registers in vector lanes ahead of the first load, none without it)
-  if (kFirst || kDecide ? TS_RARELY(leave) : leave) {
+  if (kFirst ? TS_RARELY(leave) : leave) {
     // A workgroup too many counts itself in like the others, once all its waves have read the
     // lengths and the epoch: lengths advanced while it still looks at them could send it
     // another way.
@@ -953,7 +962,10 @@ __device__ __forceinline__ void decode_units(const FusedParams& p, const FirstAr
   // the count shows that every workgroup has read the epoch word and, with one unit per
   // workgroup, its sequence length (all of them did so microseconds ago), its first
   // wave re-arms the count, advances the epoch and (append mode) the lengths.
-  if ((exchange || app) && TS_RARELY(blockIdx.x == 0 && wave_id() == 0)) {
+  // (No expectation in the builds of one workgroup per unit: out of the way, the block has registers
+  // parked for it at the kernel's head.)
+  const bool closes = blockIdx.x == 0 && wave_id() == 0;
+  if ((exchange || app) && (kCluster ? TS_RARELY(closes) : closes)) {
     if (!wait_at_least(&p.ctrl[kCtrlArrive], p.n_arrive, p.spin_limit))
       atomic_store_agent(&p.ctrl[kCtrlError], 1);
     if (lane_id() == 0) {

@@ -20,6 +20,7 @@ import pytest
 from paper_2509_12211_amd import build as tsbuild
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2509_12211_amd", "csrc")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 # head_dim 64, page size, no loop, append folded in, bf16, clusters: the builds the
@@ -34,25 +35,55 @@ SHARES = {
     "shares, append, clusters": "_ZN2ts20shares_decode_kernelILi64ELi16ELb1ELb0ELb1EEEvNS_11FusedParamsE",
     "shares, single": "_ZN2ts20shares_decode_kernelILi64ELi16ELb0ELb0ELb0EEEvNS_11FusedParamsE",
 }
+# head_dim, page size, append, half, clusters (shares) and head_dim, page size, no loop, append, int8,
+# half, no clusters (one workgroup per unit, 129 to 255 of them)
+APPEND = ["shares_decode_kernel<64, 16, true, false, true>", "shares_decode_kernel<128, 16, true, true, true>",
+          "shares_decode_kernel<64, 32, true, false, false>", "shares_decode_kernel<64, 64, true, false, false>",
+          "shares_decode_kernel<128, 32, true, true, false>",
+          "query_aware_decode_kernel<128, 16, false, true, false, false, false>",
+          "query_aware_decode_kernel<128, 64, false, true, false, false, false>",
+          "query_aware_decode_kernel<64, 8, false, true, true, false, false>",
+          "query_aware_decode_kernel<64, 32, false, true, true, false, false>",
+          "query_aware_decode_kernel<128, 32, false, true, true, false, false>"]
 
 
-@pytest.fixture(scope="module")
-def fused_asm():
+def assembly(source):
+    """The gfx950 assembly of a .hip file, compiled with the library's own flags."""
     if not os.path.exists(HIPCC):
         pytest.skip("no hipcc")
     tmp = tempfile.mkdtemp(prefix="ts_isa_")
     try:
-        out = os.path.join(tmp, "fmt_bf16_d64.s")
+        out = os.path.join(tmp, "kernels.s")
         flags = [f for f in tsbuild.HIPCC_FLAGS if f not in ("-fPIC",)]
-        cmd = [HIPCC] + flags + ["--offload-device-only", "-S",
-                                 os.path.join(ROOT, "paper_2509_12211_amd", "csrc", "fmt_bf16_d64.hip"),
-                                 "-o", out]
+        cmd = [HIPCC] + flags + ["-I", CSRC, "--offload-device-only", "-S", source, "-o", out]
         r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
         assert r.returncode == 0, r.stdout[-2000:]
         with open(out) as f:
-            yield f.read()
+            return f.read()
     finally:
         shutil.rmtree(tmp, ignore_errors=True)
+
+
+@pytest.fixture(scope="module")
+def fused_asm():
+    return assembly(os.path.join(CSRC, "fmt_bf16_d64.hip"))
+
+
+@pytest.fixture(scope="module")
+def append_asm(tmp_path_factory):
+    """The APPEND builds, of several formats, compiled by themselves."""
+    src = str(tmp_path_factory.mktemp("isa") / "append.hip")
+    with open(src, "w") as f:
+        f.write('#include "ts_fused.h"\nnamespace ts {\n' +
+                "".join(f"template __global__ void {k}(FusedParams);\n" for k in APPEND) + "}\n")
+    return assembly(src)
+
+
+def mangled(kernel):
+    """The symbol of a kernel that takes the argument struct alone, given as name<integers and truth values>."""
+    name, args = kernel[:-1].split("<")
+    code = "".join("Lb%dE" % (a == "true") if a in ("true", "false") else "Li%sE" % a for a in args.split(", "))
+    return "_ZN2ts%d%sI%sEEvNS_11FusedParamsE" % (len(name), name, code)
 
 
 def kernel_body(asm, symbol):
@@ -61,24 +92,37 @@ def kernel_body(asm, symbol):
     return [l.strip() for l in m.group(0).split("\n") if l.strip() and not l.strip().startswith(";")]
 
 
-@pytest.mark.parametrize("which", sorted(KERNELS))
-def test_arguments_arrive_in_one_trip(fused_asm, which):
-    body = kernel_body(fused_asm, KERNELS[which])
+def head_of(body):
+    """Ahead of the first vector load: trips to memory for kernel arguments that are waited for, scalar
+    registers parked in vector lanes, and whether a fetch is still on its way."""
     trips, pending, spills = 0, False, 0
     for line in body:
         if line.startswith(("global_load", "buffer_load", "flat_load")):
-            break
+            return trips, spills, pending
         if line.startswith("s_load"):
             pending = True
         elif line.startswith("s_waitcnt") and "lgkmcnt" in line and pending:
             trips, pending = trips + 1, False
         elif line.startswith("v_writelane"):
             spills += 1
-    else:
-        pytest.fail("no vector load in the kernel")
+    pytest.fail("no vector load in the kernel")
+
+
+@pytest.mark.parametrize("which", sorted(KERNELS))
+def test_arguments_arrive_in_one_trip(fused_asm, which):
+    trips, spills, pending = head_of(kernel_body(fused_asm, KERNELS[which]))
     assert not pending, "a scalar load ahead of the first vector load is never waited for?"
     assert trips == 1, f"{trips} dependent trips for kernel arguments ahead of the first load"
     assert spills == 0, f"{spills} scalar registers parked in vector lanes ahead of the first load"
+
+
+@pytest.mark.parametrize("kernel", APPEND)
+def test_arguments_of_the_append_builds_arrive_in_one_trip(append_asm, kernel):
+    """The builds with the append folded in, whose rare blocks use many arguments late (two parked
+    registers cost eight cycles; it was up to eighteen, and a second trip)."""
+    trips, spills, _ = head_of(kernel_body(append_asm, mangled(kernel)))
+    assert trips == 1, f"{trips} dependent trips for kernel arguments ahead of the first load"
+    assert spills <= 2, f"{spills} scalar registers parked in vector lanes ahead of the first load"
 
 
 @pytest.mark.parametrize("which", sorted(KERNELS) + sorted(SHARES))
