@@ -505,15 +505,24 @@ __device__ __forceinline__ void decode_units(const FusedParams& p, const FirstAr
   // (16 registers, and a second trip, with 128 channels, pages of 64, append, one workgroup per unit).
   // 192 units of 4096 tokens with an append, 64 channels, pages of 16 15.8 -> 15.4 us, the INT8 cache
   // with pages of 32 16.3 -> 15.7.  (lse and the scales go with the cluster's all the same: without
-  // them four registers are parked in the append build for 64 channels and pages of 16.)
-  if constexpr (!kFirst && !kInRegs) {
+  // them four registers are parked in the append build for 64 channels and pages of 16.  And clusters that
+  // take several units in turn ask for all of it: 128 units of four workgroups with 64 channels, pages of
+  // 16 take 33.1 us so and 33.6 with the short list.)
+  if constexpr (kLoop) {
+    asm volatile("" ::"s"(p.ctrl), "s"(p.page_min), "s"(p.page_max), "s"(p.topk_per_seq), "s"(p.k_new),
+                 "s"(p.v_new), "s"(p.topk), "s"(p.units), "s"(p.g), "s"(p.xcds), "s"(p.div_hkv.d),
+                 "s"(p.div_hkv.magic), "s"(p.div_g.d), "s"(p.div_g.magic), "s"(p.div_xcds.d),
+                 "s"(p.div_xcds.magic), "s"(at.q), "s"(at.block_table), "s"(at.seq_lens), "s"(at.Hq),
+                 "s"(at.Hkv), "s"(at.G), "s"(at.Pmax), "s"(at.lse), "s"(at.k_scale),
+                 "s"(at.v_scale));
+  } else if constexpr (!kFirst && !kInRegs) {
     asm volatile("" ::"s"(p.ctrl), "s"(p.page_min), "s"(p.page_max), "s"(p.topk_per_seq), "s"(p.topk),
                  "s"(p.div_hkv.d), "s"(p.div_hkv.magic), "s"(at.q), "s"(at.block_table), "s"(at.seq_lens),
                  "s"(at.Hq), "s"(at.Hkv), "s"(at.G), "s"(at.Pmax));
     if constexpr (kCluster)
       asm volatile("" ::"s"(p.units), "s"(p.g), "s"(p.xcds), "s"(p.div_g.d), "s"(p.div_g.magic),
                    "s"(p.div_xcds.d), "s"(p.div_xcds.magic), "s"(at.lse), "s"(at.k_scale), "s"(at.v_scale));
-    if constexpr (kApp || kLoop) asm volatile("" ::"s"(p.k_new), "s"(p.v_new));
+    if constexpr (kApp) asm volatile("" ::"s"(p.k_new), "s"(p.v_new));
   }
   const int G = kFirst ? f.G() : at.G, Pmax = kFirst ? f.Pmax() : at.Pmax;
   // which unit this workgroup works on, as which of how many members, and the size of a
