@@ -492,6 +492,7 @@ __device__ __forceinline__ void decode_units(const FusedParams& p, const FirstAr
   static_assert(!(kLoop && kApp), "the append is folded only into the loop-free build");
   static_assert(!kLoop || kCluster, "a single workgroup per unit needs no loop");
   static_assert(!(kDecide && kLoop), "shares are worked out once, at the head");
+  static_assert(!kInRegs || (!kApp && !kCluster && !kDecide), "leading arguments of with_args: one workgroup per unit, no append");
   extern __shared__ __align__(16) unsigned char smem[];
   TS_MARK_INIT();
   TS_MARK(22);
@@ -602,7 +603,7 @@ __device__ __forceinline__ void decode_units(const FusedParams& p, const FirstAr
       L_raw = at.seq_lens[b];
       K_raw = p.topk_per_seq ? p.topk_per_seq[b] : p.topk;
     }
-    scan_issue_query(scan, at.q + (kInRegs ? (size_t)uu * G : (size_t)b * at.Hq + (size_t)h * G) * D, G);
+    scan_issue_query(scan, at.q + ((size_t)b * at.Hq + (size_t)h * G) * D, G);
     if (app) {  // behind the query (needed first), ahead of the metadata (needed with it)
       const size_t row = ((size_t)b * at.Hkv + h) * D + (lane_id() % LPR) * 8;
       kn16 = *reinterpret_cast<const uint4*>(p.k_new + row);
@@ -615,19 +616,21 @@ __device__ __forceinline__ void decode_units(const FusedParams& p, const FirstAr
     scan_issue_tile(scan, p.page_min + (size_t)uu * Pmax * D, p.page_max + (size_t)uu * Pmax * D,
                        Pmax, wave_id(), kCluster ? g : 1, kCluster ? member : 0);
   };
-  if constexpr (kFirst) {
-    // (the same loads; those whose addresses need the struct come last, and wait in registers
-    // until the scores are worked out)
-    scan_issue_query(scan, f.q + (size_t)u * G * D, G);
+  if constexpr (kFirst || kInRegs) {
+    // (the same loads; those whose addresses need the struct, or that the struct's would be waited
+    // for with, come last, and with one round of scoring wait in registers until the scores are
+    // worked out)
+    scan_issue_query(scan, (kFirst ? f.q : at.q) + (size_t)u * G * D, G);
     if (app) {
       const size_t row = (size_t)u * D + (lane_id() % LPR) * 8;
       kn16 = *reinterpret_cast<const uint4*>(f.k_new + row);
       vn16 = *reinterpret_cast<const uint4*>(f.v_new + row);
     }
-    scan_issue_tile(scan, f.page_min + (size_t)u * Pmax * D, f.page_max + (size_t)u * Pmax * D,
-                       Pmax, wave_id(), kCluster ? g : 1, kCluster ? member : 0);
+    scan_issue_tile(scan, (kFirst ? f.page_min : p.page_min) + (size_t)u * Pmax * D,
+                    (kFirst ? f.page_max : p.page_max) + (size_t)u * Pmax * D, Pmax, wave_id(), kCluster ? g : 1,
+                    kCluster ? member : 0);
     __builtin_amdgcn_sched_barrier(0);
-    epoch_raw = p.ctrl[kCtrlEpoch];
+    epoch_raw = exchange ? p.ctrl[kCtrlEpoch] : 0;
     L_raw = at.seq_lens[b];
     K_raw = p.topk_per_seq ? p.topk_per_seq[b] : p.topk;
     const int32_t* bt_row = at.block_table + (size_t)b * Pmax;
@@ -1041,9 +1044,12 @@ many_units_decode_kernel(FusedParams p) {
 }
 
 // One workgroup per unit: the struct with what the unit's first loads are addressed with taken from
-// leading arguments, which are in registers when a wave starts (see FirstArgs): 504 units of 174 pages
-// 16.4 -> 16.1 us, 512 of 125 16.1 -> 15.9, 1280 of 94 37.8 -> 37.5.  Units that are not small do
-// not feel it.
+// leading arguments, which are in registers when a wave starts (see FirstArgs).  The query and the
+// first metadata tile go out on them alone, 25 instructions in, before anything of the struct or the
+// lengths is asked for: with those fetches in front, scalar loads like the lengths', the first vector
+// load stood behind a wait for them and 70 instructions.  512 units of 125 pages 14.2 -> 13.8 us, with 128
+// channels 20.0 -> 19.6, 480 of 125 pages of 32 13.9 -> 13.6, 504 of 174 11.8 -> 11.8 (and 14.5, 20.3, 14.1
+// and 12.2 with the struct alone).  Units that are not small do not feel it.
 // shape: pages of a table row | G << 16.
 __device__ __forceinline__ FusedParams with_args(FusedParams p, const uint16_t* q, const uint16_t* page_min,
                                                  const uint16_t* page_max, const int32_t* block_table,

@@ -45,6 +45,14 @@ APPEND = ["shares_decode_kernel<64, 16, true, false, true>", "shares_decode_kern
           "query_aware_decode_kernel<64, 8, false, true, true, false, false>",
           "query_aware_decode_kernel<64, 32, false, true, true, false, false>",
           "query_aware_decode_kernel<128, 32, false, true, true, false, false>"]
+# the kernels whose leading arguments are in registers when a wave starts, and their arguments: head_dim,
+# page size, append, int8, half, groups of pages a wave; head_dim, page size, half; head_dim, page
+# size, int8, half
+POINTERS, FIRST = "const uint16_t*, const uint16_t*, const uint16_t*, ", "uint32_t, uint32_t, uint32_t, uint32_t, FusedParams"
+PRELOADED = {
+    "small_units_decode_kernel": (POINTERS + "const int32_t*, const int32_t*, const int32_t*, uint32_t, uint32_t, FusedParams",
+                                  ["64, 16, false", "128, 16, false", "64, 32, true", "128, 64, false"]),
+}
 
 
 def assembly(source):
@@ -79,17 +87,41 @@ def append_asm(tmp_path_factory):
     return assembly(src)
 
 
+@pytest.fixture(scope="module")
+def preloaded_asm(tmp_path_factory):
+    src = str(tmp_path_factory.mktemp("isa") / "preloaded.hip")
+    with open(src, "w") as f:
+        f.write('#include "ts_fused.h"\nnamespace ts {\n' +
+                "".join(f"template __global__ void {k}<{a}>({args});\n"
+                        for k, (args, builds) in PRELOADED.items() for a in builds) + "}\n")
+    return assembly(src)
+
+
 def mangled(kernel):
-    """The symbol of a kernel that takes the argument struct alone, given as name<integers and truth values>."""
+    """The beginning of the symbol of a kernel given as name<integers and truth values>."""
     name, args = kernel[:-1].split("<")
     code = "".join("Lb%dE" % (a == "true") if a in ("true", "false") else "Li%sE" % a for a in args.split(", "))
-    return "_ZN2ts%d%sI%sEEvNS_11FusedParamsE" % (len(name), name, code)
+    return "_ZN2ts%d%sI%sEEv" % (len(name), name, code)
+
+
+def symbol(asm, kernel):
+    m = re.search(r"^(" + re.escape(mangled(kernel)) + r"\w*):", asm, re.M)
+    assert m, f"{kernel} not in the assembly"
+    return m.group(1)
 
 
 def kernel_body(asm, symbol):
     m = re.search(r"^" + re.escape(symbol) + r":.*?\n\s*s_endpgm", asm, re.S | re.M)
     assert m, f"{symbol} not in the assembly"
     return [l.strip() for l in m.group(0).split("\n") if l.strip() and not l.strip().startswith(";")]
+
+
+def descriptor(asm, sym, field):
+    m = re.search(r"\.amdhsa_kernel " + re.escape(sym) + r"\n(.*?)\.end_amdhsa_kernel", asm, re.S)
+    assert m, "kernel descriptor not found"
+    value = re.search(r"\.amdhsa_" + field + r" (\d+)", m.group(1))
+    assert value, f"no {field} in the kernel descriptor"
+    return int(value.group(1))
 
 
 def head_of(body):
@@ -120,16 +152,27 @@ def test_arguments_arrive_in_one_trip(fused_asm, which):
 def test_arguments_of_the_append_builds_arrive_in_one_trip(append_asm, kernel):
     """The builds with the append folded in, whose rare blocks use many arguments late (two parked
     registers cost eight cycles; it was up to eighteen, and a second trip)."""
-    trips, spills, _ = head_of(kernel_body(append_asm, mangled(kernel)))
+    trips, spills, _ = head_of(kernel_body(append_asm, symbol(append_asm, kernel)))
     assert trips == 1, f"{trips} dependent trips for kernel arguments ahead of the first load"
     assert spills <= 2, f"{spills} scalar registers parked in vector lanes ahead of the first load"
+
+
+@pytest.mark.parametrize("kernel", [f"{k}<{a}>" for k, (_, builds) in PRELOADED.items() for a in builds])
+def test_first_loads_go_out_on_arguments_in_registers(preloaded_asm, kernel):
+    """All fourteen words are asked for in the kernel's descriptor, and behind the prologue that hardware
+    with that feature skips nothing is waited for ahead of the first vector load."""
+    sym = symbol(preloaded_asm, kernel)
+    assert descriptor(preloaded_asm, sym, "user_sgpr_kernarg_preload_length") == 14
+    body = kernel_body(preloaded_asm, sym)
+    entry = next(i for i, line in enumerate(body) if line.split() == [".p2align", "8"])
+    trips, spills, _ = head_of(body[entry:])
+    assert trips == 0, f"{trips} trips for scalar loads ahead of the first vector load"
+    assert spills == 0, f"{spills} scalar registers parked in vector lanes ahead of the first load"
 
 
 @pytest.mark.parametrize("which", sorted(KERNELS) + sorted(SHARES))
 def test_no_scratch_memory(fused_asm, which):
     sym = KERNELS.get(which) or SHARES[which]
-    m = re.search(r"\.amdhsa_kernel " + re.escape(sym) + r"\n(.*?)\.end_amdhsa_kernel", fused_asm, re.S)
-    assert m, "kernel descriptor not found"
-    size = re.search(r"\.amdhsa_private_segment_fixed_size (\d+)", m.group(1))
-    assert size and int(size.group(1)) == 0, f"scratch bytes per lane: {size.group(1) if size else '?'}"
+    size = descriptor(fused_asm, sym, "private_segment_fixed_size")
+    assert size == 0, f"scratch bytes per lane: {size}"
     assert not any(l.startswith("scratch_") for l in kernel_body(fused_asm, sym))
