@@ -21,6 +21,10 @@ SRC = """
 extern "C" float even(int P, int Kb, int chunk, int S, int g) { return ts::even_rows(P, Kb, chunk, S, 1.f / g); }
 extern "C" int rounds(int total, int longest, int B, int units) { return ts::rounds_of(total, longest, B, units); }
 extern "C" int cluster(int units, int most, int P, int K, int S, int d) { return ts::cluster_members(units, most, P, K, S, d); }
+extern "C" float cluster_us(int units, int g, int P, int K, int S, int d) {
+  const int chunk = ts::chunk_of(K, g, S);
+  return ts::cluster_us(units, (K + chunk - 1) / chunk, chunk, P, S, d).all;
+}
 extern "C" int chunk(int K, int g, int S) { return ts::chunk_of(K, g, S); }
 extern "C" float members(int P, int Kb, int Kmax, int S, int exchange, float t) {
   const ts::SeqWork w = ts::seq_work(P, Kb, Kmax, S, exchange != 0);
@@ -43,6 +47,7 @@ def lib(tmp_path_factory):
     L = ctypes.CDLL(so)
     L.even.argtypes = [ctypes.c_int] * 5
     L.even.restype = ctypes.c_float
+    L.cluster_us.restype = ctypes.c_float
     L.members.argtypes = [ctypes.c_int] * 5 + [ctypes.c_float]
     L.members.restype = ctypes.c_float
     return L
@@ -149,3 +154,17 @@ def test_members_of_clusters_of_one_size(lib, S):
                     assert 2 <= g <= most and chunk * g >= K and (S >= 16 or chunk % 4 == 0)
     assert lib.cluster(4, 63, 1000, 250, S, 64) < 40
     assert lib.cluster(64, 4, 4000, 1000, S, 128) == 4
+
+
+@pytest.mark.parametrize("units", [1, 3, 4, 16, 40, 85])
+def test_search_for_the_cluster_size_ends_early_at_the_best(lib, units):
+    """Sizes that are passed over divide the list like one that was looked at, or are no better."""
+    for S in (4, 8, 16, 64):
+        for d in (64, 128):
+            for P in (1, 60, 257, 1000, 4098, 16384):
+                for K in (9, 33, 48, 250, 1500, 9345):
+                    most = min(256 // units, (K + 3) // 4, 64)
+                    if most < 2:
+                        continue
+                    us = [lib.cluster_us(units, g, P, K, S, d) for g in range(2, most + 1)]
+                    assert lib.cluster_us(units, lib.cluster(units, most, P, K, S, d), P, K, S, d) == min(us)
