@@ -149,12 +149,18 @@ static void fit_clusters(const ts_layout* L, int max_topk, int max_resident, Pla
   if (pl.shares || pl.g <= 2 || pl.units * pl.g > max_resident || L->kv_format == TS_KV_INT8 ||
       L->cluster_size != 0 || g_tune_splits.load(std::memory_order_relaxed) != 0)
     return;
-  const int g = cluster_members(pl.units, pl.g, L->max_pages_per_seq, max_topk, L->page_size, L->head_dim);
-  const int chunk = chunk_of(max_topk, g, L->page_size);
+  // (a list may be longer than the table, whose pages are all that can be kept)
+  const int K = max_topk < L->max_pages_per_seq ? max_topk : L->max_pages_per_seq;
+  int most = (K + 3) / 4;   // a page per wave, as in make_plan
+  if (most > pl.g) most = pl.g;
+  if (most < 2) most = 2;
+  const int g = cluster_members(pl.units, most, L->max_pages_per_seq, K, L->page_size, L->head_dim);
+  const int chunk = chunk_of(K, g, L->page_size);
   if (pl.lds_list + (size_t)chunk * 4 > kLdsBytes) return;
   pl.lds_fused = pl.lds_list + (size_t)chunk * 4;
   pl.chunk = chunk;
-  pl.g = (max_topk + chunk - 1) / chunk;
+  pl.g = (K + chunk - 1) / chunk;
+  if (pl.g < 2) pl.g = 2;   // (the launch stays one of clusters)
 }
 
 // ---------------------------------------------------------------------------

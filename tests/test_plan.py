@@ -67,3 +67,16 @@ def test_what_is_launched_fits_where_its_plan_does(plan, B, Hkv):
                         assert p["lds_run"] <= LDS, (B, Hkv, d, S, pages, topk, uniform, p)
                         assert p["g_run"] <= p["g"] and p["chunk_run"] * p["g_run"] >= topk
     assert fits > 100
+
+
+@pytest.mark.parametrize("S", [8, 16, 32])
+@pytest.mark.parametrize("pages,topk", [(250, 256), (250, 1000), (60, 128), (60, 4096), (20, 128), (2, 128), (1, 128)])
+def test_no_more_pages_are_kept_than_the_table_has(plan, S, pages, topk):
+    """A budget beyond the table's width divides the work like one of the whole table."""
+    for B, Hkv in ((4, 4), (1, 4), (1, 1)):
+        p = plan(B, Hkv, 64, S, pages, topk)
+        assert p["g_run"] >= 2 and p["g_run"] <= p["g"] and p["chunk_run"] * p["g_run"] >= pages
+        if pages >= 4 * p["g"]:      # (as many members as fit either way)
+            q = plan(B, Hkv, 64, S, pages, pages)
+            assert (p["g_run"], p["chunk_run"], p["lds_run"]) == (q["g_run"], q["chunk_run"], q["lds_run"])
+        assert p["g_run"] == 2 or (p["g_run"] - 1) * p["chunk_run"] < pages, "a member that never has a page"
