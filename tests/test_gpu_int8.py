@@ -285,6 +285,38 @@ def test_int8_many_units(oracle, name):
     compare_units(oracle, sess, units, scale, q_idx=1, what=f"{name} launch 1")
 
 
+@pytest.mark.parametrize("groups", [1, 9, 25, 40])
+@pytest.mark.parametrize("d,S", [(64, 16), (128, 8)])
+@pytest.mark.parametrize("opens", [False, True])
+def test_int8_scoring_in_one_round_of_groups(oracle, groups, d, S, opens):
+    """The builds whose waves score one, three or five groups of pages at the most, the appended token's page
+    in the last row of the table: of the only group, of the last group of its own, opened or widened."""
+    print(f"[case] int8 one round groups={groups} d={d} S={S} opens={opens}", flush=True)
+    g, per_group = 3, 512 // d
+    pages = groups * g * per_group
+    L = (pages - 1) * S + (0 if opens else S - 1)
+    topk = max(9, min(pages // 3, 60))
+    chunk = -(-topk // g) if S >= 16 else -(-topk // g // 4) * 4
+    assert -(-topk // chunk) == g      # as many members as asked for
+    spec = spec8("round", 2, 4, 2, d, S, L, topk, headroom=pages * S - L)
+    w = wl.make_workload(spec, DEV, seed=900 + groups, n_q=2, n_new=1, poison=0.0)
+    assert w.P_max == pages
+    f = Session8(w)
+    f.page_min.zero_()
+    f.page_max.zero_()
+    f.layout.cluster_size = g
+    f.ws = ts.new_workspace(f.layout, w.K_max, DEV)
+    ts.build_page_meta(f.layout)
+    scale = 1.0 / math.sqrt(d)
+    units = [(b, h) for b in range(spec.B) for h in range(spec.Hkv)]
+    ts.append_and_decode(f.layout, w.k_new[0], w.v_new[0], w.q[0], w.topk, w.K_max, scale, f.out, f.ws,
+                         scores_out=f.scores, sel_out=f.sel, sel_count_out=f.sel_count)
+    compare_units(oracle, f, units, scale, what=f"int8 one round {groups}/{d} append")
+    f.out.fill_(float("nan"))
+    f.fused(scale, q_idx=1)
+    compare_units(oracle, f, units, scale, q_idx=1, what=f"int8 one round {groups}/{d}")
+
+
 @pytest.mark.parametrize("name", ["tinyllama", "ragged"])
 def test_int8_full_size_sampled(oracle, name):
     """Benchmark workloads at full size with the INT8 cache, default launch shapes; the same

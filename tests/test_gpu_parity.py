@@ -1312,18 +1312,22 @@ def test_cluster_merge_in_batches(oracle, built, cluster, shape):
         compare_units(oracle, sess, units, scale, what=f"merge/cluster={cluster}/{shape}/launch {step}")
 
 
-@pytest.mark.parametrize("groups", [1, 8, 9, 24, 25, 40, 41])
+@pytest.mark.parametrize("kv,groups", [("bf16", n) for n in (1, 8, 9, 24, 25, 40, 41)]
+                         + [("fp16", n) for n in (1, 9, 25, 40)])
 @pytest.mark.parametrize("d,S", [(64, 16), (128, 8)])
 @pytest.mark.parametrize("opens", [False, True])
-def test_scoring_in_one_round_of_groups(oracle, built, groups, d, S, opens):
+def test_scoring_in_one_round_of_groups(oracle, built, kv, groups, d, S, opens):
     """The builds whose waves score at most one, three or five groups of pages, at the most groups
     a member of the cluster may have for each and one more, the table exactly as wide as that:
     the new token's page is the last row of the last group, opened by it or widened."""
-    print(f"[case] one round groups={groups} d={d} S={S} opens={opens}", flush=True)
+    print(f"[case] one round {kv} groups={groups} d={d} S={S} opens={opens}", flush=True)
     g, per_group = 3, 512 // d
     pages = groups * g * per_group
     L = (pages - 1) * S + (0 if opens else S - 1)
-    spec = wl.WorkloadSpec("round", 2, 4, 2, d, S, L, max(3, min(pages // 3, 60)), headroom=pages * S - L)
+    topk = max(9, min(pages // 3, 60))
+    chunk = -(-topk // g) if S >= 16 else -(-topk // g // 4) * 4
+    assert -(-topk // chunk) == g      # as many members as asked for
+    spec = wl.WorkloadSpec("round", 2, 4, 2, d, S, L, topk, headroom=pages * S - L, kv=kv)
     w = wl.make_workload(spec, DEV, seed=900 + groups, n_q=2, n_new=1, poison=0.0)
     assert w.P_max == pages
     f = Session(w, poison_meta=False, cluster_size=g)
@@ -1336,6 +1340,24 @@ def test_scoring_in_one_round_of_groups(oracle, built, groups, d, S, opens):
     f.out.fill_(float("nan"))
     f.fused(scale, q_idx=1)
     compare_units(oracle, f, units, scale, q_idx=1, what=f"one round {groups}/{d}")
+
+
+@pytest.mark.parametrize("L,topk,S", [(900, 300, 16), (230, 128, 8), (70, 200, 32), (15, 128, 16), (14, 128, 8)])
+def test_budget_beyond_the_table(oracle, built, L, topk, S):
+    """More pages may be kept than the table is wide: the cluster's members divide what there is."""
+    print(f"[case] budget beyond the table L={L} topk={topk} S={S}", flush=True)
+    spec = wl.WorkloadSpec("beyond", 1, 16, 4, 64, S, L, topk, headroom=1)
+    w = wl.make_workload(spec, DEV, seed=1200 + L, n_q=2, n_new=1, poison=0.0)
+    assert w.P_max < topk == w.K_max
+    f = Session(w, poison_meta=False)
+    ts.build_page_meta(f.layout)
+    units = [(0, h) for h in range(spec.Hkv)]
+    f.fused(0.125)
+    compare_units(oracle, f, units, 0.125, what=f"beyond/{L}")
+    f.out.fill_(float("nan"))
+    ts.append_and_decode(f.layout, w.k_new[0], w.v_new[0], w.q[1], w.topk, w.K_max, 0.125, f.out, f.ws,
+                         scores_out=f.scores, sel_out=f.sel, sel_count_out=f.sel_count)
+    compare_units(oracle, f, units, 0.125, q_idx=1, what=f"beyond/{L} append")
 
 
 @pytest.mark.parametrize("groups", [3, 64, 65, 192, 193, 320, 321])
