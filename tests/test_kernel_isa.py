@@ -1,11 +1,12 @@
 """Properties of the fused kernel's machine code that cost microseconds when they are lost and
 that no functional test notices (CPU only: hipcc cross-compiles gfx950 without a GPU).
 
-The latency-bound builds of query_aware_decode_kernel (one unit per cluster) must
+The latency-bound builds (one unit per cluster, or one workgroup per unit) must
   - fetch every kernel argument their first loads are addressed with in ONE trip to memory:
     a single wait for scalar loads ahead of the first vector load (scalar registers running
     out at the head of the kernel, or an argument first used behind a branch, brought a second
-    and a third trip, 0.1-0.5 us each on every launch);
+    and a third trip, 0.1-0.5 us each on every launch), and no trip at all in the builds whose
+    leading arguments are in registers when a wave starts;
   - use no scratch memory (a fragment held through a pointer once put 208 bytes per lane
     there: +9 us).
 """
@@ -23,8 +24,8 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2509_12211_amd", "csrc")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
-# head_dim 64, page size, no loop, append folded in, bf16, clusters: the builds the
-# benchmark's 64-, 16- and 8-sequence shapes run
+# head_dim 64, page size, no loop, append folded in, bf16, clusters: tables of more than 40 groups of
+# pages a member
 KERNELS = {
     "page 16": "_ZN2ts25query_aware_decode_kernelILi64ELi16ELb0ELb1ELb0ELb0ELb1EEEvNS_11FusedParamsE",
     "page 32": "_ZN2ts25query_aware_decode_kernelILi64ELi32ELb0ELb1ELb0ELb0ELb1EEEvNS_11FusedParamsE",
@@ -50,8 +51,18 @@ APPEND = ["shares_decode_kernel<64, 16, true, false, true>", "shares_decode_kern
 # size, int8, half
 POINTERS, FIRST = "const uint16_t*, const uint16_t*, const uint16_t*, ", "uint32_t, uint32_t, uint32_t, uint32_t, FusedParams"
 PRELOADED = {
+    # (the benchmark's shapes run these: the 64-, 16- and 8-sequence ones with up to five groups a wave, the
+    # single sequence with one)
+    "one_round_decode_kernel": (POINTERS + "const uint16_t*, const uint16_t*, " + FIRST,
+                                ["64, 16, true, false, false, 1", "64, 16, true, false, false, 3",
+                                 "64, 16, true, false, false, 5", "64, 16, false, false, false, 5",
+                                 "64, 32, true, false, false, 5", "64, 32, true, false, false, 3",
+                                 "128, 16, true, false, true, 3", "64, 16, true, true, false, 5"]),
     "small_units_decode_kernel": (POINTERS + "const int32_t*, const int32_t*, const int32_t*, uint32_t, uint32_t, FusedParams",
                                   ["64, 16, false", "128, 16, false", "64, 32, true", "128, 64, false"]),
+    "sparse_attention_kernel": ("const uint16_t*, const int32_t*, const int32_t*, const int32_t*, const int32_t*, "
+                                "uint32_t, int, int, int, AttendParams, int32_t*, int",
+                                ["64, 8, false, false", "128, 16, false, false", "64, 16, true, false"]),
 }
 
 
@@ -168,6 +179,8 @@ def test_first_loads_go_out_on_arguments_in_registers(preloaded_asm, kernel):
     trips, spills, _ = head_of(body[entry:])
     assert trips == 0, f"{trips} trips for scalar loads ahead of the first vector load"
     assert spills == 0, f"{spills} scalar registers parked in vector lanes ahead of the first load"
+    size = descriptor(preloaded_asm, sym, "private_segment_fixed_size")
+    assert size == 0, f"scratch bytes per lane: {size}"
 
 
 @pytest.mark.parametrize("which", sorted(KERNELS) + sorted(SHARES))
