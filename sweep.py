@@ -24,6 +24,9 @@ Prints one JSON line per configuration, then a table.
 decode steps, |S_t and S_t+1| / K (the reuse of Section 3.6's cost model), on
 the long-context random-walk workload, for query sequences of different
 step-to-step correlation, with and without always-kept first / last pages.
+
+--clusters times clusters of forced sizes against the size the library takes by itself
+(cluster_members in csrc/ts_shares.h), for 48 layouts of 1 to 85 (sequence, KV head) units.
 """
 from __future__ import annotations
 
@@ -159,8 +162,47 @@ def reuse(torch, ts, wl, steps, dev):
         print("| " + " | ".join(str(r[h]) for h in hdr) + " |")
 
 
+def clusters(torch, ts, wl, steps, dev):
+    """us per query-aware decode (no append, cold data, HIP graph) by the members of a cluster."""
+    over_rule, over_most = [], []
+    for i, (B, Hkv) in enumerate([(1, 1), (1, 4), (2, 4), (4, 4), (8, 4), (16, 4), (18, 4), (17, 5)]):
+        for j, (P, K) in enumerate([(100, 24), (250, 48), (1000, 120), (1000, 250), (4000, 500), (8000, 1000)]):
+            d, S = (64, 16) if (i + j) % 2 == 0 else (128, 32 if j % 2 else 8)
+            spec = wl.WorkloadSpec("clusters", B, Hkv * 8, Hkv, d, S, P * S, K, headroom=0)
+            per_layer = wl.algorithmic_bytes(spec, torch.full((B,), spec.L, dtype=torch.int32))["total"]
+            n_layers = int(min(16, max(2, math.ceil((512 << 20) / per_layer))))
+            layers = [bench.Layer(ts, wl, spec, 1000 + 17 * k, dev, 1) for k in range(n_layers)]
+            most = min(256 // (B * Hkv), (K + 3) // 4, 64)
+            sizes = [0] + sorted({g for g in (2, 3, 4, 6, 8, 11, 16, 23, 32, 45, 64) if g < most} | {most})
+            us, graphs, per_graph = {}, {}, max(16, n_layers)
+            for g in sizes:
+                for ly in layers:
+                    ly.layout.cluster_size = g
+                graphs[g] = bench.capture_graph(torch, layers, lambda ly, st, qi: ly.fused(st, 0), per_graph)
+                graphs[g].replay()
+            for turn in range(5):      # the sizes in turn, so that drift meets all of them
+                for g in sizes:
+                    wall, _ = bench.time_region(torch, lambda _: graphs[g].replay(), max(1, steps // per_graph))
+                    us.setdefault(g, []).append(wall / (max(1, steps // per_graph) * per_graph) * 1e6)
+            us = {g: sorted(v)[2] for g, v in us.items()}
+            best = min(us.values())
+            over_rule.append(us[0] / best - 1)
+            over_most.append(us[most] / best - 1)
+            print(f"units {B * Hkv:3d} d {d:3d} pages of {S:2d}: {P:5d} kept {K:4d}  by itself {us[0]:6.2f}  "
+                  + "  ".join(f"{g}: {us[g]:.2f}" for g in sizes[1:]), flush=True)
+            for ly in layers:
+                assert ts.workspace_status(ly.ws) == 0
+            del layers, graphs
+            torch.cuda.empty_cache()
+    n = len(over_rule)
+    print(f"{n} layouts: the library's own size is {100 * sum(over_rule) / n:.1f} % above the best on average, "
+          f"{100 * max(over_rule):.1f} % at the most; as many members as fit {100 * sum(over_most) / n:.1f} % and "
+          f"{100 * max(over_most):.1f} %")
+
+
 def main():
     ap = argparse.ArgumentParser()
+    ap.add_argument("--clusters", action="store_true", help="time clusters of forced sizes instead")
     ap.add_argument("--reuse", action="store_true",
                     help="measure the overlap of consecutive steps' selections instead")
     ap.add_argument("--steps", type=int, default=128)
@@ -178,6 +220,9 @@ def main():
     torch.cuda.set_device(0)
     if args.reuse:
         reuse(torch, ts, wl, min(args.steps, 48), dev)
+        return
+    if args.clusters:
+        clusters(torch, ts, wl, args.steps, dev)
         return
     rows = []
     for shape, keys in [(s, k) for s in args.shapes.split(",") for k in args.keys.split(",")]:
