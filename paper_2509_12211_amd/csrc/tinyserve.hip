@@ -166,9 +166,10 @@ static void fit_clusters(const ts_layout* L, int max_topk, int max_resident, Pla
 // ---------------------------------------------------------------------------
 // Staged kernels
 // ---------------------------------------------------------------------------
-// grid (gx, units): a unit's waves take its tiles of pages in turn.  R: groups of pages a wave has at the most (0: any number).  Bound by HBM beyond
-// a trip to memory and the instructions of a round: 64 units of 1024 pages 6.5 -> 5.7 us without the
-// loop over tiles of four groups, of 2048 8.6 -> 8.0 (4.2 TB/s).
+// grid (gx, units): a unit's waves take its tiles of pages in turn.  R: groups of pages a wave has at
+// the most (0: any number).  Bound by HBM beyond a trip to memory and the instructions of a round: 64
+// units of 1024 pages 6.5 -> 5.7 us without the loop over tiles of four groups, of 2048 8.6 -> 8.0
+// (4.2 TB/s).
 template <int D, bool kHalf, int R>
 __global__ __launch_bounds__(kThreads) void score_pages_kernel(const uint16_t* q,
                                                                const uint16_t* page_min,

@@ -798,8 +798,9 @@ __device__ __forceinline__ void decode_units(const FusedParams& p, const FirstAr
     // issued last would hold up the completion of the kernel), by the first
     // lanes of the last wave (the first wave carries the workgroup's atomics).
     // All of it is written through (see store_through): what the pool and the boxes of a layer
-    // receive in a step are parts of D + 1 lines a unit, whose write-back otherwise starts
-    // when the kernel is done.
+    // receive in a step are parts of some 20 lines a unit (with 64 channels and pages of 16: 16 of the
+    // value tile, whose D rows are S * 2 bytes each, one of the key tile, two boxes), whose
+    // write-back otherwise starts when the kernel is done.
     auto store_new_token = [&] {
       const int t = (int)threadIdx.x - (NT - kWave);
       if (TS_RARELY(__ballot(has_box) != 0ull) && has_box) {
