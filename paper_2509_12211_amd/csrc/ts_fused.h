@@ -501,15 +501,13 @@ __device__ __forceinline__ void decode_units(const FusedParams& p, const FirstAr
   // first branch: the compiler fetches a kernel argument in the block that first uses it,
   // and arguments first used behind the tests below came in a second and a third trip to
   // memory, each waited for, before the first load could go out.
-  // Nothing else, and of the cluster's arguments nothing in a build without one: fetched here and
-  // first used behind the rare blocks, which lie out of the way, they were parked in vector lanes
-  // (16 registers, and a second trip, with 128 channels, pages of 64, append, one workgroup per unit).
-  // 192 units of 4096 tokens with an append, 64 channels, pages of 16 15.8 -> 15.4 us, the INT8 cache
-  // with pages of 32 16.3 -> 15.7.  (lse and the scales go with the cluster's all the same: without
-  // them four registers are parked in the append build for 64 channels and pages of 16.  And clusters that
-  // take several units in turn ask for all of it: 128 units of four workgroups with 64 channels, pages of
-  // 16 take 33.1 us so and 33.6 with the short list.)
-  if constexpr (kLoop) {
+  // In the builds of one workgroup per unit nothing else: fetched here and first used behind the rare
+  // blocks, which lie out of the way, the cluster's arguments and those of the end were parked in
+  // vector lanes (16 registers, and a second trip, with 128 channels, pages of 64 and an append).
+  // 192 units of 4096 tokens with an append, 64 channels, pages of 32 15.0 -> 14.8 us, the INT8 cache
+  // 16.2 -> 15.7.  Builds with clusters ask for all of it: clusters that take several units in turn, 128
+  // units of four workgroups, are at 33.1 us so and 33.6 with the short list.
+  if constexpr (kCluster && !kFirst) {
     asm volatile("" ::"s"(p.ctrl), "s"(p.page_min), "s"(p.page_max), "s"(p.topk_per_seq), "s"(p.k_new),
                  "s"(p.v_new), "s"(p.topk), "s"(p.units), "s"(p.g), "s"(p.xcds), "s"(p.div_hkv.d),
                  "s"(p.div_hkv.magic), "s"(p.div_g.d), "s"(p.div_g.magic), "s"(p.div_xcds.d),
@@ -520,9 +518,6 @@ __device__ __forceinline__ void decode_units(const FusedParams& p, const FirstAr
     asm volatile("" ::"s"(p.ctrl), "s"(p.page_min), "s"(p.page_max), "s"(p.topk_per_seq), "s"(p.topk),
                  "s"(p.div_hkv.d), "s"(p.div_hkv.magic), "s"(at.q), "s"(at.block_table), "s"(at.seq_lens),
                  "s"(at.Hq), "s"(at.Hkv), "s"(at.G), "s"(at.Pmax));
-    if constexpr (kCluster)
-      asm volatile("" ::"s"(p.units), "s"(p.g), "s"(p.xcds), "s"(p.div_g.d), "s"(p.div_g.magic),
-                   "s"(p.div_xcds.d), "s"(p.div_xcds.magic), "s"(at.lse), "s"(at.k_scale), "s"(at.v_scale));
     if constexpr (kApp) asm volatile("" ::"s"(p.k_new), "s"(p.v_new));
   }
   const int G = kFirst ? f.G() : at.G, Pmax = kFirst ? f.Pmax() : at.Pmax;
@@ -646,10 +641,11 @@ __device__ __forceinline__ void decode_units(const FusedParams& p, const FirstAr
   if (!kLoop && !kFirst) asm volatile("" : : "s"(q_off) : "memory");
   // (a padding workgroup leaves only here, behind the loads of unit 0, whose results it
   // drops: with an exit ahead of them the kernel's arguments would be fetched in two
-  // dependent trips, the second one behind the test.  The expectation is for the builds that score in
-  // one round: in those that score in a loop over tiles the compiler, with the exit out of the
-  // way, parks 2 to 10 scalar registers in vector lanes ahead of the first load, none without it)
-  if (kFirst ? TS_RARELY(leave) : leave) {
+  // dependent trips, the second one behind the test.  The expectation is for clusters that score in
+  // one round or look at the lengths first, 12 x 8 units of 5600-8192 tokens with an append 26.0 -> 25.85 us:
+  // in the other builds the compiler, with the exit out of the way, parks 2 to 10 scalar registers in
+  // vector lanes ahead of the first load, none without it)
+  if (kFirst || (kDecide && kCluster) ? TS_RARELY(leave) : leave) {
     // A workgroup too many counts itself in like the others, once all its waves have read the
     // lengths and the epoch: lengths advanced while it still looks at them could send it
     // another way.

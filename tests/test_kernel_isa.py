@@ -36,9 +36,9 @@ SHARES = {
     "shares, append, clusters": "_ZN2ts20shares_decode_kernelILi64ELi16ELb1ELb0ELb1EEEvNS_11FusedParamsE",
     "shares, single": "_ZN2ts20shares_decode_kernelILi64ELi16ELb0ELb0ELb0EEEvNS_11FusedParamsE",
 }
-# head_dim, page size, append, half, clusters (shares) and head_dim, page size, no loop, append, int8,
-# half, no clusters (one workgroup per unit, 129 to 255 of them)
-APPEND = ["shares_decode_kernel<64, 16, true, false, true>", "shares_decode_kernel<128, 16, true, true, true>",
+# head_dim, page size, append, half, no clusters (shares) and head_dim, page size, no loop, append, int8,
+# half, no clusters: one workgroup per unit, 129 to 255 of them
+APPEND = ["shares_decode_kernel<64, 16, true, false, false>", "shares_decode_kernel<128, 4, true, false, false>",
           "shares_decode_kernel<64, 32, true, false, false>", "shares_decode_kernel<64, 64, true, false, false>",
           "shares_decode_kernel<128, 32, true, true, false>",
           "query_aware_decode_kernel<128, 16, false, true, false, false, false>",
@@ -161,8 +161,8 @@ def test_arguments_arrive_in_one_trip(fused_asm, which):
 
 @pytest.mark.parametrize("kernel", APPEND)
 def test_arguments_of_the_append_builds_arrive_in_one_trip(append_asm, kernel):
-    """The builds with the append folded in, whose rare blocks use many arguments late (two parked
-    registers cost eight cycles; it was up to eighteen, and a second trip)."""
+    """The builds with the append folded in, whose rare blocks use many arguments late (a parked
+    register costs four cycles; it was up to eighteen, and a second trip)."""
     trips, spills, _ = head_of(kernel_body(append_asm, symbol(append_asm, kernel)))
     assert trips == 1, f"{trips} dependent trips for kernel arguments ahead of the first load"
     assert spills <= 2, f"{spills} scalar registers parked in vector lanes ahead of the first load"
