@@ -759,8 +759,11 @@ struct SplitPlace { int n_split, split; size_t part_row; };
 // returns false if that wait expired.
 // kWords (tag == 0): the partial is handed on as such words too, with the tag 0 that no launch
 // has; for callers whose workspace other launches read tagged words from.
+// kPlainRing: one loop over the ring, every buffer consumed and refilled under a test of its own, for
+// builds that have no registers to spare for the rounds laid out by the buffers in use (see below).
 template <int NW, int D, int S, bool kPatch, bool kInt8, bool kHalf, bool kHaveQ = false,
-          bool kWords = false, typename PlaceOf, typename SelAt, typename PhysAt, typename Ready = NoEntries>
+          bool kWords = false, bool kPlainRing = false, typename PlaceOf, typename SelAt, typename PhysAt,
+          typename Ready = NoEntries>
 __device__ __forceinline__ bool attend_split(const AttendParams& p, int b, int h, PlaceOf place,
                                              int count, int L, const NewToken& nt, SelAt sel_at,
                                              PhysAt phys_at, float* lds, uint32_t tag = 0u,
@@ -915,6 +918,18 @@ __device__ __forceinline__ bool attend_split(const AttendParams& p, int b, int h
     //     under a test each): these are waited for together.
     // No placeholder loads anywhere: a load with nothing to fetch would still queue
     // behind the compute unit's outstanding misses.
+    if constexpr (kPlainRing) {
+#pragma unroll
+      for (int i = 0; i < NBUF; ++i) vmask[i] = issue(f[i], item[i], i);
+      for (int x0 = 0; x0 < n; x0 += NBUF) {
+#pragma unroll
+        for (int i = 0; i < NBUF; ++i) {
+          if (x0 + i < n) consume(i);
+          if (x0 + i + NBUF < n) vmask[i] = issue(f[i], item[i], x0 + i + NBUF);
+        }
+      }
+      continue;
+    }
     int live;   // fragments in buffers 0 .. live - 1 once the rounds are through
     if (n >= NBUF) {
 #pragma unroll

@@ -937,7 +937,13 @@ __device__ __forceinline__ void decode_units(const FusedParams& p, const FirstAr
     // Shares without an exchange wait for nothing at all: the member that finds itself the
     // last to have handed on its partial merges them.
     constexpr bool apart = kDecide && !kCluster;
-    const bool merged = attend_split<NW, D, S, kApp, kInt8, kHalf, true, apart>(
+    // Clusters that take several units in turn, INT8 cache, 128 channels: the expanded codes, the scales and what
+    // the loop keeps for the next unit fill the registers, and the ring's rounds put 88 bytes a lane in
+    // scratch memory (pages of 32 and 64).  128 units of four workgroups, pages of 16 43.8 -> 42.4 us, of 32
+    // 54.5 -> 49.0, of 64 54.9 -> 48.5.  With smaller pages or 64 channels the rounds are the faster way
+    // (pages of 8 57.0 against 57.7, 64 channels and pages of 16 31.6 against 33.2).
+    constexpr bool plain = kLoop && kInt8 && D == 128 && S >= 16;
+    const bool merged = attend_split<NW, D, S, kApp, kInt8, kHalf, true, apart, plain>(
         at, b, h,
         [&] {
           if constexpr (kDecide) {

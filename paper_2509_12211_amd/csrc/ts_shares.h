@@ -58,10 +58,11 @@ TS_BOTH int chunk_of(int K, int g, int S) {
 // what all have in common, in us: a round of scoring with more than one group of pages a wave; the
 // member's rows and tiles at 100 B/ns; each fragment of a wave after the first; each sixteen partials
 // merged after the first; and, with more than 96 workgroups, every further one (their polls, arrivals
-// and dispatch).  Fitted to 49 layouts of 1 to 64 units with 100 to 8000 pages, timed at 4 to 8 sizes each: 0.3 %
-// above the best size on average, 4 % at the most, where as many members as fit the device with
-// four pages each were 6 % above it, 37 % at the most (4 units, 250 of 1000 pages: 63 members 17.5
-// us, 17 12.7; 16 units, 48 of 250: 12 11.5, 6 10.7; 8 units, 120 of 1000: 30 14.0, 16 12.5).
+// and dispatch).  sweep.py --clusters times 48 layouts of 1 to 85 units with 100 to 8000 pages at up to
+// eleven sizes each: 1.0 % above the best size on average, 9.4 % at the most (1 unit, 120 of 1000 pages: 30
+// members 12.0 us, 16 11.0), where as many members as fit the device with four pages each are 4.8 % above
+// it, 38 % at the most (4 units, 250 of 1000 pages: 63 members 17.1 us, 17 12.4; 16 units, 48 of 250: 12
+// 11.1, 6 10.1; 8 units, 120 of 1000: 30 13.7, 16 11.6).
 struct ClusterTime {
   float grows;   // what only grows with fewer members
   float all;

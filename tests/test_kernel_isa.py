@@ -46,6 +46,8 @@ APPEND = ["shares_decode_kernel<64, 16, true, false, false>", "shares_decode_ker
           "query_aware_decode_kernel<64, 8, false, true, true, false, false>",
           "query_aware_decode_kernel<64, 32, false, true, true, false, false>",
           "query_aware_decode_kernel<128, 32, false, true, true, false, false>"]
+# clusters that take several units in turn, INT8 cache, 128 channels
+LOOPING = [f"query_aware_decode_kernel<128, {s}, true, false, true, false, true>" for s in (16, 32, 64)]
 # the kernels whose leading arguments are in registers when a wave starts, and their arguments: head_dim,
 # page size, append, int8, half, groups of pages a wave; head_dim, page size, half; head_dim, page
 # size, int8, half
@@ -90,11 +92,11 @@ def fused_asm():
 
 @pytest.fixture(scope="module")
 def append_asm(tmp_path_factory):
-    """The APPEND builds, of several formats, compiled by themselves."""
+    """The APPEND and LOOPING builds, of several formats, compiled by themselves."""
     src = str(tmp_path_factory.mktemp("isa") / "append.hip")
     with open(src, "w") as f:
         f.write('#include "ts_fused.h"\nnamespace ts {\n' +
-                "".join(f"template __global__ void {k}(FusedParams);\n" for k in APPEND) + "}\n")
+                "".join(f"template __global__ void {k}(FusedParams);\n" for k in APPEND + LOOPING) + "}\n")
     return assembly(src)
 
 
@@ -166,6 +168,13 @@ def test_arguments_of_the_append_builds_arrive_in_one_trip(append_asm, kernel):
     trips, spills, _ = head_of(kernel_body(append_asm, symbol(append_asm, kernel)))
     assert trips == 1, f"{trips} dependent trips for kernel arguments ahead of the first load"
     assert spills <= 2, f"{spills} scalar registers parked in vector lanes ahead of the first load"
+
+
+@pytest.mark.parametrize("kernel", LOOPING)
+def test_looping_int8_builds_use_no_scratch_memory(append_asm, kernel):
+    sym = symbol(append_asm, kernel)
+    assert descriptor(append_asm, sym, "private_segment_fixed_size") == 0
+    assert not any(line.startswith("scratch_") for line in kernel_body(append_asm, sym))
 
 
 @pytest.mark.parametrize("kernel", [f"{k}<{a}>" for k, (_, builds) in PRELOADED.items() for a in builds])
