@@ -37,11 +37,11 @@ N_QUERIES = 16      # queries a layer cycles through
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "hbm_traffic.json")
 
 WORKLOAD_DESC = {
-    "tiny": "tiny single-head: B1 1q/1kv d64 L4096 S16 K32",
-    "gpt2_345m": "GPT2-345M-shaped MHA: B8 16q/16kv d64 L8192 S16 K64, permuted pool",
-    "tinyllama": "TinyLLaMA-shaped GQA: B16 32q/4kv d64 L16384 S16 K128, outlier channels",
-    "longctx": "long-context GQA: B4 32q/4kv d64 L131072 S32 K128, random-walk keys",
-    "ragged": "ragged serving batch: 64 seqs L~U[1024,32768] 32q/32kv d128 S16 budget 25%",
+    "tiny": "configs[0] tiny single-head: B1 1q/1kv d64 L4096 S16 K32",
+    "gpt2_345m": "configs[1] GPT2-345M-shaped MHA: B8 16q/16kv d64 L8192 S16 K64, permuted pool",
+    "tinyllama": "configs[2] TinyLLaMA-shaped GQA: B16 32q/4kv d64 L16384 S16 K128, outlier channels",
+    "longctx": "configs[3] long-context GQA: B4 32q/4kv d64 L131072 S32 K128, random-walk keys",
+    "ragged": "configs[4] ragged serving batch: 64 seqs L~U[1024,32768] 32q/32kv d128 S16 budget 25%",
 }
 
 
