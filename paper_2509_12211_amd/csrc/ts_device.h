@@ -99,7 +99,7 @@ __device__ __forceinline__ int popc_below(uint64_t mask) {
 
 __device__ __forceinline__ float shfl_xor_f(float v, int m) { return __shfl_xor(v, m, kWave); }
 
-// Conditions whose likely outcome the compiler cannot know.  The latency-bound kernels run some 1500
+// Conditions whose likely outcome the compiler cannot know.  The latency-bound kernels run some 2300
 // instructions a wave once, fetched through a cold instruction cache: with the rare blocks (the
 // appended token's, the exact passes of the selection, optional outputs, expired waits) moved out
 // of the way of the others, a step takes 2-4 % less (16 x 4 units 18.5 -> 18.2 us, 8 x 16 17.6 -> 17.0,
