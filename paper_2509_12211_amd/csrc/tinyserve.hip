@@ -322,6 +322,13 @@ static MetaParams meta_params(const ts_layout* L) {
   return p;
 }
 
+// Whether a bulk rebuild writes its boxes through.  How many pages there are is on the device: no
+// more than the tables have rows, nor than the pool.
+static bool boxes_through(const ts_layout* L) {
+  const size_t rows = (size_t)L->num_seqs * L->max_pages_per_seq, phys = (size_t)L->num_phys_pages;
+  return L->page_size <= 16 && (rows < phys ? rows : phys) * L->num_kv_heads * L->head_dim * 4 >= kBoxesThrough;
+}
+
 static AttendParams attend_params(const ts_layout* L, const Plan& pl, const void* q, void* out,
                                   unsigned char* ws, int max_topk, float softmax_scale) {
   AttendParams a;
@@ -512,17 +519,24 @@ int ts_build_page_meta(const ts_layout* layout, void* stream) {
     return launch_status();
   }
   const bool half = layout->kv_format == TS_KV_FP16;
+  const bool through = boxes_through(layout);
+#define TS_LAUNCH_BUILD_ROWS(DD, HH, NN)                                                        \
+  do {                                                                                          \
+    if (through) build_page_meta_kernel<DD, HH, NN, true><<<grid, kThreads, 0, s>>>(p);         \
+    else build_page_meta_kernel<DD, HH, NN, false><<<grid, kThreads, 0, s>>>(p);                \
+  } while (0)
 #define TS_LAUNCH_BUILD(DD, HH)                                                                 \
   do {                                                                                          \
-    if (p.S == 4) build_page_meta_kernel<DD, HH, 4><<<grid, kThreads, 0, s>>>(p);               \
-    else if (p.S == 8) build_page_meta_kernel<DD, HH, 8><<<grid, kThreads, 0, s>>>(p);          \
-    else build_page_meta_kernel<DD, HH, 16><<<grid, kThreads, 0, s>>>(p);                       \
+    if (p.S == 4) TS_LAUNCH_BUILD_ROWS(DD, HH, 4);                                              \
+    else if (p.S == 8) TS_LAUNCH_BUILD_ROWS(DD, HH, 8);                                         \
+    else TS_LAUNCH_BUILD_ROWS(DD, HH, 16);                                                      \
   } while (0)
   if (layout->head_dim == 64 && !half) TS_LAUNCH_BUILD(64, false);
   else if (layout->head_dim == 64) TS_LAUNCH_BUILD(64, true);
   else if (!half) TS_LAUNCH_BUILD(128, false);
   else TS_LAUNCH_BUILD(128, true);
 #undef TS_LAUNCH_BUILD
+#undef TS_LAUNCH_BUILD_ROWS
   return launch_status();
 }
 

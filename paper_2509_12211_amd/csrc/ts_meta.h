@@ -17,6 +17,9 @@ struct MetaParams {
   float* v_scale;
 };
 
+// Bytes of boxes from which on a bulk rebuild writes them through (pages of up to 16 tokens).
+constexpr size_t kBoxesThrough = 18 << 20;
+
 // One lane's 16 bytes of a unit's boxes (`bytes` of them at base), written through.
 __device__ __forceinline__ void store_row_through(uint16_t* base, int bytes, int at, const uint4& v) {
   constexpr int kRawBuffer = 0x00020000, kSc1 = 16;   // third word of a raw descriptor; cache policy: agent scope
@@ -38,10 +41,13 @@ __device__ __forceinline__ void store_row_through(uint16_t* base, int bytes, int
 // page's tile) and ignored.  The rows are fetched with streaming loads (each
 // instruction takes whole lines that nobody reads again): -9 % on the 128 MiB pool.
 // The boxes of pages of up to 16 tokens (11 to 33 % of what the kernel moves) are written through,
-// whole lines at a time, instead of filling the L2 caches with lines that the end of the kernel
-// writes back: 128 MiB of 64 channels 38.6 -> 38.1 us, 1 GiB of 128 217 -> 212, pages of 8 32.0 -> 30.9.
-// With pages of 32 it costs 0.5 %.
-template <int D, bool kHalf, int NT>
+// whole lines at a time, where there are many: they fill the 32 MiB of the L2 caches with lines that
+// the kernel's end writes back.  64 channels, pages of 16, 66 MB of boxes 128.3 -> 118.1 us, 33 MB 70.2 ->
+// 67.1, 25 MB 54.6 -> 53.9; 128 channels, 33 MB 58.6 -> 57.3, 25 MB 44.0 -> 43.3; pages of 8, 33 MB 33.2 ->
+// 32.2, 25 MB 25.3 -> 25.0.  At 19 MB the two are equal.  Fewer would lose: 18 MB 1 % (128 channels 33.0 -> 33.5), 16
+// MB 1 to 2 %, 6 to 8 MB 6 % (15.7 -> 16.7, pages of 8 10.8 -> 11.5).  With pages of 32 it costs 0.5 %.
+// (A build of its own: a test at the stores cost the others 1 %, 8 units of 1327 pages 11.54 -> 11.70 us.)
+template <int D, bool kHalf, int NT, bool kThrough>
 __global__ __launch_bounds__(kThreads) void build_page_meta_kernel(MetaParams p) {
   constexpr int LPR = D / 8;        // lanes per page (one per 16-byte chunk of a token row)
   constexpr int PPW = kWave / LPR;  // pages per wave
@@ -88,7 +94,7 @@ __global__ __launch_bounds__(kThreads) void build_page_meta_kernel(MetaParams p)
                                pack(lo[6], lo[7]));
     const uint4 c = make_uint4(pack(hi[0], hi[1]), pack(hi[2], hi[3]), pack(hi[4], hi[5]),
                                pack(hi[6], hi[7]));
-    if (p.S <= 16) {
+    if constexpr (kThrough) {
       const size_t unit = ((size_t)b * p.Hkv + h) * p.Pmax * D;
       const int bytes = p.Pmax * D * 2, at = (j * D + cg * 8) * 2;
       store_row_through(p.page_min + unit, bytes, at, a);

@@ -1475,6 +1475,30 @@ def test_full_size_fp16(oracle, built, name):
     compare_units(oracle, sess, full_size_units(w, name), scale, q_idx=1, what=f"full fp16/{name}")
 
 
+@pytest.mark.parametrize("d,S,kv", [(64, 4, "bf16"), (128, 8, "bf16"), (128, 16, "fp16")])
+def test_rebuild_of_many_boxes(built, d, S, kv):
+    """ts_build_page_meta at 18 MiB of boxes, from which on they are written through, and one table row
+    less: every box of every page exact, the rows behind a sequence's last page untouched."""
+    print(f"[case] many boxes d={d} S={S} {kv}", flush=True)
+    B, Hkv = 4, 8
+    dt = torch.float16 if kv == "fp16" else torch.bfloat16
+    for P in ((18 << 20) // (4 * d * Hkv * B), (18 << 20) // (4 * d * Hkv * B) - 1):
+        g = torch.Generator(device=DEV).manual_seed(31 + P)
+        lens = torch.tensor([P * S, P * S - S + 1, P * S // 2 + 3, 1], dtype=torch.int32, device=DEV)
+        k = torch.randn((B * P, Hkv, S, d), generator=g, device=DEV).to(dt)
+        v = torch.zeros((B * P, Hkv, d, S), dtype=dt, device=DEV)
+        table = torch.randperm(B * P, generator=g, device=DEV).to(torch.int32).view(B, P)
+        lo = torch.full((B, Hkv, P, d), 7.0, dtype=dt, device=DEV)
+        hi = torch.full_like(lo, 7.0)
+        ts.build_page_meta(ts.make_layout(B, Hkv, Hkv, d, S, P, k, v, table, lens, lo, hi))
+        tok = (torch.arange(P * S, device=DEV).view(1, P, S) < lens.view(B, 1, 1)).view(B, P, 1, S, 1)
+        x = k.float()[table.long()]                                      # [B][P][Hkv][S][d]
+        on = (tok.any(3)).view(B, 1, P, 1)
+        for got, want in ((lo, x.masked_fill(~tok, math.inf).amin(3)), (hi, x.masked_fill(~tok, -math.inf).amax(3))):
+            want = torch.where(on, want.transpose(1, 2), torch.full_like(want.transpose(1, 2), 7.0))
+            assert torch.equal(got.float(), want)
+
+
 FULL = ["tiny", "gpt2_345m", "tinyllama", "longctx", "ragged"]
 
 
