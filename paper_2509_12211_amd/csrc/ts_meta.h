@@ -349,66 +349,63 @@ __global__ __launch_bounds__(kThreads) void build_page_meta_i8_kernel(MetaParams
 // time.  The bf16 key and value are quantised (scale = max |x| / 127, 1 for a
 // zero vector; code = x / scale rounded half to even, in fp32 with correctly
 // rounded division), stored with their scales when v_new is given, and the
-// page's box is opened / widened with the dequantised key rounded outwards.
+// page's box is opened / widened with the dequantised key rounded outwards.  As above two round trips
+// for the first head of a wave: the token's rows go out with the length, the old box with the block-table entry.
 static __global__ __launch_bounds__(kThreads) void append_token_i8_kernel(MetaParams p, int D,
                                                                    const uint16_t* k_new,
                                                                    const uint16_t* v_new,
                                                                    int advance) {
   const int b = blockIdx.x, lane = lane_id();
+  const int mine = wave_id(), c1 = D > kWave ? lane + kWave : lane;   // channels lane, c1
+  auto fetch = [&](const uint16_t* rows, int h, float (&x)[2]) {
+    const uint16_t* row = rows + ((size_t)b * p.Hkv + h) * D;
+    x[0] = bf16_to_f32(row[lane]);
+    x[1] = bf16_to_f32(row[c1]);   // (64 channels: the first again, not used)
+  };
+  float k0[2], v0[2];
+  fetch(k_new, min(mine, p.Hkv - 1), k0);
+  fetch(v_new ? v_new : k_new, min(mine, p.Hkv - 1), v0);
   const int L = p.seq_lens[b];
   const int sh = __builtin_ctz(p.S);
   const int j = L >> sh, slot = L & (p.S - 1);
   const bool fits = j < p.Pmax;
-  const int phys = p.block_table[(size_t)b * p.Pmax + (fits ? j : 0)];
+  const int jc = fits ? j : 0;
+  const int phys = p.block_table[(size_t)b * p.Pmax + jc];
   const bool ok = fits && (v_new == nullptr || (phys >= 0 && phys < p.n_phys));
-  if (ok) {
-    for (int h = wave_id(); h < p.Hkv; h += kWaves) {
-      const uint16_t* kr = k_new + ((size_t)b * p.Hkv + h) * D;
-      const uint16_t* vr = (v_new ? v_new : k_new) + ((size_t)b * p.Hkv + h) * D;
-      float kv[2], vv[2], ka = 0.f, va = 0.f;   // channels lane, lane + 64
+  for (int h = mine; h < p.Hkv; h += kWaves) {
+    const size_t row = (((size_t)b * p.Hkv + h) * p.Pmax + jc) * D;
+    float kv[2] = {k0[0], k0[1]}, vv[2] = {v0[0], v0[1]};
+    const uint16_t lo_was[2] = {p.page_min[row + lane], p.page_min[row + c1]};
+    const uint16_t hi_was[2] = {p.page_max[row + lane], p.page_max[row + c1]};
+    if (h != mine) {
+      fetch(k_new, h, kv);
+      fetch(v_new ? v_new : k_new, h, vv);
+    }
+    const float ksc = i8_row_scale(wave_max_f32(fmaxf(fabsf(kv[0]), fabsf(kv[1]))));
+    const float vsc = i8_row_scale(wave_max_f32(fmaxf(fabsf(vv[0]), fabsf(vv[1]))));
+    if (!ok) continue;
+    const size_t tile = ((size_t)phys * p.Hkv + h) * (size_t)p.tile_stride;
+    int8_t* k8 = reinterpret_cast<int8_t*>(p.k_pool_w);
+    int8_t* v8 = reinterpret_cast<int8_t*>(p.v_pool_w);
 #pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const int c = lane + 64 * i;
-        kv[i] = c < D ? bf16_to_f32(kr[c]) : 0.f;
-        vv[i] = c < D ? bf16_to_f32(vr[c]) : 0.f;
-        ka = fmaxf(ka, fabsf(kv[i]));
-        va = fmaxf(va, fabsf(vv[i]));
-      }
-#pragma unroll
-      for (int m = 1; m < kWave; m <<= 1) {
-        ka = fmaxf(ka, shfl_xor_f(ka, m));
-        va = fmaxf(va, shfl_xor_f(va, m));
-      }
-      const float ksc = i8_row_scale(ka), vsc = i8_row_scale(va);
-      const size_t tile = ((size_t)phys * p.Hkv + h) * (size_t)p.tile_stride;
-      int8_t* k8 = reinterpret_cast<int8_t*>(p.k_pool_w);
-      int8_t* v8 = reinterpret_cast<int8_t*>(p.v_pool_w);
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const int c = lane + 64 * i;
-        if (c < D) {
-          const int kq = i8_code(kv[i], ksc), vq = i8_code(vv[i], vsc);
-          if (v_new != nullptr) {
-            k8[tile + (size_t)slot * D + c] = static_cast<int8_t>(kq);
-            v8[tile + (size_t)c * p.S + slot] = static_cast<int8_t>(vq);
-          }
-          const double kd = static_cast<double>(kq) * static_cast<double>(ksc);
-          const uint16_t lo = bf16_directed(kd, false), hi = bf16_directed(kd, true);
-          const size_t m = (((size_t)b * p.Hkv + h) * p.Pmax + j) * D + c;
-          if (slot == 0) {
-            p.page_min[m] = lo;
-            p.page_max[m] = hi;
-          } else {
-            if (bf16_to_f32(lo) < bf16_to_f32(p.page_min[m])) p.page_min[m] = lo;
-            if (bf16_to_f32(hi) > bf16_to_f32(p.page_max[m])) p.page_max[m] = hi;
-          }
+    for (int i = 0; i < 2; ++i) {
+      const int c = lane + 64 * i;
+      if (c < D) {
+        const int kq = i8_code(kv[i], ksc), vq = i8_code(vv[i], vsc);
+        if (v_new != nullptr) {
+          k8[tile + (size_t)slot * D + c] = static_cast<int8_t>(kq);
+          v8[tile + (size_t)c * p.S + slot] = static_cast<int8_t>(vq);
         }
+        const double kd = static_cast<double>(kq) * static_cast<double>(ksc);
+        const uint16_t lo = bf16_directed(kd, false), hi = bf16_directed(kd, true);
+        if (slot == 0 || bf16_to_f32(lo) < bf16_to_f32(lo_was[i])) p.page_min[row + c] = lo;
+        if (slot == 0 || bf16_to_f32(hi) > bf16_to_f32(hi_was[i])) p.page_max[row + c] = hi;
       }
-      if (v_new != nullptr && lane == 0) {
-        const size_t so = ((size_t)phys * p.Hkv + h) * (size_t)p.S + slot;
-        p.k_scale[so] = ksc;
-        p.v_scale[so] = vsc;
-      }
+    }
+    if (v_new != nullptr && lane == 0) {
+      const size_t so = ((size_t)phys * p.Hkv + h) * (size_t)p.S + slot;
+      p.k_scale[so] = ksc;
+      p.v_scale[so] = vsc;
     }
   }
   __syncthreads();   // every thread has read seq_lens[b]
