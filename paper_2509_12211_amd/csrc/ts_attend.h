@@ -20,6 +20,8 @@
 // four value tokens belong to); with S = 64 a page is two fragments, its first
 // and its second 32 tokens.
 #pragma once
+#include <limits.h>
+
 #include <type_traits>
 
 #include "ts_device.h"
@@ -614,8 +616,8 @@ struct QOperand {
   }
 };
 
-// Partials handed on as tagged words (attend_split with a tag): merges the first
-// `n` partials of a unit into the running state (M, Lsum, O) of head g, channel c.
+// Partials handed on as tagged words (attend_split with a tag): merges the `n` partials of a
+// unit other than partial `own` into the running state (M, Lsum, O) of head g, channel c.
 // The words are polled until all carry this launch's tag, so the data arrive with the
 // flag, in one trip through the memory system, with no counter and no wait for store
 // acknowledgements on the producers' side.  To be called by whole waves whose threads
@@ -629,7 +631,7 @@ struct QOperand {
 // the bounded wait expired (the state is then invalid).
 // NB: partials polled together (all their loads in flight at once).
 template <int D, int NB>
-__device__ __forceinline__ bool merge_tagged(const uint64_t* part, int G, int g, int c, int n,
+__device__ __forceinline__ bool merge_tagged(const uint64_t* part, int G, int g, int c, int own, int n,
                                              uint32_t tag, int spin_limit, int& spins, float& M,
                                              float& Lsum, float& O) {
   static_assert(D % kWave == 0 && NB <= 16, "a wave works on one head; lanes i and 32 + i serve partial i");
@@ -644,11 +646,11 @@ __device__ __forceinline__ bool merge_tagged(const uint64_t* part, int G, int g,
   for (int s0 = 0; s0 < n; s0 += NB) {
     const int nb = uniform(min(NB, n - s0));
     // the head's running max and sum of the batch's partials: lane i holds the max of
-    // partial s0 + i, lane 32 + i its sum (one load for the wave instead of two per
-    // partial and thread)
+    // partial s0 + i (counted without `own`), lane 32 + i its sum (one load for the wave
+    // instead of two per partial and thread)
     const bool ml_role = (lane & 31) < nb;
-    const uint64_t* base = part + (size_t)s0 * stride;      // (uniform)
-    const uint32_t off_ml = (uint32_t)(ml_role ? (lane & 31) : 0) * stride + (uint32_t)(g * RS + D + (lane >> 5));
+    const int my_row = s0 + (ml_role ? (lane & 31) : 0);
+    const uint32_t off_ml = (uint32_t)(my_row + (my_row >= own ? 1 : 0)) * stride + (uint32_t)(g * RS + D + (lane >> 5));
     uint64_t ml = 0, v[NB];
 #pragma unroll
     for (int i = 0; i < NB; ++i) v[i] = 0;
@@ -659,8 +661,8 @@ __device__ __forceinline__ bool merge_tagged(const uint64_t* part, int G, int g,
       // loads in it, and the last rounds wait for one or two late members
 #pragma unroll
       for (int i = 0; i < NB; ++i)
-        if ((pending >> i) & 1u) v[i] = load_agent_u64(base + (size_t)i * stride + off_o);
-      if (pending >> 31) ml = load_agent_u64(base + off_ml);
+        if ((pending >> i) & 1u) v[i] = load_agent_u64(part + (size_t)(s0 + i + (s0 + i >= own ? 1 : 0)) * stride + off_o);
+      if (pending >> 31) ml = load_agent_u64(part + off_ml);
 #pragma unroll
       for (int i = 0; i < NB; ++i)
         if ((uint32_t)(v[i] >> 32) == tag) pending &= ~(1u << i);
@@ -732,6 +734,9 @@ struct NoEntries {
 };
 
 struct SplitPlace { int n_split, split; size_t part_row; };
+// How the partials of a unit's splits are handed on (attend_split): plainly, for the caller to count
+// arrivals, or as tagged words, which the last split merges, or the splits by slices of the output.
+enum { kPlain, kTagged, kTaggedDealt };
 
 // The workgroup attends `count` selected pages of unit (b, h): entry i of its
 // list is page sel_at(i), stored in physical page phys_at(page); a caller that has looked the
@@ -751,19 +756,19 @@ struct SplitPlace { int n_split, split; size_t part_row; };
 // kInt8: the cache holds int8 keys / values with per-token scales.
 // kHalf: queries, keys and values are IEEE half instead of bf16.
 // q_rows: see below.
-// tag != 0 (n_split > 1): the partial is handed on as 8-byte words {value, tag}
+// kHand (n_split > 1) other than kPlain: the partial is handed on as 8-byte words {value, tag}
 // (see merge_tagged), so the caller neither waits for the stores nor counts an
-// arrival; the partial area then holds uint64 [.][n_split][G][D + 2].  The LAST
-// split keeps its own partial in registers, polls for the others (bounded by
-// spin_limit polls per thread) and writes the unit's output; the function
-// returns false if that wait expired.
-// kWords (tag == 0): the partial is handed on as such words too, with the tag 0 that no launch
+// arrival; the partial area then holds uint64 [.][n_split][G][D + 2].  A split that merges (the
+// last one, or with kTaggedDealt every one the slices of the output that are its own) keeps its own
+// part of that in registers, polls for the others' (bounded by spin_limit polls per thread) and
+// writes the result; the function returns false if that wait expired.
+// kWords: the partial is handed on as such words too, with the tag 0 that no launch
 // has; for callers whose workspace other launches read tagged words from.
 // kPlainRing: one loop over the ring, every buffer consumed and refilled under a test of its own, for
 // builds that have no registers to spare for the rounds laid out by the buffers in use (see below).
 template <int NW, int D, int S, bool kPatch, bool kInt8, bool kHalf, bool kHaveQ = false,
-          bool kWords = false, bool kPlainRing = false, typename PlaceOf, typename SelAt, typename PhysAt,
-          typename Ready = NoEntries>
+          bool kWords = false, bool kPlainRing = false, int kHand = kPlain, typename PlaceOf, typename SelAt,
+          typename PhysAt, typename Ready = NoEntries>
 __device__ __forceinline__ bool attend_split(const AttendParams& p, int b, int h, PlaceOf place,
                                              int count, int L, const NewToken& nt, SelAt sel_at,
                                              PhysAt phys_at, float* lds, uint32_t tag = 0u,
@@ -997,56 +1002,126 @@ __device__ __forceinline__ bool attend_split(const AttendParams& p, int b, int h
   float* part = p.partials + (part_row + split) * (size_t)G * RS;
   bool ok = true;
   int spins = 0;
-  // one thread per (head, channel); the thread of channel 0 also hands on the
-  // head's running max and sum
-  for (int idx = threadIdx.x; idx < G * D; idx += NT) {
-    const int g = idx / D, c = idx % D;
-    float mw[NW], M = -INFINITY;
+  if (kHand == kTaggedDealt && n_split > 8) {
+    // From nine members on the unit's output is dealt out to them in slices of a wave's width, the first to
+    // the last member (whose part of the list is the one that can be short): a member hands on what
+    // belongs to the others' slices, all of it before it waits for anything, and then merges its own.
+    // One member merging everything fetched all partials through one compute unit, half a megabyte of
+    // tagged words with 64 members, eight heads and 128 channels: 2 x 1 units, 2043 of 4860 pages kept, INT8 33.5
+    // -> 27.0 us, 1005 of 2154, FP16 30.2 -> 23.6; 26 units of nine members 21.3 -> 20.0, 4 x 4 of sixteen 1 %.
+    // Of fewer members the last one merges everything: dealt out, three members took 9.5 -> 9.8 us (the
+    // one that is last to finish has polls of its own ahead of it), four 18.0 -> 18.2, five to eight -1 to +2 %.
+    // (Not in the builds that score in a loop, which have no registers to spare: clusters that take units in
+    // turn went to scratch memory.)
+    // A wave hands on and merges the same slices, a round of them shifted against the one before, so that no
+    // wave works a slice out twice and hardly ever has two to merge.
+    static_assert(D % kWave == 0 && (NW & (NW - 1)) == 0, "a slice belongs to one head");
+    constexpr int SL = D / kWave;
+    const int others = n_split - 1, n_slices = G * SL, mine = others - split;   // my slices: s = mine modulo n_split
+    const float inv_n = __builtin_amdgcn_rcpf((float)n_split);
+    uint64_t* unit64 = reinterpret_cast<uint64_t*>(p.partials) + part_row * (size_t)G * RS;
+    uint64_t* part64 = unit64 + (size_t)split * G * RS;
+    // the merged state of the waves for head g, channel c
+    auto merge_waves = [&](int g, int c, float& M, float& Lsum, float& O) {
+      float mw[NW];
+      M = -INFINITY;
 #pragma unroll
-    for (int w = 0; w < NW; ++w) {
-      mw[w] = lds[((size_t)w * G + g) * RS + D];
-      M = fmaxf(M, mw[w]);
-    }
-    float Lsum = 0.f, O = 0.f;
+      for (int w = 0; w < NW; ++w) {
+        mw[w] = lds[((size_t)w * G + g) * RS + D];
+        M = fmaxf(M, mw[w]);
+      }
+      Lsum = 0.f;
+      O = 0.f;
 #pragma unroll
-    for (int w = 0; w < NW; ++w) {
-      const float* row = lds + ((size_t)w * G + g) * RS;
-      const float wgt = __builtin_amdgcn_exp2f(mw[w] - M);
-      Lsum += row[D + 1] * wgt;
-      O += row[c] * wgt;
-    }
-    if (n_split == 1) {
+      for (int w = 0; w < NW; ++w) {
+        const float* row = lds + ((size_t)w * G + g) * RS;
+        const float wgt = __builtin_amdgcn_exp2f(mw[w] - M);
+        Lsum += row[D + 1] * wgt;
+        O += row[c] * wgt;
+      }
+    };
+    auto for_slices = [&](auto fn) {
+      for (int s0 = 0, j = 0; s0 < n_slices; s0 += NW, ++j) {
+        const int s = s0 + ((wave - j) & (NW - 1));
+        // (exact: (s + 1/2) / n_split stays 1/128 away from whole numbers)
+        if (s < n_slices) fn(s, s - uniform((int)(((float)s + 0.5f) * inv_n)) * n_split);
+      }
+    };
+    for_slices([&](int s, int at_member) {
+      if (at_member == mine) return;
+      const int g = s / SL, c0 = (s % SL) * kWave, c = c0 + lane;
+      float M, Lsum, O;
+      merge_waves(g, c, M, Lsum, O);
+      store_agent_tagged(part64 + g * RS + c, O, tag);
+      // the head's max and sum go with the first of its slices that is not mine
+      const bool first_of_head = c0 == 0 || (at_member == 0 ? n_split : at_member) - 1 == mine;
+      if (first_of_head && lane == 0) {
+        store_agent_tagged(part64 + g * RS + D, M, tag);
+        store_agent_tagged(part64 + g * RS + D + 1, Lsum, tag);
+      }
+    });
+    TS_MARK(29);
+    for_slices([&](int s, int at_member) {
+      if (at_member != mine) return;
+      const int g = s / SL, c = (s % SL) * kWave + lane;
+      float M, Lsum, O;
+      merge_waves(g, c, M, Lsum, O);
+      ok = merge_tagged<D, 16>(unit64, G, g, c, split, others, tag, spin_limit, spins, M, Lsum, O) && ok;
       store_out(p, ((size_t)b * p.Hq + (size_t)h * G + g) * D + c, Lsum > 0.f ? O / Lsum : 0.f);
       if (TS_RARELY(c == 0 && p.lse)) p.lse[(size_t)b * p.Hq + (size_t)h * G + g] = log_sum_exp(M, Lsum);
-    } else if (tag != 0u) {
-      uint64_t* unit64 = reinterpret_cast<uint64_t*>(p.partials) + part_row * (size_t)G * RS;
-      if (split == n_split - 1) {   // (uniform) the merging split: its own partial never leaves
-        // (small clusters take the partials four at a time, large ones sixteen)
-        const int others = n_split - 1;
-        ok = (others <= 4 ? merge_tagged<D, 4>(unit64, G, g, c, others, tag, spin_limit, spins, M, Lsum, O)
-                          : merge_tagged<D, 16>(unit64, G, g, c, others, tag, spin_limit, spins, M, Lsum, O)) && ok;
+    });
+  } else {
+    // one thread per (head, channel); the thread of channel 0 also hands on the
+    // head's running max and sum
+    for (int idx = threadIdx.x; idx < G * D; idx += NT) {
+      const int g = idx / D, c = idx % D;
+      float mw[NW], M = -INFINITY;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) {
+        mw[w] = lds[((size_t)w * G + g) * RS + D];
+        M = fmaxf(M, mw[w]);
+      }
+      float Lsum = 0.f, O = 0.f;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) {
+        const float* row = lds + ((size_t)w * G + g) * RS;
+        const float wgt = __builtin_amdgcn_exp2f(mw[w] - M);
+        Lsum += row[D + 1] * wgt;
+        O += row[c] * wgt;
+      }
+      if (n_split == 1) {
         store_out(p, ((size_t)b * p.Hq + (size_t)h * G + g) * D + c, Lsum > 0.f ? O / Lsum : 0.f);
         if (TS_RARELY(c == 0 && p.lse)) p.lse[(size_t)b * p.Hq + (size_t)h * G + g] = log_sum_exp(M, Lsum);
-      } else {
-        uint64_t* part64 = unit64 + (size_t)split * G * RS;
-        store_agent_tagged(part64 + g * RS + c, O, tag);
-        if (c == 0) {
-          store_agent_tagged(part64 + g * RS + D, M, tag);
-          store_agent_tagged(part64 + g * RS + D + 1, Lsum, tag);
+      } else if constexpr (kHand != kPlain) {
+        uint64_t* unit64 = reinterpret_cast<uint64_t*>(p.partials) + part_row * (size_t)G * RS;
+        if (split == n_split - 1) {   // (uniform) the merging split: its own partial never leaves
+          // (small clusters take the partials four at a time, large ones sixteen)
+          const int others = n_split - 1;
+          ok = (others <= 4 ? merge_tagged<D, 4>(unit64, G, g, c, INT_MAX, others, tag, spin_limit, spins, M, Lsum, O)
+                            : merge_tagged<D, 16>(unit64, G, g, c, INT_MAX, others, tag, spin_limit, spins, M, Lsum, O)) && ok;
+          store_out(p, ((size_t)b * p.Hq + (size_t)h * G + g) * D + c, Lsum > 0.f ? O / Lsum : 0.f);
+          if (TS_RARELY(c == 0 && p.lse)) p.lse[(size_t)b * p.Hq + (size_t)h * G + g] = log_sum_exp(M, Lsum);
+        } else {
+          uint64_t* part64 = unit64 + (size_t)split * G * RS;
+          store_agent_tagged(part64 + g * RS + c, O, tag);
+          if (c == 0) {
+            store_agent_tagged(part64 + g * RS + D, M, tag);
+            store_agent_tagged(part64 + g * RS + D + 1, Lsum, tag);
+          }
         }
-      }
-    } else if constexpr (kWords) {
-      uint64_t* part64 = reinterpret_cast<uint64_t*>(p.partials) + (part_row + split) * (size_t)G * RS;
-      store_agent_tagged(part64 + g * RS + c, O, 0u);
-      if (c == 0) {
-        store_agent_tagged(part64 + g * RS + D, M, 0u);
-        store_agent_tagged(part64 + g * RS + D + 1, Lsum, 0u);
-      }
-    } else {
-      store_agent(part + g * RS + c, O);
-      if (c == 0) {
-        store_agent(part + g * RS + D, M);
-        store_agent(part + g * RS + D + 1, Lsum);
+      } else if constexpr (kWords) {
+        uint64_t* part64 = reinterpret_cast<uint64_t*>(p.partials) + (part_row + split) * (size_t)G * RS;
+        store_agent_tagged(part64 + g * RS + c, O, 0u);
+        if (c == 0) {
+          store_agent_tagged(part64 + g * RS + D, M, 0u);
+          store_agent_tagged(part64 + g * RS + D + 1, Lsum, 0u);
+        }
+      } else {
+        store_agent(part + g * RS + c, O);
+        if (c == 0) {
+          store_agent(part + g * RS + D, M);
+          store_agent(part + g * RS + D + 1, Lsum);
+        }
       }
     }
   }

@@ -933,7 +933,7 @@ __device__ __forceinline__ void decode_units(const FusedParams& p, const FirstAr
     // 5. (inside the same call) the cluster's partials are handed on as tagged
     // words; the cluster's last member (its chunk of the list is the one that
     // can be short) keeps its own in registers, polls for the others and writes
-    // the output.  Nobody else waits for anything.
+    // the output, or in large clusters every member its part of it (see attend_split).
     // Shares without an exchange wait for nothing at all: the member that finds itself the
     // last to have handed on its partial merges them.
     constexpr bool apart = kDecide && !kCluster;
@@ -943,7 +943,8 @@ __device__ __forceinline__ void decode_units(const FusedParams& p, const FirstAr
     // 54.5 -> 49.0, of 64 54.9 -> 48.5.  With smaller pages or 64 channels the rounds are the faster way
     // (pages of 8 57.0 against 57.7, 64 channels and pages of 16 31.6 against 33.2).
     constexpr bool plain = kLoop && kInt8 && D == 128 && S >= 16;
-    const bool merged = attend_split<NW, D, S, kApp, kInt8, kHalf, true, apart, plain>(
+    constexpr int hand = !exchange ? kPlain : kFirst || kDecide ? kTaggedDealt : kTagged;
+    const bool merged = attend_split<NW, D, S, kApp, kInt8, kHalf, true, apart, plain, hand>(
         at, b, h,
         [&] {
           if constexpr (kDecide) {
@@ -953,7 +954,7 @@ __device__ __forceinline__ void decode_units(const FusedParams& p, const FirstAr
           }
         },
         count, L, nt, [&](int i) { return my_sel[i]; }, [&](int j) { return bt_lds[j]; },
-        reinterpret_cast<float*>(smem), exchange ? tag : 0u, nullptr, p.spin_limit, &qop);
+        reinterpret_cast<float*>(smem), tag, nullptr, p.spin_limit, &qop);
     if (apart && uniform(words[0]) > 1) {
       int* last = reinterpret_cast<int*>(smem);   // (free behind the barrier that ends the attention)
       stores_complete();
