@@ -183,7 +183,7 @@ __global__ __launch_bounds__(kThreads) void score_pages_kernel(const uint16_t* q
   const int first = blockIdx.x * kWaves + wave_id(), waves = gridDim.x * kWaves;
   ScanRegs<D, kHalf, kWaves, R> r;
   scan_issue_query(r, q + (size_t)u * G * D, G);
-  scan_issue_tile(r, pmin_u, pmax_u, Pmax, first, 1, 0, waves);
+  scan_issue_tile(r, pmin_u, pmax_u, Pmax, first);
   const int len = seq_lens[b];
   int Pb = 0;
   scan_finish<D, true>(

@@ -91,6 +91,13 @@ __device__ __forceinline__ int lane_id() { return threadIdx.x & (kWave - 1); }
 __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
 __device__ __forceinline__ int wave_id() { return uniform(threadIdx.x >> 6); }
 
+// Zero, in a vector register as far as the compiler knows: a load whose address holds it is no scalar load.
+__device__ __forceinline__ int vector_zero() {
+  int z;
+  asm("v_mov_b32 %0, 0" : "=v"(z));
+  return z;
+}
+
 // Number of set bits of `mask` below this lane.
 __device__ __forceinline__ int popc_below(uint64_t mask) {
   return __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(mask >> 32),
@@ -138,6 +145,7 @@ __device__ __forceinline__ double dpp_move_f64(double v) {
   return __hiloint2double(hi, lo);
 }
 constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E;          // quad_perm [1,0,3,2], [2,3,0,1]
+constexpr int kDppRowRor8 = 0x128;                        // lane i <- i ^ 8 of 16
 constexpr int kDppHalfMirror = 0x141, kDppMirror = 0x140;  // lane i <-> 7 - i of 8, 15 - i of 16
 
 // Four values per lane, each to be summed over the aligned group of N (8 or 16) lanes the
@@ -207,6 +215,21 @@ __device__ __forceinline__ float rows_sum_f32(float v) {
   const float m = __uint_as_float(r.x) + __uint_as_float(r.y);
   r = __builtin_amdgcn_permlane32_swap(__float_as_uint(m), __float_as_uint(m), false, false);
   return __uint_as_float(r.x) + __uint_as_float(r.y);
+}
+
+// Two fp64 values per lane summed over the lanes l and l ^ 32: the lower half of the wave gets the
+// sums of a, the upper half those of b.  (a's upper half trades places with b's lower half, so
+// the two registers then hold the summands of one value.)
+__device__ __forceinline__ double sum_halves_f64(double a, double b) {
+  const uint2s_t lo = __builtin_amdgcn_permlane32_swap((unsigned)__double2loint(a), (unsigned)__double2loint(b), false, false);
+  const uint2s_t hi = __builtin_amdgcn_permlane32_swap((unsigned)__double2hiint(a), (unsigned)__double2hiint(b), false, false);
+  return __hiloint2double((int)hi.x, (int)lo.x) + __hiloint2double((int)hi.y, (int)lo.y);
+}
+// One, summed over the lanes l and l ^ 16, for both.
+__device__ __forceinline__ double sum_row_pairs_f64(double a) {
+  const uint2s_t lo = __builtin_amdgcn_permlane16_swap((unsigned)__double2loint(a), (unsigned)__double2loint(a), false, false);
+  const uint2s_t hi = __builtin_amdgcn_permlane16_swap((unsigned)__double2hiint(a), (unsigned)__double2hiint(a), false, false);
+  return __hiloint2double((int)hi.x, (int)lo.x) + __hiloint2double((int)hi.y, (int)lo.y);
 }
 
 // Reductions over the wave; the result is returned as a scalar (lane 63 of the scan).

@@ -110,11 +110,13 @@ struct FirstArgs {
   const uint16_t* q;
   const uint16_t* page_min;
   const uint16_t* page_max;
-  const uint16_t* k_new;
-  const uint16_t* v_new;
+  const uint16_t* first;       // one group of pages a wave: the new tokens' keys and values;
+  const uint16_t* second;      // more: the control words and the lengths
   uint32_t shape;              // pages of a table row | g << 16 | (G - 1) << 24 | log2 of the XCDs << 28
   uint32_t units;
   uint32_t magic_g, magic_hkv; // FastDiv::magic
+  __device__ __forceinline__ const int32_t* ctrl() const { return reinterpret_cast<const int32_t*>(first); }
+  __device__ __forceinline__ const int32_t* seq_lens() const { return reinterpret_cast<const int32_t*>(second); }
   __device__ __forceinline__ int Pmax() const { return (int)(shape & 0xffffu); }
   __device__ __forceinline__ int g() const { return (int)((shape >> 16) & 0xffu); }
   __device__ __forceinline__ int G() const { return (int)((shape >> 24) & 15u) + 1; }
@@ -614,20 +616,39 @@ __device__ __forceinline__ void decode_units(const FusedParams& p, const FirstAr
   if constexpr (kFirst || kInRegs) {
     // (the same loads; those whose addresses need the struct, or that the struct's would be waited
     // for with, come last, and with one round of scoring wait in registers until the scores are
-    // worked out)
+    // worked out.  With several groups a wave the length and the epoch, which everything behind the
+    // query's sums waits for, go out on leading arguments ahead of the metadata, through vector
+    // addresses: scalar loads come back in any order, and with one of these under way the wait for the
+    // struct would be one for it too)
+    constexpr bool kWordsFirst = kRound > 1;
+    const size_t new_chunk = (size_t)u * D + (lane_id() % LPR) * 8;
     scan_issue_query(scan, (kFirst ? f.q : at.q) + (size_t)u * G * D, G);
-    if (app) {
-      const size_t row = (size_t)u * D + (lane_id() % LPR) * 8;
-      kn16 = *reinterpret_cast<const uint4*>(f.k_new + row);
-      vn16 = *reinterpret_cast<const uint4*>(f.v_new + row);
+    if constexpr (kWordsFirst) {
+      epoch_raw = f.ctrl()[kCtrlEpoch + vector_zero()];
+      L_raw = f.seq_lens()[b + vector_zero()];
+    } else if constexpr (app) {
+      kn16 = *reinterpret_cast<const uint4*>(f.first + new_chunk);
+      vn16 = *reinterpret_cast<const uint4*>(f.second + new_chunk);
     }
     scan_issue_tile(scan, (kFirst ? f.page_min : p.page_min) + (size_t)u * Pmax * D,
                     (kFirst ? f.page_max : p.page_max) + (size_t)u * Pmax * D, Pmax, wave_id(), kCluster ? g : 1,
                     kCluster ? member : 0);
     __builtin_amdgcn_sched_barrier(0);
-    epoch_raw = exchange ? p.ctrl[kCtrlEpoch] : 0;
-    L_raw = at.seq_lens[b];
-    K_raw = p.topk_per_seq ? p.topk_per_seq[b] : p.topk;
+    if constexpr (kWordsFirst) {
+      // (three groups: what the rest is addressed with in one trip; see above.  With five the registers run
+      // out: others were parked, and waited for, ahead of the first load)
+      if constexpr (kRound < 5)
+        asm volatile("" ::"s"(at.block_table), "s"(p.topk_per_seq), "s"(p.k_new), "s"(p.v_new), "s"(p.topk));
+      if constexpr (app) {
+        kn16 = *reinterpret_cast<const uint4*>(p.k_new + new_chunk);
+        vn16 = *reinterpret_cast<const uint4*>(p.v_new + new_chunk);
+      }
+      K_raw = p.topk_per_seq ? p.topk_per_seq[b + vector_zero()] : p.topk;
+    } else {
+      epoch_raw = exchange ? p.ctrl[kCtrlEpoch] : 0;
+      L_raw = at.seq_lens[b];
+      K_raw = p.topk_per_seq ? p.topk_per_seq[b] : p.topk;
+    }
     const int32_t* bt_row = at.block_table + (size_t)b * Pmax;
 #pragma unroll
     for (int k = 0; k < kBtRegs; ++k)   // no branch around the loads
@@ -638,7 +659,7 @@ __device__ __forceinline__ void decode_units(const FusedParams& p, const FirstAr
   // (The empty asm keeps the loads where they are: in front of anything that waits for one of
   // them, in the order of their use.  Left to the scheduler, the query's went out last and was waited
   // for with everything else.)
-  if (!kLoop && !kFirst) asm volatile("" : : "s"(q_off) : "memory");
+  if (!kLoop && (!kFirst || kRound == 3)) asm volatile("" : : "s"(q_off) : "memory");
   // (a padding workgroup leaves only here, behind the loads of unit 0, whose results it
   // drops: with an exit ahead of them the kernel's arguments would be fetched in two
   // dependent trips, the second one behind the test.  The expectation is for clusters that score in
@@ -1015,10 +1036,10 @@ query_aware_decode_kernel(FusedParams p) {
 template <int D, int S, bool kApp, bool kInt8, bool kHalf, int R>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void
 one_round_decode_kernel(const uint16_t* q, const uint16_t* page_min, const uint16_t* page_max,
-                        const uint16_t* k_new, const uint16_t* v_new, uint32_t shape, uint32_t units,
+                        const uint16_t* first, const uint16_t* second, uint32_t shape, uint32_t units,
                         uint32_t magic_g, uint32_t magic_hkv, FusedParams p) {
   decode_units<kWaves, D, S, false, kApp, kInt8, kHalf, true, false, R>(
-      p, FirstArgs{q, page_min, page_max, k_new, v_new, shape, units, magic_g, magic_hkv});
+      p, FirstArgs{q, page_min, page_max, first, second, shape, units, magic_g, magic_hkv});
 }
 
 // Up to 255 units of batches that may be ragged: see by_shares.  kCluster: the members of a
@@ -1244,12 +1265,13 @@ static bool launch_shares(const ts_layout* layout, FusedParams& p, const Plan& p
 // gap, and a longer tile would not fit the registers.
 using OneRound = void (*)(const uint16_t*, const uint16_t*, const uint16_t*, const uint16_t*, const uint16_t*,
                           uint32_t, uint32_t, uint32_t, uint32_t, FusedParams);
+static int round_groups(int D, int Pmax, int g) {   // groups of pages a wave has at the most
+  const int group = kWave / (D / 8), groups = (Pmax + group - 1) / group;
+  return ((groups + g - 1) / g + kWaves - 1) / kWaves;
+}
 template <int D, int S, bool kApp, int kFmt>
-static OneRound one_round_kernel(const FusedParams& p) {
+static OneRound one_round_kernel(int rows) {
   constexpr bool kInt8 = kFmt == TS_KV_INT8, kHalf = kFmt == TS_KV_FP16;
-  constexpr int group = ScoreLanes<D>::PPW;
-  const int groups = (p.at.Pmax + group - 1) / group;
-  const int rows = ((groups + p.g - 1) / p.g + kWaves - 1) / kWaves;
   if (rows <= 1) return one_round_decode_kernel<D, S, kApp, kInt8, kHalf, 1>;
   if (rows <= 3) return one_round_decode_kernel<D, S, kApp, kInt8, kHalf, 3>;
   if (rows <= 5) return one_round_decode_kernel<D, S, kApp, kInt8, kHalf, 5>;
@@ -1268,7 +1290,8 @@ static int launch_clusters(const ts_layout* layout, FusedParams& p, const Plan& 
   auto one_kernel = query_aware_decode_kernel<D, S, false, false, kInt8, kHalf, true>;
   auto app_kernel = query_aware_decode_kernel<D, S, false, true, kInt8, kHalf, true>;
   int st;
-  const OneRound round_kernel = k_new ? one_round_kernel<D, S, true, kFmt>(p) : one_round_kernel<D, S, false, kFmt>(p);
+  const int rows = round_groups(D, p.at.Pmax, p.g);
+  const OneRound round_kernel = k_new ? one_round_kernel<D, S, true, kFmt>(rows) : one_round_kernel<D, S, false, kFmt>(rows);
   if (round_kernel) {
     if ((st = allow_lds(round_kernel, pl.lds_fused)) != TS_OK) return st;
     int cap = resident_capacity(round_kernel, pl.lds_fused);
@@ -1280,8 +1303,11 @@ static int launch_clusters(const ts_layout* layout, FusedParams& p, const Plan& 
       p.n_arrive = pl.units * pl.g;
       const uint32_t shape = (uint32_t)p.at.Pmax | (uint32_t)p.g << 16 | (uint32_t)(p.at.G - 1) << 24 |
                              (uint32_t)xcd_bits << 28;
-      round_kernel<<<grid, kThreads, pl.lds_fused, s>>>(p.at.q, p.page_min, p.page_max, p.k_new, p.v_new, shape,
-                                                        (uint32_t)pl.units, p.div_g.magic, p.div_hkv.magic, p);
+      const uint16_t *words = reinterpret_cast<const uint16_t*>(p.ctrl),
+                     *lens = reinterpret_cast<const uint16_t*>(p.at.seq_lens);   // (see FirstArgs)
+      round_kernel<<<grid, kThreads, pl.lds_fused, s>>>(p.at.q, p.page_min, p.page_max, rows <= 1 ? p.k_new : words,
+                                                        rows <= 1 ? p.v_new : lens, shape, (uint32_t)pl.units,
+                                                        p.div_g.magic, p.div_hkv.magic, p);
       return TS_OK;
     }
   }

@@ -26,17 +26,36 @@ struct ScoreLanes {
   static constexpr int PPW = kWave / LPR;   // pages per wave-wide load
   double qp[8], qn[8];
 
-  // Qp / Qn of the unit, computed once per workgroup through LDS: the G query
-  // rows arrive with a single round of 16-byte loads (a per-lane loop over the
-  // heads would pay one memory round trip per head), threads 0..D-1 reduce one
-  // channel each over the heads, and every lane picks up its 8 channels.
-  // Split in two so the caller can issue other loads between the query load
+  // Qp / Qn of the unit.  Split in three so the caller can issue other loads between the query load
   // and its first use (loads return in issue order: what is needed first is
-  // issued first).  stage: LDS scratch of query_stage_bytes(G) bytes.
+  // issued first), and more while the waves wait for each other.  stage: LDS scratch of
+  // query_stage_bytes(G) bytes, headed by the raw rows when share_query returns (to this
+  // wave's lanes at least; to the others behind their next barrier).
+  //
+  // Two forms.  kShort is for launches that score several groups a wave in one round, where this is a link of
+  // the chain they are made of:
+  //   G = 1: a lane's sums are its own chunk of the row, which it has fetched itself: no exchange at all.
+  //   G <= 8: a wave fetches the G values of each of its D / NW channels, a lane per (row, channel),
+  //   sums them across its lanes, and the sums go round through LDS behind one barrier (ready 0.3 us sooner).
+  // Otherwise, and for larger groups, the rows themselves go through LDS, a thread sums a channel over
+  // the heads (a loop of loads per lane would pay one memory round trip per head), and the sums go
+  // round behind a second barrier: fewer loads, and 1-2 % faster where other workgroups' work
+  // covers the wait (352 units of 52 pages 18.3 against 18.55 us).
   static constexpr size_t query_stage_bytes(int G) { return (size_t)G * D * 2 + 2 * D * 8; }
   static constexpr int kQueryLoads = 16 * D / 8 / NT > 0 ? 16 * D / 8 / NT : 1;
+  static constexpr int kChannels = D / NW;            // channels a wave sums over the rows
+  static constexpr int kRows = kWave / kChannels;     // rows of them its lanes cover
+  static constexpr int kSumLoads = 8 / kRows > 0 ? 8 / kRows : 1;
 
-  struct QueryRegs { uint4 w[kQueryLoads]; };
+  template <bool kShort, int kDummy = 0>
+  struct QueryRegs {
+    uint4 w[kQueryLoads];
+  };
+  template <int kDummy>
+  struct QueryRegs<true, kDummy> {
+    uint4 w[kQueryLoads];
+    uint16_t e[kSumLoads];
+  };
 
   // Every thread loads and every thread stages what it loaded (thread i takes
   // chunk i, threads past the last chunk take the last one again; duplicates carry
@@ -44,37 +63,83 @@ struct ScoreLanes {
   // load under a branch makes the compiler wait for ALL outstanding loads
   // wherever it needs one of them, instead of counting, and a load whose only
   // use sits under a branch is moved down into that branch.
-  __device__ __forceinline__ static void issue_query(QueryRegs& r, const uint16_t* q_group, int G) {
-    const int n16 = G * D / 8;
+  template <bool kShort>
+  __device__ __forceinline__ static void issue_query(QueryRegs<kShort>& r, const uint16_t* q_group, int G) {
+    const int n16 = G * D / 8, lane = lane_id();
+    if constexpr (kShort) {
+#pragma unroll
+      for (int k = 0; k < kSumLoads; ++k)
+        r.e[k] = q_group[min(k * kRows + lane / kChannels, G - 1) * D + wave_id() * kChannels + lane % kChannels];
+    }
 #pragma unroll
     for (int k = 0; k < kQueryLoads; ++k)
-      r.w[k] = reinterpret_cast<const uint4*>(q_group)[min((int)threadIdx.x + k * NT, n16 - 1)];
+      r.w[k] = reinterpret_cast<const uint4*>(q_group)[kShort && G == 1 ? lane % LPR : min((int)threadIdx.x + k * NT, n16 - 1)];
   }
 
-  // Two barriers.
-  __device__ __forceinline__ void finish_query(const QueryRegs& r, int G, unsigned char* stage) {
+  // To be called by the whole workgroup, like share_query behind it: here the query is waited for
+  // and summed; what the caller sends out in between is on its way while the waves wait for each other.
+  template <bool kShort>
+  __device__ __forceinline__ void sum_query(const QueryRegs<kShort>& r, int G, unsigned char* stage) {
     uint4* raw = reinterpret_cast<uint4*>(stage);
     double* red = reinterpret_cast<double*>(stage + (size_t)G * D * 2);   // [2][D]
-    const int n16 = G * D / 8;
+    const int n16 = G * D / 8, lane = lane_id();
+    if (kShort && G == 1) {
+      raw[lane % LPR] = r.w[0];
+      float f[8];
+      unpack8e<kHalf>(r.w[0], f);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        qp[i] = static_cast<double>(fmaxf(f[i], 0.f));
+        qn[i] = static_cast<double>(fminf(f[i], 0.f));
+      }
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // (the row, to the other lanes of the wave)
+      return;
+    }
 #pragma unroll
     for (int k = 0; k < kQueryLoads; ++k) {
       raw[min((int)threadIdx.x + k * NT, n16 - 1)] = r.w[k];
     }
     TS_MARK(20);
-    __syncthreads();
-    TS_MARK(21);
-    if (threadIdx.x < D) {
-      const uint16_t* col = reinterpret_cast<const uint16_t*>(stage) + threadIdx.x;
-      double p = 0.0, n = 0.0;
-      for (int g = 0; g < G; ++g) {
-        const float f = elem_to_f32<kHalf>(col[g * D]);
-        p += static_cast<double>(fmaxf(f, 0.f));
-        n += static_cast<double>(fminf(f, 0.f));
+    bool summed = false;
+    if constexpr (kShort) {
+      if (TS_USUALLY(G <= 8)) {
+        static_assert(kRows * kSumLoads == 8 && kChannels <= 32, "a wave sums up to eight rows");
+        double p = 0.0, n = 0.0;
+#pragma unroll
+        for (int k = 0; k < kSumLoads; ++k) {
+          const float f = k * kRows + lane / kChannels < G ? elem_to_f32<kHalf>(r.e[k]) : 0.f;
+          p += static_cast<double>(fmaxf(f, 0.f));
+          n += static_cast<double>(fminf(f, 0.f));
+        }
+        // the lower half of the wave goes on with the positive sums, the upper half with the negative
+        double s = sum_halves_f64(p, n);
+        if (kChannels <= 16) s = sum_row_pairs_f64(s);
+        if (kChannels <= 8) s += dpp_move_f64<kDppRowRor8>(s);
+        if ((lane & 31) < kChannels) red[(lane >> 5) * D + wave_id() * kChannels + lane % kChannels] = s;
+        summed = true;
       }
-      red[threadIdx.x] = p;
-      red[D + threadIdx.x] = n;
     }
+    if (!summed) {
+      __syncthreads();
+      if (threadIdx.x < D) {
+        const uint16_t* col = reinterpret_cast<const uint16_t*>(stage) + threadIdx.x;
+        double p = 0.0, n = 0.0;
+        for (int g = 0; g < G; ++g) {
+          const float f = elem_to_f32<kHalf>(col[g * D]);
+          p += static_cast<double>(fmaxf(f, 0.f));
+          n += static_cast<double>(fminf(f, 0.f));
+        }
+        red[threadIdx.x] = p;
+        red[D + threadIdx.x] = n;
+      }
+    }
+    TS_MARK(21);
+  }
+  template <bool kShort>
+  __device__ __forceinline__ void share_query(int G, const unsigned char* stage) {
+    if (kShort && G == 1) return;
     __syncthreads();
+    const double* red = reinterpret_cast<const double*>(stage + (size_t)G * D * 2);
     const int cg = lane_id() % LPR;
 #pragma unroll
     for (int i = 0; i < 8; ++i) { qp[i] = red[cg * 8 + i]; qn[i] = red[D + cg * 8 + i]; }
@@ -107,12 +172,13 @@ struct MetaTile {
 
   // Plimit >= 1.  Pages at or past Plimit read row Plimit - 1 instead (no branch
   // around the loads); reduce() never reports them.
+  template <int U0 = 0, int U1 = U>
   __device__ __forceinline__ void load(const uint16_t* pmin_u, const uint16_t* pmax_u, int base,
                                        int Plimit, int rstep) {
     constexpr int LPR = ScoreLanes<D, kHalf>::LPR;
     const int lane = lane_id(), cg = lane % LPR, prow = lane / LPR;
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
+    for (int u = U0; u < U1; ++u) {
       const int pg = min(base + u * rstep + prow, Plimit - 1);
       mn[u] = load_stream16(pmin_u + (size_t)pg * D + cg * 8);
       mx[u] = load_stream16(pmax_u + (size_t)pg * D + cg * 8);
@@ -183,8 +249,9 @@ template <int D, bool kHalf = false, int NW = kWaves, int R = 0>
 struct ScanRegs {
   static constexpr int U = R == 0 ? 4 : (R == 1 ? 1 : R - 1);
   static constexpr bool kTail = R > 1;
+  static constexpr int kHead = R < 3 ? U : 2;                     // groups asked for ahead of the query's sums
   static constexpr int PPI = ScoreLanes<D, kHalf, NW>::PPW * U;   // pages one wave covers per iteration
-  typename ScoreLanes<D, kHalf, NW>::QueryRegs q;
+  typename ScoreLanes<D, kHalf, NW>::template QueryRegs<(R > 1)> q;
   MetaTile<D, kHalf, NW, U> tile;
   MetaTile<D, kHalf, NW, 1> tail;
 };
@@ -195,20 +262,38 @@ struct Nothing {
 
 template <int D, bool kHalf, int NW, int R>
 __device__ __forceinline__ void scan_issue_query(ScanRegs<D, kHalf, NW, R>& r, const uint16_t* q_group, int G) {
-  ScoreLanes<D, kHalf, NW>::issue_query(r.q, q_group, G);
+  ScoreLanes<D, kHalf, NW>::template issue_query<(R > 1)>(r.q, q_group, G);
 }
 template <int D, bool kHalf, int NW, int R>
 __device__ __forceinline__ void scan_issue_tile(ScanRegs<D, kHalf, NW, R>& r, const uint16_t* pmin_u,
                                                 const uint16_t* pmax_u, int Pmax, int first_iter,
-                                                int gs = 1, int goff = 0, int iter_stride = NW) {
-  constexpr int PPW = ScoreLanes<D, kHalf>::PPW, PPI = ScanRegs<D, kHalf, NW, R>::PPI;
-  r.tile.load(pmin_u, pmax_u, first_iter * PPI * gs + goff * PPW, Pmax, PPW * gs);
-  if constexpr (ScanRegs<D, kHalf, NW, R>::kTail)
+                                                int gs = 1, int goff = 0) {
+  using Regs = ScanRegs<D, kHalf, NW, R>;
+  constexpr int PPW = ScoreLanes<D, kHalf>::PPW;
+  r.tile.template load<0, Regs::kHead>(pmin_u, pmax_u, first_iter * Regs::PPI * gs + goff * PPW, Pmax, PPW * gs);
+}
+// The rest of the first loads.  A compute unit's memory pipeline takes the loads of eight waves only as
+// earlier ones drain, and a wave whose loads are not taken stands still: with all of them ahead of the
+// query's sums, those were ready 3.7 us after the kernel's entry (16 x 4 units of 1024 pages) where the
+// query had arrived after 0.9.  Two groups go out ahead of the sums, the others between them and the
+// barrier: 18.8 -> 18.4 us, one query head each (8 x 16 units of 512 pages) 17.05 -> 16.95, 4 x 4 of 4097 pages
+// 19.2 -> 18.7, the INT8 cache 17.95 -> 17.55 (with the sums' own shorter way).
+template <int D, bool kHalf, int NW, int R>
+__device__ __forceinline__ void scan_issue_rest(ScanRegs<D, kHalf, NW, R>& r, const uint16_t* pmin_u,
+                                                const uint16_t* pmax_u, int Pmax, int first_iter, int iter_stride,
+                                                int gs, int goff) {
+  using Regs = ScanRegs<D, kHalf, NW, R>;
+  constexpr int PPW = ScoreLanes<D, kHalf>::PPW, PPI = Regs::PPI;
+  if constexpr (!Regs::kTail) return;
+  asm volatile("" ::: "memory");
+  r.tile.template load<Regs::kHead, Regs::U>(pmin_u, pmax_u, first_iter * PPI * gs + goff * PPW, Pmax, PPW * gs);
+  if constexpr (Regs::kTail)
     r.tail.load(pmin_u, pmax_u, (iter_stride * PPI + first_iter * PPW) * gs + goff * PPW, Pmax, 0);
+  __builtin_amdgcn_sched_barrier(0);
 }
 
 // `after_query` runs once the query is in registers and returns Pb.  Must be
-// called by the whole workgroup (the query goes through LDS, q_stage, with
+// called by the whole workgroup (the query may go through LDS, q_stage, with
 // barriers).
 //
 // fill_to_pmax: the sink also wants the -inf of the pages from Pb to Pmax (a
@@ -237,7 +322,9 @@ __device__ __forceinline__ void scan_finish(ScanRegs<D, kHalf, NW, R>& r, const 
   const int rstep = PPW * gs;
   TS_MARK(19);
   ScoreLanes<D, kHalf, NW> ql;
-  ql.finish_query(r.q, G, q_stage);
+  ql.template sum_query<(R > 1)>(r.q, G, q_stage);
+  scan_issue_rest(r, pmin_u, pmax_u, Pmax, first_iter, iter_stride, gs, goff);
+  ql.template share_query<(R > 1)>(G, q_stage);
   TS_MARK(16);
   const int Pb = after_query();
   const int limit = uniform(fill_to_pmax ? Pmax : Pb);

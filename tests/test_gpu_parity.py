@@ -1342,6 +1342,26 @@ def test_scoring_in_one_round_of_groups(oracle, built, kv, groups, d, S, opens):
     compare_units(oracle, f, units, scale, q_idx=1, what=f"one round {groups}/{d}")
 
 
+@pytest.mark.parametrize("G", [1, 2, 3, 4, 5, 8, 9, 16])
+@pytest.mark.parametrize("d,kv", [(64, "bf16"), (128, "bf16"), (128, "fp16")])
+@pytest.mark.parametrize("groups", [1, 20, 36])
+def test_query_sums_in_one_round_of_groups(oracle, built, G, d, kv, groups):
+    """The builds that score in one round sum the query heads of a group by themselves (one head), a
+    wave per block of channels (up to eight, one or several loads a lane) or a thread per channel;
+    each with one, three and five groups of pages a wave."""
+    print(f"[case] query sums G={G} d={d} {kv} groups={groups}", flush=True)
+    g, S = 3, 16
+    pages = groups * g * (512 // d)
+    spec = wl.WorkloadSpec("sums", 2, 2 * G, 2, d, S, pages * S - 5, 12, headroom=5, kv=kv)
+    w = wl.make_workload(spec, DEV, seed=1300 + G, n_q=1, n_new=1, poison=0.0)
+    f = Session(w, poison_meta=False, cluster_size=g)
+    ts.build_page_meta(f.layout)
+    scale = 1.0 / math.sqrt(d)
+    ts.append_and_decode(f.layout, w.k_new[0], w.v_new[0], w.q[0], w.topk, w.K_max, scale, f.out, f.ws,
+                         scores_out=f.scores, sel_out=f.sel, sel_count_out=f.sel_count)
+    compare_units(oracle, f, [(b, h) for b in range(2) for h in range(2)], scale, what=f"sums G={G}/{d}/{groups}")
+
+
 @pytest.mark.parametrize("L,topk,S", [(900, 300, 16), (230, 128, 8), (70, 200, 32), (15, 128, 16), (14, 128, 8)])
 def test_budget_beyond_the_table(oracle, built, L, topk, S):
     """More pages may be kept than the table is wide: the cluster's members divide what there is."""
