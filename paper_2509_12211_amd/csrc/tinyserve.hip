@@ -29,7 +29,8 @@ constexpr int kDenseTargetWorkgroups = 1024;
 // Up to this many bytes of metadata and selected pages the units of a large batch count as
 // small (small_units_decode_kernel).  Beyond it a unit is bound by its data, and a whole
 // compute unit's waves on one unit get through them sooner: at 2.4 MB the two builds are
-// equal, at 4.7 MB and 15 MB the small one is 6 % and 18 % behind.
+// equal, at 4.7 MB and 15 MB the small one is 6 % and 18 % behind.  (The INT8 cache: at 1.8 MB 124 -> 117 us,
+// 320 units, at 1.0 MB 86 -> 78; 512 units of 0.07 MB 22.2 -> 15.7, 464 of 0.3 MB 41.1 -> 35.3.)
 constexpr size_t kSmallUnitBytes = 2 << 20;
 
 // A launch over up to 255 units goes by shares in proportion to the work where the lengths and
@@ -78,11 +79,12 @@ static Plan make_plan(const ts_layout* L, int max_topk, int target_workgroups = 
   if (g < 1) g = 1;
   pl.chunk = chunk_of(max_topk, g, L->page_size);
   pl.g = (max_topk + pl.chunk - 1) / pl.chunk;
-  const size_t unit_bytes = ((size_t)Pmax + (size_t)max_topk * L->page_size) * 4 * L->head_dim;
   // The INT8 cache keeps the same partition of a unit over waves and workgroups everywhere: its
   // operands carry a bias that cancels out of the output, so that with thousands of tokens of
   // like weight the order of the sums shows in the fourth digit.
   const bool int8 = L->kv_format == TS_KV_INT8;
+  const size_t unit_bytes = (size_t)Pmax * 4 * L->head_dim +
+                            (size_t)max_topk * L->page_size * (int8 ? 2 * L->head_dim + 8 : 4 * L->head_dim);
   // Full-cache path, two rounds of units and more: one workgroup or two each, by the lengths
   pl.rounds = target_workgroups == kDenseTargetWorkgroups && !int8 && pl.units >= 2 * kTargetWorkgroups && pl.g == 2;
   pl.per_head = kTargetWorkgroups / L->num_kv_heads;
@@ -121,11 +123,11 @@ static Plan make_plan(const ts_layout* L, int max_topk, int target_workgroups = 
   pl.total = off;
   // fused kernel LDS: select scratch (keys, bins), the query, the unit's block-table row,
   // this workgroup's selected pages; the wave-merge area aliases the keys
-  pl.small_units = !int8 && target_workgroups == kTargetWorkgroups && pl.g == 1 &&
+  pl.small_units = target_workgroups == kTargetWorkgroups && pl.g == 1 &&
                    pl.units > kTargetWorkgroups && unit_bytes <= kSmallUnitBytes;
   const int waves = pl.small_units ? kSmallWaves : kWaves;
   const size_t lds_sel = select_lds_bytes(Pmax, waves);
-  const size_t lds_att = (size_t)waves * G * (L->head_dim + 2) * 4;
+  const size_t lds_att = (size_t)(int8 ? kWaves : waves) * G * (L->head_dim + 2) * 4;   // (see kParts)
   // ... and, in an area of its own, the query staging: a wave that is done
   // scoring starts the selection (which clears the bins) while another may not
   // have picked up its query sums yet, so the two must not share memory

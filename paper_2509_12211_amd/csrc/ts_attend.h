@@ -733,6 +733,12 @@ struct NoEntries {
   static constexpr bool kAny = false;
 };
 
+// Parts that a workgroup of NW waves cuts its list into.  The INT8 cache keeps the parts of eight waves
+// in smaller workgroups too: how its weights round goes with the running maximum they are worked out
+// against, that is with the pages a part has seen, so that another partition of the list shows in the result.
+template <int NW, bool kInt8>
+constexpr int kParts = kInt8 && NW < kWaves ? kWaves : NW;
+
 struct SplitPlace { int n_split, split; size_t part_row; };
 // How the partials of a unit's splits are handed on (attend_split): plainly, for the caller to count
 // arrivals, or as tagged words, which the last split merges, or the splits by slices of the output.
@@ -741,9 +747,10 @@ enum { kPlain, kTagged, kTaggedDealt };
 // The workgroup attends `count` selected pages of unit (b, h): entry i of its
 // list is page sel_at(i), stored in physical page phys_at(page); a caller that has looked the
 // entries of the waves' first batches up already hands them over (ready).  The list is
-// cut into fragments (PageGeom<S>); wave w takes fragments w, w + NW, ...
+// cut into fragments (PageGeom<S>); wave w takes fragments w, w + NW, ... (the INT8 cache: kParts parts
+// of the list take them so, a wave several of them in turn)
 // The waves' states are merged through LDS
-// (lds: NW * G * (D + 2) floats).  With n_split == 1 the normalised result
+// (lds: kParts * G * (D + 2) floats).  With n_split == 1 the normalised result
 // goes to `out`; otherwise the unnormalised partial (o[D], m, l per head) is
 // handed to the combining workgroup through agent-scope stores.
 // place() says which part `split` of n_split on the unit the workgroup is; the unit's partials are
@@ -777,6 +784,8 @@ __device__ __forceinline__ bool attend_split(const AttendParams& p, int b, int h
                                              Ready ready = Ready{}) {
   using Geo = PageGeom<S>;
   constexpr int NT = NW * kWave;
+  constexpr int NP = kParts<NW, kInt8>;   // parts of the list, NP / NW of them a wave's, one after the other
+  static_assert(NP == NW || !kPatch, "one wave has the new token's page");
   constexpr int F = Geo::F, NS = Geo::NS, NH = Geo::NH;
   static_assert(!(kHalf && kInt8), "the INT8 cache goes with bf16 queries");
   using Frag = std::conditional_t<kInt8, PageFrag8<D, F>, PageFrag<D, F>>;
@@ -814,6 +823,9 @@ __device__ __forceinline__ bool attend_split(const AttendParams& p, int b, int h
   }
   const bool splice = kPatch && splice_item >= 0 && wave == splice_item % NW;
   if (TS_RARELY(splice)) patch.load(nt);
+  constexpr int RS = D + 2;
+  int part_id = wave;
+  do {
   WaveAcc<D> acc;
   acc.init();
   TS_MARK(27);
@@ -821,7 +833,7 @@ __device__ __forceinline__ bool attend_split(const AttendParams& p, int b, int h
   int my_j[NS], my_phys[NS];
   // lane x holds the page ids of this wave's x-th fragment of the batch
   auto look_up = [&](int batch) {
-    const int my_item = batch + lane * NW;
+    const int my_item = batch + lane * NP;
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
       my_j[s] = -1;
@@ -841,9 +853,9 @@ __device__ __forceinline__ bool attend_split(const AttendParams& p, int b, int h
       my_phys[s] = on ? ready.phys[s] : -1;
     }
   }
-  for (int batch = wave; batch < n_items; batch += kWave * NW) {
+  for (int batch = part_id; batch < n_items; batch += kWave * NP) {
     if (!Ready::kAny || batch != wave) look_up(batch);
-    const int n = min(kWave, (n_items - batch + NW - 1) / NW);
+    const int n = min(kWave, (n_items - batch + NP - 1) / NP);
     TS_MARK(28);
     // A ring of NBUF fragment buffers: up to NBUF fragments of this wave are in
     // flight (2 KiB - 8 KiB each) before the first is consumed.
@@ -856,7 +868,7 @@ __device__ __forceinline__ bool attend_split(const AttendParams& p, int b, int h
     // single cache line of it) and has no valid token: no branch around the loads.
     auto issue = [&](Frag& fr, int& it, int x) -> uint32_t {
       const int xc = min(x, n - 1);
-      it = batch + xc * NW;
+      it = batch + xc * NP;
       if constexpr (S >= 16) {
         const int j = __builtin_amdgcn_readlane(my_j[0], xc);
         const int phys = __builtin_amdgcn_readlane(my_phys[0], xc);
@@ -985,15 +997,16 @@ __device__ __forceinline__ bool attend_split(const AttendParams& p, int b, int h
   }
   // merge the wave states
   const float l = rows_sum_f32(acc.l);
-  constexpr int RS = D + 2;
   if (head < G) {
-    float* row = lds + ((size_t)wave * G + head) * RS;
+    float* row = lds + ((size_t)part_id * G + head) * RS;
 #pragma unroll
     for (int cb = 0; cb < D / 16; ++cb)
 #pragma unroll
       for (int v = 0; v < 4; ++v) row[16 * cb + 4 * kb + v] = acc.o[cb][v];
     if (kb == 0) { row[D] = acc.m; row[D + 1] = l; }
   }
+  part_id += NW;
+  } while (NP > NW && part_id < NP);
   __syncthreads();
   TS_MARK(24);
   const SplitPlace at = place();
@@ -1023,17 +1036,17 @@ __device__ __forceinline__ bool attend_split(const AttendParams& p, int b, int h
     uint64_t* part64 = unit64 + (size_t)split * G * RS;
     // the merged state of the waves for head g, channel c
     auto merge_waves = [&](int g, int c, float& M, float& Lsum, float& O) {
-      float mw[NW];
+      float mw[NP];
       M = -INFINITY;
 #pragma unroll
-      for (int w = 0; w < NW; ++w) {
+      for (int w = 0; w < NP; ++w) {
         mw[w] = lds[((size_t)w * G + g) * RS + D];
         M = fmaxf(M, mw[w]);
       }
       Lsum = 0.f;
       O = 0.f;
 #pragma unroll
-      for (int w = 0; w < NW; ++w) {
+      for (int w = 0; w < NP; ++w) {
         const float* row = lds + ((size_t)w * G + g) * RS;
         const float wgt = __builtin_amdgcn_exp2f(mw[w] - M);
         Lsum += row[D + 1] * wgt;
@@ -1075,15 +1088,15 @@ __device__ __forceinline__ bool attend_split(const AttendParams& p, int b, int h
     // head's running max and sum
     for (int idx = threadIdx.x; idx < G * D; idx += NT) {
       const int g = idx / D, c = idx % D;
-      float mw[NW], M = -INFINITY;
+      float mw[NP], M = -INFINITY;
 #pragma unroll
-      for (int w = 0; w < NW; ++w) {
+      for (int w = 0; w < NP; ++w) {
         mw[w] = lds[((size_t)w * G + g) * RS + D];
         M = fmaxf(M, mw[w]);
       }
       float Lsum = 0.f, O = 0.f;
 #pragma unroll
-      for (int w = 0; w < NW; ++w) {
+      for (int w = 0; w < NP; ++w) {
         const float* row = lds + ((size_t)w * G + g) * RS;
         const float wgt = __builtin_amdgcn_exp2f(mw[w] - M);
         Lsum += row[D + 1] * wgt;

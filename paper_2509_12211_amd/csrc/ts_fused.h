@@ -536,7 +536,7 @@ __device__ __forceinline__ void decode_units(const FusedParams& p, const FirstAr
   // the last unit leave before any barrier, see below, and are not counted in)
   const bool padding = (kCluster || kDecide) && !kLoop && where.cluster >= (kFirst ? (int)f.units : p.units);
   const SelectLds sl = carve_select<NW>(smem, Pmax);
-  const uint32_t sel_bytes = (uint32_t)select_lds_bytes(Pmax, NW), att_bytes = (uint32_t)(NW * G * (D + 2) * 4);
+  const uint32_t sel_bytes = (uint32_t)select_lds_bytes(Pmax, NW), att_bytes = (uint32_t)(kParts<NW, kInt8> * G * (D + 2) * 4);
   const uint32_t q_off = sel_bytes > att_bytes ? sel_bytes : att_bytes;
   constexpr bool exchange = kCluster;
   unsigned char* q_stage = smem + q_off;
@@ -1111,6 +1111,16 @@ small_units_decode_kernel(const uint16_t* q, const uint16_t* page_min, const uin
       with_args(p, q, page_min, page_max, block_table, seq_lens, topk_per_seq, shape, magic_hkv));
 }
 
+// The same for the INT8 cache, whose list stays cut for eight waves: a wave takes two of its parts in turn.
+template <int D, int S>
+__global__ __launch_bounds__(kSmallWaves * kWave) __attribute__((amdgpu_waves_per_eu(2, 2))) void
+small_units_i8_decode_kernel(const uint16_t* q, const uint16_t* page_min, const uint16_t* page_max,
+                             const int32_t* block_table, const int32_t* seq_lens, const int32_t* topk_per_seq,
+                             uint32_t shape, uint32_t magic_hkv, FusedParams p) {
+  decode_units<kSmallWaves, D, S, false, false, true, false, false, false, 0, true>(
+      with_args(p, q, page_min, page_max, block_table, seq_lens, topk_per_seq, shape, magic_hkv));
+}
+
 // ---------------------------------------------------------------------------
 // Host side
 // ---------------------------------------------------------------------------
@@ -1209,15 +1219,16 @@ static int launch_single(const ts_layout* layout, FusedParams& p, const Plan& pl
     if ((st = ts_append_token_meta(layout, k_new, v_new, 1, stream)) != TS_OK) return st;
     p.k_new = p.v_new = nullptr;
   }
-  if constexpr (!kInt8) {
-    if (pl.small_units) {
-      auto small_kernel = small_units_decode_kernel<D, S, kHalf>;
-      if ((st = allow_lds(small_kernel, pl.lds_fused)) != TS_OK) return st;
-      small_kernel<<<grid, kSmallWaves * kWave, pl.lds_fused, s>>>(
-          p.at.q, p.page_min, p.page_max, p.at.block_table, p.at.seq_lens, p.topk_per_seq,
-          (uint32_t)p.at.Pmax | (uint32_t)p.at.G << 16, p.div_hkv.magic, p);
-      return TS_OK;
-    }
+  if (pl.small_units) {
+    auto small_kernel = [] {
+      if constexpr (kInt8) return small_units_i8_decode_kernel<D, S>;
+      else return small_units_decode_kernel<D, S, kHalf>;
+    }();
+    if ((st = allow_lds(small_kernel, pl.lds_fused)) != TS_OK) return st;
+    small_kernel<<<grid, kSmallWaves * kWave, pl.lds_fused, s>>>(
+        p.at.q, p.page_min, p.page_max, p.at.block_table, p.at.seq_lens, p.topk_per_seq,
+        (uint32_t)p.at.Pmax | (uint32_t)p.at.G << 16, p.div_hkv.magic, p);
+    return TS_OK;
   }
   if ((st = allow_lds(many_kernel, pl.lds_fused)) != TS_OK) return st;
   many_kernel<<<grid, kThreads, pl.lds_fused, s>>>(p);

@@ -265,7 +265,7 @@ MANY8 = {
 
 @pytest.mark.parametrize("name", list(MANY8))
 def test_int8_many_units(oracle, name):
-    """More units than compute units: one workgroup of eight waves each, whatever their size."""
+    """More units than compute units: one workgroup each."""
     spec = MANY8[name]
     print(f"[case] int8 many units {name}", flush=True)
     w = wl.make_workload(spec, DEV, seed=404, n_q=2, n_new=1)
@@ -283,6 +283,30 @@ def test_int8_many_units(oracle, name):
                          sess.ws, topk_per_seq=w.topk_per_seq, scores_out=sess.scores,
                          sel_out=sess.sel, sel_count_out=sess.sel_count)
     compare_units(oracle, sess, units, scale, q_idx=1, what=f"{name} launch 1")
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("S,L,topk", [(4, 2500, 600), (8, 700, 37), (16, 520, 33), (32, 300, 3), (64, 2000, 9)])
+def test_int8_small_units_equal_their_eight_wave_form(d, S, L, topk):
+    """Many small units run in workgroups of four waves that keep the partition of eight: the same
+    sequences in a batch that fits the device at once, one workgroup of eight waves each, give the
+    same bits (lists of fewer parts than waves, of one and of several batches of a wave)."""
+    print(f"[case] int8 small units d={d} S={S} L={L} topk={topk}", flush=True)
+    spec = spec8("su", 40, 16, 8, d, S, L, topk, L_min=1)
+    w = wl.make_workload(spec, DEV, seed=515, n_q=1, n_new=1)
+    sess = Session8(w)
+    ts.build_page_meta(sess.layout)
+    scale = 1.0 / math.sqrt(d)
+    sess.fused(scale)
+    few = 31                                    # 248 units
+    lay = ts.make_layout(few, spec.Hq, spec.Hkv, d, S, w.P_max, w.k_pool, w.v_pool, w.block_table, sess.seq_lens,
+                         sess.page_min, sess.page_max, k_scale=w.k_scale, v_scale=w.v_scale, cluster_size=1)
+    out = torch.full_like(sess.out[:few], float("nan"))
+    ws = ts.new_workspace(lay, w.K_max, DEV)
+    ts.query_aware_decode(lay, w.q[0, :few], w.topk, w.K_max, scale, out, ws)
+    torch.cuda.synchronize()
+    assert ts.workspace_status(ws) == 0 and ts.workspace_status(sess.ws) == 0
+    assert torch.equal(out, sess.out[:few])
 
 
 @pytest.mark.parametrize("groups", [1, 9, 25, 40])
