@@ -174,6 +174,25 @@ __device__ __forceinline__ double group_sum4_f64(const double (&v)[4], int lane_
   return k;
 }
 
+// Eight: in lane u of the group's first eight the sum of v[u].
+template <int N>
+__device__ __forceinline__ double group_sum8_f64(const double (&v)[8], int lane_in_group) {
+  static_assert(N == 8 || N == 16, "group of 8 or 16 lanes");
+  double s[8];
+#pragma unroll
+  for (int u = 0; u < 8; ++u) {
+    s[u] = v[u];
+    if (N == 16) s[u] += dpp_move_f64<kDppMirror>(s[u]);
+  }
+  const bool upper = (lane_in_group & 4) != 0, second = (lane_in_group & 2) != 0, odd = (lane_in_group & 1) != 0;
+  double k[4], m[2];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) k[i] = (upper ? s[4 + i] : s[i]) + dpp_move_f64<kDppHalfMirror>(upper ? s[i] : s[4 + i]);
+#pragma unroll
+  for (int i = 0; i < 2; ++i) m[i] = (second ? k[2 + i] : k[i]) + dpp_move_f64<kDppXor2>(second ? k[i] : k[2 + i]);
+  return (odd ? m[1] : m[0]) + dpp_move_f64<kDppXor1>(odd ? m[0] : m[1]);
+}
+
 // One value per lane, summed over the group by the same additions: delivered to every lane.
 template <int N>
 __device__ __forceinline__ double group_sum1_f64(double k) {

@@ -1031,7 +1031,9 @@ query_aware_decode_kernel(FusedParams p) {
 // instructions for the four groups of a tile and as many again for the next tile's loads, whose
 // pages mostly do not exist.  R = 1 (8 waves, a group each): 4 units of 12 workgroups with 188
 // pages 11.5 -> 10.3 us, 1 of 8 with 257 10.6 -> 9.8; R = 3: 128 of 2 with 257 16.8 -> 16.1, 4 of 32
-// with 4098 17.9 -> 17.0; R = 5: 16 to 128 units of 513-4097 pages -0.1 us, without an append 18.5 -> 17.9.
+// with 4098 17.9 -> 17.0; R = 5: 16 to 128 units of 513-4097 pages -0.1 us, without an append 18.5 -> 17.9;
+// R = 9, 128 channels: 64 units of 1002 pages 27.5 -> 26.8, 32 of 1565 21.3 -> 20.5, the INT8 cache, 22 of 2910 28.0
+// -> 25.9; 64 channels: 64 of 1565 21.3 -> 20.75, 128 of 1002 24.7 -> 24.4.
 // The first loads' arguments come ahead of the others (FirstArgs).
 template <int D, int S, bool kApp, bool kInt8, bool kHalf, int R>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void
@@ -1272,8 +1274,7 @@ static bool launch_shares(const ts_layout* layout, FusedParams& p, const Plan& p
 }
 
 // The build for clusters whose waves score their pages in one round, nullptr where that takes more
-// than five groups each: from 40 groups a member on the rounds of four follow each other without a
-// gap, and a longer tile would not fit the registers.
+// than nine groups each: two rounds of four and a last group are the longest tile built.
 using OneRound = void (*)(const uint16_t*, const uint16_t*, const uint16_t*, const uint16_t*, const uint16_t*,
                           uint32_t, uint32_t, uint32_t, uint32_t, FusedParams);
 static int round_groups(int D, int Pmax, int g) {   // groups of pages a wave has at the most
@@ -1286,6 +1287,7 @@ static OneRound one_round_kernel(int rows) {
   if (rows <= 1) return one_round_decode_kernel<D, S, kApp, kInt8, kHalf, 1>;
   if (rows <= 3) return one_round_decode_kernel<D, S, kApp, kInt8, kHalf, 3>;
   if (rows <= 5) return one_round_decode_kernel<D, S, kApp, kInt8, kHalf, 5>;
+  if (rows <= 9) return one_round_decode_kernel<D, S, kApp, kInt8, kHalf, 9>;
   return nullptr;
 }
 

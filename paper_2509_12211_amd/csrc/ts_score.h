@@ -195,7 +195,7 @@ struct MetaTile {
   template <typename Patch>
   __device__ __forceinline__ Score scores(const ScoreLanes<D, kHalf, NW>& ql, int base, int rstep, Patch patch) {
     constexpr int LPR = ScoreLanes<D, kHalf>::LPR;
-    static_assert(U == 4 || U == 2 || U == 1, "rows folded in one butterfly");
+    static_assert(U == 8 || U == 4 || U == 2 || U == 1, "rows folded in one butterfly");
     const int lane = lane_id(), cg = lane % LPR, prow = lane / LPR;
     double part[U];
 #pragma unroll
@@ -207,7 +207,8 @@ struct MetaTile {
     // those reports it
     constexpr int LPS = 8 / U;
     Score r;
-    if constexpr (U == 4) r.s = group_sum4_f64<LPR>(part, cg);
+    if constexpr (U == 8) r.s = group_sum8_f64<LPR>(part, cg);
+    else if constexpr (U == 4) r.s = group_sum4_f64<LPR>(part, cg);
     else if constexpr (U == 2) r.s = group_sum2_f64<LPR>(part, cg);
     else r.s = group_sum1_f64<LPR>(part[0]);
     r.page = base + cg / LPS * rstep + prow;

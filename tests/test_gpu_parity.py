@@ -1342,6 +1342,14 @@ def test_scoring_in_one_round_of_groups(oracle, built, kv, groups, d, S, opens):
     compare_units(oracle, f, units, scale, q_idx=1, what=f"one round {groups}/{d}")
 
 
+@pytest.mark.parametrize("groups", [42, 63, 65, 72, 73])
+@pytest.mark.parametrize("d,S,kv", [(64, 16, "bf16"), (128, 8, "fp16")])
+def test_scoring_in_one_round_of_nine_groups(oracle, built, groups, d, S, kv):
+    """The build whose waves score up to nine groups of pages, eight of them in one tile, up to the most
+    groups a member may have for it and one more; the table is exactly as wide as that."""
+    test_scoring_in_one_round_of_groups(oracle, built, kv, groups, d, S, groups % 2 == 0)
+
+
 @pytest.mark.parametrize("G", [1, 2, 3, 4, 5, 8, 9, 16])
 @pytest.mark.parametrize("d,kv", [(64, "bf16"), (128, "bf16"), (128, "fp16")])
 @pytest.mark.parametrize("groups", [1, 20, 36])
