@@ -1026,8 +1026,8 @@ __device__ __forceinline__ bool attend_split(const AttendParams& p, int b, int h
     // one that is last to finish has polls of its own ahead of it), four 18.0 -> 18.2, five to eight -1 to +2 %.
     // (Not in the builds that score in a loop, which have no registers to spare: clusters that take units in
     // turn went to scratch memory.)
-    // A wave hands on and merges the same slices, a round of them shifted against the one before, so that no
-    // wave works a slice out twice and hardly ever has two to merge.
+    // With more slices than members a wave hands on and merges the same ones, a round of them shifted against
+    // the one before, so that no wave works a slice out twice and hardly ever has two to merge.
     static_assert(D % kWave == 0 && (NW & (NW - 1)) == 0, "a slice belongs to one head");
     constexpr int SL = D / kWave;
     const int others = n_split - 1, n_slices = G * SL, mine = others - split;   // my slices: s = mine modulo n_split
@@ -1074,15 +1074,50 @@ __device__ __forceinline__ bool attend_split(const AttendParams& p, int b, int h
       }
     });
     TS_MARK(29);
-    for_slices([&](int s, int at_member) {
-      if (at_member != mine) return;
-      const int g = s / SL, c = (s % SL) * kWave + lane;
-      float M, Lsum, O;
-      merge_waves(g, c, M, Lsum, O);
-      ok = merge_tagged<D, 16>(unit64, G, g, c, split, others, tag, spin_limit, spins, M, Lsum, O) && ok;
-      store_out(p, ((size_t)b * p.Hq + (size_t)h * G + g) * D + c, Lsum > 0.f ? O / Lsum : 0.f);
-      if (TS_RARELY(c == 0 && p.lse)) p.lse[(size_t)b * p.Hq + (size_t)h * G + g] = log_sum_exp(M, Lsum);
-    });
+    if (n_slices <= n_split) {   // a slice each at the most
+      // The waves divide the partials among them, a batch each, and the first puts the eight states together:
+      // batches of sixteen by one wave are round trips behind each other.  Clusters of 64, the two above:
+      // 26.7 -> 22.2 and 23.5 -> 18.5 us, 3 units of 64 22.4 -> 17.7, 7 of 36 with one head 14.4 -> 12.75; of twelve 10.1 -> 10.0.
+      if (uniform(mine) < n_slices) {
+        const int per = (others + NW - 1) / NW, start = wave * per, n = max(0, min(per, others - start));
+        const int g = mine / SL, c = (mine % SL) * kWave + lane;
+        float M = -INFINITY, Lsum = 0.f, O = 0.f;
+        if (wave == 0) merge_waves(g, c, M, Lsum, O);
+        ok = merge_tagged<D, 8>(unit64 + (size_t)start * G * RS, G, g, c, split - start, n, tag, spin_limit, spins, M, Lsum, O);
+        __syncthreads();   // (the waves' rows have been read)
+        float* row = lds + wave * (kWave + 2);
+        row[lane] = O;
+        if (lane == 0) { row[kWave] = M; row[kWave + 1] = Lsum; }
+        __syncthreads();
+        if (wave == 0) {
+          float Mn = M;
+#pragma unroll
+          for (int w = 1; w < NW; ++w) Mn = fmaxf(Mn, lds[w * (kWave + 2) + kWave]);
+          const float sc = __builtin_amdgcn_exp2f(M - Mn);
+          Lsum *= sc;
+          O *= sc;
+#pragma unroll
+          for (int w = 1; w < NW; ++w) {
+            const float* r = lds + w * (kWave + 2);
+            const float wgt = __builtin_amdgcn_exp2f(r[kWave] - Mn);
+            Lsum += r[kWave + 1] * wgt;
+            O += r[lane] * wgt;
+          }
+          store_out(p, ((size_t)b * p.Hq + (size_t)h * G + g) * D + c, Lsum > 0.f ? O / Lsum : 0.f);
+          if (TS_RARELY(c == 0 && p.lse)) p.lse[(size_t)b * p.Hq + (size_t)h * G + g] = log_sum_exp(Mn, Lsum);
+        }
+      }
+    } else {
+      for_slices([&](int s, int at_member) {
+        if (at_member != mine) return;
+        const int g = s / SL, c = (s % SL) * kWave + lane;
+        float M, Lsum, O;
+        merge_waves(g, c, M, Lsum, O);
+        ok = merge_tagged<D, 16>(unit64, G, g, c, split, others, tag, spin_limit, spins, M, Lsum, O) && ok;
+        store_out(p, ((size_t)b * p.Hq + (size_t)h * G + g) * D + c, Lsum > 0.f ? O / Lsum : 0.f);
+        if (TS_RARELY(c == 0 && p.lse)) p.lse[(size_t)b * p.Hq + (size_t)h * G + g] = log_sum_exp(M, Lsum);
+      });
+    }
   } else {
     // one thread per (head, channel); the thread of channel 0 also hands on the
     // head's running max and sum
