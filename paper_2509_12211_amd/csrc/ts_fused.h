@@ -214,7 +214,7 @@ __global__ __launch_bounds__(kThreads) void sparse_attention_kernel(
   if (threadIdx.x == 0) s_last = atomic_add_agent(&unit_done[u * cstride], 1) == p.n_split - 1;
   __syncthreads();
   if (!uniform(s_last)) return;
-  combine_splits<D>(p, b, h, (size_t)u * p.n_split, p.n_split);
+  combine_splits<D>(p, b, h, (size_t)u * p.n_split, p.n_split, reinterpret_cast<float*>(smem));
   if (threadIdx.x == 0) atomic_store_agent(&unit_done[u * cstride], 0);
 }
 
@@ -369,7 +369,7 @@ __global__ __launch_bounds__(kThreads) void dense_shares_kernel(AttendParams p, 
   if (threadIdx.x == 0) s_last = atomic_add_agent(&unit_done[u * cstride], 1) == g - 1;
   __syncthreads();
   if (!uniform(s_last)) return;
-  combine_splits<D>(p, b, h, (size_t)share.part_row, g);
+  combine_splits<D>(p, b, h, (size_t)share.part_row, g, reinterpret_cast<float*>(smem));
   if (threadIdx.x == 0) atomic_store_agent(&unit_done[u * cstride], 0);
 }
 
@@ -425,7 +425,7 @@ __global__ __launch_bounds__(kThreads) void dense_rounds_kernel(AttendParams p, 
   if (threadIdx.x == 0) s_last = atomic_add_agent(&unit_done[u * cstride], 1) == 1;
   __syncthreads();
   if (!uniform(s_last)) return;
-  combine_splits<D>(p, b, h, (size_t)u * 2, 2);
+  combine_splits<D>(p, b, h, (size_t)u * 2, 2, reinterpret_cast<float*>(smem));
   if (threadIdx.x == 0) atomic_store_agent(&unit_done[u * cstride], 0);
 }
 
@@ -984,7 +984,7 @@ __device__ __forceinline__ void decode_units(const FusedParams& p, const FirstAr
       if (threadIdx.x == 0) *last = atomic_add_agent(done, 1) == words[0] - 1;
       __syncthreads();
       if (uniform(*last)) {
-        combine_splits<D, true>(at, b, h, (size_t)uniform(words[2]), uniform(words[0]));
+        combine_splits<D, true>(at, b, h, (size_t)uniform(words[2]), uniform(words[0]), reinterpret_cast<float*>(smem) + 64);
         if (threadIdx.x == 0) atomic_store_agent(done, 0);
       }
     }

@@ -879,6 +879,40 @@ def test_dense_shares(oracle, built, shape, fmt):
         assert not sess.out[torch.from_numpy(~some).to(DEV)].any()
 
 
+@pytest.mark.parametrize("G", [1, 2, 3, 8, 16])
+@pytest.mark.parametrize("d,fmt", [(64, "bf16"), (128, "fp16")])
+@pytest.mark.parametrize("pages", [31, 33, 36, 70, 135, 300])
+def test_many_partials_of_a_unit(oracle, built, G, d, fmt, pages):
+    """Two ragged sequences of one KV head, cut into up to 64 parts each: eight partials and nine, one batch of
+    sixteen and several, merged by a wave per slice of the output or by several that divide them; every token
+    and a selection of all pages by the staged call, against the same reference."""
+    print(f"[case] many partials G={G} d={d} {fmt} pages={pages}", flush=True)
+    S, B = 16, 2
+    spec = wl.WorkloadSpec("parts", B, G, 1, d, S, pages * S - 3, pages, L_min=pages * S // 2, headroom=3, kv=fmt)
+    w = wl.make_workload(spec, DEV, seed=1400 + pages, n_q=1)
+    sess = Session(w)
+    scale = 1.0 / math.sqrt(d)
+    K, V = (wl.bits(x) for x in wl.logical_kv(w))
+    lens = sess.seq_lens.cpu().numpy()
+    with oracle.element_format(fmt):
+        ref, ref_lse = oracle.dense_decode_attention(wl.bits(w.q[0]), K, V, lens, scale, return_lse=True)
+    lse = torch.full((B, G), float("nan"), dtype=torch.float32, device=DEV)
+    sel = torch.arange(w.K_max, dtype=torch.int32, device=DEV).repeat(B, 1, 1).contiguous()
+    counts = ((sess.seq_lens + S - 1) // S).to(torch.int32).contiguous()
+    for what in ("dense", "staged"):
+        sess.out.fill_(float("nan"))
+        lse.fill_(float("nan"))
+        if what == "dense":
+            ts.dense_decode_attention(sess.layout, w.q[0], scale, sess.out, ts.new_dense_workspace(sess.layout, DEV), lse_out=lse)
+        else:
+            ts.sparse_decode_attention(sess.layout, w.q[0], sel, counts, w.K_max, scale, sess.out, sess.ws, lse_out=lse)
+        torch.cuda.synchronize()
+        err = np.abs(sess.out.cpu().numpy().astype(np.float64) - ref).max()
+        assert err <= 2e-3, f"{what} attention off by {err}"
+        err = np.abs(lse.cpu().numpy().astype(np.float64) - ref_lse).max()
+        assert err <= LSE_ATOL, f"{what} log-denominator off by {err}"
+
+
 @pytest.mark.parametrize("shape", [(64, 8, 64, 16, 200, 1), (64, 8, 128, 8, 90, 0), (65, 8, 64, 32, 300, 0),
                                    (65, 8, 128, 16, 150, 1), (79, 9, 64, 4, 60, 0)])
 @pytest.mark.parametrize("lengths", ["drawn", "few_long", "empty_and_one"])
