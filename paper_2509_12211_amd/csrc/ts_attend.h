@@ -1189,7 +1189,8 @@ __device__ __forceinline__ bool attend_split(const AttendParams& p, int b, int h
 // are round trips behind each other, and the first of them puts the states together.  Against rounds of eight, every
 // token of 3 x 1 units of 3-23 K, one head, 13.5 -> 9.7 us, 2 x 4 of 30 K, eight heads, 128 channels 30.7 -> 28.7, 16 of 16 K,
 // INT8 33.7 -> 29.9; 800 of 3750 kept pages, staged 31.0 -> 25.8.  Up to eight the round of eight is the shorter way
-// (8 x 16 units in two parts 47.2 against 47.9).
+// (8 x 16 units in two parts 47.2 against 47.9), and the one that is laid out first: with the batches behind it 3 x 1 units of
+// 20 K, which take them, go from 9.18 to 9.02 us, 8 x 16 of 8 K from 45.76 to 45.79 (no difference).
 template <int D, bool kWords = false>
 __device__ __forceinline__ void combine_splits(const AttendParams& p, int b, int h, size_t part_row, int n_split,
                                                float* lds) {
@@ -1231,7 +1232,7 @@ __device__ __forceinline__ void combine_splits(const AttendParams& p, int b, int
       M = Mn;
     }
   };
-  if (n_split <= 8) {   // one round: a thread fetches all it needs of the partials by itself
+  if (!TS_RARELY(n_split > 8)) {   // one round: a thread fetches all it needs of the partials by itself
     for (int idx = threadIdx.x; idx < G * D; idx += kThreads) {
       const int g = idx / D, c = idx % D;
       float o[8], m[8], l[8];
