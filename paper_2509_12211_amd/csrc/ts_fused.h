@@ -679,8 +679,8 @@ __device__ __forceinline__ void decode_units(const FusedParams& p, const FirstAr
   }
   TS_MARK(23);
 
-  // Launch tag of the score exchange.  The epoch word is read by every
-  // workgroup before it counts itself in; the launch's first workgroup advances it
+  // Launch tag of the score exchange.  The epoch word is read by every wave of a
+  // workgroup before the workgroup counts itself in; the launch's first workgroup advances it
   // for the next launch on its way out, once the count says that every workgroup
   // has read it.
   uint32_t tag = 0;
@@ -787,15 +787,21 @@ __device__ __forceinline__ void decode_units(const FusedParams& p, const FirstAr
             park_table();
             K_unit = uniform(K_raw);
           }
+        },
+        [&] {
+          // Each wave has the epoch and the length by the barrier behind the query's sums: past it the
+          // first thread may count the workgroup in.  (The builds that fetch the two words with scalar
+          // loads wait for those at that barrier as it is.)
+          if constexpr (kRound > 1) asm volatile("" : "+v"(L_raw), "+v"(epoch_raw));
         });
     TS_MARK_WAVE(32);
     const int L = uniform(L_unit);
     const int Pb = uniform(min(pages_of(L, S), Pmax));
     const int Kb = uniform(max(0, min(min(K_unit, Pb), at.Kmax)));
 
-    // count this workgroup in (once): it has read the epoch and, in append mode,
-    // the sequence length.  The count's value is not asked for: an atomic that
-    // returns one would hold this wave, and with it the barrier below, for a trip
+    // count this workgroup in (once): all its waves have read the epoch and, in append mode,
+    // the sequence length, ahead of the barrier inside the scan.  The count's value is not asked
+    // for: an atomic that returns one would hold this wave, and with it the barrier below, for a trip
     // to memory and back.
     if (exchange || app) {
       if (!counted && threadIdx.x == 0) (void)atomic_add_agent(&p.ctrl[kCtrlArrive], 1);

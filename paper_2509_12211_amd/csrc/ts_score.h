@@ -29,12 +29,11 @@ struct ScoreLanes {
   // Qp / Qn of the unit.  Split in three so the caller can issue other loads between the query load
   // and its first use (loads return in issue order: what is needed first is
   // issued first), and more while the waves wait for each other.  stage: LDS scratch of
-  // query_stage_bytes(G) bytes, headed by the raw rows when share_query returns (to this
-  // wave's lanes at least; to the others behind their next barrier).
+  // query_stage_bytes(G) bytes, headed by the raw rows when share_query returns.
   //
   // Two forms.  kShort is for launches that score several groups a wave in one round, where this is a link of
   // the chain they are made of:
-  //   G = 1: a lane's sums are its own chunk of the row, which it has fetched itself: no exchange at all.
+  //   G = 1: a lane's sums are its own chunk of the row, which it has fetched itself: no exchange.
   //   G <= 8: a wave fetches the G values of each of its D / NW channels, a lane per (row, channel),
   //   sums them across its lanes, and the sums go round through LDS behind one barrier (ready 0.3 us sooner).
   // Otherwise, and for larger groups, the rows themselves go through LDS, a thread sums a channel over
@@ -92,7 +91,6 @@ struct ScoreLanes {
         qp[i] = static_cast<double>(fmaxf(f[i], 0.f));
         qn[i] = static_cast<double>(fminf(f[i], 0.f));
       }
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // (the row, to the other lanes of the wave)
       return;
     }
 #pragma unroll
@@ -135,10 +133,12 @@ struct ScoreLanes {
     }
     TS_MARK(21);
   }
+  // (One head: the barrier is for the rows and for what the caller has asked for ahead of the sums,
+  // see before_share of scan_finish.)
   template <bool kShort>
   __device__ __forceinline__ void share_query(int G, const unsigned char* stage) {
-    if (kShort && G == 1) return;
     __syncthreads();
+    if (kShort && G == 1) return;
     const double* red = reinterpret_cast<const double*>(stage + (size_t)G * D * 2);
     const int cg = lane_id() % LPR;
 #pragma unroll
@@ -293,7 +293,8 @@ __device__ __forceinline__ void scan_issue_rest(ScanRegs<D, kHalf, NW, R>& r, co
   __builtin_amdgcn_sched_barrier(0);
 }
 
-// `after_query` runs once the query is in registers and returns Pb.  Must be
+// `before_share` runs ahead of the barrier of share_query, `after_query` once the query is in
+// registers; it returns Pb.  Must be
 // called by the whole workgroup (the query may go through LDS, q_stage, with
 // barriers).
 //
@@ -311,13 +312,14 @@ __device__ __forceinline__ void scan_issue_rest(ScanRegs<D, kHalf, NW, R>& r, co
 // no load is issued where there is no next tile, measured 0.7 us slower on the
 // 16-sequence configuration.)
 template <int D, bool kBranchless, bool kHalf, int NW, int R, typename AfterQuery, typename Patch, typename Sink,
-          typename BeforeReport = Nothing>
+          typename BeforeReport = Nothing, typename BeforeShare = Nothing>
 __device__ __forceinline__ void scan_finish(ScanRegs<D, kHalf, NW, R>& r, const uint16_t* pmin_u,
                                             const uint16_t* pmax_u, int G, int Pmax, int first_iter,
                                             int iter_stride, unsigned char* q_stage,
                                             AfterQuery after_query, Patch patch, Sink sink,
                                             int gs = 1, int goff = 0, bool fill_to_pmax = true,
-                                            BeforeReport before_report = BeforeReport{}) {
+                                            BeforeReport before_report = BeforeReport{},
+                                            BeforeShare before_share = BeforeShare{}) {
   using Regs = ScanRegs<D, kHalf, NW, R>;
   constexpr int PPW = ScoreLanes<D, kHalf>::PPW, PPI = Regs::PPI;
   const int rstep = PPW * gs;
@@ -325,6 +327,7 @@ __device__ __forceinline__ void scan_finish(ScanRegs<D, kHalf, NW, R>& r, const 
   ScoreLanes<D, kHalf, NW> ql;
   ql.template sum_query<(R > 1)>(r.q, G, q_stage);
   scan_issue_rest(r, pmin_u, pmax_u, Pmax, first_iter, iter_stride, gs, goff);
+  before_share();
   ql.template share_query<(R > 1)>(G, q_stage);
   TS_MARK(16);
   const int Pb = after_query();

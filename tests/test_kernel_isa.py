@@ -9,6 +9,9 @@ The latency-bound builds (one unit per cluster, or one workgroup per unit) must
     leading arguments are in registers when a wave starts;
   - use no scratch memory (a fragment held through a pointer once put 208 bytes per lane
     there: +9 us).
+And one that costs nothing but is a race when it is lost: a workgroup counts itself in, which allows
+the launch's first workgroup to advance the epoch and the lengths, only behind a barrier that each of its
+waves reaches with both words in hand.
 """
 import os
 import re
@@ -190,6 +193,93 @@ def test_first_loads_go_out_on_arguments_in_registers(preloaded_asm, kernel):
     assert spills == 0, f"{spills} scalar registers parked in vector lanes ahead of the first load"
     size = descriptor(preloaded_asm, sym, "private_segment_fixed_size")
     assert size == 0, f"scratch bytes per lane: {size}"
+
+
+# as in PRELOADED: with and without an append, more than one group of pages a wave in the first five
+COUNTED = ["64, 16, true, false, false, 3", "64, 16, true, false, false, 5", "64, 16, false, false, false, 9",
+           "128, 16, true, false, true, 9", "64, 16, true, true, false, 5", "64, 16, true, false, false, 1"]
+ARRIVALS = "global_atomic_add "   # (the only atomic on memory in these builds)
+
+
+@pytest.fixture(scope="module")
+def counted_asm(tmp_path_factory):
+    src = str(tmp_path_factory.mktemp("isa") / "counted.hip")
+    args = PRELOADED["one_round_decode_kernel"][0]
+    with open(src, "w") as f:
+        f.write('#include "ts_fused.h"\nnamespace ts {\n' + "".join(
+            f"template __global__ void one_round_decode_kernel<{a}>({args});\n" for a in COUNTED) + "}\n")
+    return assembly(src)
+
+
+def blocks_of(asm, sym):
+    """The kernel's basic blocks, as lists of instructions, and the blocks each can go on to."""
+    m = re.search(r"^" + re.escape(sym) + r":.*?^\.Lfunc_end", asm, re.S | re.M)
+    assert m, f"{sym} not in the assembly"
+    blocks, label, name = {}, "entry", {}
+    order = ["entry"]
+    blocks["entry"] = []
+    for line in m.group(0).split("\n")[1:]:
+        line = line.split(";")[0].strip()
+        if re.match(r"\.LBB\w+:$", line) or (blocks[label] and blocks[label][-1].startswith(("s_cbranch", "s_branch"))):
+            label = line[:-1] if line.endswith(":") else "after %d" % len(order)
+            blocks[label] = []
+            order.append(label)
+        if line and not line.startswith("."):
+            blocks[label].append(line)
+    after = {}
+    for i, label in enumerate(order):
+        last = blocks[label][-1] if blocks[label] else ""
+        target = [last.split()[1]] if last.startswith(("s_cbranch", "s_branch")) else []
+        falls = not last.startswith(("s_branch", "s_endpgm", "s_setpc"))
+        after[label] = target + ([order[i + 1]] if falls and i + 1 < len(order) else [])
+    return blocks, after
+
+
+@pytest.mark.parametrize("build", COUNTED)
+def test_a_workgroup_counts_itself_in_behind_a_barrier(counted_asm, build):
+    """On every path to the count a wave has waited for the epoch and the length, which it asks for ahead
+    of its metadata (several groups of pages a wave), and has then passed a barrier.  Loads come back
+    in order: the two are there once no more are in flight than went out behind the second."""
+    blocks, after = blocks_of(counted_asm, symbol(counted_asm, f"one_round_decode_kernel<{build}>"))
+    assert sum(line.startswith(ARRIVALS) for b in blocks.values() for line in b) >= 1
+    words = set()
+    if not build.endswith(" 1"):
+        ahead = [line for b in blocks.values() for line in b]      # up to the last group ahead of the sums
+        ahead = ahead[:[i for i, line in enumerate(ahead) if line.endswith(" nt")][3]]
+        words = {line for line in ahead if line.startswith("global_load_dword ")}
+        assert len(words) == 2 and sum("offset:64" in line for line in words) == 1, "the epoch and the length"
+
+    # a path's state, the lower the less is certain: words not yet asked for (one or two), memory
+    # operations sent out behind them, both there, a barrier behind that
+    ASKED, THERE, BARRIER = 2, 1000, 1001
+
+    def step(s, line):
+        if line in words:
+            return s + 1
+        if line.startswith(("global_", "buffer_", "scratch_", "flat_")) and ASKED <= s < THERE:
+            return min(s + 1, THERE - 1)
+        if line.startswith("s_waitcnt") and "vmcnt" in line and ASKED <= s < THERE:
+            return THERE if int(re.search(r"vmcnt\((\d+)\)", line).group(1)) <= s - ASKED else s
+        return BARRIER if line.startswith("s_barrier") and s == THERE else s
+
+    def through(s, label):
+        for line in blocks[label]:
+            s = step(s, line)
+        return s
+
+    state, work = {"entry": ASKED - 2 if words else THERE}, ["entry"]
+    while work:
+        label = work.pop()
+        s = through(state[label], label)
+        for nxt in after[label]:
+            if s < state.get(nxt, BARRIER + 1):
+                state[nxt] = s
+                work.append(nxt)
+    for label, s in state.items():
+        for line in blocks[label]:
+            if line.startswith(ARRIVALS):
+                assert s == BARRIER, "counted in with no barrier behind the epoch and the length"
+            s = step(s, line)
 
 
 @pytest.mark.parametrize("which", sorted(KERNELS) + sorted(SHARES))
