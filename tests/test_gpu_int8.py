@@ -341,6 +341,34 @@ def test_int8_scoring_in_one_round_of_groups(oracle, groups, d, S, opens):
     compare_units(oracle, f, units, scale, q_idx=1, what=f"int8 one round {groups}/{d}")
 
 
+@pytest.mark.parametrize("groups", [41, 42, 65, 72, 73])
+@pytest.mark.parametrize("d,S", [(64, 16), (64, 4), (128, 8), (128, 32)])
+def test_int8_scoring_in_one_round_of_nine_groups(oracle, groups, d, S):
+    """The build whose waves score up to nine groups, eight of them in one tile, from the fewest groups a
+    member has for it to one more than the most; the new token's page opened and widened in turn."""
+    test_int8_scoring_in_one_round_of_groups(oracle, groups, d, S, groups % 2 == 0)
+
+
+@pytest.mark.parametrize("members", [9, 16, 33, 64])
+@pytest.mark.parametrize("G,d", [(1, 64), (8, 128), (16, 128)])
+def test_int8_output_dealt_out_to_the_members(oracle, members, G, d):
+    """Clusters of more than eight, whose members merge the output by slices: with fewer slices than
+    members (the waves divide the partials) and with more (a member has several slices)."""
+    print(f"[case] int8 dealt out members={members} G={G} d={d}", flush=True)
+    S, topk = 16, 2 * members
+    spec = spec8("dealt", 1, 2 * G, 2, d, S, 3 * topk * S - 3, topk, headroom=3)
+    w = wl.make_workload(spec, DEV, seed=1600 + members, n_q=2, n_new=1, poison=0.0)
+    f = Session8(w)
+    f.layout.cluster_size = members
+    f.ws = ts.new_workspace(f.layout, w.K_max, DEV)
+    ts.build_page_meta(f.layout)
+    scale = 1.0 / math.sqrt(d)
+    for step in range(2):     # the second launch finds the first one's words in the workspace
+        f.out.fill_(float("nan"))
+        f.fused(scale, q_idx=step)
+        compare_units(oracle, f, [(0, 0), (0, 1)], scale, q_idx=step, what=f"int8 dealt out {members}/{G}/{d}")
+
+
 @pytest.mark.parametrize("name", ["tinyllama", "ragged"])
 def test_int8_full_size_sampled(oracle, name):
     """Benchmark workloads at full size with the INT8 cache, default launch shapes; the same

@@ -879,6 +879,18 @@ def test_dense_shares(oracle, built, shape, fmt):
         assert not sess.out[torch.from_numpy(~some).to(DEV)].any()
 
 
+def assert_out_relatively_close(out, ref, what):
+    """16-bit caches with logits of spread about one.  The softmax weights are carried to 16 mantissa bits
+    (2^-16 of each), sums and merges are in fp32, so that the error over many like weights is below
+    2^-16 of the output's size in the 2-norm and below 2^-13 of its root mean square anywhere; a
+    partial merged with a wrong weight, or not at all, is off by a tenth of that size and more."""
+    err = out.cpu().numpy().astype(np.float64) - ref
+    print(f"[error] {what}: rel {np.linalg.norm(err) / np.linalg.norm(ref):.2e}, "
+          f"max {np.abs(err).max() / np.sqrt((ref ** 2).mean()):.2e}", flush=True)
+    assert np.linalg.norm(err) <= 2.0 ** -16 * np.linalg.norm(ref), what
+    assert np.abs(err).max() <= 2.0 ** -13 * np.sqrt((ref ** 2).mean()), what
+
+
 @pytest.mark.parametrize("G", [1, 2, 3, 8, 16])
 @pytest.mark.parametrize("d,fmt", [(64, "bf16"), (128, "fp16")])
 @pytest.mark.parametrize("pages", [31, 33, 36, 70, 135, 300])
@@ -907,10 +919,11 @@ def test_many_partials_of_a_unit(oracle, built, G, d, fmt, pages):
         else:
             ts.sparse_decode_attention(sess.layout, w.q[0], sel, counts, w.K_max, scale, sess.out, sess.ws, lse_out=lse)
         torch.cuda.synchronize()
-        err = np.abs(sess.out.cpu().numpy().astype(np.float64) - ref).max()
-        assert err <= 2e-3, f"{what} attention off by {err}"
+        assert_out_relatively_close(sess.out, ref, f"{what} attention, {G} heads, {d} channels, {pages} pages")
         err = np.abs(lse.cpu().numpy().astype(np.float64) - ref_lse).max()
-        assert err <= LSE_ATOL, f"{what} log-denominator off by {err}"
+        print(f"[error] log-denominator {err:.2e}", flush=True)
+        # (fp32 weights, up to 300 sums of 16 of them at 2^-24 each, and one logarithm around ten)
+        assert err <= 2.0 ** -15, f"{what} log-denominator off by {err}"
 
 
 @pytest.mark.parametrize("shape", [(64, 8, 64, 16, 200, 1), (64, 8, 128, 8, 90, 0), (65, 8, 64, 32, 300, 0),
@@ -1327,11 +1340,10 @@ def test_every_length_of_a_wave_s_fragment_list(oracle, built, topk, cluster):
 @pytest.mark.parametrize("cluster", [5, 6, 9, 17, 18, 24, 40])
 @pytest.mark.parametrize("shape", ["d64_g4", "d128_g8"])
 def test_cluster_merge_in_batches(oracle, built, cluster, shape):
-    """The cluster's last member takes the other members' partial results four at a time
-    (up to five members) or sixteen at a time: cluster sizes on either side of both limits,
-    two and three batches, members that have no page at all, a head handled by one wave
-    (d = 64) and by two (d = 128, where a thread also works through two channels' worth of
-    the unit's G * d outputs)."""
+    """Clusters of up to eight: the last member takes the other members' partial results four at a time
+    (up to five members) or sixteen; from nine on every member merges its slices of the output.
+    Sizes on either side of these limits, members that have no page at all, a head that is one
+    slice (d = 64) and two (d = 128, sixteen slices of the unit's output)."""
     print(f"[case] merge batches cluster={cluster} {shape}", flush=True)
     spec = (wl.WorkloadSpec("merge64", 2, 8, 2, 64, 16, 5000, 48, keys="walk", headroom=40) if shape == "d64_g4"
             else wl.WorkloadSpec("merge128", 1, 16, 2, 128, 16, 4000, 36, keys="offset", headroom=40))
@@ -1344,6 +1356,33 @@ def test_cluster_merge_in_batches(oracle, built, cluster, shape):
         sess.out.fill_(float("nan"))
         sess.fused(scale)
         compare_units(oracle, sess, units, scale, what=f"merge/cluster={cluster}/{shape}/launch {step}")
+
+
+@pytest.mark.parametrize("members", [8, 9, 15, 16, 17, 31, 33, 64])
+@pytest.mark.parametrize("G,d,fmt", [(1, 64, "bf16"), (1, 128, "fp16"), (5, 64, "fp16"), (8, 128, "bf16"),
+                                     (16, 64, "bf16"), (16, 128, "bf16"), (16, 128, "fp16")])
+def test_output_dealt_out_to_the_members(oracle, built, members, G, d, fmt):
+    """Clusters of nine members and more merge the output by slices of a wave's width: up to 32 of them over 9
+    to 64 members, so that a member has one (its waves divide the partials among them), several
+    or none; one of eight, whose last member merges, beside them.  Logits of spread one, so that every
+    partial counts, and a bound on the error relative to the output's own size."""
+    print(f"[case] dealt out members={members} G={G} d={d} {fmt}", flush=True)
+    S, topk = 16, 2 * members
+    spec = wl.WorkloadSpec("dealt", 1, 2 * G, 2, d, S, 3 * topk * S - 3, topk, headroom=3, kv=fmt)
+    w = wl.make_workload(spec, DEV, seed=1500 + members, n_q=2, n_new=1)
+    sess = Session(w, cluster_size=members)
+    ts.build_page_meta(sess.layout)
+    scale = 1.0 / math.sqrt(d)
+    for step in range(2):     # the second launch finds the first one's words in the workspace
+        sess.out.fill_(float("nan"))
+        sess.fused(scale, q_idx=step)
+        what = f"dealt out {members}/{G}/{d}/{fmt}"
+        compare_units(oracle, sess, [(0, 0), (0, 1)], scale, q_idx=step, what=what)
+        K, V = (wl.bits(x) for x in wl.logical_kv(w))
+        with oracle.element_format(fmt):
+            ref = oracle.sparse_decode_attention(wl.bits(w.q[step]), K, V, sess.sel.cpu().numpy(),
+                                                 sess.sel_count.cpu().numpy(), sess.seq_lens.cpu().numpy(), S, scale)
+        assert_out_relatively_close(sess.out, ref, what)
 
 
 @pytest.mark.parametrize("kv,groups", [("bf16", n) for n in (1, 8, 9, 24, 25, 40, 41)]
