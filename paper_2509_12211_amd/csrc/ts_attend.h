@@ -20,8 +20,6 @@
 // four value tokens belong to); with S = 64 a page is two fragments, its first
 // and its second 32 tokens.
 #pragma once
-#include <limits.h>
-
 #include <type_traits>
 
 #include "ts_device.h"
@@ -616,8 +614,8 @@ struct QOperand {
   }
 };
 
-// Partials handed on as tagged words (attend_split with a tag): merges the `n` partials of a
-// unit other than partial `own` into the running state (M, Lsum, O) of head g, channel c.
+// Partials handed on as tagged words (attend_split with a tag): merges the first `n` partials of a
+// unit, partial `own` not counted (kOwn), into the running state (M, Lsum, O) of head g, channel c.
 // The words are polled until all carry this launch's tag, so the data arrive with the
 // flag, in one trip through the memory system, with no counter and no wait for store
 // acknowledgements on the producers' side.  To be called by whole waves whose threads
@@ -630,7 +628,7 @@ struct QOperand {
 // `spins` counts the polls of this thread against spin_limit; returns false if
 // the bounded wait expired (the state is then invalid).
 // NB: partials polled together (all their loads in flight at once).
-template <int D, int NB>
+template <int D, int NB, bool kOwn>
 __device__ __forceinline__ bool merge_tagged(const uint64_t* part, int G, int g, int c, int own, int n,
                                              uint32_t tag, int spin_limit, int& spins, float& M,
                                              float& Lsum, float& O) {
@@ -649,8 +647,9 @@ __device__ __forceinline__ bool merge_tagged(const uint64_t* part, int G, int g,
     // partial s0 + i (counted without `own`), lane 32 + i its sum (one load for the wave
     // instead of two per partial and thread)
     const bool ml_role = (lane & 31) < nb;
-    const int my_row = s0 + (ml_role ? (lane & 31) : 0);
-    const uint32_t off_ml = (uint32_t)(my_row + (my_row >= own ? 1 : 0)) * stride + (uint32_t)(g * RS + D + (lane >> 5));
+    const uint64_t* base = part + (size_t)s0 * stride;      // (uniform)
+    auto row_of = [&](int i) { return i + (kOwn && s0 + i >= own ? 1 : 0); };
+    const uint32_t off_ml = (uint32_t)row_of(ml_role ? (lane & 31) : 0) * stride + (uint32_t)(g * RS + D + (lane >> 5));
     uint64_t ml = 0, v[NB];
 #pragma unroll
     for (int i = 0; i < NB; ++i) v[i] = 0;
@@ -661,8 +660,8 @@ __device__ __forceinline__ bool merge_tagged(const uint64_t* part, int G, int g,
       // loads in it, and the last rounds wait for one or two late members
 #pragma unroll
       for (int i = 0; i < NB; ++i)
-        if ((pending >> i) & 1u) v[i] = load_agent_u64(part + (size_t)(s0 + i + (s0 + i >= own ? 1 : 0)) * stride + off_o);
-      if (pending >> 31) ml = load_agent_u64(part + off_ml);
+        if ((pending >> i) & 1u) v[i] = load_agent_u64(base + (size_t)row_of(i) * stride + off_o);
+      if (pending >> 31) ml = load_agent_u64(base + off_ml);
 #pragma unroll
       for (int i = 0; i < NB; ++i)
         if ((uint32_t)(v[i] >> 32) == tag) pending &= ~(1u << i);
@@ -743,6 +742,7 @@ struct SplitPlace { int n_split, split; size_t part_row; };
 // How the partials of a unit's splits are handed on (attend_split): plainly, for the caller to count
 // arrivals, or as tagged words, which the last split merges, or the splits by slices of the output.
 enum { kPlain, kTagged, kTaggedDealt };
+constexpr int kMergedByOne = 8;   // members up to which the last one merges
 
 // The workgroup attends `count` selected pages of unit (b, h): entry i of its
 // list is page sel_at(i), stored in physical page phys_at(page); a caller that has looked the
@@ -1015,7 +1015,7 @@ __device__ __forceinline__ bool attend_split(const AttendParams& p, int b, int h
   float* part = p.partials + (part_row + split) * (size_t)G * RS;
   bool ok = true;
   int spins = 0;
-  if (kHand == kTaggedDealt && n_split > 8) {
+  if (kHand == kTaggedDealt && n_split > kMergedByOne) {
     // From nine members on the unit's output is dealt out to them in slices of a wave's width, the first to
     // the last member (whose part of the list is the one that can be short): a member hands on what
     // belongs to the others' slices, all of it before it waits for anything, and then merges its own.
@@ -1083,7 +1083,7 @@ __device__ __forceinline__ bool attend_split(const AttendParams& p, int b, int h
         const int g = mine / SL, c = (mine % SL) * kWave + lane;
         float M = -INFINITY, Lsum = 0.f, O = 0.f;
         if (wave == 0) merge_waves(g, c, M, Lsum, O);
-        ok = merge_tagged<D, 8>(unit64 + (size_t)start * G * RS, G, g, c, split - start, n, tag, spin_limit, spins, M, Lsum, O);
+        ok = merge_tagged<D, 8, true>(unit64 + (size_t)start * G * RS, G, g, c, split - start, n, tag, spin_limit, spins, M, Lsum, O);
         __syncthreads();   // (the waves' rows have been read)
         float* row = lds + wave * (kWave + 2);
         row[lane] = O;
@@ -1113,7 +1113,7 @@ __device__ __forceinline__ bool attend_split(const AttendParams& p, int b, int h
         const int g = s / SL, c = (s % SL) * kWave + lane;
         float M, Lsum, O;
         merge_waves(g, c, M, Lsum, O);
-        ok = merge_tagged<D, 16>(unit64, G, g, c, split, others, tag, spin_limit, spins, M, Lsum, O) && ok;
+        ok = merge_tagged<D, 16, true>(unit64, G, g, c, split, others, tag, spin_limit, spins, M, Lsum, O) && ok;
         store_out(p, ((size_t)b * p.Hq + (size_t)h * G + g) * D + c, Lsum > 0.f ? O / Lsum : 0.f);
         if (TS_RARELY(c == 0 && p.lse)) p.lse[(size_t)b * p.Hq + (size_t)h * G + g] = log_sum_exp(M, Lsum);
       });
@@ -1145,8 +1145,8 @@ __device__ __forceinline__ bool attend_split(const AttendParams& p, int b, int h
         if (split == n_split - 1) {   // (uniform) the merging split: its own partial never leaves
           // (small clusters take the partials four at a time, large ones sixteen)
           const int others = n_split - 1;
-          ok = (others <= 4 ? merge_tagged<D, 4>(unit64, G, g, c, INT_MAX, others, tag, spin_limit, spins, M, Lsum, O)
-                            : merge_tagged<D, 16>(unit64, G, g, c, INT_MAX, others, tag, spin_limit, spins, M, Lsum, O)) && ok;
+          ok = (others <= 4 ? merge_tagged<D, 4, false>(unit64, G, g, c, 0, others, tag, spin_limit, spins, M, Lsum, O)
+                            : merge_tagged<D, 16, false>(unit64, G, g, c, 0, others, tag, spin_limit, spins, M, Lsum, O)) && ok;
           store_out(p, ((size_t)b * p.Hq + (size_t)h * G + g) * D + c, Lsum > 0.f ? O / Lsum : 0.f);
           if (TS_RARELY(c == 0 && p.lse)) p.lse[(size_t)b * p.Hq + (size_t)h * G + g] = log_sum_exp(M, Lsum);
         } else {

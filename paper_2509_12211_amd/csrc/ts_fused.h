@@ -445,7 +445,8 @@ __global__ __launch_bounds__(kThreads) void dense_rounds_kernel(AttendParams p, 
 //   4. attends its own 1/g of the selected pages,
 //   5. g > 1: hands its partial softmax state on as words tagged with the launch
 //      tag; the cluster's last member polls for all g partials (data and flag
-//      arrive together) and merges them.
+//      arrive together) and merges them, or each member its slices of the
+//      output in clusters of nine members and more (kDealt).
 // Members only ever wait for members of their own cluster, all of which are
 // resident: the host launches at most as many workgroups as fit on the device
 // at once.  Every wait is bounded and raises the workspace's error word.
@@ -485,8 +486,10 @@ __global__ __launch_bounds__(kThreads) void dense_rounds_kernel(AttendParams p, 
 //
 // kDecide: the lengths decide between clusters of one size and shares in proportion to the
 // work (see by_shares), ahead of the first loads.
+//
+// kDealt: clusters of more than kMergedByOne members deal the merge of their partials out (see attend_split).
 template <int NW, int D, int S, bool kLoop, bool kApp, bool kInt8, bool kHalf, bool kCluster,
-          bool kDecide = false, int kRound = 0, bool kInRegs = false>
+          bool kDecide = false, int kRound = 0, bool kInRegs = false, bool kDealt = kDecide>
 __device__ __forceinline__ void decode_units(const FusedParams& p, const FirstArgs& f = FirstArgs{}) {
   constexpr bool kFirst = kRound > 0;
   static_assert(!kFirst || (kCluster && !kLoop && !kDecide), "one round of scoring: clusters with one unit each");
@@ -970,7 +973,7 @@ __device__ __forceinline__ void decode_units(const FusedParams& p, const FirstAr
     // 54.5 -> 49.0, of 64 54.9 -> 48.5.  With smaller pages or 64 channels the rounds are the faster way
     // (pages of 8 57.0 against 57.7, 64 channels and pages of 16 31.6 against 33.2).
     constexpr bool plain = kLoop && kInt8 && D == 128 && S >= 16;
-    constexpr int hand = !exchange ? kPlain : kFirst || kDecide ? kTaggedDealt : kTagged;
+    constexpr int hand = !exchange ? kPlain : kDealt ? kTaggedDealt : kTagged;
     const bool merged = attend_split<NW, D, S, kApp, kInt8, kHalf, true, apart, plain, hand>(
         at, b, h,
         [&] {
@@ -1046,7 +1049,21 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
 one_round_decode_kernel(const uint16_t* q, const uint16_t* page_min, const uint16_t* page_max,
                         const uint16_t* first, const uint16_t* second, uint32_t shape, uint32_t units,
                         uint32_t magic_g, uint32_t magic_hkv, FusedParams p) {
-  decode_units<kWaves, D, S, false, kApp, kInt8, kHalf, true, false, R>(
+  decode_units<kWaves, D, S, false, kApp, kInt8, kHalf, true, false, R, false, (R > 1)>(
+      p, FirstArgs{q, page_min, page_max, first, second, shape, units, magic_g, magic_hkv});
+}
+
+// R = 1 for clusters of more than kMergedByOne.  The smaller ones, the shortest of all launches, do not carry the merge
+// that is dealt out to the members: 16 layers in a graph, each 1 unit of eight members, 257 pages, 8.70 -> 8.64 us, 4 of
+// eight, 188 pages 9.44 -> 9.34, the INT8 cache, 128 channels, 2 of six, 94 pages 12.63 -> 12.42; nine such shapes 0.3 % on
+// average, from -0.5 to +1.6 % (where in memory the same instructions lie makes up to 3 % by itself).  With more
+// groups a wave it is 0.4 % at the most, which no second build is for.
+template <int D, int S, bool kApp, bool kInt8, bool kHalf>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void
+one_group_dealt_decode_kernel(const uint16_t* q, const uint16_t* page_min, const uint16_t* page_max,
+                              const uint16_t* first, const uint16_t* second, uint32_t shape, uint32_t units,
+                              uint32_t magic_g, uint32_t magic_hkv, FusedParams p) {
+  decode_units<kWaves, D, S, false, kApp, kInt8, kHalf, true, false, 1, false, true>(
       p, FirstArgs{q, page_min, page_max, first, second, shape, units, magic_g, magic_hkv});
 }
 
@@ -1280,7 +1297,7 @@ static bool launch_shares(const ts_layout* layout, FusedParams& p, const Plan& p
 }
 
 // The build for clusters whose waves score their pages in one round, nullptr where that takes more
-// than nine groups each: two rounds of four and a last group are the longest tile built.
+// than nine groups each: a tile of eight and one more group are the longest that is built.
 using OneRound = void (*)(const uint16_t*, const uint16_t*, const uint16_t*, const uint16_t*, const uint16_t*,
                           uint32_t, uint32_t, uint32_t, uint32_t, FusedParams);
 static int round_groups(int D, int Pmax, int g) {   // groups of pages a wave has at the most
@@ -1288,8 +1305,9 @@ static int round_groups(int D, int Pmax, int g) {   // groups of pages a wave ha
   return ((groups + g - 1) / g + kWaves - 1) / kWaves;
 }
 template <int D, int S, bool kApp, int kFmt>
-static OneRound one_round_kernel(int rows) {
+static OneRound one_round_kernel(int rows, int g) {
   constexpr bool kInt8 = kFmt == TS_KV_INT8, kHalf = kFmt == TS_KV_FP16;
+  if (rows <= 1 && g > kMergedByOne) return one_group_dealt_decode_kernel<D, S, kApp, kInt8, kHalf>;
   if (rows <= 1) return one_round_decode_kernel<D, S, kApp, kInt8, kHalf, 1>;
   if (rows <= 3) return one_round_decode_kernel<D, S, kApp, kInt8, kHalf, 3>;
   if (rows <= 5) return one_round_decode_kernel<D, S, kApp, kInt8, kHalf, 5>;
@@ -1310,7 +1328,8 @@ static int launch_clusters(const ts_layout* layout, FusedParams& p, const Plan& 
   auto app_kernel = query_aware_decode_kernel<D, S, false, true, kInt8, kHalf, true>;
   int st;
   const int rows = round_groups(D, p.at.Pmax, p.g);
-  const OneRound round_kernel = k_new ? one_round_kernel<D, S, true, kFmt>(rows) : one_round_kernel<D, S, false, kFmt>(rows);
+  const OneRound round_kernel = k_new ? one_round_kernel<D, S, true, kFmt>(rows, p.g)
+                                      : one_round_kernel<D, S, false, kFmt>(rows, p.g);
   if (round_kernel) {
     if ((st = allow_lds(round_kernel, pl.lds_fused)) != TS_OK) return st;
     int cap = resident_capacity(round_kernel, pl.lds_fused);

@@ -1385,6 +1385,26 @@ def test_output_dealt_out_to_the_members(oracle, built, members, G, d, fmt):
         assert_out_relatively_close(sess.out, ref, what)
 
 
+@pytest.mark.parametrize("members", [8, 9, 12])
+@pytest.mark.parametrize("G,d,fmt", [(1, 64, "bf16"), (5, 128, "bf16"), (16, 64, "fp16"), (8, 128, "fp16")])
+def test_one_group_a_wave_with_an_append(oracle, built, members, G, d, fmt):
+    """Tables of at most eight groups of pages a member with the append in the launch: eight members, whose last
+    one merges, and more, who each merge slices of the output in a build of its own."""
+    print(f"[case] one group, members={members} G={G} d={d} {fmt}", flush=True)
+    S, pages = 16, 8 * members * (512 // d) - 1
+    spec = wl.WorkloadSpec("one_group", 2, 2 * G, 2, d, S, pages * S - 5, 4 * members, headroom=5, kv=fmt)
+    w = wl.make_workload(spec, DEV, seed=1700 + members, n_q=2, n_new=2, poison=0.0)
+    sess = Session(w, poison_meta=False, cluster_size=members)
+    ts.build_page_meta(sess.layout)
+    scale = 1.0 / math.sqrt(d)
+    for step in range(2):     # the second launch finds the first one's words in the workspace
+        sess.out.fill_(float("nan"))
+        ts.append_and_decode(sess.layout, w.k_new[step], w.v_new[step], w.q[step], w.topk, w.K_max, scale, sess.out,
+                             sess.ws, scores_out=sess.scores, sel_out=sess.sel, sel_count_out=sess.sel_count)
+        compare_units(oracle, sess, [(b, h) for b in range(2) for h in range(2)], scale, q_idx=step,
+                      what=f"one group {members}/{G}/{d}/{fmt}")
+
+
 @pytest.mark.parametrize("kv,groups", [("bf16", n) for n in (1, 8, 9, 24, 25, 40, 41)]
                          + [("fp16", n) for n in (1, 9, 25, 40)])
 @pytest.mark.parametrize("d,S", [(64, 16), (128, 8)])

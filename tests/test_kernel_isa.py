@@ -27,7 +27,7 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2509_12211_amd", "csrc")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
-# head_dim 64, page size, no loop, append folded in, bf16, clusters: tables of more than 40 groups of
+# head_dim 64, page size, no loop, append folded in, bf16, clusters: tables of more than 72 groups of
 # pages a member
 KERNELS = {
     "page 16": "_ZN2ts25query_aware_decode_kernelILi64ELi16ELb0ELb1ELb0ELb0ELb1EEEvNS_11FusedParamsE",
@@ -280,6 +280,21 @@ def test_a_workgroup_counts_itself_in_behind_a_barrier(counted_asm, build):
             if line.startswith(ARRIVALS):
                 assert s == BARRIER, "counted in with no barrier behind the epoch and the length"
             s = step(s, line)
+
+
+def test_small_clusters_do_not_carry_the_merge_by_slices(tmp_path):
+    """One group of pages a wave: clusters of up to eight members, whose last one merges, run a build without the
+    merge that larger ones deal out to their members (up to 2 % of the shortest launches); the two barriers
+    between the waves that divide a slice's partials are in the other build alone."""
+    args = PRELOADED["one_round_decode_kernel"][0]
+    kernels = ["one_round_decode_kernel<64, 16, true, false, false, 1>",
+               "one_group_dealt_decode_kernel<64, 16, true, false, false>"]
+    src = tmp_path / "merges.hip"
+    src.write_text('#include "ts_fused.h"\nnamespace ts {\n' +
+                   "".join(f"template __global__ void {k}({args});\n" for k in kernels) + "}\n")
+    asm = assembly(str(src))
+    barriers = [sum(line == "s_barrier" for b in blocks_of(asm, symbol(asm, k))[0].values() for line in b) for k in kernels]
+    assert barriers[1] - barriers[0] == 2, barriers
 
 
 @pytest.mark.parametrize("which", sorted(KERNELS) + sorted(SHARES))
