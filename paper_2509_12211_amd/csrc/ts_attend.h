@@ -372,7 +372,7 @@ struct NewToken {
   const uint16_t* v_row;
 };
 
-template <int D, int F, bool kInt8 = false>
+template <int D, int F>
 struct TokenPatch {
   uint4 k[PageFrag<D, F>::KQ];       // this lane's D/4 channels of the key
   uint32_t v[PageFrag<D, F>::NCB];   // value of channel 16 * cb + lane % 16
@@ -380,7 +380,7 @@ struct TokenPatch {
     const int lane = lane_id(), r = lane & 15, kb = lane >> 4;
 #pragma unroll
     for (int i = 0; i < PageFrag<D, F>::KQ; ++i)
-      k[i] = *reinterpret_cast<const uint4*>(nt.k_row + key_channel<D, kInt8>(kb, i));
+      k[i] = *reinterpret_cast<const uint4*>(nt.k_row + key_channel<D, false>(kb, i));
 #pragma unroll
     for (int cb = 0; cb < PageFrag<D, F>::NCB; ++cb) v[cb] = nt.v_row[16 * cb + r];
   }
@@ -410,22 +410,30 @@ struct TokenPatch {
 };
 
 // The same for the INT8 cache: the rows are quantised here (scale = max |x| / 127
-// over the row, code = x / scale rounded half to even), the codes spliced in as
-// the biased halves the expanded fragments hold and the two scales put where the
-// fragment keeps the token's.  To be called by a whole wave.
+// over the row, code = x / scale rounded half to even), the codes spliced into the
+// fragment as it comes from the pool, ahead of its expansion, and the two scales put where the
+// fragment keeps the token's.  (Spliced into the expanded halves, they put 20 bytes a lane in scratch
+// memory with 128 channels and pages of 32 and 64: 32 units of 1024 such pages 17.9 -> 17.3 us, 16 of 1024 pages of
+// 64 17.2 -> 16.5, 8 of 256 of 32 12.8 -> 12.3.)  To be called by a whole wave.
 template <int D, int F>
-struct TokenPatch8 : TokenPatch<D, F, true> {
+struct TokenPatch8 {
+  using Frag = PageFrag8<D, F>;
+  uint32_t k[Frag::KW];        // codes of this lane's D/4 channels of the key
+  uint32_t v[Frag::NCB / 4];   // codes of channels 16 * cb + lane % 16 of the value
   float ksc, vsc;
-  __device__ __forceinline__ static uint32_t code_half(float x, float scale) {
-    return 0x6400u | (static_cast<uint32_t>(i8_code(x, scale) + 128) & 0xffu);   // half of code + kI8Bias
-  }
   __device__ __forceinline__ void load(const NewToken& nt) {
-    TokenPatch<D, F, true>::load(nt);
+    const int lane = lane_id(), r = lane & 15, kb = lane >> 4;
+    uint4 kx[Frag::KW / 2];
+    uint32_t vx[Frag::NCB];
+#pragma unroll
+    for (int i = 0; i < Frag::KW / 2; ++i) kx[i] = *reinterpret_cast<const uint4*>(nt.k_row + key_channel<D, true>(kb, i));
+#pragma unroll
+    for (int cb = 0; cb < Frag::NCB; ++cb) vx[cb] = nt.v_row[16 * cb + r];
     float ka = 0.f, va = 0.f;
 #pragma unroll
-    for (int i = 0; i < PageFrag<D, F>::KQ; ++i) ka = fmaxf(ka, chunk_amax_bf16(this->k[i]));
+    for (int i = 0; i < Frag::KW / 2; ++i) ka = fmaxf(ka, chunk_amax_bf16(kx[i]));
 #pragma unroll
-    for (int cb = 0; cb < PageFrag<D, F>::NCB; ++cb) va = fmaxf(va, fabsf(bf16_lo(this->v[cb])));
+    for (int cb = 0; cb < Frag::NCB; ++cb) va = fmaxf(va, fabsf(bf16_lo(vx[cb])));
     // a lane holds a quarter of the key row (the quarters sit 16 lanes apart) and
     // every 16th channel of the value row (lane % 16 picks which)
     ka = fmaxf(ka, shfl_xor_f(ka, 16));
@@ -435,28 +443,41 @@ struct TokenPatch8 : TokenPatch<D, F, true> {
     ksc = i8_row_scale(ka);
     vsc = i8_row_scale(va);
 #pragma unroll
-    for (int i = 0; i < PageFrag<D, F>::KQ; ++i) {
-      const uint32_t w[4] = {this->k[i].x, this->k[i].y, this->k[i].z, this->k[i].w};
-      uint32_t o[4];
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        o[e] = code_half(bf16_lo(w[e]), ksc) | (code_half(bf16_hi(w[e]), ksc) << 16);
-      this->k[i] = make_uint4(o[0], o[1], o[2], o[3]);
+    for (int i = 0; i < Frag::KW / 2; ++i) {
+      const uint2 c = i8_chunk_codes(kx[i], ksc);
+      k[2 * i] = c.x;
+      k[2 * i + 1] = c.y;
     }
 #pragma unroll
-    for (int cb = 0; cb < PageFrag<D, F>::NCB; ++cb) this->v[cb] = code_half(bf16_lo(this->v[cb]), vsc);
-  }
-  // the token's scales, where the fragment holds them (x as in apply)
-  __device__ __forceinline__ void apply_scales(float4 (&ks)[PageFrag<D, F>::NT],
-                                               float4 (&vs)[PageFrag<D, F>::NT], int x) const {
-    const int kb = lane_id() >> 4;
+    for (int cb = 0; cb < Frag::NCB; cb += 4) {
+      v[cb / 4] = 0u;
 #pragma unroll
-    for (int t = 0; t < PageFrag<D, F>::NT; ++t) {
+      for (int i = 0; i < 4; ++i)
+        v[cb / 4] |= (static_cast<uint32_t>(i8_code(bf16_lo(vx[cb + i]), vsc)) & 0xffu) << (8 * i);
+    }
+  }
+  // x: the token's position inside the fragment
+  __device__ __forceinline__ void apply(Frag& f, int x) const {
+    const int lane = lane_id(), r = lane & 15, kb = lane >> 4;
+#pragma unroll
+    for (int t = 0; t < Frag::NT; ++t) {
+      if (tile_token<F>(t, r) == x) {
+#pragma unroll
+        for (int i = 0; i < Frag::KW; ++i) f.k[t][i] = k[i];
+      }
+      // V words of tile t hold tokens tile_token<F>(t, 4 * kb) .. + 3
       const int e = x - tile_token<F>(t, 4 * kb);
-      if (e == 0) { ks[t].x = ksc; vs[t].x = vsc; }
-      if (e == 1) { ks[t].y = ksc; vs[t].y = vsc; }
-      if (e == 2) { ks[t].z = ksc; vs[t].z = vsc; }
-      if (e == 3) { ks[t].w = ksc; vs[t].w = vsc; }
+      if (e >= 0 && e < 4) {
+#pragma unroll
+        for (int cb = 0; cb < Frag::NCB; ++cb) {
+          const uint32_t code = (v[cb / 4] >> (8 * (cb % 4))) & 0xffu;
+          f.v[t][cb] = (f.v[t][cb] & ~(0xffu << (8 * e))) | (code << (8 * e));
+        }
+      }
+      if (e == 0) { f.ks[t].x = ksc; f.vs[t].x = vsc; }
+      if (e == 1) { f.ks[t].y = ksc; f.vs[t].y = vsc; }
+      if (e == 2) { f.ks[t].z = ksc; f.vs[t].z = vsc; }
+      if (e == 3) { f.ks[t].w = ksc; f.vs[t].w = vsc; }
     }
   }
 };
@@ -909,14 +930,11 @@ __device__ __forceinline__ bool attend_split(const AttendParams& p, int b, int h
     };
     auto consume = [&](int i) {
       if constexpr (kInt8) {
+        if constexpr (kPatch) {
+          if (TS_RARELY(splice && item[i] == splice_item)) patch.apply(f[i], splice_x);
+        }
         PageFrag<D, F> fx;
         expand_frag<D, F>(f[i], fx);
-        if constexpr (kPatch) {
-          if (TS_RARELY(splice && item[i] == splice_item)) {
-            patch.apply(fx, splice_x);
-            patch.apply_scales(f[i].ks, f[i].vs, splice_x);
-          }
-        }
         attend_page<D, F, true>(fx, qf, vmask[i], p.scale_log2, acc, f[i].ks, f[i].vs, qbias);
       } else {
         if (TS_RARELY(splice && item[i] == splice_item)) patch.apply(f[i], splice_x);

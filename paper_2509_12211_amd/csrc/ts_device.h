@@ -72,6 +72,18 @@ __device__ __forceinline__ int i8_code(float x, float scale) {
   // (through the integer: a code that rounded to -0.0f is 0, as the stored byte is)
   return static_cast<int>(fminf(fmaxf(rintf(__fdiv_rn(x, scale)), -127.f), 127.f));
 }
+// The eight codes of a chunk as bytes in channel order.
+__device__ __forceinline__ uint2 i8_chunk_codes(const uint4& c, float scale) {
+  const uint32_t w[4] = {c.x, c.y, c.z, c.w};
+  uint32_t o[2] = {0u, 0u};
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const uint32_t lo = static_cast<uint32_t>(i8_code(bf16_lo(w[i]), scale)) & 0xffu;
+    const uint32_t hi = static_cast<uint32_t>(i8_code(bf16_hi(w[i]), scale)) & 0xffu;
+    o[i >> 1] |= (lo | (hi << 8)) << (16 * (i & 1));
+  }
+  return make_uint2(o[0], o[1]);
+}
 // Largest magnitude among the eight bf16 values of a 16-byte chunk.
 __device__ __forceinline__ float chunk_amax_bf16(const uint4& c) {
   const uint32_t w[4] = {c.x, c.y, c.z, c.w};

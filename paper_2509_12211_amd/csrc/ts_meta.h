@@ -195,18 +195,6 @@ __device__ __forceinline__ uint16_t bf16_directed(double x, bool up) {
   return hi;
 }
 
-// The eight codes of a chunk as bytes in channel order.
-__device__ __forceinline__ uint2 i8_chunk_codes(const uint4& c, float scale) {
-  const uint32_t w[4] = {c.x, c.y, c.z, c.w};
-  uint32_t o[2] = {0u, 0u};
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const uint32_t lo = static_cast<uint32_t>(i8_code(bf16_lo(w[i]), scale)) & 0xffu;
-    const uint32_t hi = static_cast<uint32_t>(i8_code(bf16_hi(w[i]), scale)) & 0xffu;
-    o[i >> 1] |= (lo | (hi << 8)) << (16 * (i & 1));
-  }
-  return make_uint2(o[0], o[1]);
-}
 // The dequantised values of a chunk rounded outwards to bf16: lo <= code * scale <= hi.
 __device__ __forceinline__ void i8_chunk_box(const uint4& c, float scale, uint4& lo, uint4& hi) {
   const uint32_t w[4] = {c.x, c.y, c.z, c.w};

@@ -341,6 +341,29 @@ def test_int8_scoring_in_one_round_of_groups(oracle, groups, d, S, opens):
     compare_units(oracle, f, units, scale, q_idx=1, what=f"int8 one round {groups}/{d}")
 
 
+@pytest.mark.parametrize("S", [4, 8, 16, 32, 64])
+@pytest.mark.parametrize("d", [64, 128])
+def test_int8_appended_token_in_every_slot(oracle, d, S):
+    """The attention takes the new token's codes and scales from the caller's rows, spliced into the page's fragment:
+    each position of a fragment, both fragments of a page of 64, fragments of several pages."""
+    print(f"[case] int8 splice d={d} S={S}", flush=True)
+    pages = 12
+    L = pages * S - S          # the first token of the last page, then all the others
+    spec = spec8("splice", 1, 8, 2, d, S, L, pages, headroom=S)
+    w = wl.make_workload(spec, DEV, seed=1800 + d + S, n_q=1, n_new=S, poison=0.0)
+    f = Session8(w)
+    f.page_min.zero_()
+    f.page_max.zero_()
+    f.layout.cluster_size = 2
+    f.ws = ts.new_workspace(f.layout, w.K_max, DEV)
+    ts.build_page_meta(f.layout)
+    scale = 1.0 / math.sqrt(d)
+    for slot in range(S):      # (every page is kept)
+        ts.append_and_decode(f.layout, w.k_new[slot], w.v_new[slot], w.q[0], w.topk, w.K_max, scale, f.out, f.ws,
+                             scores_out=f.scores, sel_out=f.sel, sel_count_out=f.sel_count)
+        compare_units(oracle, f, [(0, 0), (0, 1)], scale, what=f"int8 splice {d}/{S}/{slot}")
+
+
 @pytest.mark.parametrize("groups", [41, 42, 65, 72, 73])
 @pytest.mark.parametrize("d,S", [(64, 16), (64, 4), (128, 8), (128, 32)])
 def test_int8_scoring_in_one_round_of_nine_groups(oracle, groups, d, S):

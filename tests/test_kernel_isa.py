@@ -57,12 +57,21 @@ LOOPING = [f"query_aware_decode_kernel<128, {s}, true, false, true, false, true>
 POINTERS, FIRST = "const uint16_t*, const uint16_t*, const uint16_t*, ", "uint32_t, uint32_t, uint32_t, uint32_t, FusedParams"
 PRELOADED = {
     # (the benchmark's shapes run these: the 64-, 16- and 8-sequence ones with up to five groups a wave, the
-    # single sequence with one)
+    # single sequence with one; up to nine are the most there is)
     "one_round_decode_kernel": (POINTERS + "const uint16_t*, const uint16_t*, " + FIRST,
                                 ["64, 16, true, false, false, 1", "64, 16, true, false, false, 3",
                                  "64, 16, true, false, false, 5", "64, 16, false, false, false, 5",
                                  "64, 32, true, false, false, 5", "64, 32, true, false, false, 3",
-                                 "128, 16, true, false, true, 3", "64, 16, true, true, false, 5"]),
+                                 "128, 16, true, false, true, 3", "64, 16, true, true, false, 5",
+                                 "64, 16, true, false, false, 9", "64, 16, false, true, false, 9",
+                                 "128, 16, true, false, true, 9", "128, 8, true, true, false, 9",
+                                 "128, 32, true, true, false, 1", "128, 32, true, true, false, 3",
+                                 "128, 64, true, true, false, 5", "128, 32, true, true, false, 9",
+                                 "128, 64, true, true, false, 9"]),
+    "one_group_dealt_decode_kernel": (POINTERS + "const uint16_t*, const uint16_t*, " + FIRST,
+                                      ["64, 16, true, false, false", "128, 16, false, false, true"]),
+    "small_units_i8_decode_kernel": (POINTERS + "const int32_t*, const int32_t*, const int32_t*, uint32_t, uint32_t, FusedParams",
+                                     ["64, 16", "64, 8", "128, 16", "128, 32"]),
     "small_units_decode_kernel": (POINTERS + "const int32_t*, const int32_t*, const int32_t*, uint32_t, uint32_t, FusedParams",
                                   ["64, 16, false", "128, 16, false", "64, 32, true", "128, 64, false"]),
     "sparse_attention_kernel": ("const uint16_t*, const int32_t*, const int32_t*, const int32_t*, const int32_t*, "
