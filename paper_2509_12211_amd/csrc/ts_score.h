@@ -278,7 +278,7 @@ __device__ __forceinline__ void scan_issue_tile(ScanRegs<D, kHalf, NW, R>& r, co
 // query's sums, those were ready 3.7 us after the kernel's entry (16 x 4 units of 1024 pages) where the
 // query had arrived after 0.9.  Two groups go out ahead of the sums, the others between them and the
 // barrier: 18.8 -> 18.4 us, one query head each (8 x 16 units of 512 pages) 17.05 -> 16.95, 4 x 4 of 4097 pages
-// 19.2 -> 18.7, the INT8 cache 17.95 -> 17.55 (with the sums' own shorter way).
+// 19.2 -> 18.5, the INT8 cache 17.95 -> 17.55 (with the sums' own shorter way).
 template <int D, bool kHalf, int NW, int R>
 __device__ __forceinline__ void scan_issue_rest(ScanRegs<D, kHalf, NW, R>& r, const uint16_t* pmin_u,
                                                 const uint16_t* pmax_u, int Pmax, int first_iter, int iter_stride,

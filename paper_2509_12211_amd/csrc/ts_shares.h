@@ -8,7 +8,9 @@ namespace ts {
 
 #define TS_BOTH __host__ __device__ __forceinline__
 
-constexpr int kBalanceMembers = 32;   // most members of a cluster (more only lengthen its merge)
+// Most members of a cluster.  Measured when the last member merged all partials, which more of them only made
+// longer; from nine members on the merge is dealt out now, and the limit has not been looked at again.
+constexpr int kBalanceMembers = 32;
 
 // What a sequence asks of the workgroups that share one of its KV heads, in metadata rows (a
 // token's K and V are as long as a page's box): rows every member reads in full, rows divided
@@ -59,10 +61,11 @@ TS_BOTH int chunk_of(int K, int g, int S) {
 // member's rows and tiles at 100 B/ns; each fragment of a wave after the first; each sixteen partials
 // merged after the first; and, with more than 96 workgroups, every further one (their polls, arrivals
 // and dispatch).  sweep.py --clusters times 48 layouts of 1 to 85 units with 100 to 8000 pages at up to
-// eleven sizes each: 1.0 % above the best size on average, 9.4 % at the most (1 unit, 120 of 1000 pages: 30
-// members 12.0 us, 16 11.0), where as many members as fit the device with four pages each are 4.8 % above
+// eleven sizes each: where these costs were fitted, 1.0 % above the best size on average, 9.4 % at the most (1 unit, 120 of
+// 1000 pages: 30 members 12.0 us, 16 11.0), and as many members as fit the device with four pages each 4.8 % above
 // it, 38 % at the most (4 units, 250 of 1000 pages: 63 members 17.1 us, 17 12.4; 16 units, 48 of 250: 12
-// 11.1, 6 10.1; 8 units, 120 of 1000: 30 13.7, 16 11.6).
+// 11.1, 6 10.1; 8 units, 120 of 1000: 30 13.7, 16 11.6).  Since then more than eight members divide the merge and six to
+// nine groups a wave are one round, which the costs do not know of: 2.4 % and 21 % now, as many members as fit 2.4 % and 15.5 %.
 struct ClusterTime {
   float grows;   // what only grows with fewer members
   float all;
